@@ -59,7 +59,7 @@ size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
 // Offsets (bytes) of everything carved from the caller's workspace.
 struct Layout {
-    size_t x, q, q_aux, logits, attn_out, ffn_h, ln_h, x_shadow, ln_stats, mu_hat, ln_fold;
+    size_t x, q, q_aux, logits, attn_out, ffn_h, ln_h, x_shadow, ln_stats, mu_hat, kv_slot, ln_fold;
     size_t stats_elems;  // float2 per statistics buffer
     size_t shadow_bytes; // bytes per shadow buffer
     size_t act_bytes;    // [0, act_bytes): the step's activations and attention partials (x ... counters)
@@ -130,6 +130,7 @@ void make_layout(const aed_config* c, Layout* L) {
     L->stats_elems = (d / 16) * Bp;
     L->ln_stats = take(2 * L->stats_elems * 8);
     L->mu_hat = take(2 * Bp * 4);  // two buffers, alternating like the statistics
+    L->kv_slot = take(Ba * 4);
     L->part = take(Ba * H * kMaxChunks * (Dh + 2) * 4);
     L->counters = take(Ba * H * 4);
     L->act_bytes = off;  // everything above is rewritten by every step before it is read (the counters: zero between launches)
@@ -246,6 +247,9 @@ struct aed_decoder {
         st.cur_tok = at<int>(lay.cur_tok);
         st.limit = at<int>(lay.limit);
         st.n_finished = at<int>(lay.n_finished);
+        st.page_table = at<int>(lay.page_table);
+        st.max_pages = lay.max_pages;
+        st.kv_slot = act_at<int>(lay.kv_slot);
         st.prompt = prompt_len > 0 ? at<int>(lay.prompt_buf) : nullptr;
         st.out_tokens = at<int>(lay.out_buf);
         st.prompt_len = prompt_len;
@@ -336,7 +340,6 @@ void ln_consumer(const aed_decoder* d, GemmArgs& g, const float* c1, const float
     g.ln_c1 = c1;
     g.ln_c2 = c2;
     g.stat_tiles = d->cfg.d_model / 16;
-    g.m_stride = (int)(d->lay.stats_elems / (size_t)(d->cfg.d_model / 16));
 }
 
 // Small batches in bfloat16 mode: the cross-attention query product is split over the QKV launch and the launch of the
@@ -353,10 +356,7 @@ hipError_t k_ln_qkv(aed_decoder* d, int l) {
     g.out = d->act_at<float>(d->lay.q);
     g.k_pool = d->ws + d->lay.k_pool + (size_t)l * d->lay.pool_layer_elems * d->kv_esz;
     g.v_pool = d->ws + d->lay.v_pool + (size_t)l * d->lay.pool_layer_elems * d->kv_esz;
-    g.page_table = d->at<int>(d->lay.page_table);
-    g.max_pages = d->lay.max_pages;
-    g.seq_len = d->at<int>(d->lay.seq_len);
-    g.finished = d->at<int>(d->lay.finished);
+    g.kv_slot = d->act_at<int>(d->lay.kv_slot);
     if (folded_ln(d)) {
         ln_consumer(d, g, d->fold[l].qkv_c1, d->fold[l].qkv_c2, l, true);
         if (merged_products(d)) {  // the stored matrix is [Wqkv.g1 ; Wcq.g2]: the last d columns are P1 of the merged products
@@ -410,8 +410,7 @@ hipError_t k_resid(aed_decoder* d, int l, const void* A, const void* W, const vo
         g.mu_hat_in = shift_buf(d, l & 1);  // the mean of the rows that entered the layer
         g.shadow_out = shadow_buf(d, d->x_par ^ 1);
         g.stat_tiles = d->cfg.d_model / 16;
-        g.m_stride = (int)(d->lay.stats_elems / (size_t)(d->cfg.d_model / 16));
-        d->x_par ^= 1;
+            d->x_par ^= 1;
         return launch_gemm(d->dt, PRO_T, EPI_RESID_S, g, d->stream);
     }
     return launch_gemm(d->dt, PRO_T, EPI_RESID, g, d->stream);
@@ -429,7 +428,6 @@ hipError_t k_self_out_crossq(aed_decoder* d, int l) {
     a0.mu_hat_in = shift_buf(d, l & 1);
     a0.shadow_out = shadow_buf(d, d->x_par ^ 1);
     a0.stat_tiles = dm / 16;
-    a0.m_stride = (int)(d->lay.stats_elems / (size_t)(dm / 16));
     GemmArgs a1 = gemm_base(d, l);
     a1.A = d->act + d->lay.attn_out;
     a1.W = d->mw[l].w_p2;
@@ -470,7 +468,6 @@ hipError_t k_cross_attn(aed_decoder* d, int l) {
         a.q_c2 = d->fold[l].cq_c2;
         a.q_eps = d->cfg.ln_eps;
         a.q_stat_tiles = d->cfg.d_model / 16;
-        a.q_m_stride = (int)(d->lay.stats_elems / (size_t)(d->cfg.d_model / 16));
         a.q_rms = d->cfg.norm_type == 1;
     }
     return launch_attn_cross(d->dt, a, d->stream);
@@ -555,7 +552,6 @@ hipError_t enqueue_step(aed_decoder* d, const StateArgs& st, int greedy, int* st
         sa.shadow = shadow_buf(d, 0);
         sa.stats = stats_buf(d, 0);
         sa.mu_hat = shift_buf(d, 1);  // read as the shift of the rows entering layer 0
-        sa.m_stride = (int)(d->lay.stats_elems / (size_t)(d->cfg.d_model / 16));
         sa.rms = d->cfg.norm_type == 1;
     }
     e = launch_embed(d->dt, d->act_at<float>(d->lay.x), d->w.tok_emb, d->w.pos_emb, st, d->cfg.d_model,
@@ -739,7 +735,6 @@ aed_status prefill_pass(aed_decoder* d, const std::vector<int>& prompt_host, int
             sa.shadow = shadow_buf(d, 0);
                 sa.stats = stats_buf(d, 0);
             sa.mu_hat = shift_buf(d, 1);
-            sa.m_stride = (int)(d->lay.stats_elems / (size_t)(d->cfg.d_model / 16));
             sa.rms = d->cfg.norm_type == 1;
         }
         hipError_t e = launch_embed(d->dt, d->act_at<float>(d->lay.x), d->w.tok_emb, d->w.pos_emb, st, d->cfg.d_model,
@@ -1399,6 +1394,8 @@ aed_status aed_time_kernels(aed_decoder* d, int32_t cls, int32_t reps, float* ms
     if (!per_layer && cls != AED_K_LN_VOCAB && cls != AED_K_CROSS_KV) return fail(d, AED_EINVAL, "kernel class cannot be timed alone");
     d->act = d->ws;
     const int cap = d->state == aed_decoder::CONSUMED ? d->last_prompt_len + d->last_max_new : d->host_pos;
+    aed_status rc = upload_page_table(d);  // before the first step the device has none yet
+    if (rc != AED_OK) return rc;
     StateArgs st = d->state_args(0, 0);
     HIP_TRY(d, launch_prepare_timing(st, std::max(0, std::min(cap, d->cfg.max_dec_len) - 1), d->stream));
     int n = 0;

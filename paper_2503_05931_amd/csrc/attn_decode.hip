@@ -165,14 +165,14 @@ __global__ __launch_bounds__(64 * NW, sizeof(KV) <= 2 ? 4 : 1) void attn_decode_
         if constexpr (!SELF) {
             q_fix = a.q_stats != nullptr;
             // Only the first wavefront fetches what finishes the query (the row's tile statistics -- at most 64, one
-            // lane each, 64 separate lines -- and the two vectors); it hands the others rstd' and the vector
+            // lane each -- and the two vectors); it hands the others rstd' and the vector
             // c2 - rstd' (mu' - mu_hat) c1 through LDS.  Eight wavefronts fetching the same things cost 0.8 us of
             // load issue in front of the first key blocks.
             if (q_fix && wave == 0) {
                 const int n0 = h * DH + r * EPL;
                 load_f32<EPL>(a.q_c1 + n0, qc1);
                 load_f32<EPL>(a.q_c2 + n0, qc2);
-                if (lane < a.q_stat_tiles) q_st = a.q_stats[(size_t)lane * a.q_m_stride + b];
+                if (lane < a.q_stat_tiles) q_st = a.q_stats[(size_t)b * a.q_stat_tiles + lane];
                 q_muh = a.q_mu_hat[b];
             }
         }

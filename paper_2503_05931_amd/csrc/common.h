@@ -66,6 +66,25 @@ __device__ __forceinline__ f32x4 load4(const bf16_t* p) {
     return o;
 }
 
+// ---- a load from memory through a pointer that was selected from several (left to itself the compiler makes it a flat
+// load, which every later wait on memory or LDS has to wait for) ----
+template <typename V> __device__ __forceinline__ V load_global(const void* p) {
+    return *(const __attribute__((address_space(1))) V*)(uintptr_t)p;
+}
+
+// ---- a value at a wavefront-uniform address that no kernel in flight writes: a scalar load, which the memory counter of
+// the vector loads does not see ----
+template <typename V> __device__ __forceinline__ V load_const(const V* p) {
+    return *(const __attribute__((address_space(4))) V*)(uintptr_t)p;
+}
+
+// ---- 4 consecutive elements as they sit in memory, converted where they are used ----
+template <typename T> struct Raw4;
+template <> struct Raw4<float> { typedef f32x4 type; };
+template <> struct Raw4<bf16_t> { typedef bf16x4 type; };
+__device__ __forceinline__ f32x4 raw4_f32(f32x4 v) { return v; }
+__device__ __forceinline__ f32x4 raw4_f32(bf16x4 v) { return f32x4{(float)v[0], (float)v[1], (float)v[2], (float)v[3]}; }
+
 // ---- fragment layout ----
 // A [rows, K] matrix whose rows feed 16x16 MFMA tiles is kept in "fragment
 // order": 16-row x 64-k blocks, and inside a block the 16 consecutive k values
@@ -96,16 +115,28 @@ __device__ __forceinline__ float row16_sum(float v) {
     v += dpp_mov<0x140>(v);  // row_mirror
     return v;
 }
-// ---- sum / max over the four 16-lane rows of a wave (lanes l, l^16, l^32, l^48) ----
+// ---- sum / max over the four 16-lane rows of a wave (lanes l, l^16, l^32, l^48), with the lane-swap instructions
+// (a swap of a register with itself leaves the lower and the upper half-rows; no LDS round trip as __shfl_xor makes) ----
+__device__ __forceinline__ u32x2 swap16(float v) {
+    const unsigned u = __builtin_bit_cast(unsigned, v);
+    const auto p = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+    return u32x2{p[0], p[1]};
+}
+__device__ __forceinline__ u32x2 swap32(float v) {
+    const unsigned u = __builtin_bit_cast(unsigned, v);
+    const auto p = __builtin_amdgcn_permlane32_swap(u, u, false, false);
+    return u32x2{p[0], p[1]};
+}
+__device__ __forceinline__ float bits_f32(unsigned u) { return __builtin_bit_cast(float, u); }
 __device__ __forceinline__ float rows4_sum(float v) {
-    v += __shfl_xor(v, 16);
-    v += __shfl_xor(v, 32);
-    return v;
+    const u32x2 a = swap16(v);
+    const u32x2 b = swap32(bits_f32(a[0]) + bits_f32(a[1]));
+    return bits_f32(b[0]) + bits_f32(b[1]);
 }
 __device__ __forceinline__ float rows4_max(float v) {
-    v = fmaxf(v, __shfl_xor(v, 16));
-    v = fmaxf(v, __shfl_xor(v, 32));
-    return v;
+    const u32x2 a = swap16(v);
+    const u32x2 b = swap32(fmaxf(bits_f32(a[0]), bits_f32(a[1])));
+    return fmaxf(bits_f32(b[0]), bits_f32(b[1]));
 }
 
 // Folded normalisation (kernels.h, PRO_LNS): from a row's mean mu and its sum of squared deviations m2 over K
@@ -123,9 +154,7 @@ __device__ __forceinline__ float fold_norm(int rms, float K, float eps, float m2
 
 // sum over the 64 lanes of a wavefront; every lane gets the total
 __device__ __forceinline__ float wave_sum(float v) {
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off);
-    return v;
+    return rows4_sum(row16_sum(v));
 }
 
 }  // namespace aed

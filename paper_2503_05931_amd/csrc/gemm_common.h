@@ -103,10 +103,50 @@ __device__ __forceinline__ void store4_fp8(unsigned char* p, f32x4 s) {
     *reinterpret_cast<int*>(p) = w;
 }
 
+// Barrier for data exchanged through LDS: loads from memory stay in flight (__syncthreads waits for them too).
+__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+
+// (mean, sum of squared deviations) of a row from four tiles per lane of the 16 lanes that share it; every lane gets it
+__device__ __forceinline__ float2 combine_tile_stats(f32x4 u, f32x4 v, bool live, int tiles) {
+    const float mu = row16_sum(live ? (u[0] + u[2]) + (v[0] + v[2]) : 0.f) / (float)tiles;
+    const float d0 = u[0] - mu, d1 = u[2] - mu, d2 = v[0] - mu, d3 = v[2] - mu;
+    const float q = (u[1] + u[3]) + (v[1] + v[3]) + 16.f * ((d0 * d0 + d1 * d1) + (d2 * d2 + d3 * d3));
+    return float2{mu, row16_sum(live ? q : 0.f)};
+}
+// Mean and sum of squared deviations of rows [m0, m0 + BM) over all columns, from the 16-column tiles' (GemmArgs::stats_in),
+// into LDS; 256 threads, 16 lanes per row.  Mean of the tiles' means, then the tiles' own sums of squares plus
+// 16 x the squared distances of their means.  All loads first: one round trip.
+template <int BM> __device__ __forceinline__ void load_row_stats(const GemmArgs& a, int m0, float2* row_stat) {
+    constexpr int P = BM / 16;
+    const int row = threadIdx.x >> 4, t4 = 4 * (threadIdx.x & 15);
+    const bool live = t4 < a.stat_tiles;
+    f32x4 v[P][2];
+#pragma unroll
+    for (int p = 0; p < P; ++p) {
+        const f32x4* sp = reinterpret_cast<const f32x4*>(a.stats_in + (size_t)(m0 + 16 * p + row) * a.stat_tiles +
+                                                         min(t4, a.stat_tiles - 4));
+        v[p][0] = sp[0];
+        v[p][1] = sp[1];
+    }
+#pragma unroll
+    for (int p = 0; p < P; ++p) {
+        const float2 st = combine_tile_stats(v[p][0], v[p][1], live, a.stat_tiles);
+        if ((threadIdx.x & 15) == 0) row_stat[16 * p + row] = st;
+    }
+}
+
+// Where row m goes in the caches (rows from M on: anywhere valid, they are not stored)
+template <int EPI> __device__ __forceinline__ int row_slot(const GemmArgs& a, int m) {
+    if constexpr (EPI == EPI_QKV) return a.kv_slot[min(m, a.M - 1)];
+    else if constexpr (EPI == EPI_CROSSKV) return a.out_row_map ? a.out_row_map[min(m, a.M - 1)] : m;
+    else return -1;
+}
+
 // One lane's four consecutive outputs C[m][n .. n+3] (bias already added) go where the epilogue says.
-// res: the residual read earlier from the same place (EPI_RESID only).
+// res: the residual read earlier from the same place (EPI_RESID only); slot: EPI_QKV: kv_slot[m], EPI_CROSSKV: the frame
+// of row m -- read by the caller long before, so that no load stands in front of the stores.
 template <typename T, int EPI>
-__device__ __forceinline__ void gemm_epilogue(const GemmArgs& a, int m, int n, f32x4 s, f32x4 res) {
+__device__ __forceinline__ void gemm_epilogue(const GemmArgs& a, int m, int n, f32x4 s, f32x4 res, int slot) {
     constexpr int ES = sizeof(T);
     if constexpr (EPI == EPI_RESID) {
         *reinterpret_cast<f32x4*>(static_cast<char*>(a.out) + frag_elem_off<4>(m, n, a.N)) = res + s;
@@ -119,23 +159,20 @@ __device__ __forceinline__ void gemm_epilogue(const GemmArgs& a, int m, int n, f
         const int d = a.d_model;
         if (n < d) {
             store4(static_cast<float*>(a.out) + (size_t)m * d + n, s);
-        } else if (!a.finished[m]) {
+        } else if (slot >= 0) {
             const int which = n >= 2 * d;
-            const int c = n - (which ? 2 * d : d);
-            const int h = c / a.head_dim, e = c % a.head_dim;
-            const int pos = a.seq_len[m];
-            const int page = a.page_table[(size_t)m * a.max_pages + (pos >> 4)];
-            const size_t at = (((size_t)page * a.n_heads + h) * kPage + (pos & 15)) * a.head_dim + e;
+            const int c = n - (which ? 2 * d : d), sh = a.head_dim == 128 ? 7 : 6;
+            const int h = c >> sh, e = c & (a.head_dim - 1);
+            const size_t at = ((((size_t)(slot >> 4) * a.n_heads + h) * kPage + (slot & 15)) << sh) + e;
             if (a.kv_fp8) store4_fp8(static_cast<unsigned char*>(which ? a.v_pool : a.k_pool) + at, s);
             else store4(static_cast<T*>(which ? a.v_pool : a.k_pool) + at, s);
         }
     } else {  // EPI_CROSSKV
         const int d = a.d_model;
         const int which = n >= d;
-        const int c = n - (which ? d : 0);
-        const int h = c / a.head_dim, e = c % a.head_dim;
-        const size_t frame = a.out_row_map ? (size_t)a.out_row_map[m] : (size_t)m;
-        const size_t at = ((size_t)h * a.t_cap + frame) * a.head_dim + e;
+        const int c = n - (which ? d : 0), sh = a.head_dim == 128 ? 7 : 6;
+        const int h = c >> sh, e = c & (a.head_dim - 1);
+        const size_t at = (((size_t)h * a.t_cap + slot) << sh) + e;
         if (a.kv_fp8) store4_fp8(static_cast<unsigned char*>(which ? a.vc : a.kc) + at, s);
         else store4(static_cast<T*>(which ? a.vc : a.kc) + at, s);
     }

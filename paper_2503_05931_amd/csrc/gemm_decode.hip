@@ -32,20 +32,34 @@
 namespace aed {
 
 constexpr int kMaxLnBlocks = 4;  // PRO_LN: K <= 4 waves * 4 blocks * 64 = 1024
-constexpr int kMaxStatTilesPerGroup = 16;  // folded LayerNorm: d_model <= 1024 = 4 groups * 16 tiles * 16 columns
 
 // One output tile (column tile bx, row tile by) of the product described by a.
 // WNT: W is loaded with the non-temporal hint (GemmArgs::w_nt)
-template <typename T, int PRO, int EPI, int MT, int NT, bool WNT>
+// NB: 64-wide k blocks per wavefront, K = 256 NB, known at compile time; 0: any K
+//
+// What bounds a launch at decode batches is latency: 8 MB of weights stream in 1.5 us behind the first HBM access, so
+// every further round trip to memory shows.  Therefore
+//  * everything a workgroup reads -- the first blocks of both operands, then row statistics, vectors, residual tile,
+//    cache slots -- is requested before anything is waited for.  The memory counter is in order and a load behind a
+//    branch makes the compiler wait for all loads before it, so no load sits behind one: indices are clamped instead
+//    (buffers of fragment order are padded to whole tiles), null operands are read from W and replaced by zero;
+//  * with NB known the k loop is straight-line code and each block is waited for on its own; with a run-time k loop
+//    around conditional loads the compiler waited for the blocks just requested.
+template <typename T, int PRO, int EPI, int MT, int NT, bool WNT, int NB>
 __device__ __forceinline__ void gemm_decode_body(const GemmArgs& a, const int bx, const int by) {
     constexpr int BM = 16 * MT, BN = 16 * NT;
     constexpr int EP = (MT * NT * 64 + 255) / 256;  // output 4-vectors per thread in the epilogue
     constexpr int ES = sizeof(T);
-    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, r = lane & 15, g = lane >> 4;
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, r = lane & 15, g = lane >> 4;
     const int m0 = by * BM, n0 = bx * BN;
-    const int K = a.K, M = a.M;
+    const int K = NB > 0 ? NB * 256 : a.K, M = a.M;
     const int nblk = K >> 8;  // 64-wide k blocks per wavefront
     const char* __restrict__ W = static_cast<const char*>(a.W);
+    const char* __restrict__ A = static_cast<const char*>(a.A);
+
+    constexpr bool LNS = PRO == PRO_LNS;         // LayerNorm folded around the product (see kernels.h)
+    constexpr bool RS = EPI == EPI_RESID_S;      // residual update that also writes shadow and statistics
+    constexpr bool RES = EPI == EPI_RESID || RS;
 
     __shared__ f32x4 part[4][MT * NT][64];
     __shared__ float red[2][4][BM];
@@ -61,167 +75,125 @@ __device__ __forceinline__ void gemm_decode_body(const GemmArgs& a, const int bx
         return reinterpret_cast<const T*>(W + frag_block_off<ES>((n0 >> 4) + nt, i * 4 + wave, K));
     };
 
-    // ---- the operand stream (everything but the float32-mode LayerNorm prologue)
-    const char* __restrict__ A = static_cast<const char*>(a.A);
-    // U blocks are fetched per group, two groups in flight (register double buffer)
-    constexpr int U = (MT + NT) <= 2 ? 4 : ((MT + NT) <= 4 ? 2 : 1);
-    Frag16<T> af[2][U][MT], wf[2][U][NT];
-    auto fetch = [&](int buf, int blk0) {
+    // ---- the operand stream (everything but the float32-mode LayerNorm prologue): ring of D blocks in registers
+    constexpr int D0 = (MT + NT) <= 2 ? 8 : (MT + NT) <= 4 ? 4 : 2;
+    constexpr int DMAX = ES == 4 && D0 > 2 ? D0 / 2 : D0;
+    constexpr int D = PRO == PRO_LN ? 1 : (NB > 0 && NB < DMAX ? NB : DMAX);
+    Frag16<T> af[D][MT], wf[D][NT];
+    auto fetch = [&](int slot, int i) {
 #pragma unroll
-        for (int u = 0; u < U; ++u) {
-            const int i = blk0 + u;
-            if (i < nblk) {
+        for (int nt = 0; nt < NT; ++nt) wf[slot][nt] = WNT ? load_frag_nt(wblk(nt, i), lane) : load_frag(wblk(nt, i), lane);
 #pragma unroll
-                for (int nt = 0; nt < NT; ++nt) wf[buf][u][nt] = WNT ? load_frag_nt(wblk(nt, i), lane) : load_frag(wblk(nt, i), lane);
+        for (int mt = 0; mt < MT; ++mt)
+            af[slot][mt] = load_frag(reinterpret_cast<const T*>(A + frag_block_off<ES>((m0 >> 4) + mt, i * 4 + wave, K)), lane);
+    };
+    auto compute = [&](int slot) {
 #pragma unroll
-                for (int mt = 0; mt < MT; ++mt)
-                    af[buf][u][mt] = load_frag(
-                        reinterpret_cast<const T*>(A + frag_block_off<ES>((m0 >> 4) + mt, i * 4 + wave, K)), lane);
+        for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt) mma(acc[mt][nt], wf[slot][nt], af[slot][mt]);
+    };
+    // LNS: tile statistics of the rows being multiplied, 16 lanes per row, four 16-column tiles per lane.  Of 16 rows they
+    // are requested in front of the stream and combined while it is on its way (4.13 -> 3.96 us for the QKV product of one
+    // row); of more rows they would hold it back (8.2 -> 8.9 us at 256 rows) and are requested behind its first blocks.
+    constexpr int SP = LNS ? MT : 1;
+    constexpr bool ST_FIRST = MT == 1;
+    f32x4 sv[SP][2];
+    auto fetch_stats = [&]() {
+#pragma unroll
+        for (int p = 0; p < SP; ++p) {
+            const f32x4* sp = reinterpret_cast<const f32x4*>(a.stats_in + (size_t)(m0 + 16 * p + (tid >> 4)) * a.stat_tiles +
+                                                             min(4 * (tid & 15), a.stat_tiles - 4));
+            sv[p][0] = sp[0];
+            sv[p][1] = sp[1];
+        }
+    };
+    auto combine_stats = [&]() {
+#pragma unroll
+        for (int p = 0; p < SP; ++p) {
+            float2 st = combine_tile_stats(sv[p][0], sv[p][1], 4 * (tid & 15) < a.stat_tiles, a.stat_tiles);
+            const float rstd = fold_norm(a.rms, (float)K, a.ln_eps, st.y, st.x);
+            if ((tid & 15) == 0) {
+                red[0][0][16 * p + (tid >> 4)] = st.x;
+                red[1][0][16 * p + (tid >> 4)] = rstd;
             }
         }
     };
-    auto compute = [&](int buf, int blk0) {
+    if constexpr (LNS && ST_FIRST) fetch_stats();
+    if constexpr (PRO != PRO_LN) {
 #pragma unroll
-        for (int u = 0; u < U; ++u)
-            if (blk0 + u < nblk)
-#pragma unroll
-                for (int nt = 0; nt < NT; ++nt)
-#pragma unroll
-                    for (int mt = 0; mt < MT; ++mt) mma(acc[mt][nt], wf[buf][u][nt], af[buf][u][mt]);
-    };
-    // The stream's first requests go out before anything else: every request in front of them (the epilogue's
-    // operands below are a dozen or two per wavefront) holds the whole stream back by its issue time.
-    if constexpr (PRO != PRO_LN) fetch(0, 0);
+        for (int u = 0; u < D; ++u) fetch(u, NB > 0 ? u : min(u, nblk - 1));
+        __builtin_amdgcn_sched_barrier(0);
+    }
 
-    // Epilogue operands do not depend on the product: they are requested here, behind the stream's first group, and
-    // have long arrived when the stream is through.
-    constexpr bool LNS = PRO == PRO_LNS;         // LayerNorm folded around the product (see kernels.h)
-    constexpr bool RS = EPI == EPI_RESID_S;      // residual update that also writes shadow and statistics
-    constexpr bool RES = EPI == EPI_RESID || RS;
+    // ---- epilogue operands (they do not depend on the product), requested behind the stream's first blocks
     const T* __restrict__ bias = static_cast<const T*>(a.bias);
+    // columns from n_raw on are not normalised here (n_raw is a multiple of every tile width: uniform)
+    const bool raw = LNS && a.n_raw > 0 && n0 >= a.n_raw;
+    // kept as loaded (null bias / addend: whatever W holds there) until the epilogue uses them: a conversion or a select
+    // here would wait for everything requested so far
     f32x4 e_bias[EP], e_res[EP], e_aux[EP];  // e_aux: c1 (LNS)
+    typename Raw4<T>::type e_rbias[EP];      // not LNS
     float e_mu[EP];                          // LNS: the shift this row's shadow was written with; RS: the row's
                                              // mean before the update = the shift its new shadow is written with
+    int e_slot[EP];                          // EPI_QKV: cache slot of the row; EPI_CROSSKV: its frame
+    auto tile_row = [&](int t, int l) { return m0 + (t / NT) * 16 + (l & 15); };
+    auto tile_col = [&](int t, int l) { return n0 + (t % NT) * 16 + (l >> 4) * 4; };
 #pragma unroll
     for (int j = 0; j < EP; ++j) {
-        const int idx = tid + 256 * j;
-        const int t = idx >> 6, l = idx & 63;
-        const int m = m0 + (t / NT) * 16 + (l & 15);
-        const int n = n0 + (t % NT) * 16 + (l >> 4) * 4;
-        const bool live = idx < MT * NT * 64 && m < M;
-        const f32x4 zero = f32x4{0.f, 0.f, 0.f, 0.f};
+        const int t = MT * NT < 4 ? min(wave, MT * NT - 1) : wave + 4 * j;
+        const int m = tile_row(t, lane), n = tile_col(t, lane), mc = min(m, M - 1);
         if constexpr (LNS) {
-            const bool raw = a.n_raw > 0 && n >= a.n_raw;  // columns from n_raw on are not normalised here
-            e_bias[j] = !live ? zero : *reinterpret_cast<const f32x4*>(raw ? a.raw_bias + (n - a.n_raw) : a.ln_c2 + n);
-            e_aux[j] = live && !raw ? *reinterpret_cast<const f32x4*>(a.ln_c1 + n) : zero;
+            e_bias[j] = load_global<f32x4>(raw ? a.raw_bias + (n - a.n_raw) : a.ln_c2 + n);
+            e_aux[j] = *reinterpret_cast<const f32x4*>(a.ln_c1 + (raw ? n - a.n_raw : n));
         } else {
-            e_bias[j] = (bias && live) ? load4(bias + n) : zero;
+            e_rbias[j] = load_global<typename Raw4<T>::type>(bias ? static_cast<const void*>(bias + n) : W);
         }
-        if constexpr (LNS || RS) e_mu[j] = live ? a.mu_hat_in[m] : 0.f;
-        if constexpr (RES)
-            e_res[j] = live ? *reinterpret_cast<const f32x4*>(static_cast<const char*>(a.out) + frag_elem_off<4>(m, n, a.N))
-                            : zero;
+        if constexpr (LNS || RS) e_mu[j] = a.mu_hat_in[m];
+        if constexpr (RES) e_res[j] = *reinterpret_cast<const f32x4*>(static_cast<const char*>(a.out) + frag_elem_off<4>(m, n, a.N));
         if constexpr (EPI == EPI_F32 && !LNS)  // optional addend, float [M,N] row-major like the output
-            e_res[j] = (live && a.addend) ? *reinterpret_cast<const f32x4*>(a.addend + (size_t)m * a.N + n) : zero;
+            e_res[j] = load_global<f32x4>(a.addend ? static_cast<const void*>(a.addend + (size_t)mc * a.N + n) : W);
+        if constexpr (EPI == EPI_QKV) e_slot[j] = a.kv_slot[mc];
+        if constexpr (EPI == EPI_CROSSKV) e_slot[j] = load_global<int>(a.out_row_map ? static_cast<const void*>(a.out_row_map + mc) : W);
     }
-    // EPI_QKV: where this thread's key / value columns go in the paged cache (element index, -1: nowhere).  The
-    // sequence's state and its page-table entry are two dependent loads; fetched here, they are off the critical
-    // path at the end.
-    long long e_kv[EP];
-    if constexpr (EPI == EPI_QKV) {
-#pragma unroll
-        for (int j = 0; j < EP; ++j) {
-            const int idx = tid + 256 * j;
-            const int t = idx >> 6, l = idx & 63;
-            const int m = m0 + (t / NT) * 16 + (l & 15);
-            const int n = n0 + (t % NT) * 16 + (l >> 4) * 4;
-            e_kv[j] = -1;
-            if (idx < MT * NT * 64 && m < M && n >= a.d_model && n < 3 * a.d_model && !a.finished[m]) {
-                const int c = n - (n >= 2 * a.d_model ? 2 * a.d_model : a.d_model);
-                const int h = c / a.head_dim, e = c % a.head_dim;
-                const int pos = a.seq_len[m];
-                const int page = a.page_table[(size_t)m * a.max_pages + (pos >> 4)];
-                e_kv[j] = (((long long)page * a.n_heads + h) * kPage + (pos & 15)) * a.head_dim + e;
-            }
-        }
-    }
-    // the epilogue of EPI_QKV with the cache position already known
-    auto store_qkv = [&](int m, int n, f32x4 s, long long at) {
-        if (n < a.d_model) {
-            store4(static_cast<float*>(a.out) + (size_t)m * a.d_model + n, s);
-        } else if (at >= 0) {
-            void* pool = n >= 2 * a.d_model ? a.v_pool : a.k_pool;
-            if (a.kv_fp8) store4_fp8(static_cast<unsigned char*>(pool) + at, s);
-            else store4(static_cast<T*>(pool) + at, s);
-        }
-    };
-    float stat_n = 0.f;  // elements behind each of the four partial results of the row statistics
-    // mean and sum of squared deviations of local row rl over all columns, from the four partial results
-    auto row_stats = [&](int rl, float& mu, float& m2) {
-        const float a0 = red[0][0][rl], a1 = red[0][1][rl], a2 = red[0][2][rl], a3 = red[0][3][rl];
-        mu = 0.25f * (a0 + a1 + a2 + a3);
-        const float d0 = a0 - mu, d1 = a1 - mu, d2 = a2 - mu, d3 = a3 - mu;
-        m2 = red[1][0][rl] + red[1][1][rl] + red[1][2][rl] + red[1][3][rl] + stat_n * (d0 * d0 + d1 * d1 + d2 * d2 + d3 * d3);
-    };
+    if constexpr (LNS && !ST_FIRST) fetch_stats();
+    // the arguments that only the epilogue uses, into scalar registers now: read there, they are one more round trip
+    asm volatile("" ::"s"(a.out));
+    if constexpr (RS) asm volatile("" ::"s"(a.shadow_out), "s"(a.stats_out), "s"(a.N), "s"(a.stat_tiles));
+    if constexpr (EPI == EPI_QKV) asm volatile("" ::"s"(a.k_pool), "s"(a.v_pool), "s"(a.kv_fp8), "s"(a.n_heads), "s"(a.head_dim), "s"(a.d_model));
+    if constexpr (EPI == EPI_CROSSKV) asm volatile("" ::"s"(a.kc), "s"(a.vc), "s"(a.kv_fp8), "s"(a.t_cap), "s"(a.head_dim), "s"(a.d_model));
+    if constexpr (LNS) asm volatile("" ::"s"(a.mu_hat_out), "s"(a.rms), "s"(a.ln_eps), "s"(a.stat_tiles), "s"(a.N));
+    __builtin_amdgcn_sched_barrier(0);
 
-    // LNS: statistics of the rows being multiplied: four groups of threads combine a quarter of the 16-column
-    // tiles each; the epilogue combines the four.  The loads go out here, ahead of the operand stream; nothing
-    // waits for them before the stream is through.
-    float2 sv[kMaxStatTilesPerGroup];
-    const int st_row = tid % BM, st_grp = tid / BM, st_per = a.stat_tiles >> 2;
-    if constexpr (LNS) {
-        stat_n = 16.f * (float)st_per;
-        const float2* sp = a.stats_in + (size_t)((st_grp & 3) * st_per) * a.m_stride + (m0 + st_row);
-#pragma unroll
-        for (int t = 0; t < kMaxStatTilesPerGroup; ++t)
-            sv[t] = (t < st_per && st_grp < 4) ? sp[(size_t)t * a.m_stride] : float2{0.f, 0.f};
-    }
-    auto combine_row_stats = [&]() {  // equal-sized parts: mean of the means, then the parts' own sums of squares
-                                      // plus 16 x the squared distances of their means (fixed order, no long chain)
-        float sm = 0.f, sq = 0.f;
-#pragma unroll
-        for (int t = 0; t < kMaxStatTilesPerGroup; ++t) {
-            sm += sv[t].x;  // entries beyond st_per are zero
-            sq += sv[t].y;
-        }
-        const float mean = sm / (float)st_per;
-        float dev = 0.f;
-#pragma unroll
-        for (int t = 0; t < kMaxStatTilesPerGroup; ++t)
-            if (t < st_per) dev += (sv[t].x - mean) * (sv[t].x - mean);
-        if (st_grp < 4) {
-            red[0][st_grp][st_row] = mean;
-            red[1][st_grp][st_row] = sq + 16.f * dev;
-        }
-    };
-
+    if constexpr (LNS && ST_FIRST) combine_stats();
     if constexpr (PRO == PRO_LN) {
         const char* __restrict__ X = static_cast<const char*>(a.A);
-        Frag16<float> xs[MT][kMaxLnBlocks];
+        constexpr int NL = NB > 0 ? NB : kMaxLnBlocks;
+        Frag16<float> xs[MT][NL];
+        // the rows first (their statistics are needed first), then the weights; with NB known no block is conditional
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
-            for (int i = 0; i < kMaxLnBlocks; ++i)
-                if (i < nblk)
+            for (int i = 0; i < NL; ++i)
+                if (NB > 0 || i < nblk)
                     xs[mt][i] = load_frag(
                         reinterpret_cast<const float*>(X + frag_block_off<4>((m0 >> 4) + mt, i * 4 + wave, K)), lane);
         // the weight stream starts before the statistics are known
-        Frag16<T> wf[NT][kMaxLnBlocks];
+        Frag16<T> wl[NT][NL];
 #pragma unroll
-        for (int i = 0; i < kMaxLnBlocks; ++i)
-            if (i < nblk)
+        for (int i = 0; i < NL; ++i)
+            if (NB > 0 || i < nblk)
 #pragma unroll
-                for (int nt = 0; nt < NT; ++nt) wf[nt][i] = WNT ? load_frag_nt(wblk(nt, i), lane) : load_frag(wblk(nt, i), lane);
+                for (int nt = 0; nt < NT; ++nt) wl[nt][i] = WNT ? load_frag_nt(wblk(nt, i), lane) : load_frag(wblk(nt, i), lane);
         // LayerNorm gain/shift for this lane's k values, fetched before the statistics are known
         const T* __restrict__ G = static_cast<const T*>(a.ln_g);
         const T* __restrict__ Bt = static_cast<const T*>(a.ln_b);
-        Frag16<T> gam_f[kMaxLnBlocks], bet_f[kMaxLnBlocks];
+        Frag16<T> gam_f[NL], bet_f[NL];
 #pragma unroll
-        for (int i = 0; i < kMaxLnBlocks; ++i)
-            if (i < nblk) {
+        for (int i = 0; i < NL; ++i)
+            if (NB > 0 || i < nblk) {
                 gam_f[i] = load_frag_rm(G + (i * 4 + wave) * 64 + g * 16);
-                if (Bt) bet_f[i] = load_frag_rm(Bt + (i * 4 + wave) * 64 + g * 16);
-                else zero_frag(bet_f[i]);
+                bet_f[i] = load_frag_rm((Bt ? Bt : G) + (i * 4 + wave) * 64 + g * 16);
             }
         // row mean
         float mean[MT], rstd[MT];
@@ -229,22 +201,22 @@ __device__ __forceinline__ void gemm_decode_body(const GemmArgs& a, const int bx
         for (int mt = 0; mt < MT; ++mt) {
             float s = 0.f;
 #pragma unroll
-            for (int i = 0; i < kMaxLnBlocks; ++i)
-                if (i < nblk)
+            for (int i = 0; i < NL; ++i)
+                if (NB > 0 || i < nblk)
 #pragma unroll
                     for (int e = 0; e < 16; ++e) s += xs[mt][i].v[e];
             s = rows4_sum(s);
             if (g == 0) red[0][wave][mt * 16 + r] = s;
         }
-        __syncthreads();
+        lds_barrier();  // the weights stay in flight
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt) {
             int i = mt * 16 + r;
             mean[mt] = a.rms ? 0.f : (red[0][0][i] + red[0][1][i] + red[0][2][i] + red[0][3][i]) / (float)K;
             float s = 0.f;
 #pragma unroll
-            for (int b = 0; b < kMaxLnBlocks; ++b)
-                if (b < nblk)
+            for (int b = 0; b < NL; ++b)
+                if (NB > 0 || b < nblk)
 #pragma unroll
                     for (int e = 0; e < 16; ++e) {
                         float c = xs[mt][b].v[e] - mean[mt];
@@ -253,7 +225,7 @@ __device__ __forceinline__ void gemm_decode_body(const GemmArgs& a, const int bx
             s = rows4_sum(s);
             if (g == 0) red[1][wave][i] = s;
         }
-        __syncthreads();
+        lds_barrier();
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt) {
             int i = mt * 16 + r;
@@ -261,35 +233,55 @@ __device__ __forceinline__ void gemm_decode_body(const GemmArgs& a, const int bx
             rstd[mt] = 1.0f / sqrtf(var + a.ln_eps);
         }
 #pragma unroll
-        for (int i = 0; i < kMaxLnBlocks; ++i) {
-            if (i < nblk) {
+        for (int i = 0; i < NL; ++i) {
+            if (NB > 0 || i < nblk) {
                 float gam[16], bet[16];
                 unpack_frag(gam_f[i], gam);
                 unpack_frag(bet_f[i], bet);
-                Frag16<T> af[MT];
+#pragma unroll
+                for (int e = 0; e < 16; ++e) bet[e] = Bt ? bet[e] : 0.f;
+                Frag16<T> al[MT];
 #pragma unroll
                 for (int mt = 0; mt < MT; ++mt) {
                     float y[16];
 #pragma unroll
                     for (int e = 0; e < 16; ++e) y[e] = (xs[mt][i].v[e] - mean[mt]) * rstd[mt] * gam[e] + bet[e];
-                    pack_frag(y, af[mt]);
+                    pack_frag(y, al[mt]);
                 }
 #pragma unroll
                 for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
-                    for (int mt = 0; mt < MT; ++mt) mma(acc[mt][nt], wf[nt][i], af[mt]);
+                    for (int mt = 0; mt < MT; ++mt) mma(acc[mt][nt], wl[nt][i], al[mt]);
             }
         }
-    } else {
-        for (int b0 = 0; b0 < nblk; b0 += 2 * U) {
-            fetch(1, b0 + U);
-            compute(0, b0);
-            fetch(0, b0 + 2 * U);
-            compute(1, b0 + U);
+    } else if constexpr (NB > 0) {
+#pragma unroll
+        for (int i = 0; i < NB; ++i) {
+            compute(i % D);
+            if (i + D < NB) fetch(i % D, i + D);
+            __builtin_amdgcn_sched_barrier(0);
         }
+    } else {
+        int b0 = 0;
+        for (; b0 + 2 * D <= nblk; b0 += D)
+#pragma unroll
+            for (int u = 0; u < D; ++u) {
+                compute(u);
+                fetch(u, b0 + D + u);
+            }
+        const int rem = nblk - b0;  // the ring holds the next min(rem, D) blocks; rem < 2 D
+#pragma unroll
+        for (int u = 0; u < D; ++u)
+            if (u < rem) {
+                compute(u);
+                if (D + u < rem) fetch(u, b0 + D + u);
+            }
+#pragma unroll
+        for (int u = 0; u < D; ++u)
+            if (D + u < rem) compute(u);
     }
 
-    if constexpr (LNS) combine_row_stats();
+    if constexpr (LNS && !ST_FIRST) combine_stats();
     // ---- sum the four wavefronts' partial tiles in a fixed order, then the epilogue ----
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt)
@@ -299,30 +291,31 @@ __device__ __forceinline__ void gemm_decode_body(const GemmArgs& a, const int bx
 
 #pragma unroll
     for (int j = 0; j < EP; ++j) {
-        const int idx = tid + 256 * j;
-        if (idx >= MT * NT * 64) continue;
-        const int t = idx >> 6, l = idx & 63;
+        const int t = wave + 4 * j, l = lane;
+        if (MT * NT < 4 && t >= MT * NT) continue;
         f32x4 s = part[0][t][l];
         s += part[1][t][l];
         s += part[2][t][l];
         s += part[3][t][l];
-        const int mt = t / NT, nt = t % NT;
-        const int m = m0 + mt * 16 + (l & 15);
-        const int n = n0 + nt * 16 + (l >> 4) * 4;
+        const int m = tile_row(t, l), n = tile_col(t, l);
         if (m >= M) continue;
+        if constexpr (!LNS) {
+            const f32x4 b = raw4_f32(e_rbias[j]);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) e_bias[j][e] = bias ? b[e] : 0.f;
+        }
+        if constexpr (EPI == EPI_CROSSKV) e_slot[j] = a.out_row_map ? e_slot[j] : m;
         if constexpr (LNS) {
-            float mu, m2;
-            row_stats(mt * 16 + (l & 15), mu, m2);
-            const float rstd = fold_norm(a.rms, (float)K, a.ln_eps, m2, mu), shift = mu - e_mu[j];
-            if (a.n_raw > 0 && n >= a.n_raw) {
+            const int rl = m - m0;
+            const float mu = red[0][0][rl], rstd = red[1][0][rl], shift = mu - e_mu[j];
+            if (raw) {
                 // a product that belongs to a later normalisation of these rows (kernels.h, "merged products"):
                 // the bare sums (plus raw_bias) go to out2, whoever reads them finishes them
                 store4(a.out2 + (size_t)m * (a.N - a.n_raw) + (n - a.n_raw), s + e_bias[j]);
                 continue;
             }
             s = (s - shift * e_aux[j]) * rstd + e_bias[j];
-            if constexpr (EPI == EPI_QKV) store_qkv(m, n, s, e_kv[j]);
-            else gemm_epilogue<T, EPI>(a, m, n, s, e_res[j]);
+            gemm_epilogue<T, EPI>(a, m, n, s, e_res[j], e_slot[j]);
             if (n == 0 && a.mu_hat_out) a.mu_hat_out[m] = mu;  // the layer's residual updates shift their shadows by this
         } else if constexpr (RS) {
             const float mu_old = e_mu[j];
@@ -330,43 +323,35 @@ __device__ __forceinline__ void gemm_decode_body(const GemmArgs& a, const int bx
             *reinterpret_cast<f32x4*>(static_cast<char*>(a.out) + frag_elem_off<4>(m, n, a.N)) = x;
             store4(reinterpret_cast<T*>(static_cast<char*>(a.shadow_out) + frag_elem_off<ES>(m, n, a.N)), x - mu_old);
             // this row's 16 columns of the tile sit in the four lanes l, l ^ 16, l ^ 32, l ^ 48
-            float sum = (x[0] + x[1]) + (x[2] + x[3]);
-            sum += __shfl_xor(sum, 16);
-            sum += __shfl_xor(sum, 32);
-            const float tmean = sum * (1.f / 16.f);
+            const float tmean = rows4_sum((x[0] + x[1]) + (x[2] + x[3])) * (1.f / 16.f);
             const f32x4 dv = x - tmean;
-            float q = (dv[0] * dv[0] + dv[1] * dv[1]) + (dv[2] * dv[2] + dv[3] * dv[3]);
-            q += __shfl_xor(q, 16);
-            q += __shfl_xor(q, 32);
-            if ((l >> 4) == 0) {
-                a.stats_out[(size_t)(n >> 4) * a.m_stride + m] = float2{tmean, q};
-            }
+            const float q = rows4_sum((dv[0] * dv[0] + dv[1] * dv[1]) + (dv[2] * dv[2] + dv[3] * dv[3]));
+            if ((l >> 4) == 0) a.stats_out[(size_t)m * a.stat_tiles + (n >> 4)] = float2{tmean, q};
         } else {
             s += e_bias[j];
-            if constexpr (EPI == EPI_F32) s += e_res[j];
-            if constexpr (EPI == EPI_QKV) store_qkv(m, n, s, e_kv[j]);
-            else gemm_epilogue<T, EPI>(a, m, n, s, e_res[j]);
+            if constexpr (EPI == EPI_F32) { if (a.addend) s += e_res[j]; }
+            gemm_epilogue<T, EPI>(a, m, n, s, e_res[j], e_slot[j]);
         }
     }
 }
 
-template <typename T, int PRO, int EPI, int MT, int NT, bool WNT>
+template <typename T, int PRO, int EPI, int MT, int NT, bool WNT, int NB>
 __global__ __launch_bounds__(256) void gemm_decode_kernel(GemmArgs a) {
-    gemm_decode_body<T, PRO, EPI, MT, NT, WNT>(a, blockIdx.x, blockIdx.y);
+    gemm_decode_body<T, PRO, EPI, MT, NT, WNT, NB>(a, blockIdx.x, blockIdx.y);
 }
 
 // Two products of the same operand in one launch: the first n0 workgroups are the tiles of a0 (a residual update,
 // EPI_RESID_S), the others the tiles of a1 (kernels.h, "merged products").  Neither reads what the other writes.
-template <typename T, int MT0, int NT0, int EPI1, int MT1, int NT1, bool WNT>
+template <typename T, int MT, int NT, int EPI1, bool WNT, int NB>
 __global__ __launch_bounds__(256) void gemm_decode_pair_kernel(GemmArgs a0, GemmArgs a1, int n0) {
     int b = blockIdx.x;
     if (b < n0) {
-        const int nx = a0.N / (16 * NT0);
-        gemm_decode_body<T, PRO_T, EPI_RESID_S, MT0, NT0, WNT>(a0, b % nx, b / nx);
+        const int nx = a0.N / (16 * NT);
+        gemm_decode_body<T, PRO_T, EPI_RESID_S, MT, NT, WNT, NB>(a0, b % nx, b / nx);
     } else {
         b -= n0;
-        const int nx = a1.N / (16 * NT1);
-        gemm_decode_body<T, PRO_T, EPI1, MT1, NT1, WNT>(a1, b % nx, b / nx);
+        const int nx = a1.N / (16 * NT);
+        gemm_decode_body<T, PRO_T, EPI1, MT, NT, WNT, NB>(a1, b % nx, b / nx);
     }
 }
 
@@ -435,54 +420,69 @@ __global__ __launch_bounds__(256) void layernorm_frag_kernel(const char* __restr
     store_frag(reinterpret_cast<T*>(Hout + frag_block_off<ES>(row >> 4, kb, K)), frag_lane, f);
 }
 
-constexpr int kWntMaxM = 128;
+// The non-temporal hint for W (GemmArgs::w_nt) goes with launches of one workgroup per CU in at most four row tiles: the
+// workgroups that share a panel of W then ask for it at the same time.  Later ones find nothing left of it in L2 (64 x 4096
+// output of K = 1024 as 512 tiles of 16 x 32: 5.1 us without, 5.9 us with the hint; as 256 tiles of 32 x 32: 4.75, 4.62).
+constexpr long kCus = 256;
+static bool hint_w(const GemmArgs& a, long wgs, int row_tiles) { return a.w_nt && wgs <= kCus && row_tiles <= 4; }
+
+template <typename T, int PRO, int EPI, int MT, int NT, int NB>
+static hipError_t launch_nb(const GemmArgs& a, hipStream_t s) {
+    dim3 grid(a.N / (16 * NT), (a.M + 16 * MT - 1) / (16 * MT));
+    if (hint_w(a, (long)grid.x * grid.y, grid.y)) hipLaunchKernelGGL((gemm_decode_kernel<T, PRO, EPI, MT, NT, true, NB>), grid, dim3(256), 0, s, a);
+    else hipLaunchKernelGGL((gemm_decode_kernel<T, PRO, EPI, MT, NT, false, NB>), grid, dim3(256), 0, s, a);
+    return hipGetLastError();
+}
+// K = 1024 and, for the second FFN product, K = 4096 are unrolled; every other K runs the loop
 template <typename T, int PRO, int EPI, int MT, int NT>
 static hipError_t launch_one(const GemmArgs& a, hipStream_t s) {
-    dim3 grid(a.N / (16 * NT), (a.M + 16 * MT - 1) / (16 * MT));
-    // the hint only where few row tiles share W: with many (measured at M = 1024) they need it from the cache
-    if (a.w_nt && a.M <= kWntMaxM) hipLaunchKernelGGL((gemm_decode_kernel<T, PRO, EPI, MT, NT, true>), grid, dim3(256), 0, s, a);
-    else hipLaunchKernelGGL((gemm_decode_kernel<T, PRO, EPI, MT, NT, false>), grid, dim3(256), 0, s, a);
-    return hipGetLastError();
+    if (a.K == 1024) return launch_nb<T, PRO, EPI, MT, NT, 4>(a, s);
+    if constexpr (EPI == EPI_RESID || EPI == EPI_RESID_S)
+        if (a.K == 4096) return launch_nb<T, PRO, EPI, MT, NT, 16>(a, s);
+    return launch_nb<T, PRO, EPI, MT, NT, 0>(a, s);
 }
 
 // Tile choice by a traffic model: each workgroup pulls (BM * bytes(A) + BN * bytes(W)) * K
 // through its CU and the launch's workgroups are spread over the 256 CUs; pick the
-// candidate with the least bytes per CU, then the fewest workgroups.
+// candidate with the least bytes per CU, then the fewest workgroups.  n_out: output columns of the whole launch.
+enum TileId { T11, T21, T22, T24, T42, T44 };
 template <typename T, int PRO>
-static int choose_tile(const GemmArgs& a) {
+static TileId choose_tile(const GemmArgs& a, int n_out) {
     struct Cand { int mt, nt; };
-    static const Cand cands[] = {{1, 1}, {2, 2}, {2, 4}, {4, 2}, {4, 4}};
-    const double a_bytes = PRO == PRO_LN ? 4.0 : sizeof(T), w_bytes = sizeof(T);
+    static const Cand cands[] = {{1, 1}, {2, 1}, {2, 2}, {2, 4}, {4, 2}, {4, 4}};
+    // W mostly comes from memory, A from the caches; the folded LayerNorm reads 512 bytes of statistics per row of 2 KB
+    const double a_bytes = PRO == PRO_LN ? 4.0 : PRO == PRO_LNS ? 1.25 * sizeof(T) : sizeof(T), w_bytes = 1.15 * sizeof(T);
     int best = 0;
     double best_cost = 1e300;
     long best_wgs = 0;
     // float32 fragments are twice as wide, and the fused LayerNorm keeps its rows in registers: small tiles only
-    const int n_cands = (sizeof(T) == 4 || PRO == PRO_LN) ? 2 : 5;
+    const int n_cands = (sizeof(T) == 4 || PRO == PRO_LN) ? 3 : 6;
     static_assert(PRO != PRO_LNS || sizeof(T) == 2, "the folded LayerNorm is a bfloat16-mode path");
     for (int c = 0; c < n_cands; ++c) {
         const int bm = 16 * cands[c].mt, bn = 16 * cands[c].nt;
-        if (a.N % bn != 0) continue;
-        const long wgs = (long)((a.M + bm - 1) / bm) * (a.N / bn);
+        if (a.N % bn != 0 || (c == T21 && (sizeof(T) == 4 || PRO == PRO_LN))) continue;
+        const long wgs = (long)((a.M + bm - 1) / bm) * (n_out / bn);
         // Workgroups of the smaller tiles share a CU (two or three fit by registers), so beyond 256 workgroups the
         // bytes through a CU grow in proportion, not in whole rounds.  The 64 x 64 tile runs one workgroup per CU
         // and its stream costs about half more than its bytes say when K is short (measured at M = 256, K = 1024:
         // 9.7 us against 8.2 us for the 32 x 64 tile on the QKV product); over K = 4096 the start-up is a smaller
         // part and the bytes decide (second FFN product at M = 1024: 18.1 us against 19.4 us for 32 x 64).
-        const double rounds = wgs > 256 ? (double)wgs / 256.0 : 1.0;
-        const double cost = rounds * (bm * a_bytes + bn * w_bytes) * (c == 4 && a.K < 4096 ? 1.6 : 1.0);
+        const double rounds = wgs > kCus ? (double)wgs / kCus : 1.0;
+        const double cost = rounds * (bm * a_bytes + bn * w_bytes) * (c == T44 && a.K < 4096 ? 1.6 : 1.0);
         if (cost < best_cost || (cost == best_cost && wgs < best_wgs)) { best = c; best_cost = cost; best_wgs = wgs; }
     }
-    return best;
+    return (TileId)best;
 }
 
 template <typename T, int PRO, int EPI>
 static hipError_t launch_tiles(const GemmArgs& a, hipStream_t s) {
-    const int best = choose_tile<T, PRO>(a);
-    if (best == 0) return launch_one<T, PRO, EPI, 1, 1>(a, s);
-    if (best == 1) return launch_one<T, PRO, EPI, 2, 2>(a, s);
-    if constexpr (PRO != PRO_LN) {
-        if (best == 2) return launch_one<T, PRO, EPI, 2, 4>(a, s);
-        if (best == 3) return launch_one<T, PRO, EPI, 4, 2>(a, s);
+    const TileId best = choose_tile<T, PRO>(a, a.N);
+    if (best == T11) return launch_one<T, PRO, EPI, 1, 1>(a, s);
+    if (best == T22) return launch_one<T, PRO, EPI, 2, 2>(a, s);
+    if constexpr (PRO != PRO_LN && sizeof(T) == 2) {
+        if (best == T21) return launch_one<T, PRO, EPI, 2, 1>(a, s);
+        if (best == T24) return launch_one<T, PRO, EPI, 2, 4>(a, s);
+        if (best == T42) return launch_one<T, PRO, EPI, 4, 2>(a, s);
         return launch_one<T, PRO, EPI, 4, 4>(a, s);
     }
     return hipErrorInvalidValue;
@@ -493,21 +493,49 @@ constexpr int kLnFusedMaxM = 128;
 // the streaming kernel's 256+ small workgroups are faster (measured at M = 1024: N = 1024 gives 64
 // tiles and 17.8 us against 7.6 us streamed; N = 4096 gives 256 tiles and 23.8 us against 28.4 us).
 constexpr int kTiledMinTiles = 160;
-template <typename T> static bool use_tiled(const GemmArgs& a) {
-    return sizeof(T) == 2 && a.N % 128 == 0 && (long)((a.M + 127) / 128) * (a.N / 128) >= kTiledMinTiles;
+static bool use_tiled(const GemmArgs& a) {
+    return a.N % 128 == 0 && (long)((a.M + 127) / 128) * (a.N / 128) >= kTiledMinTiles;
 }
 
 // The 256 x 256 direct-to-LDS kernel (cross K/V product only) needs whole 256-row tiles in A and enough
 // tiles to occupy most of the compute units with one workgroup each.
 constexpr int kDmaMinTiles = 160;
-template <typename T> static bool use_dma_crosskv(const GemmArgs& a) {
-    return sizeof(T) == 2 && a.N % 256 == 0 && a.N == 2 * a.d_model && a.K >= 256 &&
+static bool use_dma_crosskv(const GemmArgs& a) {
+    return a.N % 256 == 0 && a.N == 2 * a.d_model && a.K >= 256 &&
            a.a_rows >= (a.M + 255) / 256 * 256 && (long)((a.M + 255) / 256) * (a.N / 256) >= kDmaMinTiles;
 }
 
-template <typename T>
-static hipError_t launch_typed(GemmPro pro, GemmEpi epi, const GemmArgs& a0, hipStream_t s) {
+// The row statistics behind a folded LayerNorm: 16 lanes share a row of at most 64 tiles (d_model <= 1024)
+static bool stat_tiles_ok(int n) { return n >= 4 && n % 4 == 0 && n <= 64; }
+
+// bfloat16: the LayerNorm is always folded around the product (PRO_LNS)
+static hipError_t launch_bf16(GemmPro pro, GemmEpi epi, const GemmArgs& a, hipStream_t s) {
+    typedef bf16_t T;
+    if (pro == PRO_LNS) {
+        if (!a.stats_in || !a.mu_hat_in || !a.ln_c1 || !a.ln_c2 || !stat_tiles_ok(a.stat_tiles)) return hipErrorInvalidValue;
+        if (epi == EPI_QKV && !a.kv_slot) return hipErrorInvalidValue;
+        if (use_tiled(a)) return launch_gemm_tiled(epi, a, s);
+        if (epi == EPI_QKV) return launch_tiles<T, PRO_LNS, EPI_QKV>(a, s);
+        if (epi == EPI_F32) return launch_tiles<T, PRO_LNS, EPI_F32>(a, s);
+        if (epi == EPI_RELU_T) return launch_tiles<T, PRO_LNS, EPI_RELU_T>(a, s);
+    }
+    if (pro == PRO_T && epi == EPI_RESID_S) {
+        if (!a.stats_out || !a.mu_hat_in || !a.shadow_out || !stat_tiles_ok(a.stat_tiles) || a.stat_tiles * 16 != a.N)
+            return hipErrorInvalidValue;
+        return launch_tiles<T, PRO_T, EPI_RESID_S>(a, s);
+    }
+    if (pro == PRO_T && epi == EPI_CROSSKV) {
+        if (use_dma_crosskv(a)) return launch_gemm_dma_crosskv(a, s);
+        if (use_tiled(a)) return launch_gemm_tiled(epi, a, s);
+        return launch_tiles<T, PRO_T, EPI_CROSSKV>(a, s);
+    }
+    return hipErrorInvalidValue;
+}
+
+static hipError_t launch_f32(GemmPro pro, GemmEpi epi, const GemmArgs& a0, hipStream_t s) {
+    typedef float T;
     GemmArgs a = a0;
+    if (epi == EPI_QKV && !a.kv_slot) return hipErrorInvalidValue;
     // fused LayerNorm while one round of 32x32 tiles covers the product; else LayerNorm once, separately
     if (pro == PRO_LN && a.M > kLnFusedMaxM && (long)((a.M + 31) / 32) * (a.N / 32) > 256) {
         // two launches: h = LN(x) in fragment order, then the plain streaming GEMM on h
@@ -518,75 +546,54 @@ static hipError_t launch_typed(GemmPro pro, GemmEpi epi, const GemmArgs& a0, hip
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
         a.A = a.ln_scratch;
-        if (use_tiled<T>(a)) return launch_gemm_tiled(epi, a, s);
         if (epi == EPI_QKV) return launch_tiles<T, PRO_T, EPI_QKV>(a, s);
         if (epi == EPI_F32) return launch_tiles<T, PRO_T, EPI_F32>(a, s);
         if (epi == EPI_RELU_T) return launch_tiles<T, PRO_T, EPI_RELU_T>(a, s);
         return hipErrorInvalidValue;
     }
-    if constexpr (sizeof(T) == 2) {
-        if (pro == PRO_LNS) {
-            if (!a.stats_in || !a.mu_hat_in || !a.ln_c1 || !a.ln_c2 || a.stat_tiles < 4 || a.stat_tiles % 4 != 0 ||
-                a.stat_tiles > 4 * kMaxStatTilesPerGroup)
-                return hipErrorInvalidValue;
-            if (use_tiled<T>(a)) return launch_gemm_tiled(epi, a, s);
-            if (epi == EPI_QKV) return launch_tiles<T, PRO_LNS, EPI_QKV>(a, s);
-            if (epi == EPI_F32) return launch_tiles<T, PRO_LNS, EPI_F32>(a, s);
-            if (epi == EPI_RELU_T) return launch_tiles<T, PRO_LNS, EPI_RELU_T>(a, s);
-            return hipErrorInvalidValue;
-        }
-        if (pro == PRO_T && epi == EPI_RESID_S) {
-            if (!a.stats_out || !a.mu_hat_in || !a.shadow_out || a.stat_tiles < 4 ||
-                a.stat_tiles % 4 != 0 || a.stat_tiles * 16 != a.N || a.stat_tiles > 4 * kMaxStatTilesPerGroup)
-                return hipErrorInvalidValue;
-            return launch_tiles<T, PRO_T, EPI_RESID_S>(a, s);
-        }
-    }
     if (pro == PRO_LN && epi == EPI_QKV) return launch_tiles<T, PRO_LN, EPI_QKV>(a, s);
     if (pro == PRO_LN && epi == EPI_F32) return launch_tiles<T, PRO_LN, EPI_F32>(a, s);
     if (pro == PRO_LN && epi == EPI_RELU_T) return launch_tiles<T, PRO_LN, EPI_RELU_T>(a, s);
-    if (pro == PRO_T && epi == EPI_CROSSKV && use_dma_crosskv<T>(a)) return launch_gemm_dma_crosskv(a, s);
-    if (pro == PRO_T && use_tiled<T>(a)) return launch_gemm_tiled(epi, a, s);
     if (pro == PRO_T && epi == EPI_RESID) return launch_tiles<T, PRO_T, EPI_RESID>(a, s);
     if (pro == PRO_T && epi == EPI_CROSSKV) return launch_tiles<T, PRO_T, EPI_CROSSKV>(a, s);
     return hipErrorInvalidValue;
 }
 
 // ---------------------------------------------------------------- two products in one launch
-template <typename T, int MT0, int NT0, int EPI1, int MT1, int NT1>
-static hipError_t launch_pair_one(const GemmArgs& a0, const GemmArgs& a1, hipStream_t s) {
-    const int n0 = (a0.N / (16 * NT0)) * ((a0.M + 16 * MT0 - 1) / (16 * MT0));
-    const int n1 = (a1.N / (16 * NT1)) * ((a1.M + 16 * MT1 - 1) / (16 * MT1));
-    if (a0.w_nt && a0.M <= kWntMaxM)
-        hipLaunchKernelGGL((gemm_decode_pair_kernel<T, MT0, NT0, EPI1, MT1, NT1, true>), dim3(n0 + n1), dim3(256), 0, s, a0, a1, n0);
+template <typename T, int MT, int NT, int EPI1, int NB>
+static hipError_t launch_pair_nb(const GemmArgs& a0, const GemmArgs& a1, hipStream_t s) {
+    const int rows = (a0.M + 16 * MT - 1) / (16 * MT);
+    const int n0 = a0.N / (16 * NT) * rows, n1 = a1.N / (16 * NT) * rows;
+    if (hint_w(a0, n0 + n1, rows))
+        hipLaunchKernelGGL((gemm_decode_pair_kernel<T, MT, NT, EPI1, true, NB>), dim3(n0 + n1), dim3(256), 0, s, a0, a1, n0);
     else
-        hipLaunchKernelGGL((gemm_decode_pair_kernel<T, MT0, NT0, EPI1, MT1, NT1, false>), dim3(n0 + n1), dim3(256), 0, s, a0, a1, n0);
+        hipLaunchKernelGGL((gemm_decode_pair_kernel<T, MT, NT, EPI1, false, NB>), dim3(n0 + n1), dim3(256), 0, s, a0, a1, n0);
     return hipGetLastError();
 }
-template <typename T, int EPI1>
-static hipError_t launch_pair_epi(const GemmArgs& a0, const GemmArgs& a1, hipStream_t s) {
-    // 16 x 16 or 32 x 32 tiles for each of the two (the batches this is used for have at most 256 rows)
-    const int t0 = choose_tile<T, PRO_T>(a0) > 0, t1 = choose_tile<T, PRO_T>(a1) > 0;
-    if (a0.N % 32 != 0 || a1.N % 32 != 0) return hipErrorInvalidValue;
-    if (!t0 && !t1) return launch_pair_one<T, 1, 1, EPI1, 1, 1>(a0, a1, s);
-    if (!t0 && t1) return launch_pair_one<T, 1, 1, EPI1, 2, 2>(a0, a1, s);
-    if (t0 && !t1) return launch_pair_one<T, 2, 2, EPI1, 1, 1>(a0, a1, s);
-    return launch_pair_one<T, 2, 2, EPI1, 2, 2>(a0, a1, s);
+template <typename T, int EPI1, int NB>
+static hipError_t launch_pair_tiles(const GemmArgs& a0, const GemmArgs& a1, hipStream_t s) {
+    switch (choose_tile<T, PRO_T>(a0, a0.N + a1.N)) {  // the batches this is used for have at most 256 rows
+        case T11: return launch_pair_nb<T, 1, 1, EPI1, NB>(a0, a1, s);
+        case T21: return launch_pair_nb<T, 2, 1, EPI1, NB>(a0, a1, s);
+        case T22: return launch_pair_nb<T, 2, 2, EPI1, NB>(a0, a1, s);
+        default: return launch_pair_nb<T, 4, 2, EPI1, NB>(a0, a1, s);
+    }
 }
 
 hipError_t launch_gemm_pair(Dtype dt, const GemmArgs& a0, GemmEpi epi1, const GemmArgs& a1, hipStream_t s) {
-    if (dt != kBF16 || a0.M < 1 || a0.M != a1.M || a0.M > 256 || a0.K % 256 != 0 || a1.K % 256 != 0) return hipErrorInvalidValue;
-    if (!a0.stats_out || !a0.mu_hat_in || !a0.shadow_out || a0.stat_tiles < 4 || a0.stat_tiles % 4 != 0 ||
-        a0.stat_tiles * 16 != a0.N || a0.stat_tiles > 4 * kMaxStatTilesPerGroup)
+    if (dt != kBF16 || a0.M < 1 || a0.M != a1.M || a0.M > 256 || a0.K % 256 != 0 || a1.K != a0.K || a1.N != a0.N || a0.N % 32 != 0)
         return hipErrorInvalidValue;
-    if (epi1 == EPI_F32) return launch_pair_epi<bf16_t, EPI_F32>(a0, a1, s);
+    if (!a0.stats_out || !a0.mu_hat_in || !a0.shadow_out || !stat_tiles_ok(a0.stat_tiles) || a0.stat_tiles * 16 != a0.N)
+        return hipErrorInvalidValue;
+    if (epi1 == EPI_F32)
+        return a0.K == 1024 ? launch_pair_tiles<bf16_t, EPI_F32, 4>(a0, a1, s) : launch_pair_tiles<bf16_t, EPI_F32, 0>(a0, a1, s);
     return hipErrorInvalidValue;
 }
 
 hipError_t launch_gemm(Dtype dt, GemmPro pro, GemmEpi epi, const GemmArgs& a, hipStream_t s) {
     if (a.M < 1 || a.K % 256 != 0 || a.N % 64 != 0) return hipErrorInvalidValue;
     if (pro == PRO_LN && a.K > 256 * kMaxLnBlocks) return hipErrorInvalidValue;
-    return dt == kBF16 ? launch_typed<bf16_t>(pro, epi, a, s) : launch_typed<float>(pro, epi, a, s);
+    return dt == kBF16 ? launch_bf16(pro, epi, a, s) : launch_f32(pro, epi, a, s);
 }
 
 // ---------------------------------------------------------------- LayerNorm folding (once, at create)

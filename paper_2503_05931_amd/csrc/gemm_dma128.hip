@@ -47,7 +47,7 @@ __global__ __launch_bounds__(256) void gemm_dma128_kernel(GemmArgs a) {
     typedef bf16_t T;
     constexpr int S = kStages;
     extern __shared__ __align__(16) char lds[];
-    __shared__ float row_stat[2][2][kBM];  // LNS: per row, two partial (mean, sum of squared deviations)
+    __shared__ float2 row_stat[kBM];  // LNS: per row, mean and sum of squared deviations
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
     const int wm = wave >> 1, wn = wave & 1;  // wavefront tile: rows [64 wm, +64), columns [64 wn, +64)
     const int r32 = lane & 31, hh = lane >> 5;
@@ -122,61 +122,31 @@ __global__ __launch_bounds__(256) void gemm_dma128_kernel(GemmArgs a) {
     };
     zero_acc();
 
-    // LNS: statistics of the tile's rows (two groups of threads combine half of the 16-column tiles each)
-    float stat_n = 0.f;
-    auto load_row_stats = [&](int ti) {
-        const int tile = t_begin + j_in + ti * per_x;
+    // LNS: statistics of the tile's rows
+    auto tile_stats = [&](int ti) {
         int tm, tn_unused;
-        tile_pos(tile, tm, tn_unused);
-        const int row = tid & 127, grp = tid >> 7, per = a.stat_tiles >> 1;
-        stat_n = 16.f * (float)per;
-        const float2* sp = a.stats_in + (size_t)(grp * per) * a.m_stride + (tm * kBM + row);
-        float2 v[32];  // d_model <= 1024: at most 32 tiles per group; all loads first, one round trip
-#pragma unroll
-        for (int t = 0; t < 32; ++t) v[t] = t < per ? sp[(size_t)t * a.m_stride] : float2{0.f, 0.f};
-        float sm = 0.f, m2 = 0.f;
-#pragma unroll
-        for (int t = 0; t < 32; ++t) {
-            sm += v[t].x;
-            m2 += v[t].y;
-        }
-        const float mean = sm / (float)per;
-        float dev = 0.f;
-#pragma unroll
-        for (int t = 0; t < 32; ++t)
-            if (t < per) dev += (v[t].x - mean) * (v[t].x - mean);
-        row_stat[0][grp][row] = mean;
-        row_stat[1][grp][row] = m2 + 16.f * dev;
+        tile_pos(t_begin + j_in + ti * per_x, tm, tn_unused);
+        load_row_stats<kBM>(a, tm * kBM, row_stat);
     };
 
-    // EPI_QKV: where the cache slot of each of this lane's two rows starts (element index for head 0; -1: the row is
-    // finished or beyond M).  Position and page are two dependent loads per row: fetched here, at the start of a
-    // tile, they are long there when the epilogue stores the keys and values.
-    long long kv_base[2] = {-1, -1};
-    auto load_kv_rows = [&](int ti) {
-        const int tile = t_begin + j_in + ti * per_x;
+    // Where each of this lane's two rows goes in the caches (EPI_QKV, EPI_CROSSKV): fetched here, at the start of a tile,
+    // it is long there when the epilogue stores the keys and values.
+    int slot_of_row[2] = {-1, -1};
+    auto load_slots = [&](int ti) {
         int tm, tn_unused;
-        tile_pos(tile, tm, tn_unused);
+        tile_pos(t_begin + j_in + ti * per_x, tm, tn_unused);
 #pragma unroll
-        for (int mt = 0; mt < 2; ++mt) {
-            const int m = tm * kBM + wm * 64 + mt * 32 + r32;
-            kv_base[mt] = -1;
-            if (m < a.M && !a.finished[m]) {
-                const int pos = a.seq_len[m];
-                const int page = a.page_table[(size_t)m * a.max_pages + (pos >> 4)];
-                kv_base[mt] = ((long long)page * a.n_heads * kPage + (pos & 15)) * a.head_dim;
-            }
-        }
+        for (int mt = 0; mt < 2; ++mt) slot_of_row[mt] = row_slot<EPI>(a, tm * kBM + wm * 64 + mt * 32 + r32);
     };
 
     set_tile_ptrs(0);
-    if constexpr (EPI == EPI_QKV) load_kv_rows(0);
+    load_slots(0);
     for (int s = 0; s < S - 1; ++s) {  // nk >= 8: all inside the first tile
 #pragma unroll
         for (int j = 0; j < 8; ++j) request_one(j);
         request_done();
     }
-    if constexpr (LNS) load_row_stats(0);
+    if constexpr (LNS) tile_stats(0);
     wait_loads_barrier<0>();  // steps 0 .. S-2 have landed
     Frags f0, f1;
     int slot = 0;  // slot of the step being computed
@@ -220,9 +190,9 @@ __global__ __launch_bounds__(256) void gemm_dma128_kernel(GemmArgs a) {
         const int ti_next = ti + 1 < my_tiles ? ti + 1 : ti;
         if (LNS && ti > 0) {
             wait_lds_barrier();  // every wavefront is through the previous tile's epilogue
-            load_row_stats(ti);
+            tile_stats(ti);
         }
-        if (EPI == EPI_QKV && ti > 0) load_kv_rows(ti);
+        if (ti > 0) load_slots(ti);
 #pragma unroll 1
         for (int ks = 0; ks < S - 2; ++ks) step(std::true_type{});  // waited for at the end of the previous tile
 #pragma unroll 1
@@ -243,10 +213,8 @@ __global__ __launch_bounds__(256) void gemm_dma128_kernel(GemmArgs a) {
 #pragma unroll
             for (int mt = 0; mt < 2; ++mt) {
                 const int rl = wm * 64 + mt * 32 + r32, m = tm * kBM + rl;
-                const float a0 = row_stat[0][0][rl], a1 = row_stat[0][1][rl];
-                float mu = 0.5f * (a0 + a1);
-                const float d0 = a0 - mu, d1 = a1 - mu;
-                const float m2 = row_stat[1][0][rl] + row_stat[1][1][rl] + stat_n * (d0 * d0 + d1 * d1);
+                float mu = row_stat[rl].x;
+                const float m2 = row_stat[rl].y;
                 rstd[mt] = fold_norm(a.rms, (float)K, a.ln_eps, m2, mu);
                 shift[mt] = m < a.M ? mu - a.mu_hat_in[m] : 0.f;
                 if (tn == 0 && wn == 0 && hh == 0 && m < a.M && a.mu_hat_out) a.mu_hat_out[m] = mu;  // for the residual updates
@@ -272,20 +240,7 @@ __global__ __launch_bounds__(256) void gemm_dma128_kernel(GemmArgs a) {
                     if (m >= a.M) continue;
                     if constexpr (LNS) v = (v - shift[mt] * c1) * rstd[mt] + bv;
                     else v += bv;
-                    if constexpr (EPI == EPI_QKV) {
-                        const int d = a.d_model;
-                        if (n < d) {
-                            store4(static_cast<float*>(a.out) + (size_t)m * d + n, v);
-                        } else if (kv_base[mt] >= 0) {
-                            const int which = n >= 2 * d;
-                            const int c = n - (which ? 2 * d : d);
-                            const long long at = kv_base[mt] + (long long)(c / a.head_dim) * kPage * a.head_dim + c % a.head_dim;
-                            if (a.kv_fp8) store4_fp8(static_cast<unsigned char*>(which ? a.v_pool : a.k_pool) + at, v);
-                            else store4(static_cast<T*>(which ? a.v_pool : a.k_pool) + at, v);
-                        }
-                    } else {
-                        gemm_epilogue<T, EPI>(a, m, n, v, f32x4{0.f, 0.f, 0.f, 0.f});
-                    }
+                    gemm_epilogue<T, EPI>(a, m, n, v, f32x4{0.f, 0.f, 0.f, 0.f}, slot_of_row[mt]);
                 }
             }
         zero_acc();

@@ -47,32 +47,11 @@ __global__ __launch_bounds__(256) void gemm_tiled_kernel(GemmArgs a) {
     if (wg >= total) return;  // the grid is rounded up to whole rounds over the XCDs
     const int tile_m = wg / n_nt, tile_n = wg % n_nt;
     const int m0 = tile_m * BM, n0 = tile_n * BN;
-    // LNS (LayerNorm folded around the product, see kernels.h): statistics of this tile's rows, two groups of
-    // threads combine half of the 16-column tiles each; read back after the k loop's last barrier
-    __shared__ float row_stat[2][2][BM];
-    float stat_n = 0.f;
+    // LNS (LayerNorm folded around the product, see kernels.h): statistics of this tile's rows, read back after the
+    // k loop's last barrier
+    __shared__ float2 row_stat[BM];
     if constexpr (LNS) {
-        static_assert(BM == 128, "one thread per row and half");
-        const int row = tid & 127, grp = tid >> 7, per = a.stat_tiles >> 1;
-        stat_n = 16.f * (float)per;
-        const float2* sp = a.stats_in + (size_t)(grp * per) * a.m_stride + (m0 + row);
-        float2 v[32];  // d_model <= 1024: at most 32 tiles per group; all loads first, one round trip
-#pragma unroll
-        for (int t = 0; t < 32; ++t) v[t] = t < per ? sp[(size_t)t * a.m_stride] : float2{0.f, 0.f};
-        float sm = 0.f, m2 = 0.f;
-#pragma unroll
-        for (int t = 0; t < 32; ++t) {
-            sm += v[t].x;  // entries beyond per are zero
-            m2 += v[t].y;
-        }
-        const float mean = sm / (float)per;
-        float dev = 0.f;
-#pragma unroll
-        for (int t = 0; t < 32; ++t)
-            if (t < per) dev += (v[t].x - mean) * (v[t].x - mean);
-        m2 += 16.f * dev;
-        row_stat[0][grp][row] = mean;
-        row_stat[1][grp][row] = m2;
+        load_row_stats<BM>(a, m0, row_stat);
     }
     const int K = a.K, nk = K >> 6;
     const char* __restrict__ A = static_cast<const char*>(a.A);
@@ -156,16 +135,17 @@ __global__ __launch_bounds__(256) void gemm_tiled_kernel(GemmArgs a) {
 
     // epilogue: lane (r, g) of tile (i, j) holds C[m][n .. n+3], m = row r of the tile, n = 4 g
     const int r = lane & 15, g = lane >> 4;
+    int slot[WM];
+#pragma unroll
+    for (int i = 0; i < WM; ++i) slot[i] = row_slot<EPI>(a, m0 + (wm * WM + i) * 16 + r);
     const T* __restrict__ bias = static_cast<const T*>(a.bias);
     float rstd[WM], shift[WM];  // LNS: per row of this lane
     if constexpr (LNS) {
 #pragma unroll
         for (int i = 0; i < WM; ++i) {
             const int rl = (wm * WM + i) * 16 + r;
-            const float a0 = row_stat[0][0][rl], a1 = row_stat[0][1][rl];
-            float mu = 0.5f * (a0 + a1);
-            const float d0 = a0 - mu, d1 = a1 - mu;
-            const float m2 = row_stat[1][0][rl] + row_stat[1][1][rl] + stat_n * (d0 * d0 + d1 * d1);
+            float mu = row_stat[rl].x;
+            const float m2 = row_stat[rl].y;
             rstd[i] = fold_norm(a.rms, (float)K, a.ln_eps, m2, mu);
             shift[i] = m0 + rl < a.M ? mu - a.mu_hat_in[m0 + rl] : 0.f;
             if (n0 == 0 && wn == 0 && g == 0 && m0 + rl < a.M && a.mu_hat_out) a.mu_hat_out[m0 + rl] = mu;  // for the residual updates
@@ -188,8 +168,8 @@ __global__ __launch_bounds__(256) void gemm_tiled_kernel(GemmArgs a) {
             f32x4 res = f32x4{0.f, 0.f, 0.f, 0.f};
             if constexpr (EPI == EPI_RESID)
                 res = *reinterpret_cast<const f32x4*>(static_cast<const char*>(a.out) + frag_elem_off<4>(m, n, a.N));
-            if constexpr (LNS) gemm_epilogue<T, EPI>(a, m, n, (acc[i][j] - shift[i] * c1) * rstd[i] + bv, res);
-            else gemm_epilogue<T, EPI>(a, m, n, acc[i][j] + bv, res);
+            if constexpr (LNS) gemm_epilogue<T, EPI>(a, m, n, (acc[i][j] - shift[i] * c1) * rstd[i] + bv, res, slot[i]);
+            else gemm_epilogue<T, EPI>(a, m, n, acc[i][j] + bv, res, slot[i]);
         }
     }
 }

@@ -41,10 +41,8 @@ struct GemmArgs {
     // EPI_QKV: columns [d,2d) and [2d,3d) go to the paged self-attention cache of this layer
     void* k_pool;         // T (or E4M3 codes, kv_fp8) [pages][H][16][Dh]
     void* v_pool;
-    const int* page_table;  // [batch][max_pages]
-    int max_pages;
-    const int* seq_len;     // position being written, per sequence
-    const int* finished;    // nonzero: do not append
+    const int* kv_slot;     // [M] page * 16 + position inside the page that row m's key / value go to, -1: nowhere
+                            // (launch_embed leaves it: one load per row and layer instead of state, page table, page)
     int n_heads, head_dim, d_model;
     // EPI_CROSSKV: columns [0,d) -> kc, [d,2d) -> vc, layout [H][t_cap][Dh]
     void* kc;
@@ -53,7 +51,8 @@ struct GemmArgs {
     const int* out_row_map;  // EPI_CROSSKV, may be null: frame slot that GEMM row m is written to (default m)
     int a_rows;              // rows the A buffer holds (0: only the next multiple of 128 above M is promised)
     // Row statistics of the residual rows: for every row and every 16-column tile, the tile's mean and its sum
-    // of squared deviations from that mean, [stat_tiles][m_stride] (stat_tiles = d_model / 16).
+    // of squared deviations from that mean, [rows][stat_tiles] (stat_tiles = d_model / 16; a row is 512 contiguous
+    // bytes at d_model = 1024, read by 16 lanes).
     const float2* stats_in;  // PRO_LNS: of A's rows
     const float* mu_hat_in;  // PRO_LNS: [M] the shift the shadow was written with;
                              // EPI_RESID_S: [M] row means before the update = the shift to write the shadow with
@@ -62,7 +61,7 @@ struct GemmArgs {
     float* mu_hat_out;       // PRO_LNS, may be null: [M] row means of A's rows, for the residual updates that follow
     float2* stats_out;       // EPI_RESID_S: of the updated rows
     void* shadow_out;        // EPI_RESID_S: T [M,N] fragment order
-    int stat_tiles, m_stride;
+    int stat_tiles;
     int kv_fp8;              // EPI_QKV / EPI_CROSSKV: the caches hold 8-bit E4M3 codes instead of T
     int rms;                 // the normalisation is RMSNorm (no mean subtraction; ln_b may be null) instead of LayerNorm:
                              // PRO_LN normalises that way, PRO_LNS reads the statistics that way (see fold_norm)
@@ -140,12 +139,12 @@ struct AttnArgs {
     float scale_log2e;    // log2(e) / sqrt(Dh)
     // cross-attention behind merged products (see "merged products" above): q holds P, and the kernel finishes it
     // with the statistics of the updated rows: q = rstd' (P - (mu' - mu_hat) c1) + c2.  q_stats null: q is final.
-    const float2* q_stats;  // [q_stat_tiles][q_m_stride] tile statistics of the updated rows
+    const float2* q_stats;  // [B][q_stat_tiles] tile statistics of the updated rows
     const float* q_mu_hat;  // [B] shift of the shadow that P was computed from
     const float* q_c1;      // [d_model]
     const float* q_c2;
     float q_eps;
-    int q_stat_tiles, q_m_stride, q_rms;
+    int q_stat_tiles, q_rms;
 };
 hipError_t launch_attn_self(Dtype dt, const AttnArgs& a, hipStream_t s);
 hipError_t launch_attn_cross(Dtype dt, const AttnArgs& a, hipStream_t s);
@@ -155,6 +154,9 @@ struct StateArgs {
     int* seq_len; int* n_gen; int* finished; int* cur_tok; int* limit; int* n_finished;
     int* prompt;      // [B, prompt_stride]
     int* out_tokens;  // [B, out_stride]
+    const int* page_table;  // [B][max_pages]
+    int* kv_slot;     // [B] see GemmArgs::kv_slot
+    int max_pages;
     int prompt_len, prompt_stride, out_stride, max_new;
     int eos_id, pad_id, batch, vocab;
 };
@@ -162,12 +164,12 @@ struct StateArgs {
 // shadow == null: not written.
 struct ShadowArgs {
     void* shadow;       // T [B, d] fragment order: x - row mean
-    float2* stats;      // [d / 16][m_stride]: mean and sum of squared deviations of every 16-column tile
+    float2* stats;      // [B][d / 16]: mean and sum of squared deviations of every 16-column tile
     float* mu_hat;      // [B] row means (the shadow's shift)
-    int m_stride;
     int rms;            // RMSNorm: the shift is 0 (the shadow is x itself in the storage type)
 };
-// x[b,:] = emb_scale * tok_emb[cur_tok[b]] + pos_emb[seq_len[b]]   (x in fragment order); d_model <= 1024
+// x[b,:] = emb_scale * tok_emb[cur_tok[b]] + pos_emb[seq_len[b]]   (x in fragment order); d_model <= 1024;
+// kv_slot[b] = where this step's key / value of sequence b go
 hipError_t launch_embed(Dtype dt, float* x, const void* tok_emb, const void* pos_emb, const StateArgs& st,
                         int d_model, int max_positions, float emb_scale, const ShadowArgs& sa, hipStream_t s);
 // greedy = 1: prompt feeding, argmax, EOS rules, output writes; greedy = 0: argmax only -> step_out (may be null)
@@ -194,7 +196,7 @@ hipError_t launch_assign_pages(int* page_table, int max_pages, int blk, int firs
 // p[0 .. n) = 0
 hipError_t launch_fill_zero(int* p, int n, hipStream_t s);
 
-// finished[b] = 0, seq_len[b] = clamp(seq_len[b], 0, max_pos): a valid mid-decode state for timing runs
+// finished[b] = 0, seq_len[b] = clamp(seq_len[b], 0, max_pos), kv_slot to match: a valid mid-decode state for timing runs
 hipError_t launch_prepare_timing(const StateArgs& st, int max_pos, hipStream_t s);
 
 }  // namespace aed

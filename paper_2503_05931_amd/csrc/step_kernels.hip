@@ -12,6 +12,11 @@
 
 namespace aed {
 
+// where position pos of sequence b is cached: page * 16 + place in the page
+__device__ __forceinline__ int slot_of(const StateArgs& st, int b, int pos) {
+    return st.page_table[(size_t)b * st.max_pages + min(max(pos, 0) >> 4, st.max_pages - 1)] * kPage + (pos & (kPage - 1));
+}
+
 template <typename T>
 __global__ __launch_bounds__(256) void embed_kernel(float* __restrict__ x, const T* __restrict__ tok_emb,
                                                     const T* __restrict__ pos_emb, StateArgs st, int d,
@@ -21,6 +26,8 @@ __global__ __launch_bounds__(256) void embed_kernel(float* __restrict__ x, const
     tok = tok < 0 ? 0 : (tok >= st.vocab ? st.vocab - 1 : tok);
     int pos = st.seq_len[b];
     pos = pos < max_positions ? pos : max_positions - 1;
+    const int slot = slot_of(st, b, pos);
+    if (tid == 0) st.kv_slot[b] = st.finished[b] ? -1 : slot;
     const T* e = tok_emb + (size_t)tok * d;
     const T* p = pos_emb + (size_t)pos * d;
     const int i = tid * 4;  // d <= 1024: one 4-vector per thread
@@ -54,7 +61,7 @@ __global__ __launch_bounds__(256) void embed_kernel(float* __restrict__ x, const
     q += __shfl_xor(q, 2);
     if (!live) return;
     store4(reinterpret_cast<T*>(static_cast<char*>(sh.shadow) + frag_elem_off<sizeof(T)>(b, i, d)), o - mean);
-    if ((tid & 3) == 0) sh.stats[(size_t)(i >> 4) * sh.m_stride + b] = float2{tmean, q};
+    if ((tid & 3) == 0) sh.stats[(size_t)b * (d >> 4) + (i >> 4)] = float2{tmean, q};
     if (tid == 0) sh.mu_hat[b] = mean;
 }
 
@@ -254,7 +261,9 @@ __global__ void prepare_timing_kernel(StateArgs st, int max_pos) {
     if (b >= st.batch) return;
     st.finished[b] = 0;
     const int p = st.seq_len[b];
-    st.seq_len[b] = p < 0 ? 0 : (p > max_pos ? max_pos : p);
+    const int pos = p < 0 ? 0 : (p > max_pos ? max_pos : p);
+    st.seq_len[b] = pos;
+    st.kv_slot[b] = slot_of(st, b, pos);
 }
 
 hipError_t launch_prepare_timing(const StateArgs& st, int max_pos, hipStream_t s) {

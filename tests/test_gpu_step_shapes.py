@@ -1,0 +1,43 @@
+"""The decoder step at the sizes where its kernels change over: every K that the
+streaming products unroll or loop over, the row counts at which their tile
+changes, and key counts around what one round of a workgroup's wavefronts
+takes.  Teacher-forced logits against the oracle, with the tolerances of the
+other parity tests."""
+import numpy as np
+import pytest
+
+from paper_2503_05931_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def torch_cuda():
+    import torch
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    return torch
+
+
+def run(oracle, tol, dtype, d_model, head_dim, enc_lens, d_ffn, steps, seed, **kw):
+    from tests import gpu_util as G
+    cfg = W.DecoderConfig(name="shapes", n_layers=2, d_model=d_model, n_heads=d_model // head_dim, head_dim=head_dim,
+                          d_ffn=d_ffn, vocab=192, dtype=dtype, batch=len(enc_lens), prompt_len=1, max_new=steps + 1, **kw)
+    wl = W.custom(cfg, enc_lens, seed, random_ln=True)
+    toks = np.random.default_rng(seed).integers(0, cfg.vocab, size=(len(enc_lens), steps)).astype(np.int32)
+    ref = oracle.Model(cfg, wl.weights).decode_forced(wl.enc, wl.enc_lens, toks)
+    dec = G.make_decoder(wl)
+    glog, gids = G.forced_logits_gpu(dec, wl, toks)
+    err, _ = G.check_forced(ref, glog, gids, G.TOL[tol])
+    print(f"{tol} d={d_model} ffn={d_ffn} batch={len(enc_lens)}: max |dlogit| = {err:.2e}")
+    dec.close()
+
+
+# K = d_model: 256 .. 768 loop, 1024 unrolled; K = d_ffn: 4096 unrolled, the others loop with a full ring, without one and
+# with remainders.  Rows: one tile of 16, then 32, 64 and 128 rows and one more.
+@pytest.mark.parametrize("dtype,d_model,head_dim,d_ffn,batch", [
+    ("bf16", 256, 64, 256, 1), ("bf16", 512, 128, 1280, 16), ("bf16", 768, 64, 2304, 17), ("bf16", 1024, 128, 4096, 33),
+    ("bf16", 1024, 128, 4352, 65), ("bf16", 1024, 64, 2048, 129), ("bf16", 1024, 128, 4096, 257),
+    ("fp32", 256, 64, 768, 17), ("fp32", 512, 128, 2048, 33), ("fp32", 1024, 128, 4096, 65), ("fp32", 768, 64, 1280, 130),
+])
+def test_product_shapes(torch_cuda, oracle, dtype, d_model, head_dim, d_ffn, batch):
+    run(oracle, dtype, dtype, d_model, head_dim, [1 + (5 * i) % 9 for i in range(batch)], d_ffn, 2, batch + d_ffn)
