@@ -41,3 +41,14 @@ def run(oracle, tol, dtype, d_model, head_dim, enc_lens, d_ffn, steps, seed, **k
 ])
 def test_product_shapes(torch_cuda, oracle, dtype, d_model, head_dim, d_ffn, batch):
     run(oracle, dtype, dtype, d_model, head_dim, [1 + (5 * i) % 9 for i in range(batch)], d_ffn, 2, batch + d_ffn)
+
+
+# Attention: 16, 8 and 4 wavefronts per workgroup (up to 256, 1024 and more workgroups of 4 heads), key counts around what
+# they have in flight, and sequences around the length from which a small batch has them cut (256 keys).
+@pytest.mark.parametrize("dtype,kv_fp8", [("bf16", 0), ("bf16", 1), ("fp32", 0)])
+@pytest.mark.parametrize("batch", [1, 2, 64, 65, 256, 257])
+def test_attention_splits(torch_cuda, oracle, dtype, kv_fp8, batch):
+    lens = ([256, 513, 257, 255, 512, 1, 16, 17] + [1 + (7 * i) % 33 for i in range(batch)])[:batch]
+    if batch == 1:
+        lens = [257]
+    run(oracle, "bf16+fp8kv" if kv_fp8 else dtype, dtype, 256, 64, lens, 256, 2, 7 + batch, kv_fp8=kv_fp8)

@@ -43,8 +43,8 @@ def test_noalloc_step_equals_step_then_a_smaller_batch():
     from tests import gpu_util as G
     assert torch.cuda.is_available()
     rng = np.random.default_rng(12)
-    # 3 sequences x 4 heads: far fewer than 128 (sequence, head) pairs, so sequences are cut into 64-key chunks:
-    # 8 chunks of cross-attention keys, up to 3 of self-attention keys at 140 positions
+    # 3 sequences x 4 heads: far fewer than 128 (sequence, head) pairs, so sequences of more than 256 keys are cut:
+    # two of the three have two chunks of cross-attention keys
     big = _workload([500, 300, 77], seed=77, max_new=140)
     small = _workload([33, 5], seed=78, max_new=140)
     cases = [(big, rng.integers(0, 256, size=(3, 140)).astype(np.int32)),
