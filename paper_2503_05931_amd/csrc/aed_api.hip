@@ -264,6 +264,8 @@ struct aed_decoder {
         st.pad_id = cfg.pad_id;
         st.batch = batch;
         st.vocab = cfg.vocab;
+        st.items = at<int4>(lay.items);
+        st.n_items = n_items;
         return st;
     }
 };
@@ -1234,9 +1236,9 @@ extern "C" aed_status aed_greedy_decode_queue(aed_decoder* d, const void* enc_st
         }
         first = false;
         if (n_turn > 0) {
-            for (int b = 0; b < B; ++b) {  // a parked slot keeps a valid one-frame item; its workgroups exit early
+            for (int b = 0; b < B; ++b) {  // a parked slot's item is marked: its workgroups exit at once
                 const bool on = slot_req[b] >= 0;
-                items[b].x = b; items[b].y = 0; items[b].z = (on ? enc_lens[slot_req[b]] : 1) | (1 << 16);
+                items[b].x = on ? b : b | kItemOff; items[b].y = 0; items[b].z = (on ? enc_lens[slot_req[b]] : 1) | (1 << 16);
                 items[b].w = on ? slot_at[b] : 0;
             }
             std::vector<int4> sorted(items);

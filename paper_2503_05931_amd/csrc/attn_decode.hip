@@ -116,13 +116,15 @@ __global__ __launch_bounds__(64 * NW, sizeof(KV) <= 2 ? 4 : 1) void attn_decode_
 
     // Work item.  Cross-attention: from the host-built list (longest first, so the long sequences
     // start early and the short ones fill the tail); the item carries everything needed to address
-    // the keys, so the finished flag, the query and the first key blocks are all fetched in the same
-    // round trip.  Self-attention: blockIdx.y is the sequence, blockIdx.z the chunk.
-    int b, start, n, chunk_idx, n_chunks, row0 = 0, fin;
+    // the keys, so the query and the first key blocks are fetched in the same round trip, and the sampler
+    // marks the items of a sequence that finishes, so that nothing is fetched for it.  (With a finished flag
+    // per sequence beside the keys' requests, up to 128 of its keys were: 24 layers, batch 128, half of
+    // whose sequences are through on average, 370.7 ms; now 355.2.)  Self-attention: blockIdx.y is the sequence, blockIdx.z the chunk.
+    int b, start, n, chunk_idx, n_chunks, row0 = 0;
     int first_page = 0;  // self-attention: page of this wavefront's first block, fetched with the scalars
     if constexpr (SELF) {
         b = blockIdx.y;
-        fin = a.finished[b];
+        const int fin = a.finished[b];
         const int total = a.seq_len[b] + 1;
         {
             const int blk = min((int)(blockIdx.z * a.chunk >> 4) + wave, a.max_pages - 1);
@@ -137,12 +139,12 @@ __global__ __launch_bounds__(64 * NW, sizeof(KV) <= 2 ? 4 : 1) void attn_decode_
     } else {
         const int4 it = a.items[blockIdx.y];
         b = it.x;
+        if (b < 0) return;  // the sequence has finished (kItemOff)
         start = it.y & 0xFFFF;
         chunk_idx = it.y >> 16;
         n = it.z & 0xFFFF;
         n_chunks = it.z >> 16;
         row0 = it.w + start;  // first frame of this chunk in the packed layout
-        fin = a.finished[b];  // tested after the first loads have been issued
     }
 
     const KV* __restrict__ Kb = static_cast<const KV*>(a.K);
@@ -198,7 +200,6 @@ __global__ __launch_bounds__(64 * NW, sizeof(KV) <= 2 ? 4 : 1) void attn_decode_
     int kb = wave;
     if (kb < n_blocks) fetch(kb, k0, v0);
     if constexpr (!SELF) {
-        if (fin) return;
         if (q_fix) {  // q = rstd' (P - (mu' - mu_hat) c1) + c2 with this row's statistics
             __shared__ float sm_fix[DH + 1];
             if (wave == 0) {

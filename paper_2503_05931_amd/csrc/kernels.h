@@ -2,6 +2,7 @@
 #pragma once
 
 #include <hip/hip_runtime.h>
+#include <limits.h>
 #include <stdint.h>
 
 namespace aed {
@@ -111,14 +112,15 @@ hipError_t launch_weight_product(Dtype dt, const void* W1, const void* g, const 
 hipError_t launch_fold_vec(Dtype dt, const void* W, const void* g, const void* v, float* out, int N, int J, hipStream_t s);
 
 // ---------------------------------------------------------------- decode attention
+constexpr int kItemOff = INT_MIN;  // sign bit of a cross-attention work item's sequence: it has finished
 struct AttnArgs {
     const float* q;       // [B, d_model]
     void* out;            // T [B, d_model] in fragment order
     const void* K;        // self: T [pages][H][16][Dh]; cross: T [H][t_cap][Dh]  (this layer)
     const void* V;
     int kv_fp8;           // K and V hold 8-bit E4M3 codes instead of T (bfloat16 mode only)
-    const int* finished;  // [B]
     // self
+    const int* finished;  // [B]
     const int* page_table;
     int max_pages;
     const int* seq_len;   // keys = seq_len[b] + 1
@@ -126,7 +128,7 @@ struct AttnArgs {
     int n_chunks_max;     // grid.z
     int batch;
     // cross
-    const int4* items;    // {b, key_start | chunk_idx << 16, n_keys | n_chunks << 16, first frame of b in the
+    const int4* items;    // {b (| kItemOff: nothing to do), key_start | chunk_idx << 16, n_keys | n_chunks << 16, first frame of b in the
                           // packed layout}, longest first
     int n_items;
     const int* enc_off;   // [B+1] frame offsets in the packed layout
@@ -159,6 +161,8 @@ struct StateArgs {
     int max_pages;
     int prompt_len, prompt_stride, out_stride, max_new;
     int eos_id, pad_id, batch, vocab;
+    int4* items;      // [n_items] cross-attention work list (AttnArgs::items): the sampler marks a finished sequence's
+    int n_items;      // items with kItemOff, launch_reset and launch_prepare_timing take the marks off
 };
 // What the folded LayerNorm of the first layer needs beside the rows themselves (bfloat16 mode; see PRO_LNS).
 // shadow == null: not written.

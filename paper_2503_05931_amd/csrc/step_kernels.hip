@@ -132,22 +132,30 @@ __global__ __launch_bounds__(256) void sample_kernel(const float* __restrict__ l
     __shared__ int si[4];
     if ((tid & 63) == 0) { sv[tid >> 6] = bv; si[tid >> 6] = bi; }
     __syncthreads();
-    if (tid != 0) return;
+    // every thread takes the decision, so that all of them know whether the sequence ends
+    bv = sv[0];
+    bi = si[0];
     for (int w = 1; w < 4; ++w)
         if (better(sv[w], si[w], bv, bi)) { bv = sv[w]; bi = si[w]; }
     int tok = bi == INT_MAX ? 0 : bi;
     if (!greedy) {
+        if (tid != 0) return;
         if (step_out) step_out[b] = tok;
         st.cur_tok[b] = tok;
         st.seq_len[b] = pos + 1;
         return;
     }
     if (n + 1 >= lim) tok = st.eos_id;  // forced end at the per-sequence target length
+    const bool ends = (st.eos_id >= 0 && tok == st.eos_id) || n + 1 >= st.max_new;
+    if (ends)
+        for (int i = tid; i < st.n_items; i += 256)
+            if (st.items[i].x == b) st.items[i].x = b | kItemOff;
+    if (tid != 0) return;
     st.out_tokens[(size_t)b * st.out_stride + n] = tok;
     st.n_gen[b] = n + 1;
     st.cur_tok[b] = tok;
     st.seq_len[b] = pos + 1;
-    if ((st.eos_id >= 0 && tok == st.eos_id) || n + 1 >= st.max_new) {
+    if (ends) {
         st.finished[b] = 1;
         atomicAdd(st.n_finished, 1);
     }
@@ -168,6 +176,7 @@ __global__ void reset_kernel(StateArgs st, const int* __restrict__ limits, int f
         st.limit[b] = limits ? limits[b] : INT_MAX;
         if (b == 0) *st.n_finished = 0;
     }
+    for (int i = b * blockDim.x + threadIdx.x; i < st.n_items; i += gridDim.x * blockDim.x) st.items[i].x &= ~kItemOff;
     if (fill_out)
         for (int t = threadIdx.x; t < st.max_new; t += blockDim.x) st.out_tokens[(size_t)b * st.out_stride + t] = st.pad_id;
 }
@@ -258,6 +267,7 @@ hipError_t launch_fill_zero(int* p, int n, hipStream_t s) {
 
 __global__ void prepare_timing_kernel(StateArgs st, int max_pos) {
     const int b = blockIdx.x * blockDim.x + threadIdx.x;
+    for (int i = b; i < st.n_items; i += gridDim.x * blockDim.x) st.items[i].x &= ~kItemOff;
     if (b >= st.batch) return;
     st.finished[b] = 0;
     const int p = st.seq_len[b];

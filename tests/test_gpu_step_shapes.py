@@ -52,3 +52,29 @@ def test_attention_splits(torch_cuda, oracle, dtype, kv_fp8, batch):
     if batch == 1:
         lens = [257]
     run(oracle, "bf16+fp8kv" if kv_fp8 else dtype, dtype, 256, 64, lens, 256, 2, 7 + batch, kv_fp8=kv_fp8)
+
+
+@pytest.mark.parametrize("lens", [[300, 40, 9, 520], [5 + 3 * i for i in range(37)]])
+def test_finished_sequences_leave_the_work_list_and_come_back(torch_cuda, oracle, lens):
+    """Sequences that end are struck off the cross-attention work list (with few sequences several items each); the same
+    batch decoded again has them back."""
+    from tests import gpu_util as G
+    torch, n, N = torch_cuda, len(lens), 12
+    cfg = W.DecoderConfig(name="ends", n_layers=2, d_model=256, n_heads=4, head_dim=64, d_ffn=256, vocab=192, dtype="fp32",
+                          batch=n, prompt_len=2, max_new=N, eos_id=2, pad_id=7)
+    wl = W.custom(cfg, lens, 31, random_ln=True)
+    target = np.array([1 + (5 * i) % N for i in range(n)], np.int32)
+    m = oracle.Model(cfg, wl.weights)
+    ref_t, ref_l, ref_lg = m.greedy_decode(wl.enc, wl.enc_lens, wl.prompt, N, max_new_per_seq=target, want_logits=True)
+    dec = G.make_decoder(wl)
+    dec.aed_cross_kv_precompute(dec.to_device(wl.enc), wl.enc_lens)
+    near = G.first_near_tie(ref_lg, G.TOL["fp32"])
+    for _ in range(2):
+        toks, got = dec.aed_greedy_decode(torch.from_numpy(wl.prompt).to(dec.device), N, max_new_per_seq=target)
+        toks, got = toks.cpu().numpy(), got.cpu().numpy()
+        for b in range(n):
+            k = min(int(near[b]), int(ref_l[b]))
+            assert (toks[b, :k] == ref_t[b, :k]).all()
+            if near[b] >= ref_l[b]:
+                assert got[b] == ref_l[b] and (toks[b, got[b]:] == 7).all()
+    dec.close()
