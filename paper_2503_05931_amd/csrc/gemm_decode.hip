@@ -731,26 +731,45 @@ hipError_t launch_fold_vec(Dtype dt, const void* W, const void* g, const void* v
     return hipGetLastError();
 }
 
-// dst (fragment order, [M, K]) <- rows of a row-major source, row m taken from src row row_map[m] (or m)
+// dst (fragment order, [M, K]) <- rows of a row-major source, row m taken from src row row_map[m] (or m).  A copy, bound
+// by memory: a wavefront moves 16-row x 64-k blocks, lane (r, g) the 16 elements of row r that it would hold for the MFMA,
+// so a block's loads take whole 128-byte lines of 16 rows and every store instruction writes 1 KB in one piece; all loads
+// of four blocks are in flight before the first store.  (One workgroup per row, whose stores were 16-byte pieces 256 bytes
+// apart, took 1272 us for 512 000 rows of 1024 bf16 = 1.65 TB/s and 120 us for 63 913 gathered rows.)
 template <typename T>
 __global__ __launch_bounds__(256) void reorder_rows_kernel(const T* __restrict__ src, const int* __restrict__ row_map,
                                                            char* __restrict__ dst, int M, int K) {
-    constexpr int ES = sizeof(T), EPP = 16 / ES;
-    const int m = blockIdx.x;
+    constexpr int ES = sizeof(T);
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nkb = K >> 6;
+    const int m = blockIdx.x * 16 + (lane & 15);
+    if (m >= M) return;
     const size_t srow = row_map ? (size_t)row_map[m] : (size_t)m;
-    for (int k = threadIdx.x * EPP; k < K; k += 256 * EPP) {
-        const f32x4 v = *reinterpret_cast<const f32x4*>(src + srow * K + k);
-        *reinterpret_cast<f32x4*>(dst + frag_elem_off<ES>(m, k, K)) = v;
+    const T* p = src + srow * K + (lane >> 4) * 16;
+    char* q = dst + frag_block_off<ES>(blockIdx.x, 0, K) + lane * 16;
+    for (int k0 = wave; k0 < nkb; k0 += 16) {
+        f32x4 v[4][ES];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const T* s = p + (size_t)min(k0 + 4 * u, nkb - 1) * 64;
+#pragma unroll
+            for (int j = 0; j < ES; ++j) v[u][j] = reinterpret_cast<const f32x4*>(s)[j];
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            if (k0 + 4 * u < nkb)
+#pragma unroll
+                for (int j = 0; j < ES; ++j)
+                    *reinterpret_cast<f32x4*>(q + ((size_t)(k0 + 4 * u) * ES + j) * 1024) = v[u][j];
     }
 }
 
 hipError_t launch_reorder_rows(Dtype dt, const void* src, const int* row_map, void* dst, int M, int K, hipStream_t s) {
     if (M < 1 || K % 64 != 0) return hipErrorInvalidValue;
     if (dt == kBF16)
-        hipLaunchKernelGGL(reorder_rows_kernel<bf16_t>, dim3(M), dim3(256), 0, s, static_cast<const bf16_t*>(src), row_map,
+        hipLaunchKernelGGL(reorder_rows_kernel<bf16_t>, dim3((M + 15) / 16), dim3(256), 0, s, static_cast<const bf16_t*>(src), row_map,
                            static_cast<char*>(dst), M, K);
     else
-        hipLaunchKernelGGL(reorder_rows_kernel<float>, dim3(M), dim3(256), 0, s, static_cast<const float*>(src), row_map,
+        hipLaunchKernelGGL(reorder_rows_kernel<float>, dim3((M + 15) / 16), dim3(256), 0, s, static_cast<const float*>(src), row_map,
                            static_cast<char*>(dst), M, K);
     return hipGetLastError();
 }
