@@ -416,7 +416,7 @@ hipError_t k_resid(aed_decoder* d, int l, const void* A, const void* W, const vo
         g.mu_hat_in = shift_buf(d, l & 1);  // the mean of the rows that entered the layer
         g.shadow_out = shadow_buf(d, d->x_par ^ 1);
         g.stat_tiles = d->cfg.d_model / 16;
-            d->x_par ^= 1;
+        d->x_par ^= 1;
         return launch_gemm(d->dt, PRO_T, EPI_RESID_S, g, d->stream);
     }
     return launch_gemm(d->dt, PRO_T, EPI_RESID, g, d->stream);
@@ -739,7 +739,7 @@ aed_status prefill_pass(aed_decoder* d, const std::vector<int>& prompt_host, int
         if (folded_ln(d)) {
             d->x_par = 0;
             sa.shadow = shadow_buf(d, 0);
-                sa.stats = stats_buf(d, 0);
+            sa.stats = stats_buf(d, 0);
             sa.mu_hat = shift_buf(d, 1);
             sa.rms = d->cfg.norm_type == 1;
         }
