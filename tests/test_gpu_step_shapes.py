@@ -38,6 +38,7 @@ def run(oracle, tol, dtype, d_model, head_dim, enc_lens, d_ffn, steps, seed, **k
     ("bf16", 256, 64, 256, 1), ("bf16", 512, 128, 1280, 16), ("bf16", 768, 64, 2304, 17), ("bf16", 1024, 128, 4096, 33),
     ("bf16", 1024, 128, 4352, 65), ("bf16", 1024, 64, 2048, 129), ("bf16", 1024, 128, 4096, 257),
     ("fp32", 256, 64, 768, 17), ("fp32", 512, 128, 2048, 33), ("fp32", 1024, 128, 4096, 65), ("fp32", 768, 64, 1280, 130),
+    ("fp32", 1024, 128, 4096, 17), ("fp32", 1024, 64, 4096, 32),
 ])
 def test_product_shapes(torch_cuda, oracle, dtype, d_model, head_dim, d_ffn, batch):
     run(oracle, dtype, dtype, d_model, head_dim, [1 + (5 * i) % 9 for i in range(batch)], d_ffn, 2, batch + d_ffn)
