@@ -455,11 +455,13 @@ static TileId choose_tile(const GemmArgs& a, int n_out) {
     int best = 0;
     double best_cost = 1e300;
     long best_wgs = 0;
-    // float32 fragments are twice as wide, and the fused LayerNorm keeps its rows in registers: small tiles only.  Its
-    // kernels run one workgroup per CU, so 17 .. 32 rows take 32 x 16 tiles: a 32 x 4096 output is one round
-    // of 256 workgroups that read W once (float32, batch 32, K = 1024: FFN1 12.3 -> 10.1 us as 32 x 16 instead of 32 x 32,
-    // QKV 11.7 -> 9.9 instead of 16 x 16; 4 layers, 36 positions: 12.35 -> 11.81 ms).
-    const int n_cands = (sizeof(T) == 4 || PRO == PRO_LN) ? 3 : 6;
+    // The fused LayerNorm keeps its float32 rows in registers: small tiles only.  Its kernels run one workgroup per CU, so
+    // 17 .. 32 rows take 32 x 16 tiles: a 32 x 4096 output is one round of 256 workgroups that read W once (float32, batch
+    // 32, K = 1024: FFN1 12.3 -> 10.1 us as 32 x 16 instead of 32 x 32, QKV 11.7 -> 9.9 instead of 16 x 16; 4 layers, 36
+    // positions: 12.35 -> 11.81 ms).  Plain float32 products take all tiles, which their cross K/V product of thousands of
+    // rows needs: on 32 x 32 tiles it is held by operand traffic and by its reductions through LDS (342 us a layer
+    // at batch 32; the same pass 11.81 -> 11.32 ms with 64 x 32 and larger ones).
+    const int n_cands = PRO == PRO_LN ? 3 : 6;
     static_assert(PRO != PRO_LNS || sizeof(T) == 2, "the folded LayerNorm is a bfloat16-mode path");
     for (int c = 0; c < n_cands; ++c) {
         const int bm = 16 * cands[c].mt, bn = 16 * cands[c].nt;
@@ -483,7 +485,7 @@ static hipError_t launch_tiles(const GemmArgs& a, hipStream_t s) {
     if (best == T11) return launch_one<T, PRO, EPI, 1, 1>(a, s);
     if (best == T22) return launch_one<T, PRO, EPI, 2, 2>(a, s);
     if (best == T21) return launch_one<T, PRO, EPI, 2, 1>(a, s);
-    if constexpr (PRO != PRO_LN && sizeof(T) == 2) {
+    if constexpr (PRO != PRO_LN) {
         if (best == T24) return launch_one<T, PRO, EPI, 2, 4>(a, s);
         if (best == T42) return launch_one<T, PRO, EPI, 4, 2>(a, s);
         return launch_one<T, PRO, EPI, 4, 4>(a, s);
