@@ -460,7 +460,7 @@ static TileId choose_tile(const GemmArgs& a, int n_out) {
     // 32, K = 1024: FFN1 12.3 -> 10.1 us as 32 x 16 instead of 32 x 32, QKV 11.7 -> 9.9 instead of 16 x 16; 4 layers, 36
     // positions: 12.35 -> 11.81 ms).  Plain float32 products take all tiles, which their cross K/V product of thousands of
     // rows needs: on 32 x 32 tiles it is held by operand traffic and by its reductions through LDS (342 us a layer
-    // at batch 32; the same pass 11.81 -> 11.32 ms with 64 x 32 and larger ones).
+    // at batch 32, 210 us on 64 x 32; the same pass 11.81 -> 11.32 ms).
     const int n_cands = PRO == PRO_LN ? 3 : 6;
     static_assert(PRO != PRO_LNS || sizeof(T) == 2, "the folded LayerNorm is a bfloat16-mode path");
     for (int c = 0; c < n_cands; ++c) {
