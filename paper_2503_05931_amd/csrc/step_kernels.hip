@@ -101,6 +101,7 @@ __global__ __launch_bounds__(256) void sample_kernel(const float* __restrict__ l
     }
     if (fin) return;
     if (greedy && pos + 1 < st.prompt_len) {  // still feeding the prompt: no token is emitted
+        __syncthreads();  // every wavefront has read the position before it moves on
         if (tid == 0) {
             st.cur_tok[b] = st.prompt[(size_t)b * st.prompt_stride + pos + 1];
             st.seq_len[b] = pos + 1;
