@@ -63,11 +63,11 @@ size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
 // Offsets (bytes) of everything carved from the caller's workspace.
 struct Layout {
-    size_t x, q, q_aux, logits, attn_out, ffn_h, ln_h, x_shadow, ln_stats, mu_hat, kv_slot, ln_fold;
+    size_t x, q, q_aux, logits, attn_out, ffn_h, ln_h, x_shadow, ln_stats, mu_hat, ln_fold;
     size_t stats_elems;  // float2 per statistics buffer
     size_t shadow_bytes; // bytes per shadow buffer
     size_t act_bytes;    // [0, act_bytes): the step's activations and attention partials (x ... counters)
-    size_t seq_len, n_gen, finished, cur_tok, limit, limits_in, n_finished, step_tok;
+    size_t seq_len, n_gen, finished, cur_tok, limit, limits_in, n_finished, step_tok, kv_slot;
     size_t prompt_buf, out_buf, page_table, enc_off, row_map, frame_map, turn_buf, items, part, counters;
     size_t v_seq_len, v_finished, v_cur_tok, v_page_table, v_items;  // state of a prompt-prefill pass's rows
     int act_rows;  // rows the activation buffers hold: max(max_batch, prefill_rows)
@@ -134,7 +134,6 @@ void make_layout(const aed_config* c, Layout* L) {
     L->stats_elems = (d / 16) * Bp;
     L->ln_stats = take(2 * L->stats_elems * 8);
     L->mu_hat = take(2 * Bp * 4);  // two buffers, alternating like the statistics
-    L->kv_slot = take(Ba * 4);
     L->part = take(Ba * H * kMaxChunks * (Dh + 2) * 4);
     L->counters = take(Ba * H * 4);
     L->act_bytes = off;  // everything above is rewritten by every step before it is read (the counters: zero between launches)
@@ -147,6 +146,7 @@ void make_layout(const aed_config* c, Layout* L) {
     L->limits_in = take(B * 4);
     L->n_finished = take(256);
     L->step_tok = take(B * 4);
+    L->kv_slot = take(Ba * 4);
     L->prompt_buf = take(B * (size_t)c->max_dec_len * 4);
     L->out_buf = take(B * (size_t)c->max_dec_len * 4);
     L->page_table = take(B * (size_t)L->max_pages * 4);
@@ -253,7 +253,7 @@ struct aed_decoder {
         st.n_finished = at<int>(lay.n_finished);
         st.page_table = at<int>(lay.page_table);
         st.max_pages = lay.max_pages;
-        st.kv_slot = act_at<int>(lay.kv_slot);
+        st.kv_slot = at<int>(lay.kv_slot);
         st.prompt = prompt_len > 0 ? at<int>(lay.prompt_buf) : nullptr;
         st.out_tokens = at<int>(lay.out_buf);
         st.prompt_len = prompt_len;
@@ -362,7 +362,7 @@ hipError_t k_ln_qkv(aed_decoder* d, int l) {
     g.out = d->act_at<float>(d->lay.q);
     g.k_pool = d->ws + d->lay.k_pool + (size_t)l * d->lay.pool_layer_elems * d->kv_esz;
     g.v_pool = d->ws + d->lay.v_pool + (size_t)l * d->lay.pool_layer_elems * d->kv_esz;
-    g.kv_slot = d->act_at<int>(d->lay.kv_slot);
+    g.kv_slot = d->at<int>(d->lay.kv_slot);
     if (folded_ln(d)) {
         ln_consumer(d, g, d->fold[l].qkv_c1, d->fold[l].qkv_c2, l, true);
         if (merged_products(d)) {  // the stored matrix is [Wqkv.g1 ; Wcq.g2]: the last d columns are P1 of the merged products

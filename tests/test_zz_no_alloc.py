@@ -90,3 +90,18 @@ def test_noalloc_step_rejects_a_decoder_that_does_not_fit():
     assert dec.lib.aed_decode_step(dec.handle, C.c_void_p(tok.data_ptr()), C.c_void_p(out.data_ptr()), None) == binding.AED_OK
     dec.stream.synchronize()
     dec.close()
+
+
+def test_noalloc_step_takes_a_decoder_that_fills_the_scratch_array():
+    """The largest step activations that fit: 62 rows of this model are 8 MiB to the byte."""
+    import torch
+    cfg = W.DecoderConfig(name="unit", n_layers=1, d_model=512, n_heads=8, head_dim=64, d_ffn=3584, vocab=16128,
+                          dtype="fp32", batch=3, prompt_len=1, max_new=7)
+    wl = W.custom(cfg, [4, 1, 9], 5, random_ln=True)
+    dec = binding.Decoder(cfg, wl.weights, max_batch=62, max_total_enc_frames=64, max_dec_len=16)
+    toks = np.random.default_rng(5).integers(0, cfg.vocab, size=(3, 3)).astype(np.int32)
+    got_l, got_i = _run(dec, wl, toks, noalloc=True)
+    ref_l, ref_i = _run(dec, wl, toks, noalloc=False)
+    assert np.isfinite(got_l).all() and (got_l == ref_l).all() and (got_i == ref_i).all()
+    dec.close()
+    torch.cuda.synchronize()
