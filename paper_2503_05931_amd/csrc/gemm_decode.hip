@@ -25,7 +25,10 @@
 // exchanges (mean, then centred sum of squares) and normalises in place, so the
 // rows are read once per workgroup.  Larger batches normalise once in a
 // separate small kernel (layernorm_frag_kernel) and stream the result.
+#include <algorithm>
+
 #include "common.h"
+#include "device_once.h"
 #include "gemm_common.h"
 #include "kernels.h"
 
@@ -442,14 +445,33 @@ __global__ __launch_bounds__(256) void layernorm_frag_kernel(const char* __restr
 // The non-temporal hint for W (GemmArgs::w_nt) goes with launches of one workgroup per CU in at most four row tiles: the
 // workgroups that share a panel of W then ask for it at the same time.  Later ones find nothing left of it in L2 (64 x 4096
 // output of K = 1024 as 512 tiles of 16 x 32: 5.1 us without, 5.9 us with the hint; as 256 tiles of 32 x 32: 4.75, 4.62).
-constexpr long kCus = 256;
+constexpr long kCus = 256;  // compute units of an unpartitioned MI355X; the rules here are measured on one
 static bool hint_w(const GemmArgs& a, long wgs, int row_tiles) { return a.w_nt && wgs <= kCus && row_tiles <= 4; }
+
+// Dynamic LDS that keeps a second workgroup of the float32 32 x 32, 32 x 64 and 64 x 32 tiles off a CU (16 to 34 KB of 160
+// are their own).  By registers two or three fit, and then each runs at less than half its speed: 528 rows, N = 4096,
+// K = 1024 on 32 x 32 tiles 69.3 us shared, 55.4 alone; 64 x 32: 77.9, 57.8; N = 1024, K = 4096 on 32 x 32: 67.3, 51.9.  A
+// launch of one round does not need it (130 rows, K = 4096: 17.9 us without, 19.0 with).
+constexpr unsigned kOneWgLds = 66 << 10;
 
 template <typename T, int PRO, int EPI, int MT, int NT, int NB>
 static hipError_t launch_nb(const GemmArgs& a, hipStream_t s) {
     dim3 grid(a.N / (16 * NT), (a.M + 16 * MT - 1) / (16 * MT));
-    if (hint_w(a, (long)grid.x * grid.y, grid.y)) hipLaunchKernelGGL((gemm_decode_kernel<T, PRO, EPI, MT, NT, true, NB>), grid, dim3(256), 0, s, a);
-    else hipLaunchKernelGGL((gemm_decode_kernel<T, PRO, EPI, MT, NT, false, NB>), grid, dim3(256), 0, s, a);
+    const long wgs = (long)grid.x * grid.y;
+    unsigned lds = 0;
+    if constexpr (sizeof(T) == 4 && PRO == PRO_T && MT * NT >= 4 && MT * NT <= 8) {
+        if (wgs > kCus) {
+            static DeviceOnce once;
+            hipError_t e = once.run([] {
+                return hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_decode_kernel<T, PRO, EPI, MT, NT, false, NB>),
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, kOneWgLds);
+            });
+            if (e != hipSuccess) return e;
+            lds = kOneWgLds;
+        }
+    }
+    if (hint_w(a, wgs, grid.y)) hipLaunchKernelGGL((gemm_decode_kernel<T, PRO, EPI, MT, NT, true, NB>), grid, dim3(256), 0, s, a);
+    else hipLaunchKernelGGL((gemm_decode_kernel<T, PRO, EPI, MT, NT, false, NB>), grid, dim3(256), lds, s, a);
     return hipGetLastError();
 }
 // K = 1024 and, for the second FFN product, K = 4096 are unrolled; every other K runs the loop
@@ -461,38 +483,51 @@ static hipError_t launch_one(const GemmArgs& a, hipStream_t s) {
     return launch_nb<T, PRO, EPI, MT, NT, 0>(a, s);
 }
 
-// Tile choice by a traffic model: each workgroup pulls (BM * bytes(A) + BN * bytes(W)) * K
-// through its CU and the launch's workgroups are spread over the 256 CUs; pick the
-// candidate with the least bytes per CU, then the fewest workgroups.  n_out: output columns of the whole launch.
+// Tile choice: the candidate with the least cost per CU, then the fewest workgroups.  n_out: output columns of the whole
+// launch.
+//
+// bfloat16: a traffic model.  Each workgroup pulls (BM * bytes(A) + BN * bytes(W)) * K through its CU and the launch's
+// workgroups are spread over the 256 CUs.  W mostly comes from memory, A from the caches; the folded LayerNorm reads 512
+// bytes of statistics per row of 2 KB.  Workgroups of the smaller tiles share a CU (two or three fit by registers), so
+// beyond 256 workgroups the bytes through a CU grow in proportion, not in whole rounds.  The 64 x 64 tile runs one workgroup
+// per CU and its stream costs about half more than its bytes say when K is short (measured at M = 256, K = 1024: 9.7 us
+// against 8.2 us for the 32 x 64 tile on the QKV product); over K = 4096 the start-up is a smaller part and the bytes decide
+// (second FFN product at M = 1024: 18.1 us against 19.4 us for 32 x 64).
+//
+// float32: whole rounds of 256 workgroups, because workgroups that share a CU gain little or lose (kOneWgLds; the fused
+// LayerNorm keeps its rows in registers, small tiles only, one workgroup per CU).  A round costs
+//  * behind the fused LayerNorm in proportion to BM + BN (K = 1024: 16 x 16 4.8 us, 32 x 16 7.0, 32 x 32 9.0, and 2.3 a launch);
+//  * else per k the larger of the matrix instructions (BM * BN at 154 TFLOP/s) and what the CU takes in, and 2.5 us of
+//    start-up.  Measured at K = 1024 / 4096, us a round: 16 x 16 2.8 / 7.5, 32 x 16 4.2 / 10.3, 32 x 32 6.4 / 17.5, 32 x 64 and
+//    64 x 32 11 / 33.5, 64 x 64 19.5 / 65.
+// Over 9 row counts from 65 to 1000 and the seven products of a 4-layer decoder (d_model 1024, FFN 4096, the cross K/V
+// product on four times the rows) this choice is on average 0.6 % slower than the fastest tile and nowhere more than 6 %;
+// choosing by bytes among all tiles was 20 % slower (130 rows: cross-attention query 15.0 us on 32 x 16, 10.2 on 32 x 32; FFN1
+// 35.0 on 32 x 64, 24.1 on 64 x 64; FFN2 27.1 on 32 x 16, 17.9 on 32 x 32).
 enum TileId { T11, T21, T22, T24, T42, T44 };
 template <typename T, int PRO>
 static TileId choose_tile(const GemmArgs& a, int n_out) {
     struct Cand { int mt, nt; };
     static const Cand cands[] = {{1, 1}, {2, 1}, {2, 2}, {2, 4}, {4, 2}, {4, 4}};
-    // W mostly comes from memory, A from the caches; the folded LayerNorm reads 512 bytes of statistics per row of 2 KB
-    const double a_bytes = PRO == PRO_LN ? 4.0 : PRO == PRO_LNS ? 1.25 * sizeof(T) : sizeof(T), w_bytes = 1.15 * sizeof(T);
+    const double a_bytes = PRO == PRO_LNS ? 1.25 * sizeof(T) : sizeof(T), w_bytes = 1.15 * sizeof(T);
     int best = 0;
     double best_cost = 1e300;
     long best_wgs = 0;
-    // The fused LayerNorm keeps its float32 rows in registers: small tiles only.  Its kernels run one workgroup per CU, so
-    // 17 .. 32 rows take 32 x 16 tiles: a 32 x 4096 output is one round of 256 workgroups that read W once (float32, batch
-    // 32, K = 1024: FFN1 12.3 -> 10.1 us as 32 x 16 instead of 32 x 32, QKV 11.7 -> 9.9 instead of 16 x 16; 4 layers, 36
-    // positions: 12.35 -> 11.81 ms).  Plain float32 products take all tiles, which their cross K/V product of thousands of
-    // rows needs: on 32 x 32 tiles it is held by operand traffic and by its reductions through LDS (342 us a layer
-    // at batch 32, 210 us on 64 x 32; the same pass 11.81 -> 11.32 ms).
     const int n_cands = PRO == PRO_LN ? 3 : 6;
     static_assert(PRO != PRO_LNS || sizeof(T) == 2, "the folded LayerNorm is a bfloat16-mode path");
+    static_assert(PRO != PRO_LN || sizeof(T) == 4, "the fused LayerNorm is a float32-mode path");
     for (int c = 0; c < n_cands; ++c) {
         const int bm = 16 * cands[c].mt, bn = 16 * cands[c].nt;
         if (a.N % bn != 0) continue;
         const long wgs = (long)((a.M + bm - 1) / bm) * (n_out / bn);
-        // Workgroups of the smaller tiles share a CU (two or three fit by registers), so beyond 256 workgroups the
-        // bytes through a CU grow in proportion, not in whole rounds.  The 64 x 64 tile runs one workgroup per CU
-        // and its stream costs about half more than its bytes say when K is short (measured at M = 256, K = 1024:
-        // 9.7 us against 8.2 us for the 32 x 64 tile on the QKV product); over K = 4096 the start-up is a smaller
-        // part and the bytes decide (second FFN product at M = 1024: 18.1 us against 19.4 us for 32 x 64).
-        const double rounds = wgs > kCus ? (double)wgs / kCus : 1.0;
-        const double cost = rounds * (bm * a_bytes + bn * w_bytes) * (c == T44 && a.K < 4096 ? 1.6 : 1.0);
+        double cost;
+        if constexpr (sizeof(T) == 4) {
+            const double rounds = (double)((wgs + kCus - 1) / kCus);
+            cost = rounds * (PRO == PRO_LN ? bm + bn : (double)a.K * std::max(bm * bn, 14 * (bm + bn)) + 450.0 * 1024);
+        } else {
+            const double rounds = wgs > kCus ? (double)wgs / kCus : 1.0;
+            cost = rounds * (bm * a_bytes + bn * w_bytes) * (c == T44 && a.K < 4096 ? 1.6 : 1.0);
+        }
         if (cost < best_cost || (cost == best_cost && wgs < best_wgs)) { best = c; best_cost = cost; best_wgs = wgs; }
     }
     return (TileId)best;

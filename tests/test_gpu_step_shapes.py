@@ -34,13 +34,16 @@ def run(oracle, tol, dtype, d_model, head_dim, enc_lens, d_ffn, steps, seed, **k
 
 # K = d_model: 256 .. 768 loop or, where they have fewer blocks than the ring, are fetched whole; 1024 unrolled; K = d_ffn:
 # 4096 unrolled, the others loop with a full ring, without one and with remainders.  Rows: one tile of 16, then 32, 64 and
-# 128 rows and one more; 300 rows for short K on the larger tiles.
+# 128 rows and one more; 300 rows for short K on the larger tiles; 130 to 900 rows of float32, where every tile is taken, in
+# one round of workgroups and in several.
 @pytest.mark.parametrize("dtype,d_model,head_dim,d_ffn,batch", [
     ("bf16", 256, 64, 256, 1), ("bf16", 512, 128, 1280, 16), ("bf16", 768, 64, 2304, 17), ("bf16", 1024, 128, 4096, 33),
     ("bf16", 1024, 128, 4352, 65), ("bf16", 1024, 64, 2048, 129), ("bf16", 1024, 128, 4096, 257),
     ("fp32", 256, 64, 768, 17), ("fp32", 512, 128, 2048, 33), ("fp32", 1024, 128, 4096, 65), ("fp32", 768, 64, 1280, 130),
     ("fp32", 1024, 128, 4096, 17), ("fp32", 1024, 64, 4096, 32),
     ("bf16", 256, 64, 256, 300), ("bf16", 512, 64, 768, 300), ("fp32", 256, 64, 256, 300), ("fp32", 512, 128, 512, 300),
+    ("fp32", 1024, 128, 4096, 130), ("fp32", 1024, 128, 4096, 300), ("fp32", 1024, 64, 4096, 528), ("fp32", 1024, 128, 4096, 656),
+    ("fp32", 768, 64, 3072, 300), ("fp32", 1024, 128, 4352, 900),
 ])
 def test_product_shapes(torch_cuda, oracle, dtype, d_model, head_dim, d_ffn, batch):
     run(oracle, dtype, dtype, d_model, head_dim, [1 + (5 * i) % 9 for i in range(batch)], d_ffn, 2, batch + d_ffn)
