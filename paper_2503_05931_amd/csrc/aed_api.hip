@@ -51,9 +51,16 @@ hipError_t scratch_of_current_device(char** out) {
 constexpr int kMaxChunks = 8;       // split-K chunks per (sequence, head)
 constexpr int kTargetItems = 512;      // work items aimed at per attention launch when sequences are cut
 constexpr int kMinItemsNoSplit = 128;  // batch * heads from which sequences are never cut
-// Sequences are not cut into pieces of fewer keys: 8 wavefronts have 256 keys in flight at once, and merging partial
-// results costs 1 us a launch (2-layer float32 decoder, batch 4, at most 98 keys: 2667 us for 36 steps cut into 64-key
-// pieces, 2593 us whole).
+// Sequences are not cut into pieces of fewer keys: 16 wavefronts (float32: 8) take 256 (128) keys a round, with fewer some
+// idle, and merging costs 1 us a launch.  Milliseconds for 40 positions with pieces of at least 64 / 128 / 256 keys
+// (bfloat16 24 layers, float32 4 layers, 8 heads; encoder frames x batch):
+//            200 x 1             500 x 1             200 x 4             500 x 4             300 x 8
+//   bf16     33.1  32.6  31.2    35.3  34.0  33.6    33.8  33.3  31.9    37.3  35.0  34.3    35.9  34.8  34.8
+//   float32   9.8   9.8  10.0    10.3  10.2  10.6                        10.8  10.6  11.1    11.3  10.9  11.4
+//   bf16, 440 positions of history, batch 1, 24 layers:  392  379  363
+// 8-bit caches go with bf16 (500 x 4: 38.5, 36.5, 35.7).  For float32 128 would be better with few sequences, but not where
+// the pieces outnumber the CUs (400 x 12: 12.3 at 128, 11.7 at 256; 200 x 15: 10.7, 10.4).  From 2048 keys on kMaxChunks makes
+// the pieces longer anyway.
 constexpr int kMinChunk = 256;
 constexpr int kMaxPrefillPositions = 8;  // prompt positions per prefill pass
 

@@ -192,12 +192,11 @@ def test_longest_and_shortest_sequence_in_one_batch(torch_cuda, oracle, dtype, n
     dec.close()
 
 
-@pytest.mark.parametrize("dtype", ["fp32", "bf16"])
-def test_long_decode_many_self_chunks(torch_cuda, oracle, dtype):
-    """A decode of 1 100 positions for a batch of two: the paged self-attention cache grows to 69 pages per sequence and
-    is read in the largest number of chunks (the small batch has its long sequences cut), merged by the last arriver."""
+@pytest.mark.parametrize("dtype,S", [("fp32", 1100), ("bf16", 1100), ("fp32", 2040), ("bf16", 2040)])
+def test_long_decode_many_self_chunks(torch_cuda, oracle, dtype, S):
+    """A long decode for a batch of two, whose sequences are cut and merged by the last arriver: 1 100 positions (69 pages
+    per sequence) are read in 5 chunks, 2 040 in 8, the largest number."""
     from tests import gpu_util as G
-    S = 1100
     wl = unit_workload(dtype, 256, 4, 64, [40, 9], seed=91, max_new=S - 4)
     toks = random_tokens(wl.cfg, 2, S, 13)
     m = oracle.Model(wl.cfg, wl.weights)

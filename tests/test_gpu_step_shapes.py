@@ -49,8 +49,8 @@ def test_product_shapes(torch_cuda, oracle, dtype, d_model, head_dim, d_ffn, bat
     run(oracle, dtype, dtype, d_model, head_dim, [1 + (5 * i) % 9 for i in range(batch)], d_ffn, 2, batch + d_ffn)
 
 
-# Attention: 16, 8 and 4 wavefronts per workgroup (up to 256, 1024 and more workgroups of 4 heads), key counts around what
-# they have in flight, and sequences around the length from which a small batch has them cut (256 keys).
+# Cross-attention: 16, 8 and 4 wavefronts per workgroup (up to 256, 1024 and more workgroups of 4 heads), key counts around
+# what they have in flight, and sequences around the length from which a small batch has them cut (256 keys).
 @pytest.mark.parametrize("dtype,kv_fp8", [("bf16", 0), ("bf16", 1), ("fp32", 0)])
 @pytest.mark.parametrize("batch", [1, 2, 64, 65, 256, 257])
 def test_attention_splits(torch_cuda, oracle, dtype, kv_fp8, batch):
@@ -58,6 +58,16 @@ def test_attention_splits(torch_cuda, oracle, dtype, kv_fp8, batch):
     if batch == 1:
         lens = [257]
     run(oracle, "bf16+fp8kv" if kv_fp8 else dtype, dtype, 256, 64, lens, 256, 2, 7 + batch, kv_fp8=kv_fp8)
+
+
+# Self-attention with as much history: batch 32 (128 workgroups, sequences whole) takes the second round of 16 wavefronts
+# (float32: the third of 8); small batches are cut, the last length just past a whole number of chunks.
+@pytest.mark.parametrize("dtype,kv_fp8,batch,steps", [
+    ("bf16", 0, 32, 300), ("bf16", 1, 32, 300), ("fp32", 0, 32, 300), ("bf16", 0, 3, 513), ("bf16", 1, 2, 300), ("fp32", 0, 2, 300),
+])
+def test_self_attention_history(torch_cuda, oracle, dtype, kv_fp8, batch, steps):
+    lens = [1 + (7 * i) % 33 for i in range(batch)]
+    run(oracle, "bf16+fp8kv" if kv_fp8 else dtype, dtype, 256, 64, lens, 256, steps, steps + batch, kv_fp8=kv_fp8)
 
 
 @pytest.mark.parametrize("lens", [[300, 40, 9, 520], [5 + 3 * i for i in range(37)]])

@@ -44,14 +44,15 @@ def test_noalloc_step_equals_step_then_a_smaller_batch():
     assert torch.cuda.is_available()
     rng = np.random.default_rng(12)
     # 3 sequences x 4 heads: far fewer than 128 (sequence, head) pairs, so sequences of more than 256 keys are cut:
-    # two of the three have two chunks of cross-attention keys
-    big = _workload([500, 300, 77], seed=77, max_new=140)
-    small = _workload([33, 5], seed=78, max_new=140)
-    cases = [(big, rng.integers(0, 256, size=(3, 140)).astype(np.int32)),
+    # two of the three have two chunks of cross-attention keys, and from position 256 on all of them two of
+    # self-attention keys
+    big = _workload([500, 300, 77], seed=77, max_new=290)
+    small = _workload([33, 5], seed=78, max_new=290)
+    cases = [(big, rng.integers(0, 256, size=(3, 290)).astype(np.int32)),
              (small, rng.integers(0, 256, size=(2, 21)).astype(np.int32))]
     for wl, toks in cases:
         # a workspace full of NaN patterns: the static-array path must not depend on the workspace's activations
-        dec = G.make_decoder(wl, max_batch=5, max_total=1500, max_dec_len=160, poison=True)
+        dec = G.make_decoder(wl, max_batch=5, max_total=1500, max_dec_len=300, poison=True)
         got_l, got_i = _run(dec, wl, toks, noalloc=True)
         ref_l, ref_i = _run(dec, wl, toks, noalloc=False)
         assert np.isfinite(got_l).all()
