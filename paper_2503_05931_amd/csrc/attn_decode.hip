@@ -215,8 +215,7 @@ __global__ __launch_bounds__(64 * NW, sizeof(KV) <= 2 ? 4 : 1) void attn_decode_
                 }
                 if (lane == 0) sm_fix[DH] = r0;
             }
-            // LDS only: the key / value loads in flight are not waited for here
-            asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+            lds_barrier();  // the key / value loads in flight are not waited for here
             const float rstd = sm_fix[DH];
 #pragma unroll
             for (int e = 0; e < EPL; ++e) q[e] = rstd * q[e] + sm_fix[r * EPL + e];
@@ -350,6 +349,7 @@ __global__ __launch_bounds__(64 * NW, sizeof(KV) <= 2 ? 4 : 1) void attn_decode_
 // flight at once (24 layers, batch 16, steps with logits: 25.73 -> 25.36 ms a
 // pass).  Float32 rows are twice as wide and leave 16 wavefronts registers for
 // one block in flight only: 4 layers at batch 32, 12.33 -> 13.01 ms, so they keep 8.
+// (256: the compute units of an unpartitioned MI355X, on which this was measured.)
 template <typename T, typename KV, int LPK, int DH, bool SELF>
 static void launch_nw(const AttnArgs& a, dim3 grid, hipStream_t s) {
     const size_t wgs = (size_t)grid.x * grid.y * grid.z;

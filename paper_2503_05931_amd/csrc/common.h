@@ -72,11 +72,8 @@ template <typename V> __device__ __forceinline__ V load_global(const void* p) {
     return *(const __attribute__((address_space(1))) V*)(uintptr_t)p;
 }
 
-// ---- a value at a wavefront-uniform address that no kernel in flight writes: a scalar load, which the memory counter of
-// the vector loads does not see ----
-template <typename V> __device__ __forceinline__ V load_const(const V* p) {
-    return *(const __attribute__((address_space(4))) V*)(uintptr_t)p;
-}
+// ---- barrier for data exchanged through LDS: loads from memory stay in flight (__syncthreads waits for them too) ----
+__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
 // ---- 4 consecutive elements as they sit in memory, converted where they are used ----
 template <typename T> struct Raw4;

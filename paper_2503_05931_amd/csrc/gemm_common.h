@@ -59,14 +59,6 @@ __device__ __forceinline__ Frag16<float> load_frag_rm(const float* p) {
     load_f32<16>(p, f.v);
     return f;
 }
-__device__ __forceinline__ void zero_frag(Frag16<bf16_t>& f) {
-#pragma unroll
-    for (int i = 0; i < 8; ++i) { f.lo[i] = (bf16_t)0.f; f.hi[i] = (bf16_t)0.f; }
-}
-__device__ __forceinline__ void zero_frag(Frag16<float>& f) {
-#pragma unroll
-    for (int i = 0; i < 16; ++i) f.v[i] = 0.f;
-}
 __device__ __forceinline__ void pack_frag(const float* y, Frag16<bf16_t>& f) {
 #pragma unroll
     for (int i = 0; i < 8; ++i) { f.lo[i] = (bf16_t)y[i]; f.hi[i] = (bf16_t)y[8 + i]; }
@@ -102,9 +94,6 @@ __device__ __forceinline__ void store4_fp8(unsigned char* p, f32x4 s) {
     w = __builtin_amdgcn_cvt_pk_fp8_f32(s[2], s[3], w, true);
     *reinterpret_cast<int*>(p) = w;
 }
-
-// Barrier for data exchanged through LDS: loads from memory stay in flight (__syncthreads waits for them too).
-__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
 // (mean, sum of squared deviations) of a row from four tiles per lane of the 16 lanes that share it; every lane gets it
 __device__ __forceinline__ float2 combine_tile_stats(f32x4 u, f32x4 v, bool live, int tiles) {
@@ -144,7 +133,7 @@ template <int EPI> __device__ __forceinline__ int row_slot(const GemmArgs& a, in
 
 // One lane's four consecutive outputs C[m][n .. n+3] (bias already added) go where the epilogue says.
 // res: the residual read earlier from the same place (EPI_RESID only); slot: EPI_QKV: kv_slot[m], EPI_CROSSKV: the frame
-// of row m -- read by the caller long before, so that no load stands in front of the stores.
+// of row m -- read by the caller once per row, ahead of the stores.
 template <typename T, int EPI>
 __device__ __forceinline__ void gemm_epilogue(const GemmArgs& a, int m, int n, f32x4 s, f32x4 res, int slot) {
     constexpr int ES = sizeof(T);

@@ -45,7 +45,8 @@ constexpr int kMaxLnBlocks = 4;  // PRO_LN: K <= 4 waves * 4 blocks * 64 = 1024
 //  * everything a workgroup reads -- the first blocks of both operands, then row statistics, vectors, residual tile,
 //    cache slots -- is requested before anything is waited for.  The memory counter is in order and a load behind a
 //    branch makes the compiler wait for all loads before it, so no load sits behind one: indices are clamped instead
-//    (buffers of fragment order are padded to whole tiles), null operands are read from W and replaced by zero;
+//    (buffers of fragment order are padded to whole tiles), null operands are read from W and replaced by zero
+//    (the loads of the fused LayerNorm over a K that is not 1024 are the exception);
 //  * with NB known the k loop is straight-line code and each block is waited for on its own; with a run-time k loop
 //    around conditional loads the compiler waited for the blocks just requested.
 template <typename T, int PRO, int EPI, int MT, int NT, bool WNT, int NB>
@@ -129,7 +130,8 @@ __device__ __forceinline__ void gemm_decode_body(const GemmArgs& a, const int bx
         __builtin_amdgcn_sched_barrier(0);
     };
 
-    // ---- epilogue operands (they do not depend on the product), requested behind the stream's first blocks
+    // ---- epilogue operands (they do not depend on the product), requested behind the stream's first blocks (in front of
+    // the rows and weights where the fused LayerNorm reads them, which has no ring)
     const T* __restrict__ bias = static_cast<const T*>(a.bias);
     // columns from n_raw on are not normalised here (n_raw is a multiple of every tile width: uniform)
     const bool raw = LNS && a.n_raw > 0 && n0 >= a.n_raw;
@@ -155,7 +157,7 @@ __device__ __forceinline__ void gemm_decode_body(const GemmArgs& a, const int bx
             }
             if constexpr (LNS || RS) e_mu[j] = a.mu_hat_in[m];
             if constexpr (RES) e_res[j] = *reinterpret_cast<const f32x4*>(static_cast<const char*>(a.out) + frag_elem_off<4>(m, n, a.N));
-            if constexpr (EPI == EPI_F32 && !LNS)  // optional addend, float [M,N] row-major like the output
+            if constexpr (EPI == EPI_F32 && PRO == PRO_T)  // optional addend, float [M,N] row-major like the output
                 e_res[j] = load_global<f32x4>(a.addend ? static_cast<const void*>(a.addend + (size_t)mc * a.N + n) : W);
             if constexpr (EPI == EPI_QKV) e_slot[j] = a.kv_slot[mc];
             if constexpr (EPI == EPI_CROSSKV) e_slot[j] = load_global<int>(a.out_row_map ? static_cast<const void*>(a.out_row_map + mc) : W);
@@ -351,7 +353,7 @@ __device__ __forceinline__ void gemm_decode_body(const GemmArgs& a, const int bx
             if ((l >> 4) == 0) a.stats_out[(size_t)m * a.stat_tiles + (n >> 4)] = float2{tmean, q};
         } else {
             s += e_bias[j];
-            if constexpr (EPI == EPI_F32) { if (a.addend) s += e_res[j]; }
+            if constexpr (EPI == EPI_F32 && PRO == PRO_T) { if (a.addend) s += e_res[j]; }
             gemm_epilogue<T, EPI>(a, m, n, s, e_res[j], e_slot[j]);
         }
     }
@@ -443,8 +445,9 @@ __global__ __launch_bounds__(256) void layernorm_frag_kernel(const char* __restr
 }
 
 // The non-temporal hint for W (GemmArgs::w_nt) goes with launches of one workgroup per CU in at most four row tiles: the
-// workgroups that share a panel of W then ask for it at the same time.  Later ones find nothing left of it in L2 (64 x 4096
-// output of K = 1024 as 512 tiles of 16 x 32: 5.1 us without, 5.9 us with the hint; as 256 tiles of 32 x 32: 4.75, 4.62).
+// workgroups that share a panel of W then ask for it at the same time, later ones find nothing left of it in L2.  24 layers,
+// 24 positions, ms without the hint / with it everywhere / by this rule: batch 64 25.6, 24.1, 24.1; 128 34.9, 33.3, 33.4; 160
+// 39.3, 41.3, 39.1; 250 44.5 each.
 constexpr long kCus = 256;  // compute units of an unpartitioned MI355X; the rules here are measured on one
 static bool hint_w(const GemmArgs& a, long wgs, int row_tiles) { return a.w_nt && wgs <= kCus && row_tiles <= 4; }
 
@@ -470,8 +473,13 @@ static hipError_t launch_nb(const GemmArgs& a, hipStream_t s) {
             lds = kOneWgLds;
         }
     }
-    if (hint_w(a, wgs, grid.y)) hipLaunchKernelGGL((gemm_decode_kernel<T, PRO, EPI, MT, NT, true, NB>), grid, dim3(256), 0, s, a);
-    else hipLaunchKernelGGL((gemm_decode_kernel<T, PRO, EPI, MT, NT, false, NB>), grid, dim3(256), lds, s, a);
+    if constexpr (sizeof(T) == 2) {  // float32 W is loaded the same way in both
+        if (hint_w(a, wgs, grid.y)) {
+            hipLaunchKernelGGL((gemm_decode_kernel<T, PRO, EPI, MT, NT, true, NB>), grid, dim3(256), 0, s, a);
+            return hipGetLastError();
+        }
+    }
+    hipLaunchKernelGGL((gemm_decode_kernel<T, PRO, EPI, MT, NT, false, NB>), grid, dim3(256), lds, s, a);
     return hipGetLastError();
 }
 // K = 1024 and, for the second FFN product, K = 4096 are unrolled; every other K runs the loop

@@ -63,7 +63,6 @@ __device__ __forceinline__ void load_to_lds16(const void* g, unsigned lds_base) 
 template <int N> __device__ __forceinline__ void wait_loads_barrier() {
     asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(N) : "memory");
 }
-__device__ __forceinline__ void wait_lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
 }  // namespace
 
@@ -159,7 +158,7 @@ __global__ __launch_bounds__(512) void gemm_dma_crosskv_kernel(GemmArgs a) {
     // a chain of branches there leaves the matrix pipeline idle, because all wavefronts are at the same place.
     auto step = [&](auto waited_before) {
         __builtin_amdgcn_sched_barrier(0);
-        if (decltype(waited_before)::value) wait_lds_barrier();
+        if (decltype(waited_before)::value) lds_barrier();
         else wait_loads_barrier<(S - 3) * 4>();  // the requests of the two steps after the next may be in flight
         read_frags(slot, 1, wf1, af1);
         slot = slot == S - 1 ? 0 : slot + 1;

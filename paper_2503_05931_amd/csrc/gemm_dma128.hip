@@ -38,7 +38,6 @@ __device__ __forceinline__ void load_to_lds16(const void* g, unsigned lds_base) 
 template <int N> __device__ __forceinline__ void wait_loads_barrier() {
     asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(N) : "memory");
 }
-__device__ __forceinline__ void wait_lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
 }  // namespace
 
@@ -161,7 +160,7 @@ __global__ __launch_bounds__(256) void gemm_dma128_kernel(GemmArgs a) {
     // One k-step: after the barrier step t+1 is complete in LDS and nobody reads the slot of step t-1 any more.
     auto step = [&](auto waited_before) {
         __builtin_amdgcn_sched_barrier(0);
-        if (decltype(waited_before)::value) wait_lds_barrier();
+        if (decltype(waited_before)::value) lds_barrier();
         else wait_loads_barrier<(S - 2) * 8>();  // the requests of the two steps after this one may be in flight
         const int cur = slot;
         slot = slot == S - 1 ? 0 : slot + 1;
@@ -189,7 +188,7 @@ __global__ __launch_bounds__(256) void gemm_dma128_kernel(GemmArgs a) {
         // they fetch that tile's own first steps again (never used), which keeps every step alike.
         const int ti_next = ti + 1 < my_tiles ? ti + 1 : ti;
         if (LNS && ti > 0) {
-            wait_lds_barrier();  // every wavefront is through the previous tile's epilogue
+            lds_barrier();  // every wavefront is through the previous tile's epilogue
             tile_stats(ti);
         }
         if (ti > 0) load_slots(ti);

@@ -29,7 +29,7 @@ struct GemmArgs {
     int n_raw;            // PRO_LNS + EPI_QKV, streaming kernel: columns [n_raw, N) (n_raw = 3 d_model) are not normalised and not
     float* out2;          // part of q/k/v: their bare sums plus raw_bias go to out2, float [M, N - n_raw] row-major.  0: no such columns
     const float* raw_bias;  // [N - n_raw]
-    const float* addend;  // PRO_T / PRO_LN + EPI_F32, streaming kernel, may be null: float [M,N] row-major added to the result
+    const float* addend;  // PRO_T + EPI_F32, streaming kernel, may be null: float [M,N] row-major added to the result
     const void* W;        // T [N,K] in fragment order (launch_reorder_weight)
     const void* bias;     // T [N] or null
     const void* ln_g;     // T [K]  (PRO_LN)
