@@ -297,11 +297,10 @@ aed_status fail(aed_decoder* d, aed_status st, const char* fmt, ...) {
 
 // Keys per attention work item.  Whole sequences (one workgroup per sequence and
 // head, no merge) whenever batch * heads gives the 256 CUs something to do:
-// measured on MI355X, cutting the 24-layer batch-64 and the 4-layer batch-256
-// workloads into 128-key chunks did not shorten the attention kernels (they are
-// bound by the launch's total bytes at the achievable HBM rate plus fixed
-// launch and first-access latency, not by the longest workgroup).  Only a batch
-// too small to occupy the GPU (batch * heads < kMinItemsNoSplit) has its long
+// measured on MI355X, cutting every sequence of the 24-layer batch-64 and the
+// 4-layer batch-256 workloads into 128-key chunks did not shorten the attention
+// kernels (cutting only a batch's longest sequences has not been tried).  Only a
+// batch too small to occupy the GPU (batch * heads < kMinItemsNoSplit) has its long
 // sequences cut, aiming at kTargetItems items of at least kMinChunk keys and at most
 // kMaxChunks per sequence.
 int pick_chunk(long long total_keys, int max_len, int batch, int n_heads) {
