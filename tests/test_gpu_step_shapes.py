@@ -94,3 +94,20 @@ def test_finished_sequences_leave_the_work_list_and_come_back(torch_cuda, oracle
             if near[b] >= ref_l[b]:
                 assert got[b] == ref_l[b] and (toks[b, got[b]:] == 7).all()
     dec.close()
+
+
+def test_prompt_fed_by_steps_before_a_single_token(torch_cuda, oracle):
+    """A prompt that goes through whole steps (no prefill rows), then one token: no sequence may be off the work list
+    (of more than 64 items) before that token, so its logits are the oracle's."""
+    from tests import gpu_util as G
+    torch, B = torch_cuda, 100
+    cfg = W.DecoderConfig(name="one", n_layers=2, d_model=256, n_heads=4, head_dim=64, d_ffn=256, vocab=192, dtype="fp32",
+                          batch=B, prompt_len=3, max_new=1)
+    wl = W.custom(cfg, [1 + (7 * i) % 33 for i in range(B)], 41, random_ln=True)
+    ref = oracle.Model(cfg, wl.weights).decode_forced(wl.enc, wl.enc_lens, wl.prompt)
+    dec = G.make_decoder(wl)
+    dec.aed_cross_kv_precompute(dec.to_device(wl.enc), wl.enc_lens)
+    _, lens = dec.aed_greedy_decode(torch.from_numpy(wl.prompt).to(dec.device), 1)
+    assert (lens.cpu().numpy() == 1).all()
+    assert np.abs(dec.aed_read_logits() - ref[:, -1]).max() <= G.TOL["fp32"]
+    dec.close()
