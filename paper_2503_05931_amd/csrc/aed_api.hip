@@ -48,7 +48,6 @@ hipError_t scratch_of_current_device(char** out) {
     return hipSuccess;
 }
 
-constexpr int kMaxChunks = 8;       // split-K chunks per (sequence, head)
 constexpr int kTargetItems = 512;      // work items aimed at per attention launch when sequences are cut
 constexpr int kMinItemsNoSplit = 128;  // batch * heads from which sequences are never cut
 // Sequences are not cut into pieces of fewer keys: 16 wavefronts (float32: 8) take 256 (128) keys a round, with fewer some

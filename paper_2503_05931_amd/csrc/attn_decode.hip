@@ -327,16 +327,24 @@ __global__ __launch_bounds__(64 * NW, sizeof(KV) <= 2 ? 4 : 1) void attn_decode_
     if (!sm_last) return;
     float* base = a.part + (size_t)bh * a.max_chunks * (DH + 2);
     if (owner) {
-        float M = -INFINITY;
-        for (int c = 0; c < n_chunks; ++c)
-            M = fmaxf(M, __hip_atomic_load(&base[(size_t)c * (DH + 2) + DH], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+        // every chunk's triple is requested before the first is used: one trip to memory for all of them
+        float pm[kMaxChunks], pl[kMaxChunks], po[kMaxChunks];
+#pragma unroll
+        for (int c = 0; c < kMaxChunks; ++c) {
+            float* pc = base + (size_t)min(c, n_chunks - 1) * (DH + 2);
+            pm[c] = __hip_atomic_load(&pc[DH], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            pl[c] = __hip_atomic_load(&pc[DH + 1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            po[c] = __hip_atomic_load(&pc[tid], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        float M = pm[0];
+#pragma unroll
+        for (int c = 1; c < kMaxChunks; ++c) M = fmaxf(M, pm[c]);
         float L = 0.f, O = 0.f;
-        for (int c = 0; c < n_chunks; ++c) {
-            float* pc = base + (size_t)c * (DH + 2);
-            const float f = __builtin_amdgcn_exp2f(
-                __hip_atomic_load(&pc[DH], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) - M);
-            L += __hip_atomic_load(&pc[DH + 1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) * f;
-            O += __hip_atomic_load(&pc[tid], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) * f;
+#pragma unroll
+        for (int c = 0; c < kMaxChunks; ++c) {
+            const float f = c < n_chunks ? __builtin_amdgcn_exp2f(pm[c] - M) : 0.f;
+            L += pl[c] * f;
+            O += po[c] * f;
         }
         *out = from_f32<T>(O / L);
     }

@@ -47,6 +47,27 @@ __device__ __forceinline__ void store_frag(float* blk, int lane, const Frag16<fl
 #pragma unroll
     for (int j = 0; j < 4; ++j) p[64 * j] = f32x4{f.v[4 * j], f.v[4 * j + 1], f.v[4 * j + 2], f.v[4 * j + 3]};
 }
+// A 16-row tile of a fragment-order operand, n_rows rows of it present.  Lanes of absent rows point past the descriptor's
+// end: such a load returns zeros and asks memory for nothing.
+template <int ES> struct FragRows {
+    static constexpr int kEnd = 0x40000000;  // offsets of present rows are below (16 rows of K elements), of absent ones above
+    __amdgpu_buffer_rsrc_t rsrc;
+    int voff;  // this lane's bytes within a 1 KB piece
+    __device__ __forceinline__ FragRows(const char* base, int n_rows, int lane)
+        : rsrc(__builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(base), 0, kEnd, 0x20000)),
+          voff((lane & 15) < n_rows ? lane * 16 : 0x7ffffff0) {}
+    __device__ __forceinline__ void load(int kb, Frag16<bf16_t>& f) const {
+        f.lo = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(rsrc, voff, kb * 2048, 0));
+        f.hi = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(rsrc, voff, kb * 2048 + 1024, 0));
+    }
+    __device__ __forceinline__ void load(int kb, Frag16<float>& f) const {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const f32x4 v = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rsrc, voff, kb * 4096 + 1024 * j, 0));
+            f.v[4 * j + 0] = v[0]; f.v[4 * j + 1] = v[1]; f.v[4 * j + 2] = v[2]; f.v[4 * j + 3] = v[3];
+        }
+    }
+};
 // row-major source (LayerNorm gain/shift vectors): 16 consecutive elements
 __device__ __forceinline__ Frag16<bf16_t> load_frag_rm(const bf16_t* p) {
     Frag16<bf16_t> f;

@@ -112,6 +112,7 @@ hipError_t launch_weight_product(Dtype dt, const void* W1, const void* g, const 
 hipError_t launch_fold_vec(Dtype dt, const void* W, const void* g, const void* v, float* out, int N, int J, hipStream_t s);
 
 // ---------------------------------------------------------------- decode attention
+constexpr int kMaxChunks = 8;      // chunks per (sequence, head)
 constexpr int kItemOff = INT_MIN;  // sign bit of a cross-attention work item's sequence: it has finished
 struct AttnArgs {
     const float* q;       // [B, d_model]
