@@ -8,6 +8,7 @@
 #include <string.h>
 
 #include <algorithm>
+#include <functional>
 #include <mutex>
 #include <string>
 #include <vector>
@@ -190,10 +191,10 @@ constexpr double kCacheResidentWeightBytes = 192e6;
 constexpr double kResidentLayerBytes = 220e6;
 
 struct GraphKey {
-    int batch = -1, n_items = 0, self_chunk = 0, self_nchunks = 0, prompt_len = 0, max_new = 0;
+    int batch = -1, n_items = 0, cross_keys = 0, self_chunk = 0, self_nchunks = 0, prompt_len = 0, max_new = 0;
     long long total_enc = 0;
     bool operator==(const GraphKey& o) const {
-        return batch == o.batch && n_items == o.n_items && total_enc == o.total_enc && self_chunk == o.self_chunk &&
+        return batch == o.batch && n_items == o.n_items && cross_keys == o.cross_keys && total_enc == o.total_enc && self_chunk == o.self_chunk &&
                self_nchunks == o.self_nchunks && prompt_len == o.prompt_len && max_new == o.max_new;
     }
 };
@@ -229,7 +230,7 @@ struct aed_decoder {
     int host_pos = 0;     // positions fed so far (step API)
     int pages_used = 0;
     int n_items = 0;
-    int self_chunk = 64, self_nchunks = 1, cross_chunk = 64;
+    int self_chunk = 64, self_nchunks = 1, cross_keys = 0;  // cross_keys: most keys of a cross-attention item
     int last_prompt_len = 0, last_max_new = 0;
     long long total_enc = 0;
     const void* last_enc = nullptr;
@@ -309,6 +310,44 @@ int pick_chunk(long long total_keys, int max_len, int batch, int n_heads) {
     c = std::max(c, ((long long)max_len + kMaxChunks - 1) / kMaxChunks);
     c = std::max<long long>(kMinChunk, (c + 63) / 64 * 64);
     return (int)std::min(c, whole);
+}
+
+// Cross-attention work items.  A sequence of more than `longest` keys is cut into pieces of about `piece` keys.
+struct CrossCut { int longest, piece; };
+CrossCut cross_cut(long long total_keys, int n_heads, Dtype dt) {
+    const long long share = total_keys * n_heads / 256 * (dt == kF32 ? 2 : 1);
+    CrossCut c;
+    c.longest = (int)std::min<long long>(std::max<long long>(192, share * 7 / 8), INT_MAX);
+    c.piece = (int)std::min<long long>(std::max<long long>(64, share * 7 / 16 / 32 * 32), INT_MAX);
+    return c;
+}
+int cross_pieces(int len, const CrossCut& c) {
+    return len <= c.longest ? 1 : std::min(kMaxChunks, (len + c.piece - 1) / c.piece);
+}
+int piece_keys(int len, const CrossCut& c) {
+    const int n = cross_pieces(len, c);
+    return ((len + n - 1) / n + 15) / 16 * 16;
+}
+// most keys of an item where the longest sequence has max_len
+int longest_item(int max_len, const CrossCut& c) {
+    return max_len <= c.longest ? max_len : std::max(c.longest, piece_keys(max_len, c));
+}
+// the work items of sequence b of len keys, the first at frame first_frame of the packed layout
+void add_items(std::vector<int4>& items, int b, int len, int first_frame, const CrossCut& c) {
+    const int per = piece_keys(len, c), n = (len + per - 1) / per;
+    for (int k = 0; k < n; ++k) {
+        int4 it;
+        it.x = b; it.y = (k * per) | (k << 16); it.z = std::min(per, len - k * per) | (n << 16); it.w = first_frame;
+        items.push_back(it);
+    }
+}
+// Cut sequences first, so that their merge is over when the rest is; then longest first.  Stable, so that the list is a
+// function of the lengths alone.
+void order_items(std::vector<int4>& items) {
+    std::stable_sort(items.begin(), items.end(), [](const int4& p, const int4& q) {
+        const bool pc = p.z >> 16 > 1, qc = q.z >> 16 > 1;
+        return pc != qc ? pc : (p.z & 0xFFFF) > (q.z & 0xFFFF);
+    });
 }
 
 // ---------------------------------------------------------------- kernel argument builders
@@ -469,8 +508,8 @@ hipError_t k_cross_attn(aed_decoder* d, int l) {
     a.V = d->ws + d->lay.vc + (size_t)l * d->lay.cross_layer_elems * d->kv_esz;
     a.items = d->at<int4>(d->lay.items);
     a.n_items = d->n_items;
+    a.chunk = d->cross_keys;
     a.enc_off = d->at<int>(d->lay.enc_off);
-    a.chunk = d->cross_chunk;
     a.t_cap = d->cfg.max_total_enc_frames;
     if (merged_products(d)) {  // q holds the merged product: the kernel finishes the normalisation
         a.q_stats = stats_buf(d, d->x_par);        // of the rows after the self-attention update
@@ -610,21 +649,11 @@ aed_status start_batch(aed_decoder* d, const void* enc, bool padded, int t_max, 
     // host tables: frame offsets, cross-attention work list, optional row map
     std::vector<int> off(batch + 1, 0);
     for (int b = 0; b < batch; ++b) off[b + 1] = off[b] + enc_lens[b];
-    const int chunk = pick_chunk(total, max_len, batch, d->cfg.n_heads);
+    const CrossCut cut = cross_cut(total, d->cfg.n_heads, d->dt);
     std::vector<int4> items;
-    for (int b = 0; b < batch; ++b) {
-        const int nc = (enc_lens[b] + chunk - 1) / chunk;
-        for (int c = 0; c < nc; ++c) {
-            int4 it;
-            it.x = b; it.y = (c * chunk) | (c << 16); it.z = std::min(chunk, enc_lens[b] - c * chunk) | (nc << 16);
-            it.w = off[b];
-            items.push_back(it);
-        }
-    }
+    for (int b = 0; b < batch; ++b) add_items(items, b, enc_lens[b], off[b], cut);
     if ((int)items.size() > d->lay.max_items) return fail(d, AED_ECAPACITY, "cross-attention work list overflow");
-    // longest first (stable: equal lengths stay in batch order, so the list is a function of the lengths alone)
-    std::stable_sort(items.begin(), items.end(),
-                     [](const int4& p, const int4& q) { return (p.z & 0xFFFF) > (q.z & 0xFFFF); });
+    order_items(items);
 
     HIP_TRY(d, hipStreamSynchronize(d->stream));  // the previous batch's work is done with the old tables
     // the chunk merge's arrival counters return to zero by themselves after every launch; a batch still starts
@@ -640,8 +669,8 @@ aed_status start_batch(aed_decoder* d, const void* enc, bool padded, int t_max, 
     }
     d->batch = batch;
     d->n_items = (int)items.size();
+    d->cross_keys = longest_item(max_len, cut);
     d->items_host = items;
-    d->cross_chunk = chunk;
     d->total_enc = total;
     d->last_enc = enc;
     d->last_enc_padded = padded;
@@ -761,7 +790,7 @@ aed_status prefill_pass(aed_decoder* d, const std::vector<int>& prompt_host, int
     hipError_t e = hipSuccess;
     if (d->stream != nullptr) {
         GraphKey key;
-        key.batch = R; key.n_items = d->n_items; key.self_chunk = d->self_chunk; key.self_nchunks = 1;
+        key.batch = R; key.n_items = d->n_items; key.cross_keys = d->cross_keys; key.self_chunk = d->self_chunk; key.self_nchunks = 1;
         key.total_enc = d->total_enc;
         grc = ensure_graph_of(d, enqueue, key, &d->pf_gexec, &d->pf_gkey);
         if (grc == AED_OK) e = hipGraphLaunch(d->pf_gexec, d->stream);
@@ -968,7 +997,7 @@ aed_status aed_decode_step(aed_decoder* d, const int32_t* tokens_in, int32_t* to
         // the step itself is a replayed graph working on the library's own buffers; the caller's
         // pointers only appear in the small copies around it
         GraphKey key;
-        key.batch = d->batch; key.n_items = d->n_items; key.self_chunk = d->self_chunk;
+        key.batch = d->batch; key.n_items = d->n_items; key.cross_keys = d->cross_keys; key.self_chunk = d->self_chunk;
         key.self_nchunks = d->self_nchunks; key.total_enc = d->total_enc;
         aed_status grc = ensure_graph(d, st, 0, d->at<int>(d->lay.step_tok), key, &d->step_gexec, &d->step_gkey);
         if (grc != AED_OK) return grc;
@@ -1094,7 +1123,7 @@ aed_status aed_greedy_decode(aed_decoder* d, const int32_t* prompt, int32_t prom
     const bool use_graph = d->stream != nullptr;
     if (use_graph) {
         GraphKey key;
-        key.batch = B; key.n_items = d->n_items; key.self_chunk = d->self_chunk; key.self_nchunks = d->self_nchunks;
+        key.batch = B; key.n_items = d->n_items; key.cross_keys = d->cross_keys; key.self_chunk = d->self_chunk; key.self_nchunks = d->self_nchunks;
         key.prompt_len = prompt_len; key.max_new = max_new; key.total_enc = d->total_enc;
         aed_status grc = ensure_graph(d, st, 1, nullptr, key, &d->gexec, &d->gkey);
         if (grc != AED_OK) return grc;
@@ -1176,8 +1205,17 @@ extern "C" aed_status aed_greedy_decode_queue(aed_decoder* d, const void* enc_st
     HIP_TRY(d, hipMemsetAsync(d->ws + d->lay.counters, 0, (size_t)d->lay.act_rows * d->cfg.n_heads * 4, d->stream));
     d->state = aed_decoder::NO_BATCH;  // the per-batch inspection calls do not apply to a queue run
     d->batch = B;
-    d->n_items = B;  // one work item per slot (whole sequences), so that the captured launch shape never changes
-    d->cross_chunk = std::max(64, (max_len + 63) / 64 * 64);
+    // as many work items as the B requests with the most need, so that the captured launch shape never changes
+    const CrossCut cut = cross_cut(src_off[n_requests] * B / n_requests, d->cfg.n_heads, d->dt);
+    {
+        std::vector<int> pieces(n_requests);
+        for (int r = 0; r < n_requests; ++r) pieces[r] = cross_pieces(enc_lens[r], cut);
+        std::partial_sort(pieces.begin(), pieces.begin() + B, pieces.end(), std::greater<int>());
+        long long most = 0;
+        for (int b = 0; b < B; ++b) most += pieces[b];
+        d->n_items = (int)std::min<long long>(most, d->lay.max_items);
+    }
+    d->cross_keys = longest_item(max_len, cut);
     d->total_enc = -1;
     d->page_table.assign((size_t)B * MP, 0);
     for (int b = 0; b < B; ++b)
@@ -1191,7 +1229,7 @@ extern "C" aed_status aed_greedy_decode_queue(aed_decoder* d, const void* enc_st
     const bool use_graph = d->stream != nullptr;
     if (use_graph) {
         GraphKey key;
-        key.batch = B; key.n_items = B; key.self_chunk = d->self_chunk; key.self_nchunks = d->self_nchunks;
+        key.batch = B; key.n_items = d->n_items; key.cross_keys = d->cross_keys; key.self_chunk = d->self_chunk; key.self_nchunks = d->self_nchunks;
         key.prompt_len = prompt_len; key.max_new = max_new; key.total_enc = -1;
         if ((rc = ensure_graph(d, st, 1, nullptr, key, &d->gexec, &d->gkey)) != AED_OK) return rc;
     }
@@ -1205,7 +1243,7 @@ extern "C" aed_status aed_greedy_decode_queue(aed_decoder* d, const void* enc_st
     int* flags = d->pin_poll + 64;
     const int poll_every = 8;
     std::vector<int> h_turn, h_src, h_dst;
-    std::vector<int4> items(B);
+    std::vector<int4> items;
 
     for (;;) {
         // ---- turn slots over: hand finished requests out, start queued ones where frames are free (queue order)
@@ -1241,16 +1279,15 @@ extern "C" aed_status aed_greedy_decode_queue(aed_decoder* d, const void* enc_st
         }
         first = false;
         if (n_turn > 0) {
-            for (int b = 0; b < B; ++b) {  // a parked slot's item is marked: its workgroups exit at once
-                const bool on = slot_req[b] >= 0;
-                items[b].x = on ? b : b | kItemOff; items[b].y = 0; items[b].z = (on ? enc_lens[slot_req[b]] : 1) | (1 << 16);
-                items[b].w = on ? slot_at[b] : 0;
-            }
-            std::vector<int4> sorted(items);
-            std::stable_sort(sorted.begin(), sorted.end(),
-                             [](const int4& p, const int4& q) { return (p.z & 0xFFFF) > (q.z & 0xFFFF); });
+            items.clear();
+            for (int b = 0; b < B; ++b)
+                if (slot_req[b] >= 0) add_items(items, b, enc_lens[slot_req[b]], slot_at[b], cut);
+            order_items(items);
+            int4 off_item;  // the rest of the list is marked: its workgroups exit at once
+            off_item.x = kItemOff; off_item.y = 0; off_item.z = 1 | (1 << 16); off_item.w = 0;
+            items.resize(d->n_items, off_item);
             HIP_TRY(d, hipMemcpyAsync(turn, h_turn.data(), h_turn.size() * 4, hipMemcpyHostToDevice, d->stream));
-            HIP_TRY(d, hipMemcpyAsync(d->at<int4>(d->lay.items), sorted.data(), sorted.size() * 16, hipMemcpyHostToDevice,
+            HIP_TRY(d, hipMemcpyAsync(d->at<int4>(d->lay.items), items.data(), items.size() * 16, hipMemcpyHostToDevice,
                                       d->stream));
             HIP_TRY(d, launch_turn_over_slots(st, turn, turn + B, turn + 2 * B, turn + 3 * B, n_turn, prompts, out_tokens,
                                               out_lens, d->stream));

@@ -284,16 +284,20 @@ __global__ __launch_bounds__(64 * NW, sizeof(KV) <= 2 ? 4 : 1) void attn_decode_
     __syncthreads();
     const bool owner = tid < DH;  // thread tid owns output element tid of this head
 
-    // merge the wavefronts in order (a wavefront without keys has m = -inf, l = 0, acc = 0)
-    float m_tot = sm_m[0];
+    // merge the wavefronts in order (a wavefront without keys has m = -inf, l = 0, acc = 0); no read sits behind a
+    // branch, so that all of them are on their way at once
+    float wm[NW], wl[NW], wo[NW];
 #pragma unroll
-    for (int w = 1; w < NW; ++w) m_tot = fmaxf(m_tot, sm_m[w]);
+    for (int w = 0; w < NW; ++w) { wm[w] = sm_m[w]; wl[w] = sm_l[w]; wo[w] = sm_acc[w][tid % DH]; }
+    float m_tot = wm[0];
+#pragma unroll
+    for (int w = 1; w < NW; ++w) m_tot = fmaxf(m_tot, wm[w]);
     float l_tot = 0.f, o = 0.f;
 #pragma unroll
     for (int w = 0; w < NW; ++w) {
-        const float f = __builtin_amdgcn_exp2f(sm_m[w] - m_tot);
-        l_tot += sm_l[w] * f;
-        if (owner) o += sm_acc[w][tid] * f;
+        const float f = __builtin_amdgcn_exp2f(wm[w] - m_tot);
+        l_tot += wl[w] * f;
+        o += wo[w] * f;
     }
     T* out = reinterpret_cast<T*>(static_cast<char*>(a.out) + frag_elem_off<sizeof(T)>(b, h * DH + (owner ? tid : 0), H * DH));
     if (n_chunks == 1) {  // the output feeds the next GEMM: fragment order
@@ -351,24 +355,25 @@ __global__ __launch_bounds__(64 * NW, sizeof(KV) <= 2 ? 4 : 1) void attn_decode_
     if (tid == 0) __hip_atomic_store(&a.counters[bh], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);  // for the next launch
 }
 
-// Wavefronts per workgroup: 8 when the launch has few workgroups (the longest
-// sequence sets the kernel's duration), 4 when there are plenty; 16 when every
-// workgroup has a CU of its own, which then has 512 keys of its sequence in
-// flight at once (24 layers, batch 16, steps with logits: 25.73 -> 25.36 ms a
-// pass).  Float32 rows are twice as wide and leave 16 wavefronts registers for
-// one block in flight only: 4 layers at batch 32, 12.33 -> 13.01 ms, so they keep 8.
-// (256: the compute units of an unpartitioned MI355X, on which this was measured.)
+// Wavefronts per workgroup.  What counts is that every workgroup is resident from the start (4096 wavefronts fit the 256
+// CUs, of float32 rows 2048) and that a wavefront has a block or two to itself: with 8 wavefronts where 8 do not fit, a
+// second round of workgroups starts when the first is over (self-attention, 24 layers, batch 128, 33 positions: 44.4 ms with
+// 8, 42.9 with 4; batch 64 125.0 and 125.4 for 131), and wavefronts without a block still cost the merge (one utterance,
+// cross- and self-attention on 16 and on 4: 92.6 and 90.1 ms).  16 only where a long item has a CU to itself.
 template <typename T, typename KV, int LPK, int DH, bool SELF>
 static void launch_nw(const AttnArgs& a, dim3 grid, hipStream_t s) {
-    const size_t wgs = (size_t)grid.x * grid.y * grid.z;
+    const size_t wgs = (size_t)grid.x * grid.y * grid.z, resident = sizeof(KV) <= 2 ? 4096 : 2048;
+    if (wgs * 8 > resident || a.chunk <= 64) {
+        hipLaunchKernelGGL((attn_decode_kernel<T, KV, LPK, DH, SELF, 4>), grid, dim3(256), 0, s, a);
+        return;
+    }
     if constexpr (sizeof(KV) <= 2) {
-        if (wgs <= 256) {
+        if (wgs * 16 <= resident && a.chunk > 256) {
             hipLaunchKernelGGL((attn_decode_kernel<T, KV, LPK, DH, SELF, 16>), grid, dim3(1024), 0, s, a);
             return;
         }
     }
-    if (wgs <= 1024) hipLaunchKernelGGL((attn_decode_kernel<T, KV, LPK, DH, SELF, 8>), grid, dim3(512), 0, s, a);
-    else hipLaunchKernelGGL((attn_decode_kernel<T, KV, LPK, DH, SELF, 4>), grid, dim3(256), 0, s, a);
+    hipLaunchKernelGGL((attn_decode_kernel<T, KV, LPK, DH, SELF, 8>), grid, dim3(512), 0, s, a);
 }
 template <typename T, typename KV, int LPK, bool SELF>
 static hipError_t launch_kv(const AttnArgs& a, dim3 grid, hipStream_t s) {
@@ -394,7 +399,7 @@ hipError_t launch_attn_self(Dtype dt, const AttnArgs& a, hipStream_t s) {
 }
 
 hipError_t launch_attn_cross(Dtype dt, const AttnArgs& a, hipStream_t s) {
-    if (a.chunk < 64 || a.chunk % 64 != 0 || !a.items || a.n_items < 1) return hipErrorInvalidValue;
+    if (a.chunk < 1 || !a.items || a.n_items < 1) return hipErrorInvalidValue;
     dim3 grid(a.n_heads, a.n_items);
     return dt == kBF16 ? launch_dh<bf16_t, false>(a, grid, s) : launch_dh<float, false>(a, grid, s);
 }

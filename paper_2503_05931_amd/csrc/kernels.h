@@ -125,12 +125,12 @@ struct AttnArgs {
     const int* page_table;
     int max_pages;
     const int* seq_len;   // keys = seq_len[b] + 1
-    int chunk;            // keys per work item, multiple of 64 (self and cross)
+    int chunk;            // most keys of a work item (self: every one but a sequence's last, a multiple of 64)
     int n_chunks_max;     // grid.z
     int batch;
     // cross
     const int4* items;    // {b (| kItemOff: nothing to do), key_start | chunk_idx << 16, n_keys | n_chunks << 16, first frame of b in the
-                          // packed layout}, longest first
+                          // packed layout}, sequences of several chunks first, then longest first
     int n_items;
     const int* enc_off;   // [B+1] frame offsets in the packed layout
     long long t_cap;
