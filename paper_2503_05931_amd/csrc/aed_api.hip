@@ -191,10 +191,11 @@ constexpr double kCacheResidentWeightBytes = 192e6;
 constexpr double kResidentLayerBytes = 220e6;
 
 struct GraphKey {
-    int batch = -1, n_items = 0, cross_keys = 0, self_chunk = 0, self_nchunks = 0, prompt_len = 0, max_new = 0;
+    int batch = -1, n_items = 0, cross_keys = 0, cross_long = 0, self_chunk = 0, self_nchunks = 0, prompt_len = 0, max_new = 0;
     long long total_enc = 0;
     bool operator==(const GraphKey& o) const {
-        return batch == o.batch && n_items == o.n_items && cross_keys == o.cross_keys && total_enc == o.total_enc && self_chunk == o.self_chunk &&
+        return batch == o.batch && n_items == o.n_items && cross_keys == o.cross_keys && cross_long == o.cross_long &&
+               total_enc == o.total_enc && self_chunk == o.self_chunk &&
                self_nchunks == o.self_nchunks && prompt_len == o.prompt_len && max_new == o.max_new;
     }
 };
@@ -230,7 +231,7 @@ struct aed_decoder {
     int host_pos = 0;     // positions fed so far (step API)
     int pages_used = 0;
     int n_items = 0;
-    int self_chunk = 64, self_nchunks = 1, cross_keys = 0;  // cross_keys: most keys of a cross-attention item
+    int self_chunk = 64, self_nchunks = 1, cross_keys = 0, cross_long = 0;  // cross_keys: most keys of a cross-attention item
     int last_prompt_len = 0, last_max_new = 0;
     long long total_enc = 0;
     const void* last_enc = nullptr;
@@ -509,6 +510,7 @@ hipError_t k_cross_attn(aed_decoder* d, int l) {
     a.items = d->at<int4>(d->lay.items);
     a.n_items = d->n_items;
     a.chunk = d->cross_keys;
+    a.long_items = d->cross_long;
     a.enc_off = d->at<int>(d->lay.enc_off);
     a.t_cap = d->cfg.max_total_enc_frames;
     if (merged_products(d)) {  // q holds the merged product: the kernel finishes the normalisation
@@ -670,6 +672,7 @@ aed_status start_batch(aed_decoder* d, const void* enc, bool padded, int t_max, 
     d->batch = batch;
     d->n_items = (int)items.size();
     d->cross_keys = longest_item(max_len, cut);
+    d->cross_long = total >= (long long)kLongItem * d->n_items;
     d->items_host = items;
     d->total_enc = total;
     d->last_enc = enc;
@@ -790,7 +793,7 @@ aed_status prefill_pass(aed_decoder* d, const std::vector<int>& prompt_host, int
     hipError_t e = hipSuccess;
     if (d->stream != nullptr) {
         GraphKey key;
-        key.batch = R; key.n_items = d->n_items; key.cross_keys = d->cross_keys; key.self_chunk = d->self_chunk; key.self_nchunks = 1;
+        key.batch = R; key.n_items = d->n_items; key.cross_keys = d->cross_keys; key.cross_long = d->cross_long; key.self_chunk = d->self_chunk; key.self_nchunks = 1;
         key.total_enc = d->total_enc;
         grc = ensure_graph_of(d, enqueue, key, &d->pf_gexec, &d->pf_gkey);
         if (grc == AED_OK) e = hipGraphLaunch(d->pf_gexec, d->stream);
@@ -997,7 +1000,7 @@ aed_status aed_decode_step(aed_decoder* d, const int32_t* tokens_in, int32_t* to
         // the step itself is a replayed graph working on the library's own buffers; the caller's
         // pointers only appear in the small copies around it
         GraphKey key;
-        key.batch = d->batch; key.n_items = d->n_items; key.cross_keys = d->cross_keys; key.self_chunk = d->self_chunk;
+        key.batch = d->batch; key.n_items = d->n_items; key.cross_keys = d->cross_keys; key.cross_long = d->cross_long; key.self_chunk = d->self_chunk;
         key.self_nchunks = d->self_nchunks; key.total_enc = d->total_enc;
         aed_status grc = ensure_graph(d, st, 0, d->at<int>(d->lay.step_tok), key, &d->step_gexec, &d->step_gkey);
         if (grc != AED_OK) return grc;
@@ -1123,7 +1126,7 @@ aed_status aed_greedy_decode(aed_decoder* d, const int32_t* prompt, int32_t prom
     const bool use_graph = d->stream != nullptr;
     if (use_graph) {
         GraphKey key;
-        key.batch = B; key.n_items = d->n_items; key.cross_keys = d->cross_keys; key.self_chunk = d->self_chunk; key.self_nchunks = d->self_nchunks;
+        key.batch = B; key.n_items = d->n_items; key.cross_keys = d->cross_keys; key.cross_long = d->cross_long; key.self_chunk = d->self_chunk; key.self_nchunks = d->self_nchunks;
         key.prompt_len = prompt_len; key.max_new = max_new; key.total_enc = d->total_enc;
         aed_status grc = ensure_graph(d, st, 1, nullptr, key, &d->gexec, &d->gkey);
         if (grc != AED_OK) return grc;
@@ -1216,6 +1219,7 @@ extern "C" aed_status aed_greedy_decode_queue(aed_decoder* d, const void* enc_st
         d->n_items = (int)std::min<long long>(most, d->lay.max_items);
     }
     d->cross_keys = longest_item(max_len, cut);
+    d->cross_long = src_off[n_requests] * B / n_requests >= (long long)kLongItem * d->n_items;
     d->total_enc = -1;
     d->page_table.assign((size_t)B * MP, 0);
     for (int b = 0; b < B; ++b)
@@ -1229,7 +1233,7 @@ extern "C" aed_status aed_greedy_decode_queue(aed_decoder* d, const void* enc_st
     const bool use_graph = d->stream != nullptr;
     if (use_graph) {
         GraphKey key;
-        key.batch = B; key.n_items = d->n_items; key.cross_keys = d->cross_keys; key.self_chunk = d->self_chunk; key.self_nchunks = d->self_nchunks;
+        key.batch = B; key.n_items = d->n_items; key.cross_keys = d->cross_keys; key.cross_long = d->cross_long; key.self_chunk = d->self_chunk; key.self_nchunks = d->self_nchunks;
         key.prompt_len = prompt_len; key.max_new = max_new; key.total_enc = -1;
         if ((rc = ensure_graph(d, st, 1, nullptr, key, &d->gexec, &d->gkey)) != AED_OK) return rc;
     }

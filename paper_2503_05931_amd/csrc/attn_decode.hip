@@ -359,11 +359,13 @@ __global__ __launch_bounds__(64 * NW, sizeof(KV) <= 2 ? 4 : 1) void attn_decode_
 // CUs, of float32 rows 2048) and that a wavefront has a block or two to itself: with 8 wavefronts where 8 do not fit, a
 // second round of workgroups starts when the first is over (self-attention, 24 layers, batch 128, 33 positions: 44.4 ms with
 // 8, 42.9 with 4; batch 64 125.0 and 125.4 for 131), and wavefronts without a block still cost the merge (one utterance,
-// cross- and self-attention on 16 and on 4: 92.6 and 90.1 ms).  16 only where a long item has a CU to itself.
+// cross- and self-attention on 16 and on 4: 92.6 and 90.1 ms).  16 only where a long item has a CU to itself.  Items that are
+// long on average (AttnArgs::long_items) keep memory busy in two rounds as well, and 8 wavefronts are through with the last
+// ones sooner (24 layers, batch 128 of 12 to 500 frames, half of whose sequences are through on average: 357 and 350 ms).
 template <typename T, typename KV, int LPK, int DH, bool SELF>
 static void launch_nw(const AttnArgs& a, dim3 grid, hipStream_t s) {
     const size_t wgs = (size_t)grid.x * grid.y * grid.z, resident = sizeof(KV) <= 2 ? 4096 : 2048;
-    if (wgs * 8 > resident || a.chunk <= 64) {
+    if (wgs * 8 > (a.long_items ? 2 * resident : resident) || a.chunk <= 64) {
         hipLaunchKernelGGL((attn_decode_kernel<T, KV, LPK, DH, SELF, 4>), grid, dim3(256), 0, s, a);
         return;
     }

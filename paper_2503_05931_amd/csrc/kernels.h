@@ -113,6 +113,7 @@ hipError_t launch_fold_vec(Dtype dt, const void* W, const void* g, const void* v
 
 // ---------------------------------------------------------------- decode attention
 constexpr int kMaxChunks = 8;      // chunks per (sequence, head)
+constexpr int kLongItem = 192;
 constexpr int kItemOff = INT_MIN;  // sign bit of a cross-attention work item's sequence: it has finished
 struct AttnArgs {
     const float* q;       // [B, d_model]
@@ -126,6 +127,7 @@ struct AttnArgs {
     int max_pages;
     const int* seq_len;   // keys = seq_len[b] + 1
     int chunk;            // most keys of a work item (self: every one but a sequence's last, a multiple of 64)
+    int long_items;       // cross: the items have kLongItem keys or more on average
     int n_chunks_max;     // grid.z
     int batch;
     // cross
