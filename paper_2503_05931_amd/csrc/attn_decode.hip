@@ -49,20 +49,15 @@ typedef unsigned char fp8_t;  // one E4M3 code (OCP 8-bit floating point; the co
 template <> struct RawRow<fp8_t, 16> { u32x4 v; };
 template <> struct RawRow<fp8_t, 8> { u32x2 v; };
 
-template <int EPL> __device__ __forceinline__ RawRow<bf16_t, EPL> load_raw(const bf16_t* p) {
-    RawRow<bf16_t, EPL> r;
-    r.v = __builtin_nontemporal_load(reinterpret_cast<const decltype(r.v)*>(p));
-    return r;
-}
-template <int EPL> __device__ __forceinline__ RawRow<float, EPL> load_raw(const float* p) {
-    RawRow<float, EPL> r;
+// base: the same for the whole wavefront (a scalar register); off: this lane's bytes
+template <int EPL, typename KV> __device__ __forceinline__ RawRow<KV, EPL> load_raw(const char* base, unsigned off) {
+    RawRow<KV, EPL> r;
+    if constexpr (sizeof(KV) < 4) {
+        r.v = __builtin_nontemporal_load(reinterpret_cast<const decltype(r.v)*>(base + off));
+    } else {
 #pragma unroll
-    for (int i = 0; i < EPL / 4; ++i) r.v[i] = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(p) + i);
-    return r;
-}
-template <int EPL> __device__ __forceinline__ RawRow<fp8_t, EPL> load_raw(const fp8_t* p) {
-    RawRow<fp8_t, EPL> r;
-    r.v = __builtin_nontemporal_load(reinterpret_cast<const decltype(r.v)*>(p));
+        for (int i = 0; i < EPL / 4; ++i) r.v[i] = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(base + off) + i);
+    }
     return r;
 }
 // The row slice as floats.  bf16 / float rows are converted element by element where they are used (the
@@ -111,7 +106,7 @@ __global__ __launch_bounds__(64 * NW, sizeof(KV) <= 2 ? 4 : 1) void attn_decode_
     constexpr int EPL = DH / LPK;   // head_dim elements per lane
     constexpr int KPI = 64 / LPK;   // keys per load instruction
     constexpr int NI = 16 / KPI;    // load instructions per 16-key block
-    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, r = lane % LPK, g = lane / LPK;
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, r = lane % LPK, g = lane / LPK;
     const int h = blockIdx.x, H = a.n_heads;
 
     // Work item.  Cross-attention: from the host-built list (longest first, so the long sequences
@@ -121,15 +116,17 @@ __global__ __launch_bounds__(64 * NW, sizeof(KV) <= 2 ? 4 : 1) void attn_decode_
     // per sequence beside the keys' requests, up to 128 of its keys were: 24 layers, batch 128, half of
     // whose sequences are through on average, 370.7 ms; now 355.2.)  Self-attention: blockIdx.y is the sequence, blockIdx.z the chunk.
     int b, start, n, chunk_idx, n_chunks, row0 = 0;
-    int first_page = 0;  // self-attention: page of this wavefront's first block, fetched with the scalars
+    int page0 = 0, page1 = 0;  // self-attention: pages of this wavefront's first two blocks, fetched with the scalars
+    const int* __restrict__ pages = nullptr;
+    int last_page = 0;
     if constexpr (SELF) {
         b = blockIdx.y;
         const int fin = a.finished[b];
         const int total = a.seq_len[b] + 1;
-        {
-            const int blk = min((int)(blockIdx.z * a.chunk >> 4) + wave, a.max_pages - 1);
-            first_page = a.page_table[(size_t)b * a.max_pages + blk];
-        }
+        pages = a.page_table + (size_t)b * a.max_pages + (blockIdx.z * a.chunk >> 4);
+        last_page = a.max_pages - 1 - (int)(blockIdx.z * a.chunk >> 4);
+        page0 = pages[min(wave, last_page)];
+        page1 = pages[min(wave + NW, last_page)];
         if (fin) return;
         n_chunks = (total + a.chunk - 1) / a.chunk;
         chunk_idx = blockIdx.z;
@@ -147,12 +144,7 @@ __global__ __launch_bounds__(64 * NW, sizeof(KV) <= 2 ? 4 : 1) void attn_decode_
         row0 = it.w + start;  // first frame of this chunk in the packed layout
     }
 
-    const KV* __restrict__ Kb = static_cast<const KV*>(a.K);
-    const KV* __restrict__ Vb = static_cast<const KV*>(a.V);
-    size_t cross_base = 0;
-    if constexpr (!SELF) cross_base = ((size_t)h * a.t_cap + row0) * DH;
     const int n_blocks = (n + 15) >> 4;
-    const int* __restrict__ pages = SELF ? a.page_table + (size_t)b * a.max_pages + (start >> 4) : nullptr;
 
     // the query row slice and, behind merged products, what finishes it: requested here, before the first key
     // blocks, and used after them, so that the keys and values do not wait for this round trip
@@ -174,55 +166,56 @@ __global__ __launch_bounds__(64 * NW, sizeof(KV) <= 2 ? 4 : 1) void attn_decode_
                 const int n0 = h * DH + r * EPL;
                 load_f32<EPL>(a.q_c1 + n0, qc1);
                 load_f32<EPL>(a.q_c2 + n0, qc2);
-                if (lane < a.q_stat_tiles) q_st = a.q_stats[(size_t)b * a.q_stat_tiles + lane];
+                q_st = a.q_stats[(size_t)b * a.q_stat_tiles + min(lane, a.q_stat_tiles - 1)];
                 q_muh = a.q_mu_hat[b];
             }
         }
     }
     typedef RawRow<KV, EPL> Raw;
-    // element offset of this lane's slice of key (KPI i + g) of block kb (clamped to the valid keys)
-    auto fetch = [&](int kb, Raw* kf, Raw* vf) {
-        size_t blk_base;
-        if constexpr (SELF) blk_base = ((size_t)(kb == wave ? first_page : pages[kb]) * H + h) * kPage * DH;
-        else blk_base = cross_base + (size_t)kb * 16 * DH;
+    constexpr int ROW = DH * sizeof(KV), BLOCK = 16 * ROW;  // bytes of a key row, of a block
+    // block kb (self-attention: in page `page`); a lane whose key would be past the end reads the last valid one
+    auto fetch = [&](int kb, int page, Raw* kf, Raw* vf) {
+        size_t at;
+        if constexpr (SELF) at = ((size_t)page * H + h) * BLOCK;
+        else at = ((size_t)h * a.t_cap + row0) * ROW + (size_t)kb * BLOCK;
+        const char *kp = static_cast<const char*>(a.K) + at, *vp = static_cast<const char*>(a.V) + at;
         const int last = n - 1 - kb * 16;
 #pragma unroll
         for (int i = 0; i < NI; ++i) {
-            const int j = i * KPI + g;
-            const int jc = j < last ? j : last;  // never read past the valid keys
-            const size_t off = blk_base + (size_t)jc * DH + r * EPL;
-            kf[i] = load_raw<EPL>(Kb + off);
-            vf[i] = load_raw<EPL>(Vb + off);
+            const unsigned off = min(i * KPI + g, last) * ROW + r * EPL * (int)sizeof(KV);
+            kf[i] = load_raw<EPL, KV>(kp, off);
+            vf[i] = load_raw<EPL, KV>(vp, off);
         }
+        __builtin_amdgcn_sched_barrier(0);  // a block's requests and its use stay whole: interleaved they do not fit the registers
     };
-    // two blocks in flight per wavefront: fetch block i+1 while block i is consumed
-    Raw k0[NI], v0[NI], k1[NI], v1[NI];
-    int kb = wave;
-    if (kb < n_blocks) fetch(kb, k0, v0);
-    if constexpr (!SELF) {
-        if (q_fix) {  // q = rstd' (P - (mu' - mu_hat) c1) + c2 with this row's statistics
-            __shared__ float sm_fix[DH + 1];
-            if (wave == 0) {
-                const int tiles = a.q_stat_tiles;
-                float mu = wave_sum(q_st.x) / (float)tiles;
-                const float dev = lane < tiles ? (q_st.x - mu) * (q_st.x - mu) : 0.f;
-                const float m2 = wave_sum(q_st.y) + 16.f * wave_sum(dev);
-                const float r0 = fold_norm(a.q_rms, 16.f * (float)tiles, a.q_eps, m2, mu);
-                const float sh = r0 * (mu - q_muh);
-                if (g == 0) {
+    // finishes the query (behind the first requests for keys and values)
+    auto finish_query = [&]() {
+        if constexpr (!SELF) {
+            if (q_fix) {  // q = rstd' (P - (mu' - mu_hat) c1) + c2 with this row's statistics
+                __shared__ float sm_fix[DH + 1];
+                if (wave == 0) {
+                    const int tiles = a.q_stat_tiles;
+                    const bool on = lane < tiles;  // the other lanes hold the last tile's once more
+                    float mu = wave_sum(on ? q_st.x : 0.f) / (float)tiles;
+                    const float dev = on ? (q_st.x - mu) * (q_st.x - mu) : 0.f;
+                    const float m2 = wave_sum(on ? q_st.y : 0.f) + 16.f * wave_sum(dev);
+                    const float r0 = fold_norm(a.q_rms, 16.f * (float)tiles, a.q_eps, m2, mu);
+                    const float sh = r0 * (mu - q_muh);
+                    if (g == 0) {
 #pragma unroll
-                    for (int e = 0; e < EPL; ++e) sm_fix[r * EPL + e] = qc2[e] - sh * qc1[e];
+                        for (int e = 0; e < EPL; ++e) sm_fix[r * EPL + e] = qc2[e] - sh * qc1[e];
+                    }
+                    if (lane == 0) sm_fix[DH] = r0;
                 }
-                if (lane == 0) sm_fix[DH] = r0;
+                lds_barrier();  // the key / value loads in flight are not waited for here
+                const float rstd = sm_fix[DH];
+#pragma unroll
+                for (int e = 0; e < EPL; ++e) q[e] = rstd * q[e] + sm_fix[r * EPL + e];
             }
-            lds_barrier();  // the key / value loads in flight are not waited for here
-            const float rstd = sm_fix[DH];
-#pragma unroll
-            for (int e = 0; e < EPL; ++e) q[e] = rstd * q[e] + sm_fix[r * EPL + e];
         }
-    }
 #pragma unroll
-    for (int e = 0; e < EPL; ++e) q[e] *= a.scale_log2e;
+        for (int e = 0; e < EPL; ++e) q[e] *= a.scale_log2e;
+    };
 
     float m_run = -INFINITY, l_run = 0.f;
     float acc[EPL];
@@ -258,16 +251,51 @@ __global__ __launch_bounds__(64 * NW, sizeof(KV) <= 2 ? 4 : 1) void attn_decode_
             for (int e = 0; e < EPL; ++e) acc[e] = fmaf(p, raw_at<EPL>(vx, e), acc[e]);
         }
         m_run = m_new;
+        __builtin_amdgcn_sched_barrier(0);
     };
 
-    while (kb < n_blocks) {
-        if (kb + NW < n_blocks) fetch(kb + NW, k1, v1);
+    // Two blocks in flight per wavefront.  No request sits behind a branch that a path without it joins: there the compiler's
+    // wait for the block in use waited for the next one too, and the wait for what finishes the query for all keys and
+    // values.  24 layers: three utterances one at a time 89.9 -> 86.1 ms, batch 16 with logits 23.6 -> 22.7, batch 64 125.9 ->
+    // 123.9; 4 layers: batch 256 42.4 -> 41.6, batch 203 with 8-bit caches 17.4 -> 16.8.  (The same through a buffer
+    // descriptor that ends with the keys, every request unconditional: requests past the end cost their issue, 42.6.)
+    Raw k0[NI], v0[NI], k1[NI], v1[NI];
+    const int mine = (n_blocks - wave + NW - 1) / NW;  // this wavefront's blocks: wave, wave + NW, ..
+    int kb = wave;
+    if (mine >= 2) {
+        int left = mine - 2;  // blocks not requested yet
+        if (left & 1) {       // an odd number: the first apart, so that the loop below has pairs
+            fetch(kb, page0, k1, v1);
+            fetch(kb + NW, page1, k0, v0);
+            if constexpr (SELF) page0 = pages[kb + 2 * NW];
+            finish_query();
+            consume(kb, k1, v1);
+            fetch(kb + 2 * NW, page0, k1, v1);
+            kb += NW;
+            --left;
+        } else {
+            fetch(kb, page0, k0, v0);
+            fetch(kb + NW, page1, k1, v1);
+            finish_query();
+        }
+        for (; left > 0; left -= 2, kb += 2 * NW) {
+            if constexpr (SELF) {
+                page0 = pages[kb + 2 * NW];
+                page1 = pages[kb + 3 * NW];
+            }
+            consume(kb, k0, v0);
+            fetch(kb + 2 * NW, page0, k0, v0);
+            consume(kb + NW, k1, v1);
+            fetch(kb + 3 * NW, page1, k1, v1);
+        }
         consume(kb, k0, v0);
-        kb += NW;
-        if (kb >= n_blocks) break;
-        if (kb + NW < n_blocks) fetch(kb + NW, k0, v0);
-        consume(kb, k1, v1);
-        kb += NW;
+        consume(kb + NW, k1, v1);
+    } else if (mine == 1) {
+        fetch(kb, page0, k0, v0);
+        finish_query();
+        consume(kb, k0, v0);
+    } else {
+        finish_query();  // its barrier counts every wavefront
     }
     // lanes of different groups g hold different keys: add them up
     l_run = keys_sum<LPK>(l_run);
