@@ -315,7 +315,10 @@ int pick_chunk(long long total_keys, int max_len, int batch, int n_heads) {
 
 // Cross-attention work items.  A sequence of more than `longest` keys is cut into pieces of about `piece` keys.
 struct CrossCut { int longest, piece; };
-CrossCut cross_cut(long long total_keys, int n_heads, Dtype dt) {
+// Batches of more than 4096 are left whole: a CU has 32 workgroups and more then, and with the pieces a prompt pass's list
+// (kMaxPrefillPositions times as long) could pass what a launch grid holds in y.
+CrossCut cross_cut(long long total_keys, int batch, int n_heads, Dtype dt) {
+    if (batch > 4096) return CrossCut{INT_MAX, INT_MAX};
     const long long share = total_keys * n_heads / 256 * (dt == kF32 ? 2 : 1);
     CrossCut c;
     c.longest = (int)std::min<long long>(std::max<long long>(192, share * 7 / 8), INT_MAX);
@@ -651,7 +654,7 @@ aed_status start_batch(aed_decoder* d, const void* enc, bool padded, int t_max, 
     // host tables: frame offsets, cross-attention work list, optional row map
     std::vector<int> off(batch + 1, 0);
     for (int b = 0; b < batch; ++b) off[b + 1] = off[b] + enc_lens[b];
-    const CrossCut cut = cross_cut(total, d->cfg.n_heads, d->dt);
+    const CrossCut cut = cross_cut(total, batch, d->cfg.n_heads, d->dt);
     std::vector<int4> items;
     for (int b = 0; b < batch; ++b) add_items(items, b, enc_lens[b], off[b], cut);
     if ((int)items.size() > d->lay.max_items) return fail(d, AED_ECAPACITY, "cross-attention work list overflow");
@@ -1209,7 +1212,7 @@ extern "C" aed_status aed_greedy_decode_queue(aed_decoder* d, const void* enc_st
     d->state = aed_decoder::NO_BATCH;  // the per-batch inspection calls do not apply to a queue run
     d->batch = B;
     // as many work items as the B requests with the most need, so that the captured launch shape never changes
-    const CrossCut cut = cross_cut(src_off[n_requests] * B / n_requests, d->cfg.n_heads, d->dt);
+    const CrossCut cut = cross_cut(src_off[n_requests] * B / n_requests, B, d->cfg.n_heads, d->dt);
     {
         std::vector<int> pieces(n_requests);
         for (int r = 0; r < n_requests; ++r) pieces[r] = cross_pieces(enc_lens[r], cut);

@@ -19,9 +19,12 @@ def torch_cuda():
 
 
 def queue_workload(dtype, n_req, seed, max_new, d_model=256, n_heads=4, head_dim=64, max_enc=130, eos_id=-1, pad_id=0,
-                   min_enc=1, kv_fp8=0):
+                   min_enc=1, kv_fp8=0, long_every=1):
     rng = np.random.default_rng(seed)
     enc_lens = rng.integers(min_enc, max_enc + 1, size=n_req)
+    if long_every > 1:
+        enc_lens[np.arange(n_req) % long_every != 0] //= 10
+        enc_lens = np.maximum(enc_lens, 1)
     enc_lens[rng.integers(0, n_req)] = max_enc          # the longest length occurs
     cfg = W.DecoderConfig(name="queue", n_layers=2, d_model=d_model, n_heads=n_heads, head_dim=head_dim, d_ffn=512,
                           vocab=256, dtype=dtype, batch=n_req, prompt_len=3, max_new=max_new, eos_id=eos_id,
@@ -89,6 +92,11 @@ def test_queue_frames_scarce(torch_cuda, oracle):
 def test_queue_bf16(torch_cuda, oracle):
     run_queue_case(torch_cuda, oracle, "bf16", n_req=50, slots=16, seed=13, max_new=20, d_model=512, n_heads=4,
                    head_dim=128, max_enc=300)
+
+
+def test_queue_of_long_requests_among_short_ones(torch_cuda, oracle):
+    # one request in six has ten times the others' frames and is cut into several work items; the others pad the list
+    run_queue_case(torch_cuda, oracle, "fp32", n_req=30, slots=5, seed=37, max_new=10, max_enc=700, long_every=6)
 
 
 def test_queue_large_refill_through_the_frame_map(torch_cuda, oracle):

@@ -70,6 +70,19 @@ def test_self_attention_history(torch_cuda, oracle, dtype, kv_fp8, batch, steps)
     run(oracle, "bf16+fp8kv" if kv_fp8 else dtype, dtype, 256, 64, lens, 256, steps, steps + batch, kv_fp8=kv_fp8)
 
 
+# Cross-attention of whole sequences of every number of blocks that a wavefront's loop tells apart (none, one, two, odd, even):
+# 256 sequences of up to 340 keys on 4 wavefronts, on 8 where they are long on average, and some of several times the mean's
+# keys among short ones, which are cut into 2 to 8 pieces (float32: others than bfloat16), the last one key long.
+@pytest.mark.parametrize("dtype,kv_fp8", [("bf16", 0), ("bf16", 1), ("fp32", 0)])
+@pytest.mark.parametrize("batch,lens", [
+    (256, lambda i: 1 + (37 * i) % 340), (256, lambda i: 160 + (37 * i) % 180),
+    (40, lambda i: [192, 193, 321, 449, 512, 600, 1500][i // 5 % 7] if i % 5 == 0 else 1 + 7 * i % 60),
+])
+def test_cross_attention_blocks_and_pieces(torch_cuda, oracle, dtype, kv_fp8, batch, lens):
+    run(oracle, "bf16+fp8kv" if kv_fp8 else dtype, dtype, 256, 64, [lens(i) for i in range(batch)], 256, 1, 3 + batch,
+        kv_fp8=kv_fp8)
+
+
 @pytest.mark.parametrize("lens", [[300, 40, 9, 520], [5 + 3 * i for i in range(37)]])
 def test_finished_sequences_leave_the_work_list_and_come_back(torch_cuda, oracle, lens):
     """Sequences that end are struck off the cross-attention work list (with few sequences several items each); the same
