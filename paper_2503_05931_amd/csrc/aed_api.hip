@@ -190,13 +190,26 @@ constexpr double kCacheResidentWeightBytes = 192e6;
 // layers are the optimum, 1.195 -> 1.160 ms per step; from 9 on the cache thrashes and the gain is gone.)
 constexpr double kResidentLayerBytes = 220e6;
 
+// What the launches of a captured step or prompt pass depend on; everything else they read from device memory.
 struct GraphKey {
     int batch = -1, n_items = 0, cross_keys = 0, cross_long = 0, self_chunk = 0, self_nchunks = 0, prompt_len = 0, max_new = 0;
-    long long total_enc = 0;
     bool operator==(const GraphKey& o) const {
         return batch == o.batch && n_items == o.n_items && cross_keys == o.cross_keys && cross_long == o.cross_long &&
-               total_enc == o.total_enc && self_chunk == o.self_chunk &&
-               self_nchunks == o.self_nchunks && prompt_len == o.prompt_len && max_new == o.max_new;
+               self_chunk == o.self_chunk && self_nchunks == o.self_nchunks && prompt_len == o.prompt_len && max_new == o.max_new;
+    }
+};
+// The graphs of the last few shapes (24 layers, three utterances of other lengths in turn 87.5 -> 84.9 ms); the one unused for longest makes room.  Every change of shape comes after the stream
+// has been waited for, so a graph that goes is not running.
+constexpr int kGraphs = 4;
+struct GraphPool {
+    struct Entry { GraphKey key; hipGraphExec_t exec = nullptr; unsigned long long used = 0; };
+    Entry e[kGraphs];
+    unsigned long long clock = 0;
+    void clear() {
+        for (Entry& g : e) {
+            if (g.exec) (void)hipGraphExecDestroy(g.exec);
+            g = Entry();
+        }
     }
 };
 
@@ -241,12 +254,9 @@ struct aed_decoder {
     int* pin_poll = nullptr;  // pinned host memory for the finished-count poll
     hipEvent_t poll_event[2] = {nullptr, nullptr};
     hipEvent_t t0 = nullptr, t1 = nullptr;
-    hipGraphExec_t gexec = nullptr;       // one greedy step (prompt feeding, EOS rules, output writes)
-    GraphKey gkey;
-    hipGraphExec_t step_gexec = nullptr;  // one aed_decode_step step (argmax only, ids into step_tok)
-    GraphKey step_gkey;
-    hipGraphExec_t pf_gexec = nullptr;    // one prompt-prefill pass
-    GraphKey pf_gkey;
+    GraphPool greedy_graphs;  // one greedy step (prompt feeding, EOS rules, output writes)
+    GraphPool step_graphs;    // one aed_decode_step step (argmax only, ids into step_tok)
+    GraphPool prefill_graphs; // one prompt-prefill pass
     std::string err;
 
     template <typename T> T* at(size_t off) const { return reinterpret_cast<T*>(ws + off); }
@@ -700,11 +710,24 @@ aed_status start_batch(aed_decoder* d, const void* enc, bool padded, int t_max, 
     return AED_OK;
 }
 
-// Capture what enqueue launches into a launch graph; an existing graph of the same shape is kept.
+// The shape of the present batch's launches, for a graph of them.
+GraphKey graph_key(const aed_decoder* d) {
+    GraphKey key;
+    key.batch = d->batch; key.n_items = d->n_items;
+    key.cross_keys = attn_keys_class(d->cross_keys); key.cross_long = d->cross_long;
+    key.self_chunk = d->self_chunk; key.self_nchunks = d->self_nchunks;
+    return key;
+}
+// Capture what enqueue launches into a launch graph; a graph of the same shape that the pool still has is taken.
 template <typename F>
-aed_status ensure_graph_of(aed_decoder* d, F enqueue, const GraphKey& key, hipGraphExec_t* exec, GraphKey* have) {
-    if (*exec && key == *have) return AED_OK;
-    if (*exec) { (void)hipGraphExecDestroy(*exec); *exec = nullptr; }
+aed_status ensure_graph_of(aed_decoder* d, F enqueue, const GraphKey& key, GraphPool* pool, hipGraphExec_t* out) {
+    GraphPool::Entry* g = &pool->e[0];
+    for (GraphPool::Entry& c : pool->e) {
+        if (c.exec && key == c.key) { c.used = ++pool->clock; *out = c.exec; return AED_OK; }
+        if (c.used < g->used) g = &c;
+    }
+    if (g->exec) (void)hipGraphExecDestroy(g->exec);
+    *g = GraphPool::Entry();
     hipGraph_t graph = nullptr;
     HIP_TRY(d, hipStreamBeginCapture(d->stream, hipStreamCaptureModeThreadLocal));
     hipError_t e = enqueue();
@@ -713,16 +736,18 @@ aed_status ensure_graph_of(aed_decoder* d, F enqueue, const GraphKey& key, hipGr
         if (graph) (void)hipGraphDestroy(graph);
         return fail(d, AED_EHIP, "graph capture: %s", hipGetErrorString(e != hipSuccess ? e : e2));
     }
-    e = hipGraphInstantiate(exec, graph, nullptr, nullptr, 0);
+    e = hipGraphInstantiate(&g->exec, graph, nullptr, nullptr, 0);
     (void)hipGraphDestroy(graph);
-    if (e != hipSuccess) { *exec = nullptr; return fail(d, AED_EHIP, "hipGraphInstantiate: %s", hipGetErrorString(e)); }
-    *have = key;
+    if (e != hipSuccess) { g->exec = nullptr; return fail(d, AED_EHIP, "hipGraphInstantiate: %s", hipGetErrorString(e)); }
+    g->key = key;
+    g->used = ++pool->clock;
+    *out = g->exec;
     return AED_OK;
 }
 // one step (greedy or plain)
-aed_status ensure_graph(aed_decoder* d, const StateArgs& st, int greedy, int* step_out, const GraphKey& key,
-                        hipGraphExec_t* exec, GraphKey* have) {
-    return ensure_graph_of(d, [&]() { return enqueue_step(d, st, greedy, step_out); }, key, exec, have);
+aed_status ensure_graph(aed_decoder* d, const StateArgs& st, int greedy, int* step_out, const GraphKey& key, GraphPool* pool,
+                        hipGraphExec_t* out) {
+    return ensure_graph_of(d, [&]() { return enqueue_step(d, st, greedy, step_out); }, key, pool, out);
 }
 
 aed_status upload_page_table(aed_decoder* d) {
@@ -795,11 +820,9 @@ aed_status prefill_pass(aed_decoder* d, const std::vector<int>& prompt_host, int
     aed_status grc = AED_OK;
     hipError_t e = hipSuccess;
     if (d->stream != nullptr) {
-        GraphKey key;
-        key.batch = R; key.n_items = d->n_items; key.cross_keys = d->cross_keys; key.cross_long = d->cross_long; key.self_chunk = d->self_chunk; key.self_nchunks = 1;
-        key.total_enc = d->total_enc;
-        grc = ensure_graph_of(d, enqueue, key, &d->pf_gexec, &d->pf_gkey);
-        if (grc == AED_OK) e = hipGraphLaunch(d->pf_gexec, d->stream);
+        hipGraphExec_t g = nullptr;
+        grc = ensure_graph_of(d, enqueue, graph_key(d), &d->prefill_graphs, &g);
+        if (grc == AED_OK) e = hipGraphLaunch(g, d->stream);
     } else {
         e = enqueue();
     }
@@ -958,9 +981,9 @@ aed_status aed_decoder_create(const aed_config* cfg, const aed_weights* weights,
 aed_status aed_decoder_destroy(aed_decoder* d) {
     if (!d) return AED_OK;
     (void)hipStreamSynchronize(d->stream);
-    if (d->gexec) (void)hipGraphExecDestroy(d->gexec);
-    if (d->step_gexec) (void)hipGraphExecDestroy(d->step_gexec);
-    if (d->pf_gexec) (void)hipGraphExecDestroy(d->pf_gexec);
+    d->greedy_graphs.clear();
+    d->step_graphs.clear();
+    d->prefill_graphs.clear();
     for (int i = 0; i < 2; ++i)
         if (d->poll_event[i]) (void)hipEventDestroy(d->poll_event[i]);
     if (d->t0) (void)hipEventDestroy(d->t0);
@@ -1002,12 +1025,10 @@ aed_status aed_decode_step(aed_decoder* d, const int32_t* tokens_in, int32_t* to
     if (d->stream != nullptr) {
         // the step itself is a replayed graph working on the library's own buffers; the caller's
         // pointers only appear in the small copies around it
-        GraphKey key;
-        key.batch = d->batch; key.n_items = d->n_items; key.cross_keys = d->cross_keys; key.cross_long = d->cross_long; key.self_chunk = d->self_chunk;
-        key.self_nchunks = d->self_nchunks; key.total_enc = d->total_enc;
-        aed_status grc = ensure_graph(d, st, 0, d->at<int>(d->lay.step_tok), key, &d->step_gexec, &d->step_gkey);
+        hipGraphExec_t g = nullptr;
+        aed_status grc = ensure_graph(d, st, 0, d->at<int>(d->lay.step_tok), graph_key(d), &d->step_graphs, &g);
         if (grc != AED_OK) return grc;
-        HIP_TRY(d, hipGraphLaunch(d->step_gexec, d->stream));
+        HIP_TRY(d, hipGraphLaunch(g, d->stream));
         if (tokens_out)
             HIP_TRY(d, hipMemcpyAsync(tokens_out, d->at<int>(d->lay.step_tok), (size_t)d->batch * 4,
                                       hipMemcpyDeviceToDevice, d->stream));
@@ -1127,11 +1148,11 @@ aed_status aed_greedy_decode(aed_decoder* d, const int32_t* prompt, int32_t prom
 
     // one launch graph per shape; replayed for every step
     const bool use_graph = d->stream != nullptr;
+    hipGraphExec_t graph = nullptr;
     if (use_graph) {
-        GraphKey key;
-        key.batch = B; key.n_items = d->n_items; key.cross_keys = d->cross_keys; key.cross_long = d->cross_long; key.self_chunk = d->self_chunk; key.self_nchunks = d->self_nchunks;
-        key.prompt_len = prompt_len; key.max_new = max_new; key.total_enc = d->total_enc;
-        aed_status grc = ensure_graph(d, st, 1, nullptr, key, &d->gexec, &d->gkey);
+        GraphKey key = graph_key(d);
+        key.prompt_len = prompt_len; key.max_new = max_new;
+        aed_status grc = ensure_graph(d, st, 1, nullptr, key, &d->greedy_graphs, &graph);
         if (grc != AED_OK) return grc;
     }
     // Early stop: every poll_every steps the finished count is copied to pinned
@@ -1143,7 +1164,7 @@ aed_status aed_greedy_decode(aed_decoder* d, const int32_t* prompt, int32_t prom
     int issued = 0, seen = 0;
     bool done = false;
     for (int s = 0; s < n_steps && !done; ++s) {
-        if (use_graph) HIP_TRY(d, hipGraphLaunch(d->gexec, d->stream));
+        if (use_graph) HIP_TRY(d, hipGraphLaunch(graph, d->stream));
         else HIP_TRY(d, enqueue_step(d, st, 1, nullptr));
         if (!can_stop_early) continue;
         while (seen < issued && hipEventQuery(d->poll_event[seen & 1]) == hipSuccess) {
@@ -1234,11 +1255,11 @@ extern "C" aed_status aed_greedy_decode_queue(aed_decoder* d, const void* enc_st
     d->self_nchunks = (total_len + d->self_chunk - 1) / d->self_chunk;
     const StateArgs st = d->state_args(prompt_len, max_new);
     const bool use_graph = d->stream != nullptr;
+    hipGraphExec_t graph = nullptr;
     if (use_graph) {
-        GraphKey key;
-        key.batch = B; key.n_items = d->n_items; key.cross_keys = d->cross_keys; key.cross_long = d->cross_long; key.self_chunk = d->self_chunk; key.self_nchunks = d->self_nchunks;
-        key.prompt_len = prompt_len; key.max_new = max_new; key.total_enc = -1;
-        if ((rc = ensure_graph(d, st, 1, nullptr, key, &d->gexec, &d->gkey)) != AED_OK) return rc;
+        GraphKey key = graph_key(d);
+        key.prompt_len = prompt_len; key.max_new = max_new;
+        if ((rc = ensure_graph(d, st, 1, nullptr, key, &d->greedy_graphs, &graph)) != AED_OK) return rc;
     }
 
     FrameSpace frames(d->cfg.max_total_enc_frames);
@@ -1317,7 +1338,7 @@ extern "C" aed_status aed_greedy_decode_queue(aed_decoder* d, const void* enc_st
         bool any = false;
         while (!any) {
             for (int s = 0; s < poll_every; ++s) {
-                if (use_graph) HIP_TRY(d, hipGraphLaunch(d->gexec, d->stream));
+                if (use_graph) HIP_TRY(d, hipGraphLaunch(graph, d->stream));
                 else HIP_TRY(d, enqueue_step(d, st, 1, nullptr));
             }
             n_steps += poll_every;

@@ -393,12 +393,12 @@ __global__ __launch_bounds__(64 * NW, sizeof(KV) <= 2 ? 4 : 1) void attn_decode_
 template <typename T, typename KV, int LPK, int DH, bool SELF>
 static void launch_nw(const AttnArgs& a, dim3 grid, hipStream_t s) {
     const size_t wgs = (size_t)grid.x * grid.y * grid.z, resident = sizeof(KV) <= 2 ? 4096 : 2048;
-    if (wgs * 8 > (a.long_items ? 2 * resident : resident) || a.chunk <= 64) {
+    if (wgs * 8 > (a.long_items ? 2 * resident : resident) || attn_keys_class(a.chunk) == 0) {
         hipLaunchKernelGGL((attn_decode_kernel<T, KV, LPK, DH, SELF, 4>), grid, dim3(256), 0, s, a);
         return;
     }
     if constexpr (sizeof(KV) <= 2) {
-        if (wgs * 16 <= resident && a.chunk > 256) {
+        if (wgs * 16 <= resident && attn_keys_class(a.chunk) == 2) {
             hipLaunchKernelGGL((attn_decode_kernel<T, KV, LPK, DH, SELF, 16>), grid, dim3(1024), 0, s, a);
             return;
         }

@@ -57,6 +57,44 @@ def test_two_decoders_interleaved_on_one_device(oracle):
     dec_b.close()
 
 
+@pytest.mark.parametrize("dtype,prefill_rows", [("bf16", 48), ("fp32", 0)])
+def test_batches_of_many_shapes_in_turn(oracle, dtype, prefill_rows):
+    """More shapes than a decoder keeps graphs of, and the first ones again, greedy and by steps: every batch comes out
+    as on a decoder that has seen nothing else, bit for bit, and the first as the oracle has it."""
+    import torch
+    from tests import gpu_util as G
+    shapes = [[20], [300, 7], [5, 6, 7], [400], [9, 200, 33, 1], [64] * 5, [20], [21], [300, 7], [7, 300], [260]]
+    wl = _unit(dtype, 256, 4, 64, [400] * 5, seed=12)
+    kw = dict(max_batch=5, max_total=2000, prefill_rows=prefill_rows)
+    rng = np.random.default_rng(4)
+    enc = {i: W.draw_enc_states(wl.cfg, rng, np.array(s, np.int32)) for i, s in enumerate(shapes)}
+
+    def decode(dec, i):
+        lens = np.array(shapes[i], np.int32)
+        prompt = torch.from_numpy(wl.prompt[:len(lens)].copy()).to(dec.device)
+        dev = dec.to_device(enc[i])
+        dec.aed_cross_kv_precompute(dev, lens)
+        toks, _ = dec.aed_greedy_decode(prompt, 7)
+        out = [toks.cpu().numpy(), dec.aed_read_logits()]
+        dec.aed_cross_kv_precompute(dev, lens)
+        for t in range(2):
+            ids, lg = dec.aed_decode_step(prompt[:, t].contiguous())
+            out += [ids.cpu().numpy(), lg.cpu().numpy()]
+        return out
+
+    shared = G.make_decoder(wl, **kw)
+    for i, lens in enumerate(shapes):
+        got = decode(shared, i)
+        alone = G.make_decoder(wl, **kw)
+        for a, b in zip(got, decode(alone, i)):
+            assert np.array_equal(a, b), f"batch {i} of {lens}"
+        alone.close()
+        if i == 0:
+            ref = oracle.Model(wl.cfg, wl.weights).decode_forced(enc[0], np.array(lens, np.int32), wl.prompt[:1, :2].copy())
+            assert np.abs(np.stack([got[3], got[5]], 1) - ref).max() <= G.TOL[dtype]
+    shared.close()
+
+
 def test_create_destroy_many_times_leaves_nothing_behind():
     """40 handles created, used (one batch, a few greedy tokens: graphs, events and pinned memory come into being) and
     destroyed: the device's free memory afterwards is what it was after the first few (torch's own caches warm up
