@@ -607,26 +607,35 @@ hipError_t k_class(aed_decoder* d, int cls, int l) {
     }
 }
 
-// One decoder step for the whole batch, enqueued on the stream.
+// Where the embedding goes: the rows that enter layer 0.
+EmbedArgs embed_args(const aed_decoder* d) {
+    EmbedArgs ea;
+    memset(&ea, 0, sizeof ea);
+    ea.x = d->act_at<float>(d->lay.x);
+    ea.tok_emb = d->w.tok_emb; ea.pos_emb = d->w.pos_emb;
+    ea.d = d->cfg.d_model; ea.max_positions = d->cfg.max_positions; ea.emb_scale = d->cfg.emb_scale;
+    if (folded_ln(d)) {
+        ea.sh.shadow = shadow_buf(d, 0);
+        ea.sh.stats = stats_buf(d, 0);
+        ea.sh.mu_hat = shift_buf(d, 1);  // read as the shift of the rows entering layer 0
+        ea.sh.rms = d->cfg.norm_type == 1;
+    }
+    return ea;
+}
+hipError_t k_embed(aed_decoder* d, const StateArgs& st) { return launch_embed(d->dt, embed_args(d), st, d->stream); }
+
+// One decoder step for the whole batch, enqueued on the stream.  A greedy step embeds what the next one feeds at its end;
+// k_embed goes before the first and after every change of the state from outside.
 hipError_t enqueue_step(aed_decoder* d, const StateArgs& st, int greedy, int* step_out) {
     hipError_t e;
-    ShadowArgs sa;
-    memset(&sa, 0, sizeof sa);
-    if (folded_ln(d)) {
-        d->x_par = 0;
-        sa.shadow = shadow_buf(d, 0);
-        sa.stats = stats_buf(d, 0);
-        sa.mu_hat = shift_buf(d, 1);  // read as the shift of the rows entering layer 0
-        sa.rms = d->cfg.norm_type == 1;
-    }
-    e = launch_embed(d->dt, d->act_at<float>(d->lay.x), d->w.tok_emb, d->w.pos_emb, st, d->cfg.d_model,
-                     d->cfg.max_positions, d->cfg.emb_scale, sa, d->stream);
-    if (e != hipSuccess) return e;
+    if (!greedy && (e = k_embed(d, st)) != hipSuccess) return e;
+    d->x_par = 0;
     for (int l = 0; l < d->cfg.n_layers; ++l)
         for (int cls = AED_K_LN_QKV; cls <= AED_K_FFN2; ++cls)
             if ((e = k_class(d, cls, l)) != hipSuccess) return e;
     if ((e = k_ln_vocab(d)) != hipSuccess) return e;
-    return launch_sample(d->act_at<float>(d->lay.logits), st, greedy, step_out, d->stream);
+    if (greedy) return launch_sample_embed(d->dt, d->act_at<float>(d->lay.logits), st, embed_args(d), d->stream);
+    return launch_sample(d->act_at<float>(d->lay.logits), st, 0, step_out, d->stream);
 }
 
 aed_status check_weights(const aed_config* c, const aed_weights* w) {
@@ -799,17 +808,8 @@ aed_status prefill_pass(aed_decoder* d, const std::vector<int>& prompt_host, int
     d->self_nchunks = 1;
     const StateArgs st = d->state_args(0, 0);
     auto enqueue = [&]() -> hipError_t {
-        ShadowArgs sa;
-        memset(&sa, 0, sizeof sa);
-        if (folded_ln(d)) {
-            d->x_par = 0;
-            sa.shadow = shadow_buf(d, 0);
-            sa.stats = stats_buf(d, 0);
-            sa.mu_hat = shift_buf(d, 1);
-            sa.rms = d->cfg.norm_type == 1;
-        }
-        hipError_t e = launch_embed(d->dt, d->act_at<float>(d->lay.x), d->w.tok_emb, d->w.pos_emb, st, d->cfg.d_model,
-                                    d->cfg.max_positions, d->cfg.emb_scale, sa, d->stream);
+        d->x_par = 0;
+        hipError_t e = k_embed(d, st);
         for (int l = 0; l < d->cfg.n_layers && e == hipSuccess; ++l) {
             const int last_cls = l + 1 < d->cfg.n_layers ? AED_K_FFN2 : AED_K_LN_QKV;
             for (int cls = AED_K_LN_QKV; cls <= last_cls && e == hipSuccess; ++cls) e = k_class(d, cls, l);
@@ -1144,6 +1144,7 @@ aed_status aed_greedy_decode(aed_decoder* d, const int32_t* prompt, int32_t prom
         }
     }
     HIP_TRY(d, launch_reset(st, max_new_per_seq ? d->at<int>(d->lay.limits_in) : nullptr, 1, start_pos, d->stream));
+    HIP_TRY(d, k_embed(d, st));
     d->state = aed_decoder::CONSUMED;
 
     // one launch graph per shape; replayed for every step
@@ -1319,6 +1320,7 @@ extern "C" aed_status aed_greedy_decode_queue(aed_decoder* d, const void* enc_st
                                       d->stream));
             HIP_TRY(d, launch_turn_over_slots(st, turn, turn + B, turn + 2 * B, turn + 3 * B, n_turn, prompts, out_tokens,
                                               out_lens, d->stream));
+            HIP_TRY(d, k_embed(d, st));
             if (!h_src.empty()) {
                 const long long rows = (long long)h_src.size();
                 HIP_TRY(d, hipMemcpyAsync(d->at<int>(d->lay.row_map), h_src.data(), h_src.size() * 4, hipMemcpyHostToDevice,

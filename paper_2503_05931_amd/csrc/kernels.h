@@ -43,7 +43,7 @@ struct GemmArgs {
     void* k_pool;         // T (or E4M3 codes, kv_fp8) [pages][H][16][Dh]
     void* v_pool;
     const int* kv_slot;     // [M] page * 16 + position inside the page that row m's key / value go to, -1: nowhere
-                            // (launch_embed leaves it: one load per row and layer instead of state, page table, page)
+                            // (launch_embed / launch_sample_embed leave it: one load per row and layer instead of state, page table, page)
     int n_heads, head_dim, d_model;
     // EPI_CROSSKV: columns [0,d) -> kc, [d,2d) -> vc, layout [H][t_cap][Dh]
     void* kc;
@@ -177,12 +177,20 @@ struct ShadowArgs {
     float* mu_hat;      // [B] row means (the shadow's shift)
     int rms;            // RMSNorm: the shift is 0 (the shadow is x itself in the storage type)
 };
-// x[b,:] = emb_scale * tok_emb[cur_tok[b]] + pos_emb[seq_len[b]]   (x in fragment order); d_model <= 1024;
-// kv_slot[b] = where this step's key / value of sequence b go
-hipError_t launch_embed(Dtype dt, float* x, const void* tok_emb, const void* pos_emb, const StateArgs& st,
-                        int d_model, int max_positions, float emb_scale, const ShadowArgs& sa, hipStream_t s);
+struct EmbedArgs {
+    float* x;  // [B, d] fragment order
+    const void *tok_emb, *pos_emb;
+    int d, max_positions;  // d <= 1024
+    float emb_scale;
+    ShadowArgs sh;
+};
+// x[b,:] = emb_scale * tok_emb[cur_tok[b]] + pos_emb[seq_len[b]];  kv_slot[b] = where this step's key / value of
+// sequence b go
+hipError_t launch_embed(Dtype dt, const EmbedArgs& ea, const StateArgs& st, hipStream_t s);
 // greedy = 1: prompt feeding, argmax, EOS rules, output writes; greedy = 0: argmax only -> step_out (may be null)
 hipError_t launch_sample(const float* logits, const StateArgs& st, int greedy, int* step_out, hipStream_t s);
+// launch_sample with greedy = 1, then launch_embed of the state that it leaves
+hipError_t launch_sample_embed(Dtype dt, const float* logits, const StateArgs& st, const EmbedArgs& ea, hipStream_t s);
 // seq_len = start_pos, cur_tok = prompt[b][start_pos], n_gen = finished = 0, n_finished = 0,
 // limit = limits ? limits[b] : INT_MAX, out_tokens = pad (fill_out)
 hipError_t launch_reset(const StateArgs& st, const int* limits_dev, int fill_out, int start_pos, hipStream_t s);
