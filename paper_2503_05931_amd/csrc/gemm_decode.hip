@@ -4,7 +4,7 @@
 // C[M,N] = prologue(A)[M,K] . W[N,K]^T: M is the decode batch (1..1024), the
 // weights W are read exactly once per launch and dominate the traffic, so the
 // kernel is organised around streaming W:
-//   * a workgroup (4 wavefronts) owns a (16*MT) x (16*NT) output tile;
+//   * a workgroup (4 wavefronts; 8 where launch_nb says so) owns a (16*MT) x (16*NT) output tile;
 //   * the four wavefronts split K: wavefront w takes the 64-wide k blocks
 //     w, w+4, w+8, ..., and the partial tiles are summed through LDS in a
 //     fixed order (deterministic);
@@ -38,7 +38,7 @@ constexpr int kMaxLnBlocks = 4;  // PRO_LN: K <= 4 waves * 4 blocks * 64 = 1024
 
 // One output tile (column tile bx, row tile by) of the product described by a.
 // WNT: W is loaded with the non-temporal hint (GemmArgs::w_nt)
-// NB: 64-wide k blocks per wavefront, K = 256 NB, known at compile time; 0: any K
+// NB: 64-wide k blocks per wavefront, K = 64 NW NB, known at compile time; 0: any K.  NW: wavefronts
 //
 // What bounds a launch at decode batches is latency: 8 MB of weights stream in 1.5 us behind the first HBM access, so
 // every further round trip to memory shows.  Therefore
@@ -49,14 +49,15 @@ constexpr int kMaxLnBlocks = 4;  // PRO_LN: K <= 4 waves * 4 blocks * 64 = 1024
 //    (the loads of the fused LayerNorm over a K that is not 1024 are the exception);
 //  * with NB known the k loop is straight-line code and each block is waited for on its own; with a run-time k loop
 //    around conditional loads the compiler waited for the blocks just requested.
-template <typename T, int PRO, int EPI, int MT, int NT, bool WNT, int NB>
+template <typename T, int PRO, int EPI, int MT, int NT, bool WNT, int NB, int NW = 4>
 __device__ __forceinline__ void gemm_decode_body(const GemmArgs& a, const int bx, const int by) {
     constexpr int BM = 16 * MT, BN = 16 * NT;
     constexpr int EP = (MT * NT * 64 + 255) / 256;  // output 4-vectors per thread in the epilogue
     constexpr int ES = sizeof(T);
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, r = lane & 15, g = lane >> 4;
     const int m0 = by * BM, n0 = bx * BN;
-    const int K = NB > 0 ? NB * 256 : a.K, M = a.M;
+    const int K = NB > 0 ? NB * NW * 64 : a.K, M = a.M;
+    static_assert(NW == 4 || (PRO == PRO_T && MT * NT == 1 && NB > 0), "more wavefronts: one 16 x 16 tile, known K");
     const int nblk = K >> 8;  // 64-wide k blocks per wavefront
     const char* __restrict__ W = static_cast<const char*>(a.W);
     const char* __restrict__ A = static_cast<const char*>(a.A);
@@ -65,7 +66,7 @@ __device__ __forceinline__ void gemm_decode_body(const GemmArgs& a, const int bx
     constexpr bool RS = EPI == EPI_RESID_S;      // residual update that also writes shadow and statistics
     constexpr bool RES = EPI == EPI_RESID || RS;
 
-    __shared__ f32x4 part[4][MT * NT][64];
+    __shared__ f32x4 part[NW][MT * NT][64];
     __shared__ float red[2][4][BM];
 
     f32x4 acc[MT][NT];
@@ -76,7 +77,7 @@ __device__ __forceinline__ void gemm_decode_body(const GemmArgs& a, const int bx
 
     // block (n tile, k block i*4 + wave) of the re-ordered weights
     auto wblk = [&](int nt, int i) {
-        return reinterpret_cast<const T*>(W + frag_block_off<ES>((n0 >> 4) + nt, i * 4 + wave, K));
+        return reinterpret_cast<const T*>(W + frag_block_off<ES>((n0 >> 4) + nt, i * NW + wave, K));
     };
 
     // ---- the operand stream (everything but the float32-mode LayerNorm prologue): ring of D blocks in registers
@@ -94,8 +95,8 @@ __device__ __forceinline__ void gemm_decode_body(const GemmArgs& a, const int bx
     auto fetch_a = [&](int slot, int i) {
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt) {
-            if constexpr (MT == 1) rows.load(i * 4 + wave, af[slot][mt]);
-            else af[slot][mt] = load_frag(reinterpret_cast<const T*>(A + frag_block_off<ES>((m0 >> 4) + mt, i * 4 + wave, K)), lane);
+            if constexpr (MT == 1) rows.load(i * NW + wave, af[slot][mt]);
+            else af[slot][mt] = load_frag(reinterpret_cast<const T*>(A + frag_block_off<ES>((m0 >> 4) + mt, i * NW + wave, K)), lane);
         }
     };
     auto fetch = [&](int slot, int i) {
@@ -331,7 +332,7 @@ __device__ __forceinline__ void gemm_decode_body(const GemmArgs& a, const int bx
     }
 
     if constexpr (LNS && !ST_FIRST) combine_stats();
-    // ---- sum the four wavefronts' partial tiles in a fixed order, then the epilogue ----
+    // ---- sum the wavefronts' partial tiles in a fixed order, then the epilogue ----
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
@@ -343,9 +344,8 @@ __device__ __forceinline__ void gemm_decode_body(const GemmArgs& a, const int bx
         const int t = wave + 4 * j, l = lane;
         if (MT * NT < 4 && t >= MT * NT) continue;
         f32x4 s = part[0][t][l];
-        s += part[1][t][l];
-        s += part[2][t][l];
-        s += part[3][t][l];
+#pragma unroll
+        for (int w = 1; w < NW; ++w) s += part[w][t][l];
         const int m = tile_row(t, l), n = tile_col(t, l);
         if (m >= M) continue;
         if constexpr (!LNS) {
@@ -384,9 +384,9 @@ __device__ __forceinline__ void gemm_decode_body(const GemmArgs& a, const int bx
     }
 }
 
-template <typename T, int PRO, int EPI, int MT, int NT, bool WNT, int NB>
-__global__ __launch_bounds__(256) void gemm_decode_kernel(GemmArgs a) {
-    gemm_decode_body<T, PRO, EPI, MT, NT, WNT, NB>(a, blockIdx.x, blockIdx.y);
+template <typename T, int PRO, int EPI, int MT, int NT, bool WNT, int NB, int NW = 4>
+__global__ __launch_bounds__(64 * NW) void gemm_decode_kernel(GemmArgs a) {
+    gemm_decode_body<T, PRO, EPI, MT, NT, WNT, NB, NW>(a, blockIdx.x, blockIdx.y);
 }
 
 // Two products of the same operand in one launch: the first n0 workgroups are the tiles of a0 (a residual update,
@@ -487,6 +487,17 @@ static hipError_t launch_nb(const GemmArgs& a, hipStream_t s) {
     dim3 grid(a.N / (16 * NT), (a.M + 16 * MT - 1) / (16 * MT));
     const long wgs = (long)grid.x * grid.y;
     unsigned lds = 0;
+    // K = 4096 on 16 x 16 tiles: eight wavefronts have a workgroup's whole share of both operands under way at once, four half
+    // of it.  24 layers: batch 64, 131 positions 124.1 -> 122.9 ms, batch 16, 24 positions 22.6 -> 22.3; one row 84.6 and 84.7;
+    // sixteen: batch 16 22.7, one row 85.2.  Beyond one workgroup per CU two of four share it.  (float32, batch 32: 10.27 and
+    // 10.26 ms with eight, 10.99 with sixteen: four.)
+    if constexpr (sizeof(T) == 2 && PRO == PRO_T && MT * NT == 1 && NB == 16) {
+        if (wgs <= kCus) {
+            if (hint_w(a, wgs, grid.y)) hipLaunchKernelGGL((gemm_decode_kernel<T, PRO, EPI, MT, NT, true, NB / 2, 8>), grid, dim3(512), 0, s, a);
+            else hipLaunchKernelGGL((gemm_decode_kernel<T, PRO, EPI, MT, NT, false, NB / 2, 8>), grid, dim3(512), 0, s, a);
+            return hipGetLastError();
+        }
+    }
     if constexpr (sizeof(T) == 4 && PRO == PRO_T && MT * NT >= 4 && MT * NT <= 8) {
         if (wgs > kCus) {
             static DeviceOnce once;
