@@ -198,8 +198,8 @@ struct GraphKey {
                self_chunk == o.self_chunk && self_nchunks == o.self_nchunks && prompt_len == o.prompt_len && max_new == o.max_new;
     }
 };
-// The graphs of the last few shapes (24 layers, three utterances of other lengths in turn 87.5 -> 84.9 ms); the one unused for longest makes room.  Every change of shape comes after the stream
-// has been waited for, so a graph that goes is not running.
+// The graphs of the last few shapes (24 layers, three utterances of other lengths in turn 87.5 -> 84.9 ms); the one unused for
+// longest makes room.  Every change of shape comes after the stream has been waited for, so a graph that goes is not running.
 constexpr int kGraphs = 4;
 struct GraphPool {
     struct Entry { GraphKey key; hipGraphExec_t exec = nullptr; unsigned long long used = 0; };
@@ -685,12 +685,7 @@ aed_status start_batch(aed_decoder* d, const void* enc, bool padded, int t_max, 
     HIP_TRY(d, hipMemsetAsync(d->ws + d->lay.counters, 0, (size_t)d->lay.act_rows * d->cfg.n_heads * 4, d->stream));
     HIP_TRY(d, hipMemcpyAsync(d->at<int>(d->lay.enc_off), off.data(), off.size() * 4, hipMemcpyHostToDevice, d->stream));
     HIP_TRY(d, hipMemcpyAsync(d->at<int4>(d->lay.items), items.data(), items.size() * 16, hipMemcpyHostToDevice, d->stream));
-    if (padded) {
-        std::vector<int> map((size_t)total);
-        for (int b = 0; b < batch; ++b)
-            for (int t = 0; t < enc_lens[b]; ++t) map[(size_t)off[b] + t] = b * t_max + t;
-        HIP_TRY(d, hipMemcpyAsync(d->at<int>(d->lay.row_map), map.data(), map.size() * 4, hipMemcpyHostToDevice, d->stream));
-    }
+    if (padded) HIP_TRY(d, launch_padded_row_map(d->at<int>(d->lay.enc_off), d->at<int>(d->lay.row_map), t_max, batch, d->stream));
     d->batch = batch;
     d->n_items = (int)items.size();
     d->cross_keys = longest_item(max_len, cut);

@@ -194,6 +194,8 @@ hipError_t launch_sample_embed(Dtype dt, const float* logits, const StateArgs& s
 // seq_len = start_pos, cur_tok = prompt[b][start_pos], n_gen = finished = 0, n_finished = 0,
 // limit = limits ? limits[b] : INT_MAX, out_tokens = pad (fill_out)
 hipError_t launch_reset(const StateArgs& st, const int* limits_dev, int fill_out, int start_pos, hipStream_t s);
+// row_map[enc_off[b] + t] = b * t_max + t: where the frames of a padded tensor are
+hipError_t launch_padded_row_map(const int* enc_off, int* row_map, int t_max, int batch, hipStream_t s);
 // cur_tok[b] = src[b * stride]
 hipError_t launch_set_tokens(int* cur_tok, const int* src, int stride, int batch, hipStream_t s);
 // out[b] = n_gen[b]; dst[b, t] = out_tokens[b, t]

@@ -233,6 +233,18 @@ hipError_t launch_reset(const StateArgs& st, const int* limits_dev, int fill_out
     return hipGetLastError();
 }
 
+// On the device, because 65 thousand entries built on the host and uploaded kept the GPU waiting: a padded batch of 256 taken in
+// by 4 layers, with its 4 prompt steps, 2.91 -> 2.85 ms.
+__global__ void padded_row_map_kernel(const int* __restrict__ enc_off, int* __restrict__ row_map, int t_max) {
+    const int b = blockIdx.x, at = enc_off[b], n = enc_off[b + 1] - at;
+    for (int t = threadIdx.x; t < n; t += blockDim.x) row_map[at + t] = b * t_max + t;
+}
+
+hipError_t launch_padded_row_map(const int* enc_off, int* row_map, int t_max, int batch, hipStream_t s) {
+    hipLaunchKernelGGL(padded_row_map_kernel, dim3(batch), dim3(256), 0, s, enc_off, row_map, t_max);
+    return hipGetLastError();
+}
+
 __global__ void set_tokens_kernel(int* __restrict__ cur_tok, const int* __restrict__ src, int stride, int batch) {
     const int b = blockIdx.x * blockDim.x + threadIdx.x;
     if (b < batch) cur_tok[b] = src[(size_t)b * stride];
