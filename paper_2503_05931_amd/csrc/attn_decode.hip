@@ -7,8 +7,8 @@
 // Work item = (head, sequence, chunk of keys).  Self-attention: the grid's z
 // axis counts chunks and items beyond a sequence's current length exit at
 // once.  Cross-attention: items come from a list built on the host from the
-// true encoder lengths, longest first, so neither padding frames nor empty
-// chunks exist and the longest sequences are scheduled first.
+// true encoder lengths, cut sequences first, then longest first, so neither
+// padding frames nor empty chunks exist and what takes longest starts first.
 //
 // Inside a workgroup (NW = 4, 8 or 16 wavefronts) the chunk is cut into 16-key
 // blocks (= one page of the self-attention cache), wavefront w takes blocks w,
@@ -23,9 +23,10 @@
 // (max, sum, weighted values) is kept per wavefront in base-2 exponent form,
 // the wavefronts are merged through LDS.  Sequences of this workload are short
 // (at most 500 encoder frames, a few hundred decoded tokens), so one workgroup
-// per (sequence, head) is the normal case.  When the batch is too small to
-// occupy the GPU, sequences of more than 256 keys are cut into chunks handled by
-// different workgroups, and the last workgroup of a (sequence, head) to finish
+// per (sequence, head) is the normal case.  Cross-attention of sequences with
+// more than a CU's share of the batch's keys, and self-attention when the batch
+// is too small to occupy the GPU, is cut into chunks handled by different
+// workgroups, and the last workgroup of a (sequence, head) to finish
 // combines the partial (max, sum, values) triples in chunk order.
 #include "common.h"
 #include "kernels.h"
@@ -109,7 +110,7 @@ __global__ __launch_bounds__(64 * NW, sizeof(KV) <= 2 ? 4 : 1) void attn_decode_
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, r = lane % LPK, g = lane / LPK;
     const int h = blockIdx.x, H = a.n_heads;
 
-    // Work item.  Cross-attention: from the host-built list (longest first, so the long sequences
+    // Work item.  Cross-attention: from the host-built list (cut sequences, then longest first, so the long sequences
     // start early and the short ones fill the tail); the item carries everything needed to address
     // the keys, so the query and the first key blocks are fetched in the same round trip, and the sampler
     // marks the items of a sequence that finishes, so that nothing is fetched for it.  (With a finished flag

@@ -5,8 +5,8 @@
 // weights W are read exactly once per launch and dominate the traffic, so the
 // kernel is organised around streaming W:
 //   * a workgroup (4 wavefronts; 8 where launch_nb says so) owns a (16*MT) x (16*NT) output tile;
-//   * the four wavefronts split K: wavefront w takes the 64-wide k blocks
-//     w, w+4, w+8, ..., and the partial tiles are summed through LDS in a
+//   * the NW wavefronts split K: wavefront w takes the 64-wide k blocks
+//     w, w+NW, w+2 NW, ..., and the partial tiles are summed through LDS in a
 //     fixed order (deterministic);
 //   * lane (r, g) (r = lane % 16, g = lane / 16) holds, for row r of a 16-row
 //     operand, the 16 consecutive k values k0 + 16 g .. +15 of a 64-wide block.
