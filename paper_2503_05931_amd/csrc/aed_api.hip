@@ -635,7 +635,7 @@ hipError_t enqueue_step(aed_decoder* d, const StateArgs& st, int greedy, int* st
             if ((e = k_class(d, cls, l)) != hipSuccess) return e;
     if ((e = k_ln_vocab(d)) != hipSuccess) return e;
     if (greedy) return launch_sample_embed(d->dt, d->act_at<float>(d->lay.logits), st, embed_args(d), d->stream);
-    return launch_sample(d->act_at<float>(d->lay.logits), st, 0, step_out, d->stream);
+    return launch_sample(d->act_at<float>(d->lay.logits), st, step_out, d->stream);
 }
 
 aed_status check_weights(const aed_config* c, const aed_weights* w) {

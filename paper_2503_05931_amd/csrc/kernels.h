@@ -187,9 +187,9 @@ struct EmbedArgs {
 // x[b,:] = emb_scale * tok_emb[cur_tok[b]] + pos_emb[seq_len[b]];  kv_slot[b] = where this step's key / value of
 // sequence b go
 hipError_t launch_embed(Dtype dt, const EmbedArgs& ea, const StateArgs& st, hipStream_t s);
-// greedy = 1: prompt feeding, argmax, EOS rules, output writes; greedy = 0: argmax only -> step_out (may be null)
-hipError_t launch_sample(const float* logits, const StateArgs& st, int greedy, int* step_out, hipStream_t s);
-// launch_sample with greedy = 1, then launch_embed of the state that it leaves
+// a step's end: the argmax, fed next and -> step_out (may be null); every sequence advances
+hipError_t launch_sample(const float* logits, const StateArgs& st, int* step_out, hipStream_t s);
+// a greedy step's end: prompt feeding, argmax, EOS rules, output writes, then launch_embed of the state that this leaves
 hipError_t launch_sample_embed(Dtype dt, const float* logits, const StateArgs& st, const EmbedArgs& ea, hipStream_t s);
 // seq_len = start_pos, cur_tok = prompt[b][start_pos], n_gen = finished = 0, n_finished = 0,
 // limit = limits ? limits[b] : INT_MAX, out_tokens = pad (fill_out)

@@ -92,17 +92,18 @@ __device__ __forceinline__ bool better(float v, int i, float bv, int bi) { retur
 // What a sequence feeds next: token, position, and whether it is through.  The same in every thread of the workgroup.
 struct Next { int tok, pos; bool through; };
 
+// GREEDY: prompt feeding, EOS rules, output writes; else the argmax alone, into step_out (may be null) too.
 // request(pos, fin): what else the caller reads that depends on the state words only, asked for behind the row's first loads
-template <typename F>
-__device__ __forceinline__ Next sample_row(const float* __restrict__ logits, const StateArgs& st, int greedy,
-                                           int* __restrict__ step_out, F request) {
+template <bool GREEDY, typename F>
+__device__ __forceinline__ Next sample_row(const float* __restrict__ logits, const StateArgs& st, int* __restrict__ step_out,
+                                           F request) {
     const int b = blockIdx.x, tid = threadIdx.x;
     // everything the decision needs is requested at once: the state words and this thread's share of the row
     // (vocab is a multiple of 64: 4-vectors; up to four per thread in flight, then the rest of a long row)
-    const int fin = greedy ? st.finished[b] : 0;
+    const int fin = GREEDY ? st.finished[b] : 0;
     const int pos = st.seq_len[b];
-    const int n = greedy ? st.n_gen[b] : 0;
-    const int lim = greedy ? st.limit[b] : INT_MAX;
+    const int n = GREEDY ? st.n_gen[b] : 0;
+    const int lim = GREEDY ? st.limit[b] : INT_MAX;
     const float* row = logits + (size_t)b * st.vocab;
     f32x4 v[4];
 #pragma unroll
@@ -112,7 +113,7 @@ __device__ __forceinline__ Next sample_row(const float* __restrict__ logits, con
     }
     request(pos, fin);
     if (fin) return Next{st.cur_tok[b], pos, true};
-    if (greedy && pos + 1 < st.prompt_len) {  // still feeding the prompt: no token is emitted
+    if (GREEDY && pos + 1 < st.prompt_len) {  // still feeding the prompt: no token is emitted
         const int fed = st.prompt[(size_t)b * st.prompt_stride + pos + 1];
         __syncthreads();  // every wavefront has read the position before it moves on
         if (tid == 0) {
@@ -152,7 +153,7 @@ __device__ __forceinline__ Next sample_row(const float* __restrict__ logits, con
     for (int w = 1; w < 4; ++w)
         if (better(sv[w], si[w], bv, bi)) { bv = sv[w]; bi = si[w]; }
     int tok = bi == INT_MAX ? 0 : bi;
-    if (!greedy) {
+    if (!GREEDY) {
         const Next next{tok, pos + 1, false};
         if (tid != 0) return next;
         if (step_out) step_out[b] = tok;
@@ -178,9 +179,8 @@ __device__ __forceinline__ Next sample_row(const float* __restrict__ logits, con
     return next;
 }
 
-__global__ __launch_bounds__(256) void sample_kernel(const float* __restrict__ logits, StateArgs st, int greedy,
-                                                     int* __restrict__ step_out) {
-    sample_row(logits, st, greedy, step_out, [](int, int) {});
+__global__ __launch_bounds__(256) void sample_kernel(const float* __restrict__ logits, StateArgs st, int* __restrict__ step_out) {
+    sample_row<false>(logits, st, step_out, [](int, int) {});
 }
 
 // The greedy step's last kernel: the sampler, then the embedding of what the sequence feeds next, so that a step begins
@@ -193,7 +193,7 @@ __global__ __launch_bounds__(256) void sample_embed_kernel(const float* __restri
     const int b = blockIdx.x;
     f32x4 pv;
     int slot;
-    const Next next = sample_row(logits, st, 1, nullptr, [&](int pos, int fin) {
+    const Next next = sample_row<true>(logits, st, nullptr, [&](int pos, int fin) {
         const int at = fin ? pos : pos + 1;
         pv = pos_row<T>(ea, at);
         slot = slot_of(st, b, min(at, ea.max_positions - 1));
@@ -208,8 +208,8 @@ hipError_t launch_sample_embed(Dtype dt, const float* logits, const StateArgs& s
     return hipGetLastError();
 }
 
-hipError_t launch_sample(const float* logits, const StateArgs& st, int greedy, int* step_out, hipStream_t s) {
-    hipLaunchKernelGGL(sample_kernel, dim3(st.batch), dim3(256), 0, s, logits, st, greedy, step_out);
+hipError_t launch_sample(const float* logits, const StateArgs& st, int* step_out, hipStream_t s) {
+    hipLaunchKernelGGL(sample_kernel, dim3(st.batch), dim3(256), 0, s, logits, st, step_out);
     return hipGetLastError();
 }
 

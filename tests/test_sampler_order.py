@@ -1,5 +1,5 @@
-"""The greedy sampler's workgroup with its wavefronts in any order (CPU): the
-kernel's own source, compiled for the host with one fiber per thread."""
+"""The workgroup that ends a step -- a greedy one: sampler and embedding of what is fed next; a plain one: argmax -- with
+its wavefronts in any order (CPU): the kernels' own source, compiled for the host with one fiber per thread."""
 import os
 import subprocess
 
