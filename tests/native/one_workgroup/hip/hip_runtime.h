@@ -44,3 +44,18 @@ template <typename... A> static inline Unreached2 unreached2(A...) { __builtin_t
 #define __builtin_amdgcn_permlane32_swap unreached2
 #define __builtin_amdgcn_update_dpp unreached
 #define __builtin_amdgcn_mov_dpp unreached
+struct Anything { template <typename T> operator T() const { __builtin_trap(); } };
+template <typename... A> static inline Anything anything(A...) { __builtin_trap(); }
+#define __builtin_amdgcn_mfma_f32_16x16x32_bf16 anything
+#define __builtin_amdgcn_mfma_f32_16x16x4f32 anything
+#define __builtin_amdgcn_cvt_pk_fp8_f32 unreached
+
+// Buffer descriptors (base, stride 0, bytes, flags) and a 16-byte load through one, which returns the address that it would
+// read, twice: zeros where lane and wavefront offset together are past the descriptor's end.
+typedef unsigned int BufferVec __attribute__((ext_vector_type(4)));
+struct Buffer { const char* base; uint64_t bytes; };
+static inline Buffer __builtin_amdgcn_make_buffer_rsrc(const char* base, short, int bytes, int) { return Buffer{base, (uint32_t)bytes}; }
+static inline BufferVec __builtin_amdgcn_raw_buffer_load_b128(Buffer b, int voff, int soff, int) {
+    const uint64_t off = (uint64_t)(uint32_t)voff + (uint32_t)soff, at = off + 16 <= b.bytes ? (uint64_t)(b.base + off) : 0;
+    return BufferVec{(uint32_t)at, (uint32_t)(at >> 32), (uint32_t)at, (uint32_t)(at >> 32)};
+}
