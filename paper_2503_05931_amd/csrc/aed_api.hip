@@ -14,6 +14,7 @@
 #include <vector>
 
 #include "../../include/aed.h"
+#include "attn_split.h"
 #include "frame_space.h"
 #include "kernels.h"
 
@@ -192,9 +193,9 @@ constexpr double kResidentLayerBytes = 220e6;
 
 // What the launches of a captured step or prompt pass depend on; everything else they read from device memory.
 struct GraphKey {
-    int batch = -1, n_items = 0, cross_keys = 0, cross_long = 0, self_chunk = 0, self_nchunks = 0, prompt_len = 0, max_new = 0;
+    int batch = -1, n_items = 0, cross_short = 0, cross_long = 0, self_chunk = 0, self_nchunks = 0, prompt_len = 0, max_new = 0;
     bool operator==(const GraphKey& o) const {
-        return batch == o.batch && n_items == o.n_items && cross_keys == o.cross_keys && cross_long == o.cross_long &&
+        return batch == o.batch && n_items == o.n_items && cross_short == o.cross_short && cross_long == o.cross_long &&
                self_chunk == o.self_chunk && self_nchunks == o.self_nchunks && prompt_len == o.prompt_len && max_new == o.max_new;
     }
 };
@@ -321,47 +322,6 @@ int pick_chunk(long long total_keys, int max_len, int batch, int n_heads) {
     c = std::max(c, ((long long)max_len + kMaxChunks - 1) / kMaxChunks);
     c = std::max<long long>(kMinChunk, (c + 63) / 64 * 64);
     return (int)std::min(c, whole);
-}
-
-// Cross-attention work items.  A sequence of more than `longest` keys is cut into pieces of about `piece` keys.
-struct CrossCut { int longest, piece; };
-// Batches of more than 4096 are left whole: a CU has 32 workgroups and more then, and with the pieces a prompt pass's list
-// (kMaxPrefillPositions times as long) could pass what a launch grid holds in y.
-CrossCut cross_cut(long long total_keys, int batch, int n_heads, Dtype dt) {
-    if (batch > 4096) return CrossCut{INT_MAX, INT_MAX};
-    const long long share = total_keys * n_heads / 256 * (dt == kF32 ? 2 : 1);
-    CrossCut c;
-    c.longest = (int)std::min<long long>(std::max<long long>(192, share * 7 / 8), INT_MAX);
-    c.piece = (int)std::min<long long>(std::max<long long>(64, share * 7 / 16 / 32 * 32), INT_MAX);
-    return c;
-}
-int cross_pieces(int len, const CrossCut& c) {
-    return len <= c.longest ? 1 : std::min(kMaxChunks, (len + c.piece - 1) / c.piece);
-}
-int piece_keys(int len, const CrossCut& c) {
-    const int n = cross_pieces(len, c);
-    return ((len + n - 1) / n + 15) / 16 * 16;
-}
-// most keys of an item where the longest sequence has max_len
-int longest_item(int max_len, const CrossCut& c) {
-    return max_len <= c.longest ? max_len : std::max(c.longest, piece_keys(max_len, c));
-}
-// the work items of sequence b of len keys, the first at frame first_frame of the packed layout
-void add_items(std::vector<int4>& items, int b, int len, int first_frame, const CrossCut& c) {
-    const int per = piece_keys(len, c), n = (len + per - 1) / per;
-    for (int k = 0; k < n; ++k) {
-        int4 it;
-        it.x = b; it.y = (k * per) | (k << 16); it.z = std::min(per, len - k * per) | (n << 16); it.w = first_frame;
-        items.push_back(it);
-    }
-}
-// Cut sequences first, so that their merge is over when the rest is; then longest first.  Stable, so that the list is a
-// function of the lengths alone.
-void order_items(std::vector<int4>& items) {
-    std::stable_sort(items.begin(), items.end(), [](const int4& p, const int4& q) {
-        const bool pc = p.z >> 16 > 1, qc = q.z >> 16 > 1;
-        return pc != qc ? pc : (p.z & 0xFFFF) > (q.z & 0xFFFF);
-    });
 }
 
 // ---------------------------------------------------------------- kernel argument builders
@@ -718,7 +678,7 @@ aed_status start_batch(aed_decoder* d, const void* enc, bool padded, int t_max, 
 GraphKey graph_key(const aed_decoder* d) {
     GraphKey key;
     key.batch = d->batch; key.n_items = d->n_items;
-    key.cross_keys = attn_keys_class(d->cross_keys); key.cross_long = d->cross_long;
+    key.cross_short = attn_short_items(d->cross_keys); key.cross_long = d->cross_long;
     key.self_chunk = d->self_chunk; key.self_nchunks = d->self_nchunks;
     return key;
 }

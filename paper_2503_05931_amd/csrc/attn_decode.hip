@@ -10,7 +10,7 @@
 // true encoder lengths, cut sequences first, then longest first, so neither
 // padding frames nor empty chunks exist and what takes longest starts first.
 //
-// Inside a workgroup (NW = 4, 8 or 16 wavefronts) the chunk is cut into 16-key
+// Inside a workgroup (NW = 4 or 8 wavefronts) the chunk is cut into 16-key
 // blocks (= one page of the self-attention cache), wavefront w takes blocks w,
 // w+NW,.. and keeps two blocks in flight (the next block is fetched while the
 // current one is consumed).
@@ -28,6 +28,7 @@
 // is too small to occupy the GPU, is cut into chunks handled by different
 // workgroups, and the last workgroup of a (sequence, head) to finish
 // combines the partial (max, sum, values) triples in chunk order.
+#include "attn_split.h"
 #include "common.h"
 #include "kernels.h"
 
@@ -384,27 +385,13 @@ __global__ __launch_bounds__(64 * NW, sizeof(KV) <= 2 ? 4 : 1) void attn_decode_
     if (tid == 0) __hip_atomic_store(&a.counters[bh], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);  // for the next launch
 }
 
-// Wavefronts per workgroup.  What counts is that every workgroup is resident from the start (4096 wavefronts fit the 256
-// CUs, of float32 rows 2048) and that a wavefront has a block or two to itself: with 8 wavefronts where 8 do not fit, a
-// second round of workgroups starts when the first is over (self-attention, 24 layers, batch 128, 33 positions: 44.4 ms with
-// 8, 42.9 with 4; batch 64 125.0 and 125.4 for 131), and wavefronts without a block still cost the merge (one utterance,
-// cross- and self-attention on 16 and on 4: 92.6 and 90.1 ms).  16 only where a long item has a CU to itself.  Items that are
-// long on average (AttnArgs::long_items) keep memory busy in two rounds as well, and 8 wavefronts are through with the last
-// ones sooner (24 layers, batch 128 of 12 to 500 frames, half of whose sequences are through on average: 357 and 350 ms).
 template <typename T, typename KV, int LPK, int DH, bool SELF>
 static void launch_nw(const AttnArgs& a, dim3 grid, hipStream_t s) {
-    const size_t wgs = (size_t)grid.x * grid.y * grid.z, resident = sizeof(KV) <= 2 ? 4096 : 2048;
-    if (wgs * 8 > (a.long_items ? 2 * resident : resident) || attn_keys_class(a.chunk) == 0) {
+    const size_t wgs = (size_t)grid.x * grid.y * grid.z;
+    if (attn_wavefronts(wgs, sizeof(KV), a.chunk, a.long_items) == 4)
         hipLaunchKernelGGL((attn_decode_kernel<T, KV, LPK, DH, SELF, 4>), grid, dim3(256), 0, s, a);
-        return;
-    }
-    if constexpr (sizeof(KV) <= 2) {
-        if (wgs * 16 <= resident && attn_keys_class(a.chunk) == 2) {
-            hipLaunchKernelGGL((attn_decode_kernel<T, KV, LPK, DH, SELF, 16>), grid, dim3(1024), 0, s, a);
-            return;
-        }
-    }
-    hipLaunchKernelGGL((attn_decode_kernel<T, KV, LPK, DH, SELF, 8>), grid, dim3(512), 0, s, a);
+    else
+        hipLaunchKernelGGL((attn_decode_kernel<T, KV, LPK, DH, SELF, 8>), grid, dim3(512), 0, s, a);
 }
 template <typename T, typename KV, int LPK, bool SELF>
 static hipError_t launch_kv(const AttnArgs& a, dim3 grid, hipStream_t s) {

@@ -113,9 +113,7 @@ hipError_t launch_fold_vec(Dtype dt, const void* W, const void* g, const void* v
 
 // ---------------------------------------------------------------- decode attention
 constexpr int kMaxChunks = 8;      // chunks per (sequence, head)
-constexpr int kLongItem = 192;     // cross-attention items of that many keys on average are long ones (launch_nw)
-// how far the choice of a cross-attention launch's wavefronts depends on the most keys of an item
-constexpr int attn_keys_class(int keys) { return keys <= 64 ? 0 : keys <= 256 ? 1 : 2; }
+constexpr int kLongItem = 192;     // cross-attention items of that many keys on average are long ones (attn_wavefronts)
 constexpr int kItemOff = INT_MIN;  // sign bit of a cross-attention work item's sequence: it has finished
 struct AttnArgs {
     const float* q;       // [B, d_model]

@@ -1,0 +1,98 @@
+// The rules of csrc/attn_split.h over many batches: every key in one item, lists that fit what holds them, and the choices
+// themselves where they change over.
+#include <stdio.h>
+
+#include "attn_split.h"
+
+using namespace aed;
+
+FiberIdx::operator unsigned() const { return 0; }
+FiberIdx3 threadIdx;
+dim3 blockIdx, blockDim, gridDim;
+void __syncthreads() {}
+uint32_t exchange(uint32_t, int) { return 0; }
+
+static int bad = 0;
+static void expect(bool ok, const char* what, long long a, long long b, long long c) {
+    if (!ok && bad++ < 20) printf("%s: %lld, %lld, %lld\n", what, a, b, c);
+}
+static unsigned seed = 1;
+static unsigned rnd(unsigned n) { seed = seed * 1664525u + 1013904223u; return (seed >> 8) % n; }
+
+static std::vector<int4> list_of(const std::vector<int>& lens, const CrossCut& cut) {
+    std::vector<int4> items;
+    int at = 0;
+    for (size_t b = 0; b < lens.size(); ++b) {
+        add_items(items, (int)b, lens[b], at, cut);
+        at += lens[b];
+    }
+    order_items(items);
+    return items;
+}
+static long long sum(const std::vector<int>& v) {
+    long long s = 0;
+    for (int x : v) s += x;
+    return s;
+}
+
+static void check_list(const std::vector<int>& lens, int heads, Dtype dt) {
+    const int B = (int)lens.size();
+    const long long total = sum(lens);
+    const CrossCut cut = cross_cut(total, B, heads, dt);
+    const std::vector<int4> items = list_of(lens, cut);
+    // the list has room for every 64 frames and every sequence; a prompt pass repeats it for 8 positions in one grid's y
+    expect((long long)items.size() <= total / 64 + B, "more items than the list holds", items.size(), total, B);
+    expect(B > 4096 ? (int)items.size() == B : items.size() * 8 <= 65535, "more items than a prompt pass's grid", items.size(), B, heads);
+    std::vector<int> covered(B, 0), pieces(B, 0);
+    std::vector<int> first(B, 0);
+    for (int b = 1; b < B; ++b) first[b] = first[b - 1] + lens[b - 1];
+    for (size_t i = 0; i < items.size(); ++i) {
+        const int b = items[i].x, start = items[i].y & 0xFFFF, idx = items[i].y >> 16, n = items[i].z & 0xFFFF, of = items[i].z >> 16;
+        expect(b >= 0 && b < B && n >= 1 && of >= 1 && of <= kMaxChunks && idx >= 0 && idx < of, "item fields", i, idx, of);
+        expect(items[i].w == first[b], "first frame", i, items[i].w, first[b]);
+        expect(of == 1 || start % 16 == 0, "a piece starts inside a block", i, start, n);
+        expect(start + n <= lens[b], "past the sequence's end", b, start + n, lens[b]);
+        expect(start == idx * piece_keys(lens[b], cut), "start", b, start, idx);
+        covered[b] += n;
+        pieces[b] += 1;
+        if (i) {
+            const bool cut_before = items[i - 1].z >> 16 > 1, cut_now = of > 1;
+            expect(cut_before >= cut_now && (cut_before != cut_now || (items[i - 1].z & 0xFFFF) >= n), "order", i, cut_before, cut_now);
+        }
+    }
+    std::vector<int> of(B, 0);
+    for (const int4& it : items) of[it.x] = it.z >> 16;
+    for (int b = 0; b < B; ++b) expect(covered[b] == lens[b] && of[b] == pieces[b], "keys and pieces", b, covered[b], of[b]);
+}
+
+int main() {
+    // lists of every kind of batch
+    for (int heads : {2, 4, 8, 16})
+        for (Dtype dt : {kBF16, kF32})
+            for (int B : {1, 2, 3, 7, 8, 12, 13, 16, 24, 31, 32, 33, 36, 63, 64, 65, 100, 128, 255, 256, 700, 1024, 4096, 4097, 8191})
+                for (int kind = 0; kind < 6; ++kind) {
+                    std::vector<int> lens(B);
+                    for (int b = 0; b < B; ++b)
+                        lens[b] = kind == 0 ? 500 : kind == 1 ? 1 + (int)rnd(500) : kind == 2 ? 1 + (int)rnd(64) : kind == 3 ? (b == B / 2 ? 65535 : 1)
+                                  : kind == 4 ? 300 + (int)rnd(201) : (rnd(6) ? 1 + (int)rnd(80) : 193 + (int)rnd(3000));
+                    check_list(lens, heads, dt);
+                }
+    for (int len : {1, 63, 64, 65, 191, 192, 193, 256, 257, 511, 512, 513, 2047, 2048, 2049, 65535}) check_list({len}, 4, kBF16);
+    // the longest sequence that is taken, whole: its count fills the item's field
+    {
+        std::vector<int> lens(4097, 1);
+        lens[7] = 65535;
+        const std::vector<int4> items = list_of(lens, cross_cut(sum(lens), 4097, 2, kBF16));
+        expect(items[0].x == 7 && (items[0].y & 0xFFFF) == 0 && items[0].z == (65535 | (1 << 16)), "65535 keys whole", items[0].x, items[0].y, items[0].z);
+    }
+    // wavefronts: 8 while 8 are resident (twice that of long items), 4 beyond and for short items
+    struct { long wgs; int kv, keys, lng, want; } nw[] = {
+        {8, 2, 500, 0, 8}, {8, 2, 64, 0, 4}, {8, 2, 65, 0, 8}, {256, 2, 500, 1, 8}, {512, 2, 100, 0, 8}, {513, 2, 100, 0, 4}, {1024, 2, 400, 1, 8},
+        {1025, 2, 400, 1, 4}, {256, 4, 500, 0, 8}, {257, 4, 100, 0, 4}, {512, 4, 400, 1, 8}, {513, 4, 400, 1, 4}, {512, 1, 100, 0, 8}, {513, 1, 100, 0, 4}};
+    for (const auto& c : nw) {
+        const int got = attn_wavefronts(c.wgs, c.kv, c.keys, c.lng);
+        expect(got == c.want, "wavefronts", c.wgs, got, c.want);
+    }
+    printf("%d wrong\n", bad);
+    return bad != 0;
+}
