@@ -619,13 +619,11 @@ aed_status start_batch(aed_decoder* d, const void* enc, bool padded, int t_max, 
     if (batch < 1) return fail(d, AED_EINVAL, "batch must be >= 1");
     if (batch > d->cfg.max_batch) return fail(d, AED_ECAPACITY, "batch %d > max_batch %d", batch, d->cfg.max_batch);
     long long total = 0;
-    int max_len = 0;
     for (int b = 0; b < batch; ++b) {
         if (enc_lens[b] < 1) return fail(d, AED_EINVAL, "enc_lens[%d] = %d (must be >= 1)", b, enc_lens[b]);
         if (enc_lens[b] > 65535) return fail(d, AED_EUNSUPPORTED, "enc_lens[%d] = %d: more than 65535 frames per sequence", b, enc_lens[b]);
         if (padded && enc_lens[b] > t_max) return fail(d, AED_EINVAL, "enc_lens[%d] = %d > t_max %d", b, enc_lens[b], t_max);
         total += enc_lens[b];
-        max_len = std::max(max_len, enc_lens[b]);
     }
     if (total > d->cfg.max_total_enc_frames)
         return fail(d, AED_ECAPACITY, "sum(enc_lens) = %lld > max_total_enc_frames %d", total, d->cfg.max_total_enc_frames);
@@ -648,7 +646,8 @@ aed_status start_batch(aed_decoder* d, const void* enc, bool padded, int t_max, 
     if (padded) HIP_TRY(d, launch_padded_row_map(d->at<int>(d->lay.enc_off), d->at<int>(d->lay.row_map), t_max, batch, d->stream));
     d->batch = batch;
     d->n_items = (int)items.size();
-    d->cross_keys = longest_item(max_len, cut);
+    d->cross_keys = 0;
+    for (const int4& it : items) d->cross_keys = std::max(d->cross_keys, it.z & 0xFFFF);
     d->cross_long = total >= (long long)kLongItem * d->n_items;
     d->items_host = items;
     d->total_enc = total;
@@ -1168,7 +1167,6 @@ extern "C" aed_status aed_greedy_decode_queue(aed_decoder* d, const void* enc_st
         return fail(d, AED_ECAPACITY, "self-attention page pool too small: %lld pages needed, %d available",
                     (long long)B * need_pages, d->lay.n_pages);
     std::vector<long long> src_off((size_t)n_requests + 1, 0);
-    int max_len = 0;
     for (int r = 0; r < n_requests; ++r) {
         if (enc_lens[r] < 1) return fail(d, AED_EINVAL, "enc_lens[%d] = %d (must be >= 1)", r, enc_lens[r]);
         if (enc_lens[r] > 65535)
@@ -1178,7 +1176,6 @@ extern "C" aed_status aed_greedy_decode_queue(aed_decoder* d, const void* enc_st
                         d->cfg.max_total_enc_frames);
         if (max_new_per_req && max_new_per_req[r] < 1) return fail(d, AED_EINVAL, "max_new_per_req[%d] < 1", r);
         src_off[r + 1] = src_off[r] + enc_lens[r];
-        max_len = std::max(max_len, enc_lens[r]);
     }
     if (src_off[n_requests] > INT_MAX) return fail(d, AED_EUNSUPPORTED, "more than 2^31 - 1 encoder frames in the queue");
 
@@ -1192,13 +1189,16 @@ extern "C" aed_status aed_greedy_decode_queue(aed_decoder* d, const void* enc_st
     const CrossCut cut = cross_cut(src_off[n_requests] * B / n_requests, B, d->cfg.n_heads, d->dt);
     {
         std::vector<int> pieces(n_requests);
-        for (int r = 0; r < n_requests; ++r) pieces[r] = cross_pieces(enc_lens[r], cut);
+        d->cross_keys = 0;
+        for (int r = 0; r < n_requests; ++r) {
+            pieces[r] = cross_pieces(enc_lens[r], cut);
+            d->cross_keys = std::max(d->cross_keys, item_keys(enc_lens[r], cut));
+        }
         std::partial_sort(pieces.begin(), pieces.begin() + B, pieces.end(), std::greater<int>());
         long long most = 0;
         for (int b = 0; b < B; ++b) most += pieces[b];
         d->n_items = (int)std::min<long long>(most, d->lay.max_items);
     }
-    d->cross_keys = longest_item(max_len, cut);
     d->cross_long = src_off[n_requests] * B / n_requests >= (long long)kLongItem * d->n_items;
     d->total_enc = -1;
     d->page_table.assign((size_t)B * MP, 0);

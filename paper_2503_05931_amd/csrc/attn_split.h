@@ -29,10 +29,8 @@ inline int piece_keys(int len, const CrossCut& c) {
     const int n = cross_pieces(len, c);
     return ((len + n - 1) / n + 15) / 16 * 16;
 }
-// most keys of an item where the longest sequence has max_len
-inline int longest_item(int max_len, const CrossCut& c) {
-    return max_len <= c.longest ? max_len : std::max(c.longest, piece_keys(max_len, c));
-}
+// most keys of an item of a sequence of len keys
+inline int item_keys(int len, const CrossCut& c) { return std::min(len, piece_keys(len, c)); }
 // the work items of sequence b of len keys, the first at frame first_frame of the packed layout
 inline void add_items(std::vector<int4>& items, int b, int len, int first_frame, const CrossCut& c) {
     const int per = piece_keys(len, c), n = (len + per - 1) / per;
@@ -51,7 +49,6 @@ inline void order_items(std::vector<int4>& items) {
     });
 }
 
-// Items of at most 64 keys are four blocks: further wavefronts would have none.
 constexpr bool attn_short_items(int most_keys) { return most_keys <= 64; }
 
 // Wavefronts per workgroup, 4 or 8, of a launch of wgs workgroups over caches of kv_bytes an element.  What counts is that
@@ -65,6 +62,8 @@ constexpr bool attn_short_items(int most_keys) { return most_keys <= 64; }
 // 8.1 / 8.1, batch 32 11.4 / 10.6 / 10.3; 500 keys 11.3 / 9.7 / 10.1 and 15.1 / 13.3 / 13.4; self-attention over 440 positions,
 // batch 16 8.4 / 7.9 / 7.8, batch 32 11.6 / 11.1 / 11.0; 4 heads of 64, 500 keys, batch 64 9.1 / 7.7 / 8.0): the keys of 8 are as
 // many as a CU has under way, and the merge of 16 takes longer.
+// Items of at most 64 keys are 4 blocks.  (Taken for as long as a sequence that is just not cut, they had 8: one utterance of
+// 200 / 350 / 500 keys 5.18 / 5.27 / 5.40 us, 5.12 / 5.19 / 5.32 on 4; 8-bit caches, batch 16 of 200 keys 7.7 and 6.8.)
 inline int attn_wavefronts(size_t wgs, int kv_bytes, int most_keys, bool long_items) {
     const size_t resident = kv_bytes <= 2 ? 4096 : 2048;
     return wgs * 8 > (long_items ? 2 * resident : resident) || attn_short_items(most_keys) ? 4 : 8;

@@ -45,6 +45,7 @@ static void check_list(const std::vector<int>& lens, int heads, Dtype dt) {
     expect(B > 4096 ? (int)items.size() == B : items.size() * 8 <= 65535, "more items than a prompt pass's grid", items.size(), B, heads);
     std::vector<int> covered(B, 0), pieces(B, 0);
     std::vector<int> first(B, 0);
+    int most = 0;
     for (int b = 1; b < B; ++b) first[b] = first[b - 1] + lens[b - 1];
     for (size_t i = 0; i < items.size(); ++i) {
         const int b = items[i].x, start = items[i].y & 0xFFFF, idx = items[i].y >> 16, n = items[i].z & 0xFFFF, of = items[i].z >> 16;
@@ -55,11 +56,15 @@ static void check_list(const std::vector<int>& lens, int heads, Dtype dt) {
         expect(start == idx * piece_keys(lens[b], cut), "start", b, start, idx);
         covered[b] += n;
         pieces[b] += 1;
+        most = std::max(most, n);
         if (i) {
             const bool cut_before = items[i - 1].z >> 16 > 1, cut_now = of > 1;
             expect(cut_before >= cut_now && (cut_before != cut_now || (items[i - 1].z & 0xFFFF) >= n), "order", i, cut_before, cut_now);
         }
     }
+    int said = 0;
+    for (int len : lens) said = std::max(said, item_keys(len, cut));
+    expect(said == most, "most keys of an item", said, most, B);
     std::vector<int> of(B, 0);
     for (const int4& it : items) of[it.x] = it.z >> 16;
     for (int b = 0; b < B; ++b) expect(covered[b] == lens[b] && of[b] == pieces[b], "keys and pieces", b, covered[b], of[b]);
@@ -85,6 +90,8 @@ int main() {
         const std::vector<int4> items = list_of(lens, cross_cut(sum(lens), 4097, 2, kBF16));
         expect(items[0].x == 7 && (items[0].y & 0xFFFF) == 0 && items[0].z == (65535 | (1 << 16)), "65535 keys whole", items[0].x, items[0].y, items[0].z);
     }
+    // single utterances come out in pieces of at most 64 keys
+    for (int len : {193, 300, 400, 500, 512}) expect(item_keys(len, cross_cut(len, 1, 8, kBF16)) <= 64, "one utterance's pieces", len, 0, 0);
     // wavefronts: 8 while 8 are resident (twice that of long items), 4 beyond and for short items
     struct { long wgs; int kv, keys, lng, want; } nw[] = {
         {8, 2, 500, 0, 8}, {8, 2, 64, 0, 4}, {8, 2, 65, 0, 8}, {256, 2, 500, 1, 8}, {512, 2, 100, 0, 8}, {513, 2, 100, 0, 4}, {1024, 2, 400, 1, 8},
