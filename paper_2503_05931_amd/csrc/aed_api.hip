@@ -631,7 +631,7 @@ aed_status start_batch(aed_decoder* d, const void* enc, bool padded, int t_max, 
     // host tables: frame offsets, cross-attention work list, optional row map
     std::vector<int> off(batch + 1, 0);
     for (int b = 0; b < batch; ++b) off[b + 1] = off[b] + enc_lens[b];
-    const CrossCut cut = cross_cut(total, batch, d->cfg.n_heads, d->dt);
+    const CrossCut cut = cross_cut(total, *std::max_element(enc_lens, enc_lens + batch), batch, d->cfg.n_heads, (int)d->kv_esz);
     std::vector<int4> items;
     for (int b = 0; b < batch; ++b) add_items(items, b, enc_lens[b], off[b], cut);
     if ((int)items.size() > d->lay.max_items) return fail(d, AED_ECAPACITY, "cross-attention work list overflow");
@@ -1186,7 +1186,8 @@ extern "C" aed_status aed_greedy_decode_queue(aed_decoder* d, const void* enc_st
     d->state = aed_decoder::NO_BATCH;  // the per-batch inspection calls do not apply to a queue run
     d->batch = B;
     // as many work items as the B requests with the most need, so that the captured launch shape never changes
-    const CrossCut cut = cross_cut(src_off[n_requests] * B / n_requests, B, d->cfg.n_heads, d->dt);
+    const CrossCut cut = cross_cut(src_off[n_requests] * B / n_requests, *std::max_element(enc_lens, enc_lens + n_requests), B,
+                                   d->cfg.n_heads, (int)d->kv_esz);
     {
         std::vector<int> pieces(n_requests);
         d->cross_keys = 0;

@@ -12,11 +12,32 @@ namespace aed {
 
 // Cross-attention work items.  A sequence of more than `longest` keys is cut into pieces of about `piece` keys.
 struct CrossCut { int longest, piece; };
-// Batches of more than 4096 are left whole: a CU has 32 workgroups and more then, and with the pieces a prompt pass's list
-// (kMaxPrefillPositions times as long) could pass what a launch grid holds in y.
-inline CrossCut cross_cut(long long total_keys, int batch, int n_heads, Dtype dt) {
-    if (batch > 4096) return CrossCut{INT_MAX, INT_MAX};
-    const long long share = total_keys * n_heads / 256 * (dt == kF32 ? 2 : 1);
+// Which ones, from the batch's lengths and the bytes of a cached element (4: float32).  `share`: the keys of a CU if the
+// batch's were dealt evenly, of two CUs in float32.
+//  * Batches of more than 4096 are left whole: a CU has 32 workgroups and more then, and with the pieces a prompt pass's list
+//    (kMaxPrefillPositions times as long) could pass what a launch grid holds in y.
+//  * So are balanced ones, no sequence longer than 4/3 of the mean, of more than 96 (8-bit caches 48) and at most 256
+//    workgroups: all of their sequences would be cut, and merging all of them takes longer than the idle CUs are worth.  24
+//    layers, 8 heads of 128, us a launch, whole / cut by the last rule:
+//      sequences           8            14           16           20           24            28            32
+//      200 keys     5.96  5.95   6.22  7.05   6.28  7.13   6.52  7.83   6.92   8.08   7.26   8.83   7.73   9.14
+//      350 keys     7.55  7.39   7.92  8.22   8.05  8.77   8.48  9.27   9.04  10.40   9.79  11.12  10.58  11.71
+//      500 keys     9.02  8.42   9.50  9.55   9.68 10.54  10.22 11.46  11.05  12.21  12.19  14.30  13.35  15.34
+//      300 to 500   8.76  7.94   9.20  9.06   9.20  9.38   9.65 10.31  10.10  11.15  10.99  12.69  11.81  13.09
+//      12 to 500    8.54  6.98   8.99  8.00   8.89  7.38   9.07  8.00   9.24   8.50   9.84  10.24  10.05  10.21
+//      8-bit, 200   5.29  5.80   5.44  6.78   5.48  6.88   5.63  7.55   5.78   7.81   5.92   8.36   6.12   8.52
+//      8-bit, 500   7.05  7.87   7.31  8.89   7.45  9.29   7.58  9.88   7.97   9.92   8.47  11.31   8.98  11.73
+//    Beyond 256 workgroups some CUs have two sequences and others one, and pieces even that out (36 of 350 keys 14.3 and 13.5).
+//    Float32 rows are twice as long: 16 of 200 / 350 / 500 keys 11.0 and 9.9, 16.5 and 14.2, 22.5 and 18.7.
+//  * Else sequences of more than 7/8 of a share are cut into pieces of half of that, at least 192 and 64 keys: one of 500 keys
+//    among 31 / 127 of 40 8.9 and 5.9, 10.9 and 8.0; log-normal lengths (mean 115), batch 16 / 32 / 64 9.0 and 6.4, 9.4 and 6.9,
+//    11.0 and 8.9; from batch 128 on little is cut (15.8 and 15.6).
+inline CrossCut cross_cut(long long total_keys, int longest_len, int batch, int n_heads, int kv_bytes) {
+    const CrossCut whole{INT_MAX, INT_MAX};
+    const long long wgs = (long long)batch * n_heads;
+    if (batch > 4096) return whole;
+    if (kv_bytes <= 2 && wgs > 48 * kv_bytes && wgs <= 256 && 3ll * longest_len * batch <= 4 * total_keys) return whole;
+    const long long share = total_keys * n_heads / 256 * (kv_bytes == 4 ? 2 : 1);
     CrossCut c;
     c.longest = (int)std::min<long long>(std::max<long long>(192, share * 7 / 8), INT_MAX);
     c.piece = (int)std::min<long long>(std::max<long long>(64, share * 7 / 16 / 32 * 32), INT_MAX);

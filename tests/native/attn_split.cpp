@@ -35,10 +35,13 @@ static long long sum(const std::vector<int>& v) {
     return s;
 }
 
-static void check_list(const std::vector<int>& lens, int heads, Dtype dt) {
+static CrossCut cut_of(const std::vector<int>& lens, int heads, int kv) {
+    return cross_cut(sum(lens), *std::max_element(lens.begin(), lens.end()), (int)lens.size(), heads, kv);
+}
+static void check_list(const std::vector<int>& lens, int heads, int kv) {
     const int B = (int)lens.size();
     const long long total = sum(lens);
-    const CrossCut cut = cross_cut(total, B, heads, dt);
+    const CrossCut cut = cut_of(lens, heads, kv);
     const std::vector<int4> items = list_of(lens, cut);
     // the list has room for every 64 frames and every sequence; a prompt pass repeats it for 8 positions in one grid's y
     expect((long long)items.size() <= total / 64 + B, "more items than the list holds", items.size(), total, B);
@@ -73,25 +76,37 @@ static void check_list(const std::vector<int>& lens, int heads, Dtype dt) {
 int main() {
     // lists of every kind of batch
     for (int heads : {2, 4, 8, 16})
-        for (Dtype dt : {kBF16, kF32})
+        for (int kv : {1, 2, 4})
             for (int B : {1, 2, 3, 7, 8, 12, 13, 16, 24, 31, 32, 33, 36, 63, 64, 65, 100, 128, 255, 256, 700, 1024, 4096, 4097, 8191})
                 for (int kind = 0; kind < 6; ++kind) {
                     std::vector<int> lens(B);
                     for (int b = 0; b < B; ++b)
                         lens[b] = kind == 0 ? 500 : kind == 1 ? 1 + (int)rnd(500) : kind == 2 ? 1 + (int)rnd(64) : kind == 3 ? (b == B / 2 ? 65535 : 1)
                                   : kind == 4 ? 300 + (int)rnd(201) : (rnd(6) ? 1 + (int)rnd(80) : 193 + (int)rnd(3000));
-                    check_list(lens, heads, dt);
+                    check_list(lens, heads, kv);
                 }
-    for (int len : {1, 63, 64, 65, 191, 192, 193, 256, 257, 511, 512, 513, 2047, 2048, 2049, 65535}) check_list({len}, 4, kBF16);
+    for (int len : {1, 63, 64, 65, 191, 192, 193, 256, 257, 511, 512, 513, 2047, 2048, 2049, 65535}) check_list({len}, 4, 2);
     // the longest sequence that is taken, whole: its count fills the item's field
     {
         std::vector<int> lens(4097, 1);
         lens[7] = 65535;
-        const std::vector<int4> items = list_of(lens, cross_cut(sum(lens), 4097, 2, kBF16));
+        const std::vector<int4> items = list_of(lens, cut_of(lens, 2, 2));
         expect(items[0].x == 7 && (items[0].y & 0xFFFF) == 0 && items[0].z == (65535 | (1 << 16)), "65535 keys whole", items[0].x, items[0].y, items[0].z);
     }
     // single utterances come out in pieces of at most 64 keys
-    for (int len : {193, 300, 400, 500, 512}) expect(item_keys(len, cross_cut(len, 1, 8, kBF16)) <= 64, "one utterance's pieces", len, 0, 0);
+    for (int len : {193, 300, 400, 500, 512}) expect(item_keys(len, cut_of({len}, 8, 2)) <= 64, "one utterance's pieces", len, 0, 0);
+    // balanced batches of one workgroup a CU stay whole, but for few sequences and float32; one long sequence among them is cut
+    for (int heads : {4, 8, 16})
+        for (int kv : {1, 2, 4})
+            for (int B = 1; B <= 300 / heads; ++B)
+                for (int len : {193, 350, 500}) {
+                    std::vector<int> lens(B, len);
+                    lens[B / 2] = len * 5 / 4;
+                    const bool whole = kv <= 2 && B * heads > 48 * kv && B * heads <= 256;
+                    expect(!whole || (int)list_of(lens, cut_of(lens, heads, kv)).size() == B, "a balanced batch is cut", B, heads, kv);
+                    lens[B / 2] = len * 6;
+                    expect(B < 4 || B * heads > 256 || (int)list_of(lens, cut_of(lens, heads, kv)).size() > B, "the long one is not", B, heads, kv);
+                }
     // wavefronts: 8 while 8 are resident (twice that of long items), 4 beyond and for short items
     struct { long wgs; int kv, keys, lng, want; } nw[] = {
         {8, 2, 500, 0, 8}, {8, 2, 64, 0, 4}, {8, 2, 65, 0, 8}, {256, 2, 500, 1, 8}, {512, 2, 100, 0, 8}, {513, 2, 100, 0, 4}, {1024, 2, 400, 1, 8},
