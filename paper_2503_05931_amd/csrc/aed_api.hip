@@ -193,9 +193,9 @@ constexpr double kResidentLayerBytes = 220e6;
 
 // What the launches of a captured step or prompt pass depend on; everything else they read from device memory.
 struct GraphKey {
-    int batch = -1, n_items = 0, cross_short = 0, cross_long = 0, self_chunk = 0, self_nchunks = 0, prompt_len = 0, max_new = 0;
+    int batch = -1, n_items = 0, cross_wavefronts = 0, self_chunk = 0, self_nchunks = 0, prompt_len = 0, max_new = 0;
     bool operator==(const GraphKey& o) const {
-        return batch == o.batch && n_items == o.n_items && cross_short == o.cross_short && cross_long == o.cross_long &&
+        return batch == o.batch && n_items == o.n_items && cross_wavefronts == o.cross_wavefronts &&
                self_chunk == o.self_chunk && self_nchunks == o.self_nchunks && prompt_len == o.prompt_len && max_new == o.max_new;
     }
 };
@@ -245,7 +245,9 @@ struct aed_decoder {
     int host_pos = 0;     // positions fed so far (step API)
     int pages_used = 0;
     int n_items = 0;
-    int self_chunk = 64, self_nchunks = 1, cross_keys = 0, cross_long = 0;  // cross_keys: most keys of a cross-attention item
+    int self_chunk = 64, self_nchunks = 1;
+    int cross_keys = 0;                         // most keys of a cross-attention item
+    bool cross_long = false, cross_even = false;  // see attn_wavefronts
     int last_prompt_len = 0, last_max_new = 0;
     long long total_enc = 0;
     const void* last_enc = nullptr;
@@ -420,6 +422,7 @@ hipError_t k_self_attn(aed_decoder* d, int l) {
     a.seq_len = d->at<int>(d->lay.seq_len);
     a.chunk = d->self_chunk;
     a.n_chunks_max = d->self_nchunks;
+    a.wavefronts = attn_wavefronts((long long)d->batch * d->cfg.n_heads * d->self_nchunks, 0, (int)d->kv_esz, d->self_chunk, false, false);
     return launch_attn_self(d->dt, a, d->stream);
 }
 
@@ -476,14 +479,18 @@ hipError_t k_ln_crossq(aed_decoder* d, int l) {
     return launch_gemm(d->dt, PRO_LN, EPI_F32, g, d->stream);
 }
 
+int cross_wavefronts(const aed_decoder* d) {
+    const int H = d->cfg.n_heads;
+    return attn_wavefronts((long long)d->n_items * H, (long long)d->batch * H, (int)d->kv_esz, d->cross_keys, d->cross_long, d->cross_even);
+}
+
 hipError_t k_cross_attn(aed_decoder* d, int l) {
     AttnArgs a = attn_base(d);
     a.K = d->ws + d->lay.kc + (size_t)l * d->lay.cross_layer_elems * d->kv_esz;
     a.V = d->ws + d->lay.vc + (size_t)l * d->lay.cross_layer_elems * d->kv_esz;
     a.items = d->at<int4>(d->lay.items);
     a.n_items = d->n_items;
-    a.chunk = d->cross_keys;
-    a.long_items = d->cross_long;
+    a.wavefronts = cross_wavefronts(d);
     a.enc_off = d->at<int>(d->lay.enc_off);
     a.t_cap = d->cfg.max_total_enc_frames;
     if (merged_products(d)) {  // q holds the merged product: the kernel finishes the normalisation
@@ -631,7 +638,8 @@ aed_status start_batch(aed_decoder* d, const void* enc, bool padded, int t_max, 
     // host tables: frame offsets, cross-attention work list, optional row map
     std::vector<int> off(batch + 1, 0);
     for (int b = 0; b < batch; ++b) off[b + 1] = off[b] + enc_lens[b];
-    const CrossCut cut = cross_cut(total, *std::max_element(enc_lens, enc_lens + batch), batch, d->cfg.n_heads, (int)d->kv_esz);
+    const int longest = *std::max_element(enc_lens, enc_lens + batch);
+    const CrossCut cut = cross_cut(total, longest, batch, d->cfg.n_heads, (int)d->kv_esz);
     std::vector<int4> items;
     for (int b = 0; b < batch; ++b) add_items(items, b, enc_lens[b], off[b], cut);
     if ((int)items.size() > d->lay.max_items) return fail(d, AED_ECAPACITY, "cross-attention work list overflow");
@@ -649,6 +657,7 @@ aed_status start_batch(aed_decoder* d, const void* enc, bool padded, int t_max, 
     d->cross_keys = 0;
     for (const int4& it : items) d->cross_keys = std::max(d->cross_keys, it.z & 0xFFFF);
     d->cross_long = total >= (long long)kLongItem * d->n_items;
+    d->cross_even = even_lengths(total, longest, batch);
     d->items_host = items;
     d->total_enc = total;
     d->last_enc = enc;
@@ -677,7 +686,7 @@ aed_status start_batch(aed_decoder* d, const void* enc, bool padded, int t_max, 
 GraphKey graph_key(const aed_decoder* d) {
     GraphKey key;
     key.batch = d->batch; key.n_items = d->n_items;
-    key.cross_short = attn_short_items(d->cross_keys); key.cross_long = d->cross_long;
+    key.cross_wavefronts = cross_wavefronts(d);
     key.self_chunk = d->self_chunk; key.self_nchunks = d->self_nchunks;
     return key;
 }
@@ -1186,8 +1195,9 @@ extern "C" aed_status aed_greedy_decode_queue(aed_decoder* d, const void* enc_st
     d->state = aed_decoder::NO_BATCH;  // the per-batch inspection calls do not apply to a queue run
     d->batch = B;
     // as many work items as the B requests with the most need, so that the captured launch shape never changes
-    const CrossCut cut = cross_cut(src_off[n_requests] * B / n_requests, *std::max_element(enc_lens, enc_lens + n_requests), B,
-                                   d->cfg.n_heads, (int)d->kv_esz);
+    const long long in_slots = src_off[n_requests] * B / n_requests;  // frames, on average
+    const int longest = *std::max_element(enc_lens, enc_lens + n_requests);
+    const CrossCut cut = cross_cut(in_slots, longest, B, d->cfg.n_heads, (int)d->kv_esz);
     {
         std::vector<int> pieces(n_requests);
         d->cross_keys = 0;
@@ -1200,7 +1210,8 @@ extern "C" aed_status aed_greedy_decode_queue(aed_decoder* d, const void* enc_st
         for (int b = 0; b < B; ++b) most += pieces[b];
         d->n_items = (int)std::min<long long>(most, d->lay.max_items);
     }
-    d->cross_long = src_off[n_requests] * B / n_requests >= (long long)kLongItem * d->n_items;
+    d->cross_long = in_slots >= (long long)kLongItem * d->n_items;
+    d->cross_even = even_lengths(in_slots, longest, B);
     d->total_enc = -1;
     d->page_table.assign((size_t)B * MP, 0);
     for (int b = 0; b < B; ++b)

@@ -28,7 +28,6 @@
 // is too small to occupy the GPU, is cut into chunks handled by different
 // workgroups, and the last workgroup of a (sequence, head) to finish
 // combines the partial (max, sum, values) triples in chunk order.
-#include "attn_split.h"
 #include "common.h"
 #include "kernels.h"
 
@@ -387,11 +386,8 @@ __global__ __launch_bounds__(64 * NW, sizeof(KV) <= 2 ? 4 : 1) void attn_decode_
 
 template <typename T, typename KV, int LPK, int DH, bool SELF>
 static void launch_nw(const AttnArgs& a, dim3 grid, hipStream_t s) {
-    const size_t wgs = (size_t)grid.x * grid.y * grid.z;
-    if (attn_wavefronts(wgs, sizeof(KV), a.chunk, a.long_items) == 4)
-        hipLaunchKernelGGL((attn_decode_kernel<T, KV, LPK, DH, SELF, 4>), grid, dim3(256), 0, s, a);
-    else
-        hipLaunchKernelGGL((attn_decode_kernel<T, KV, LPK, DH, SELF, 8>), grid, dim3(512), 0, s, a);
+    if (a.wavefronts == 4) hipLaunchKernelGGL((attn_decode_kernel<T, KV, LPK, DH, SELF, 4>), grid, dim3(256), 0, s, a);
+    else hipLaunchKernelGGL((attn_decode_kernel<T, KV, LPK, DH, SELF, 8>), grid, dim3(512), 0, s, a);
 }
 template <typename T, typename KV, int LPK, bool SELF>
 static hipError_t launch_kv(const AttnArgs& a, dim3 grid, hipStream_t s) {
@@ -410,14 +406,14 @@ static hipError_t launch_dh(const AttnArgs& a, dim3 grid, hipStream_t s) {
 }
 
 hipError_t launch_attn_self(Dtype dt, const AttnArgs& a, hipStream_t s) {
-    if (a.chunk < 64 || a.chunk % 64 != 0 || a.n_chunks_max < 1 || a.n_chunks_max > a.max_chunks)
+    if (a.chunk < 64 || a.chunk % 64 != 0 || a.n_chunks_max < 1 || a.n_chunks_max > a.max_chunks || (a.wavefronts != 4 && a.wavefronts != 8))
         return hipErrorInvalidValue;
     dim3 grid(a.n_heads, a.batch, a.n_chunks_max);
     return dt == kBF16 ? launch_dh<bf16_t, true>(a, grid, s) : launch_dh<float, true>(a, grid, s);
 }
 
 hipError_t launch_attn_cross(Dtype dt, const AttnArgs& a, hipStream_t s) {
-    if (a.chunk < 1 || !a.items || a.n_items < 1) return hipErrorInvalidValue;
+    if (!a.items || a.n_items < 1 || (a.wavefronts != 4 && a.wavefronts != 8)) return hipErrorInvalidValue;
     dim3 grid(a.n_heads, a.n_items);
     return dt == kBF16 ? launch_dh<bf16_t, false>(a, grid, s) : launch_dh<float, false>(a, grid, s);
 }

@@ -10,13 +10,20 @@
 
 namespace aed {
 
+// Float32 rows: one workgroup of 8 wavefronts fills a CU.  Up to so many of them, two rounds, longest first, come out even
+// enough by themselves.
+constexpr long long kF32TwoRounds = 512;
+
+// no sequence is longer than 4/3 of the mean
+inline bool even_lengths(long long total_keys, int longest_len, int batch) { return 3ll * longest_len * batch <= 4 * total_keys; }
+
 // Cross-attention work items.  A sequence of more than `longest` keys is cut into pieces of about `piece` keys.
 struct CrossCut { int longest, piece; };
 // Which ones, from the batch's lengths and the bytes of a cached element (4: float32).  `share`: the keys of a CU if the
 // batch's were dealt evenly, of two CUs in float32.
 //  * Batches of more than 4096 are left whole: a CU has 32 workgroups and more then, and with the pieces a prompt pass's list
 //    (kMaxPrefillPositions times as long) could pass what a launch grid holds in y.
-//  * So are balanced ones, no sequence longer than 4/3 of the mean, of more than 96 (8-bit caches 48) and at most 256
+//  * So are those of even lengths and of more than 96 (8-bit caches 48) and at most 256
 //    workgroups: all of their sequences would be cut, and merging all of them takes longer than the idle CUs are worth.  24
 //    layers, 8 heads of 128, us a launch, whole / cut by the last rule:
 //      sequences           8            14           16           20           24            28            32
@@ -31,15 +38,17 @@ struct CrossCut { int longest, piece; };
 //    Float32 rows are twice as long: 16 of 200 / 350 / 500 keys 11.0 and 9.9, 16.5 and 14.2, 22.5 and 18.7.
 //  * Else sequences of more than 7/8 of a share are cut into pieces of half of that, at least 192 and 64 keys: one of 500 keys
 //    among 31 / 127 of 40 8.9 and 5.9, 10.9 and 8.0; log-normal lengths (mean 115), batch 16 / 32 / 64 9.0 and 6.4, 9.4 and 6.9,
-//    11.0 and 8.9; from batch 128 on little is cut (15.8 and 15.6).
+//    11.0 and 8.9; from batch 128 on little is cut (15.8 and 15.6).  Float32 is cut from 7/8 of two CUs' share up to kF32TwoRounds,
+//    of one beyond: log-normal lengths, from two / one CU's share, batch 80 25.1 and 18.9, 96 26.9 and 21.0, 128 30.3 and 28.7; 12 to
+//    500 keys, batch 40 22.4 and 25.9, 48 22.0 and 27.6, 64 29.9 and 32.3, 80 37.1 and 37.1.
 inline CrossCut cross_cut(long long total_keys, int longest_len, int batch, int n_heads, int kv_bytes) {
     const CrossCut whole{INT_MAX, INT_MAX};
     const long long wgs = (long long)batch * n_heads;
     if (batch > 4096) return whole;
-    if (kv_bytes <= 2 && wgs > 48 * kv_bytes && wgs <= 256 && 3ll * longest_len * batch <= 4 * total_keys) return whole;
+    if (kv_bytes <= 2 && wgs > 48 * kv_bytes && wgs <= 256 && even_lengths(total_keys, longest_len, batch)) return whole;
     const long long share = total_keys * n_heads / 256 * (kv_bytes == 4 ? 2 : 1);
     CrossCut c;
-    c.longest = (int)std::min<long long>(std::max<long long>(192, share * 7 / 8), INT_MAX);
+    c.longest = (int)std::min<long long>(std::max<long long>(192, (kv_bytes == 4 && wgs > kF32TwoRounds ? share / 2 : share) * 7 / 8), INT_MAX);
     c.piece = (int)std::min<long long>(std::max<long long>(64, share * 7 / 16 / 32 * 32), INT_MAX);
     return c;
 }
@@ -70,24 +79,30 @@ inline void order_items(std::vector<int4>& items) {
     });
 }
 
-constexpr bool attn_short_items(int most_keys) { return most_keys <= 64; }
-
 // Wavefronts per workgroup, 4 or 8, of a launch of wgs workgroups over caches of kv_bytes an element.  What counts is that
 // every workgroup is resident from the start (4096 wavefronts fit the 256 CUs, of float32 rows 2048) and that a wavefront has
 // a block or two to itself: with 8 wavefronts where 8 do not fit, a second round of workgroups starts when the first is over
 // (self-attention, 24 layers, batch 128, 33 positions: 44.4 ms with 8, 42.9 with 4; batch 64 125.0 and 125.4 for 131), and
 // wavefronts without a block still cost the merge (one utterance, cross- and self-attention on 16 and on 4: 92.6 and 90.1 ms).
 // Items that are long on average (kLongItem) keep memory busy in two rounds as well, and 8 wavefronts are through with the last
-// ones sooner (24 layers, batch 128 of 12 to 500 frames, half of whose sequences are through on average: 357 and 350 ms).
+// ones sooner (24 layers, batch 128 of 12 to 500 frames, half of whose sequences are through on average: 357 and 350 ms; us a
+// launch on 4 / 8, batch 72 / 96 / 128: 12 to 500 keys 18.4 / 17.4, 20.0 / 18.0, 23.3 / 21.7; 100 to 400 17.5 / 15.8, 19.1 / 18.0, 22.9 /
+// 22.0; 500 each 27.8 / 27.5, 32.0 / 32.0, 41.4 / 41.3; but 200 each 14.0 / 14.1, 15.5 / 16.0, 19.3 / 19.8).
 // 16 are nowhere better than 8 (bfloat16, 8 heads of 128, us a launch on 16 / 8 / 4: cross-attention of 350 keys, batch 16 8.8 /
 // 8.1 / 8.1, batch 32 11.4 / 10.6 / 10.3; 500 keys 11.3 / 9.7 / 10.1 and 15.1 / 13.3 / 13.4; self-attention over 440 positions,
 // batch 16 8.4 / 7.9 / 7.8, batch 32 11.6 / 11.1 / 11.0; 4 heads of 64, 500 keys, batch 64 9.1 / 7.7 / 8.0): the keys of 8 are as
 // many as a CU has under way, and the merge of 16 takes longer.
+// Float32 cross-attention of uneven lengths has 8 up to kF32TwoRounds (sequence, head) pairs (us on 4 / 8: log-normal lengths,
+// batch 48 16.5 and 14.3, 64 21.8 and 18.9; 12 to 250 keys, batch 48 16.4 and 13.8; but batch 128 of log-normal ones 29.8 and 31.1,
+// 100 keys each, batch 64 12.4 and 13.6).
 // Items of at most 64 keys are 4 blocks.  (Taken for as long as a sequence that is just not cut, they had 8: one utterance of
 // 200 / 350 / 500 keys 5.18 / 5.27 / 5.40 us, 5.12 / 5.19 / 5.32 on 4; 8-bit caches, batch 16 of 200 keys 7.7 and 6.8.)
-inline int attn_wavefronts(size_t wgs, int kv_bytes, int most_keys, bool long_items) {
-    const size_t resident = kv_bytes <= 2 ? 4096 : 2048;
-    return wgs * 8 > (long_items ? 2 * resident : resident) || attn_short_items(most_keys) ? 4 : 8;
+// pairs: of cross-attention sequences and heads, 0: self-attention; even: even_lengths of the batch.
+inline int attn_wavefronts(long long wgs, long long pairs, int kv_bytes, int most_keys, bool long_items, bool even) {
+    if (most_keys <= 64) return 4;
+    if (kv_bytes == 4 && !long_items && !even && pairs > 256 && pairs <= kF32TwoRounds) return 8;
+    const long long resident = kv_bytes <= 2 ? 4096 : 2048;
+    return wgs * 8 > (long_items ? 2 * resident : resident) ? 4 : 8;
 }
 
 }  // namespace aed

@@ -126,9 +126,9 @@ struct AttnArgs {
     const int* page_table;
     int max_pages;
     const int* seq_len;   // keys = seq_len[b] + 1
-    int chunk;            // most keys of a work item (self: every one but a sequence's last, a multiple of 64)
-    int long_items;       // cross: the items have kLongItem keys or more on average
+    int chunk;            // keys per work item but a sequence's last, a multiple of 64
     int n_chunks_max;     // grid.z
+    int wavefronts;       // per workgroup, self and cross: 4 or 8 (attn_wavefronts)
     int batch;
     // cross
     const int4* items;    // {b (| kItemOff: nothing to do), key_start | chunk_idx << 16, n_keys | n_chunks << 16, first frame of b in the

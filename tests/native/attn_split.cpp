@@ -107,12 +107,23 @@ int main() {
                     lens[B / 2] = len * 6;
                     expect(B < 4 || B * heads > 256 || (int)list_of(lens, cut_of(lens, heads, kv)).size() > B, "the long one is not", B, heads, kv);
                 }
+    // float32: one long sequence in ten of a large batch is cut
+    for (int B : {65, 80, 96, 128}) {
+        std::vector<int> lens(B, 80);
+        for (int b = 0; b < B; b += 10) lens[b] = 500;
+        expect((int)list_of(lens, cut_of(lens, 8, 4)).size() > B, "long float32 sequences are not cut", B, 0, 0);
+    }
     // wavefronts: 8 while 8 are resident (twice that of long items), 4 beyond and for short items
-    struct { long wgs; int kv, keys, lng, want; } nw[] = {
-        {8, 2, 500, 0, 8}, {8, 2, 64, 0, 4}, {8, 2, 65, 0, 8}, {256, 2, 500, 1, 8}, {512, 2, 100, 0, 8}, {513, 2, 100, 0, 4}, {1024, 2, 400, 1, 8},
-        {1025, 2, 400, 1, 4}, {256, 4, 500, 0, 8}, {257, 4, 100, 0, 4}, {512, 4, 400, 1, 8}, {513, 4, 400, 1, 4}, {512, 1, 100, 0, 8}, {513, 1, 100, 0, 4}};
+    struct { long wgs; long long pairs; int kv, keys, lng, even, want; } nw[] = {
+        {8, 8, 2, 500, 0, 0, 8}, {8, 8, 2, 64, 0, 1, 4}, {8, 8, 2, 65, 0, 1, 8}, {256, 256, 2, 500, 1, 1, 8}, {512, 512, 2, 100, 0, 0, 8},
+        {513, 512, 2, 100, 0, 0, 4}, {1024, 1024, 2, 400, 1, 0, 8}, {1025, 1024, 2, 400, 1, 0, 4}, {512, 512, 1, 100, 0, 0, 8},
+        {513, 512, 1, 100, 0, 0, 4}, {512, 0, 2, 400, 0, 0, 8}, {513, 0, 2, 400, 0, 0, 4},
+        // float32: two rounds of 8 of uneven lengths, whatever the pieces make of them, and of long items; one in self-attention
+        {256, 256, 4, 500, 0, 1, 8}, {300, 200, 4, 100, 0, 0, 4}, {300, 257, 4, 100, 0, 0, 8}, {300, 257, 4, 100, 0, 1, 4}, {700, 512, 4, 100, 0, 0, 8},
+        {700, 512, 4, 64, 0, 0, 4}, {700, 513, 4, 100, 0, 0, 4}, {512, 600, 4, 400, 1, 0, 8}, {513, 600, 4, 400, 1, 0, 4}, {256, 0, 4, 400, 0, 0, 8},
+        {257, 0, 4, 400, 0, 0, 4}};
     for (const auto& c : nw) {
-        const int got = attn_wavefronts(c.wgs, c.kv, c.keys, c.lng);
+        const int got = attn_wavefronts(c.wgs, c.pairs, c.kv, c.keys, c.lng, c.even);
         expect(got == c.want, "wavefronts", c.wgs, got, c.want);
     }
     printf("%d wrong\n", bad);

@@ -77,6 +77,7 @@ def test_self_attention_history(torch_cuda, oracle, dtype, kv_fp8, batch, steps)
 @pytest.mark.parametrize("batch,lens", [
     (256, lambda i: 1 + (37 * i) % 340), (256, lambda i: 160 + (37 * i) % 180),
     (40, lambda i: [192, 193, 321, 449, 512, 600, 1500][i // 5 % 7] if i % 5 == 0 else 1 + 7 * i % 60),
+    (136, lambda i: 200 + 19 * i if i % 9 == 0 else 1 + 7 * i % 60),
 ])
 def test_cross_attention_blocks_and_pieces(torch_cuda, oracle, dtype, kv_fp8, batch, lens):
     run(oracle, "bf16+fp8kv" if kv_fp8 else dtype, dtype, 256, 64, [lens(i) for i in range(batch)], 256, 1, 3 + batch,
