@@ -165,12 +165,12 @@ def test_split_chunks_and_capacity_slack(torch_cuda, oracle):
     dec.close()
 
 
-@pytest.mark.parametrize("dtype,n_short", [("fp32", 2), ("bf16", 2), ("bf16", 31)])
+@pytest.mark.parametrize("dtype,n_short", [("fp32", 2), ("bf16", 2), ("bf16", 31), ("bf16", 4096)])
 def test_longest_and_shortest_sequence_in_one_batch(torch_cuda, oracle, dtype, n_short):
     """The most frames the library takes for one sequence (65 535: key offsets and counts are 16-bit fields of a
-    cross-attention work item) next to sequences of a single frame.  With 3 sequences the long one is cut into the
-    largest number of chunks and merged; with 32 (x 4 heads: enough work items not to cut) it is one work item of
-    65 535 keys.  One frame more is refused before anything is launched."""
+    cross-attention work item) next to sequences of a single frame.  With 3 and with 32 sequences the long one is cut
+    into the largest number of chunks and merged; with 4097, of which none is cut, it is one work item of 65 535 keys.
+    One frame more is refused before anything is launched."""
     from tests import gpu_util as G
     from paper_2503_05931_amd import binding
     lens = [1, 65535] + [1] * (n_short - 1)

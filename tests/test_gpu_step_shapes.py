@@ -49,8 +49,8 @@ def test_product_shapes(torch_cuda, oracle, dtype, d_model, head_dim, d_ffn, bat
     run(oracle, dtype, dtype, d_model, head_dim, [1 + (5 * i) % 9 for i in range(batch)], d_ffn, 2, batch + d_ffn)
 
 
-# Cross-attention: 16, 8 and 4 wavefronts per workgroup (up to 256, 1024 and more workgroups of 4 heads), key counts around
-# what they have in flight, and sequences around the length from which a small batch has them cut (256 keys).
+# Cross-attention of one or two sequences, and of a few long ones among short ones: those of more than 192 keys are cut, into 4 to 8
+# pieces of 64 keys (80 of 513), on 8 wavefronts, or on 4 where no item has more than 64 keys (batch 1) or 8 are not all resident.
 @pytest.mark.parametrize("dtype,kv_fp8", [("bf16", 0), ("bf16", 1), ("fp32", 0)])
 @pytest.mark.parametrize("batch", [1, 2, 64, 65, 256, 257])
 def test_attention_splits(torch_cuda, oracle, dtype, kv_fp8, batch):
@@ -60,8 +60,8 @@ def test_attention_splits(torch_cuda, oracle, dtype, kv_fp8, batch):
     run(oracle, "bf16+fp8kv" if kv_fp8 else dtype, dtype, 256, 64, lens, 256, 2, 7 + batch, kv_fp8=kv_fp8)
 
 
-# Self-attention with as much history: batch 32 (128 workgroups, sequences whole) takes the second round of 16 wavefronts
-# (float32: the third of 8); small batches are cut, the last length just past a whole number of chunks.
+# Self-attention with a long history: batch 32 (128 workgroups, sequences whole) has up to three blocks to each of 8 wavefronts;
+# small batches are cut, the last length just past a whole number of chunks.
 @pytest.mark.parametrize("dtype,kv_fp8,batch,steps", [
     ("bf16", 0, 32, 300), ("bf16", 1, 32, 300), ("fp32", 0, 32, 300), ("bf16", 0, 3, 513), ("bf16", 1, 2, 300), ("fp32", 0, 2, 300),
 ])
@@ -70,12 +70,13 @@ def test_self_attention_history(torch_cuda, oracle, dtype, kv_fp8, batch, steps)
     run(oracle, "bf16+fp8kv" if kv_fp8 else dtype, dtype, 256, 64, lens, 256, steps, steps + batch, kv_fp8=kv_fp8)
 
 
-# Cross-attention of whole sequences of every number of blocks that a wavefront's loop tells apart (none, one, two, odd, even):
-# 256 sequences of up to 340 keys on 4 wavefronts, on 8 where they are long on average, and some of several times the mean's
-# keys among short ones, which are cut into 2 to 8 pieces (float32: others than bfloat16), the last one key long.
+# Cross-attention of whole sequences of every number of blocks that a wavefront's loop tells apart (none, one, two, odd, even), on 4
+# wavefronts (256 sequences of up to 340 keys) and on 8 (bfloat16: 160 to 339 keys on average long, and 32 of like length, one
+# workgroup a CU; float32: 100 uneven ones); then sequences of several times the mean's keys among short ones, which are cut into 2
+# to 8 pieces, the last one key long (136: where float32 has more than 512 workgroups).
 @pytest.mark.parametrize("dtype,kv_fp8", [("bf16", 0), ("bf16", 1), ("fp32", 0)])
 @pytest.mark.parametrize("batch,lens", [
-    (256, lambda i: 1 + (37 * i) % 340), (256, lambda i: 160 + (37 * i) % 180),
+    (256, lambda i: 1 + (37 * i) % 340), (256, lambda i: 160 + (37 * i) % 180), (32, lambda i: 380 + (37 * i) % 121), (100, lambda i: 1 + (37 * i) % 340),
     (40, lambda i: [192, 193, 321, 449, 512, 600, 1500][i // 5 % 7] if i % 5 == 0 else 1 + 7 * i % 60),
     (136, lambda i: 200 + 19 * i if i % 9 == 0 else 1 + 7 * i % 60),
 ])
