@@ -32,6 +32,11 @@
  *    finished-count and synchronises the stream before returning) and
  *    aed_greedy_decode_queue (blocks until the queue is empty).
  *    One decoder = one stream = one host thread.
+ *  - Results: the same calls give the same bits.  In which order float32 sums
+ *    are added up depends on the number of sequences and on the lengths of
+ *    all of them, so a sequence's logits differ in rounding from those it has
+ *    in another batch, and where two ids are as good as tied the other one
+ *    may be taken.
  *  - Errors: every call returns an aed_status; argument errors are found on
  *    the host before any launch and leave the decoder unchanged.
  *    aed_last_error gives a message for the most recent failure.
@@ -184,7 +189,8 @@ aed_status aed_greedy_decode(aed_decoder *dec, const int32_t *prompt, int32_t pr
  * instead of idling until the slowest sequence of a fixed batch is done (the
  * decoded length varies per utterance and the decoder runs one step per
  * token for the whole batch: Sec. 1; Fig. 3 caption).  Each request's result
- * is what aed_greedy_decode gives for it in any batch.
+ * is what aed_greedy_decode gives for it in a batch (but for rounding, see
+ * Results above).
  * A refill computes the new requests' cross-attention K/V (all layers) into
  * free frames of the cache, re-uses the slot's self-attention pages from
  * position 0, and hands the finished request's tokens to the caller's rows.

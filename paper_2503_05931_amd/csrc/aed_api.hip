@@ -50,18 +50,16 @@ hipError_t scratch_of_current_device(char** out) {
     return hipSuccess;
 }
 
-constexpr int kTargetItems = 512;      // work items aimed at per attention launch when sequences are cut
+// Self-attention (pick_chunk; cross-attention: attn_split.h)
+constexpr int kTargetItems = 512;      // work items aimed at per launch when sequences are cut
 constexpr int kMinItemsNoSplit = 128;  // batch * heads from which sequences are never cut
-// Sequences are not cut into pieces of fewer keys: 16 wavefronts (float32: 8) take 256 (128) keys a round, with fewer some
-// idle, and merging costs 1 us a launch.  Milliseconds for 40 positions with pieces of at least 64 / 128 / 256 keys
-// (bfloat16 24 layers, float32 4 layers, 8 heads; encoder frames x batch):
-//            200 x 1             500 x 1             200 x 4             500 x 4             300 x 8
-//   bf16     33.1  32.6  31.2    35.3  34.0  33.6    33.8  33.3  31.9    37.3  35.0  34.3    35.9  34.8  34.8
-//   float32   9.8   9.8  10.0    10.3  10.2  10.6                        10.8  10.6  11.1    11.3  10.9  11.4
-//   bf16, 440 positions of history, batch 1, 24 layers:  392  379  363
-// 8-bit caches go with bf16 (500 x 4: 38.5, 36.5, 35.7).  For float32 128 would be better with few sequences, but not where
-// the pieces outnumber the CUs (400 x 12: 12.3 at 128, 11.7 at 256; 200 x 15: 10.7, 10.4).  From 2048 keys on kMaxChunks makes
-// the pieces longer anyway.
+// Sequences are not cut into pieces of fewer keys: with few sequences smaller pieces gain up to 2.5 %, with more they lose as
+// much.  24 layers, 8 heads, greedy decoding, us a step with pieces of at least 64 / 128 / 256 / 512 keys and whole:
+//   positions    batch 1                       batch 4                       batch 8                       batch 15
+//     440        682 690 697 695 694           694 699 706 702 702           715 712 714 707 707           745 746 738 727 726
+//     900        698 698 716 739 742           715 715 728 749 752           743 744 744 760 761           800 800 800 795 785
+//    1500        713 713 725 759 806           735 735 743 771 818           776 776 785 789 830
+// From 2048 keys on kMaxChunks makes the pieces longer anyway.
 constexpr int kMinChunk = 256;
 constexpr int kMaxPrefillPositions = 8;  // prompt positions per prefill pass
 
@@ -144,7 +142,9 @@ void make_layout(const aed_config* c, Layout* L) {
     L->mu_hat = take(2 * Bp * 4);  // two buffers, alternating like the statistics
     L->part = take(Ba * H * kMaxChunks * (Dh + 2) * 4);
     L->counters = take(Ba * H * 4);
-    L->act_bytes = off;  // everything above is rewritten by every step before it is read (the counters: zero between launches)
+    // Everything above is written before it is read by every step of the step calls (the counters: zero between launches).
+    // Greedy steps keep the rows that the next one starts from: x, their shadow, statistics and shifts.
+    L->act_bytes = off;
     L->ln_fold = take(((size_t)c->n_layers * (4 * d + (size_t)c->d_ffn) + (size_t)c->vocab) * 2 * 4);
     L->seq_len = take(B * 4);
     L->n_gen = take(B * 4);
@@ -309,14 +309,10 @@ aed_status fail(aed_decoder* d, aed_status st, const char* fmt, ...) {
         if (e_ != hipSuccess) return fail(d, AED_EHIP, "%s: %s", #expr, hipGetErrorString(e_));  \
     } while (0)
 
-// Keys per attention work item.  Whole sequences (one workgroup per sequence and
-// head, no merge) whenever batch * heads gives the 256 CUs something to do:
-// measured on MI355X, cutting every sequence of the 24-layer batch-64 and the
-// 4-layer batch-256 workloads into 128-key chunks did not shorten the attention
-// kernels (cutting only a batch's longest sequences has not been tried).  Only a
-// batch too small to occupy the GPU (batch * heads < kMinItemsNoSplit) has its long
-// sequences cut, aiming at kTargetItems items of at least kMinChunk keys and at most
-// kMaxChunks per sequence.
+// Keys per self-attention work item.  Whole sequences (one workgroup per sequence and head, no merge) whenever batch * heads
+// gives the 256 CUs something to do: the sequences of a batch have about as many positions each, so cutting them evens
+// nothing out.  Only those of a batch too small to occupy the GPU (batch * heads < kMinItemsNoSplit) are cut when they are
+// long, aiming at kTargetItems items of at least kMinChunk keys and at most kMaxChunks per sequence.
 int pick_chunk(long long total_keys, int max_len, int batch, int n_heads) {
     const long long whole = std::max<long long>(64, ((long long)max_len + 63) / 64 * 64);
     if ((long long)batch * n_heads >= kMinItemsNoSplit) return (int)whole;
@@ -746,7 +742,7 @@ aed_status prefill_pass(aed_decoder* d, const std::vector<int>& prompt_host, int
             for (int k = 0; k < MP; ++k) pt[(size_t)r * MP + k] = b < B ? d->page_table[(size_t)b * MP + k] : 0;
         }
     }
-    for (const int4& it : d->items_host)  // longest first stays longest first
+    for (const int4& it : d->items_host)  // in the list's order
         for (int q = 0; q < np; ++q) {
             int4 v = it;
             v.x = q * Bs + it.x;

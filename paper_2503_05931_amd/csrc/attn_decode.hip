@@ -23,9 +23,9 @@
 // (max, sum, weighted values) is kept per wavefront in base-2 exponent form,
 // the wavefronts are merged through LDS.  Sequences of this workload are short
 // (at most 500 encoder frames, a few hundred decoded tokens), so one workgroup
-// per (sequence, head) is the normal case.  Cross-attention of sequences with
-// more than a CU's share of the batch's keys, and self-attention when the batch
-// is too small to occupy the GPU, is cut into chunks handled by different
+// per (sequence, head) is the normal case.  Cross-attention of sequences that
+// are long beside the batch's others (attn_split.h), and self-attention when the
+// batch is too small to occupy the GPU, is cut into chunks handled by different
 // workgroups, and the last workgroup of a (sequence, head) to finish
 // combines the partial (max, sum, values) triples in chunk order.
 #include "common.h"

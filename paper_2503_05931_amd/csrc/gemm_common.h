@@ -48,29 +48,24 @@ __device__ __forceinline__ void store_frag(float* blk, int lane, const Frag16<fl
     for (int j = 0; j < 4; ++j) p[64 * j] = f32x4{f.v[4 * j], f.v[4 * j + 1], f.v[4 * j + 2], f.v[4 * j + 3]};
 }
 // A 16-row tile of a fragment-order operand, n_rows rows of it present.  Lanes of absent rows point past the descriptor's
-// end: such a load returns zeros and asks memory for nothing.  A descriptor's offsets count from its base and end at kEnd, so
-// a K that is known (at most KMAX) has one descriptor for all blocks, any other K (KMAX 0) one whose base is the block.
-template <int ES, int KMAX> struct FragRows {
-    static constexpr int kEnd = 0x40000000;  // offsets of present rows are below, of absent ones above
-    static_assert((long long)KMAX * 16 * ES <= kEnd, "16 rows of K elements behind one descriptor");
-    char* base;
+// end: such a load returns zeros and asks memory for nothing.  K up to kMaxK; beyond, 16 rows have more bytes than the
+// descriptor's offsets reach, and a product takes tiles of more rows (choose_tile).
+template <int ES> struct FragRows {
+    static constexpr int kEnd = 0x40000000;  // offsets of present rows are below (16 rows of K elements), of absent ones above
+    static constexpr int kMaxK = kEnd / (16 * ES);
+    __amdgpu_buffer_rsrc_t rsrc;
     int voff;  // this lane's bytes within a 1 KB piece
-    __device__ __forceinline__ FragRows(const char* tile, int n_rows, int lane)
-        : base(const_cast<char*>(tile)), voff((lane & 15) < n_rows ? lane * 16 : 0x7ffffff0) {}
-    // piece j of block kb
-    __device__ __forceinline__ u32x4 piece(int kb, int j) const {
-        const size_t at = frag_block_off<ES>(0, kb, 0);
-        const auto rsrc = __builtin_amdgcn_make_buffer_rsrc(KMAX > 0 ? base : base + at, 0, kEnd, 0x20000);
-        return __builtin_amdgcn_raw_buffer_load_b128(rsrc, voff, (KMAX > 0 ? (int)at : 0) + 1024 * j, 0);
-    }
+    __device__ __forceinline__ FragRows(const char* base, int n_rows, int lane)
+        : rsrc(__builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(base), 0, kEnd, 0x20000)),
+          voff((lane & 15) < n_rows ? lane * 16 : 0x7ffffff0) {}
     __device__ __forceinline__ void load(int kb, Frag16<bf16_t>& f) const {
-        f.lo = __builtin_bit_cast(bf16x8, piece(kb, 0));
-        f.hi = __builtin_bit_cast(bf16x8, piece(kb, 1));
+        f.lo = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(rsrc, voff, kb * 2048, 0));
+        f.hi = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(rsrc, voff, kb * 2048 + 1024, 0));
     }
     __device__ __forceinline__ void load(int kb, Frag16<float>& f) const {
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-            const f32x4 v = __builtin_bit_cast(f32x4, piece(kb, j));
+            const f32x4 v = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rsrc, voff, kb * 4096 + 1024 * j, 0));
             f.v[4 * j + 0] = v[0]; f.v[4 * j + 1] = v[1]; f.v[4 * j + 2] = v[2]; f.v[4 * j + 3] = v[3];
         }
     }

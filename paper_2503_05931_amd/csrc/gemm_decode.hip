@@ -87,7 +87,7 @@ __device__ __forceinline__ void gemm_decode_body(const GemmArgs& a, const int bx
     Frag16<T> af[D][MT], wf[D][NT];
     // 16-row tiles: A through a buffer descriptor; the lanes of rows from M on ask beyond its end and get zeros without a
     // request.  One row, 24 layers: 97.5 -> 95.3 ms for three utterances of 40 tokens.  Larger tiles have few such rows.
-    const FragRows<ES, NB * NW * 64> rows(A + frag_block_off<ES>(m0 >> 4, 0, K), M - m0, lane);
+    const FragRows<ES> rows(A + frag_block_off<ES>(m0 >> 4, 0, K), M - m0, lane);
     auto fetch_w = [&](int slot, int i) {
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt) wf[slot][nt] = WNT ? load_frag_nt(wblk(nt, i), lane) : load_frag(wblk(nt, i), lane);
@@ -562,7 +562,7 @@ static TileId choose_tile(const GemmArgs& a, int n_out) {
     static_assert(PRO != PRO_LN || sizeof(T) == 4, "the fused LayerNorm is a float32-mode path");
     for (int c = 0; c < n_cands; ++c) {
         const int bm = 16 * cands[c].mt, bn = 16 * cands[c].nt;
-        if (a.N % bn != 0) continue;
+        if (a.N % bn != 0 || (cands[c].mt == 1 && a.K > FragRows<sizeof(T)>::kMaxK)) continue;
         const long wgs = (long)((a.M + bm - 1) / bm) * (n_out / bn);
         double cost;
         if constexpr (sizeof(T) == 4) {

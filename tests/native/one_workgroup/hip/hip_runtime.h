@@ -13,8 +13,11 @@ struct int4 { int x, y, z, w; };
 struct float2 { float x, y; };
 typedef int hipError_t;
 typedef void* hipStream_t;
-enum { hipSuccess = 0, hipErrorInvalidValue = 1 };
+enum { hipSuccess = 0, hipErrorInvalidValue = 1, hipErrorInvalidDevice, hipDeviceAttributeMultiprocessorCount, hipFuncAttributeMaxDynamicSharedMemorySize };
 static inline hipError_t hipGetLastError() { return hipSuccess; }
+template <typename... A> static inline hipError_t hipGetDevice(A...) { return hipErrorInvalidDevice; }
+template <typename... A> static inline hipError_t hipDeviceGetAttribute(A...) { return hipErrorInvalidDevice; }
+template <typename... A> static inline hipError_t hipFuncSetAttribute(A...) { return hipErrorInvalidDevice; }
 #define hipLaunchKernelGGL(...) ((void)0)
 
 #define __global__
@@ -44,6 +47,8 @@ template <typename... A> static inline Unreached2 unreached2(A...) { __builtin_t
 #define __builtin_amdgcn_permlane32_swap unreached2
 #define __builtin_amdgcn_update_dpp unreached
 #define __builtin_amdgcn_mov_dpp unreached
+#define __builtin_amdgcn_readfirstlane unreached
+#define __builtin_amdgcn_sched_barrier(x) ((void)0)
 struct Anything { template <typename T> operator T() const { __builtin_trap(); } };
 template <typename... A> static inline Anything anything(A...) { __builtin_trap(); }
 #define __builtin_amdgcn_mfma_f32_16x16x32_bf16 anything
@@ -54,6 +59,7 @@ template <typename... A> static inline Anything anything(A...) { __builtin_trap(
 // read, twice: zeros where lane and wavefront offset together are past the descriptor's end.
 typedef unsigned int BufferVec __attribute__((ext_vector_type(4)));
 struct Buffer { const char* base; uint64_t bytes; };
+#define __amdgpu_buffer_rsrc_t Buffer
 static inline Buffer __builtin_amdgcn_make_buffer_rsrc(const char* base, short, int bytes, int) { return Buffer{base, (uint32_t)bytes}; }
 static inline BufferVec __builtin_amdgcn_raw_buffer_load_b128(Buffer b, int voff, int soff, int) {
     const uint64_t off = (uint64_t)(uint32_t)voff + (uint32_t)soff, at = off + 16 <= b.bytes ? (uint64_t)(b.base + off) : 0;

@@ -1,6 +1,6 @@
 """The addresses of a 16-row tile's loads (CPU): csrc/gemm_common.h compiled for the host, with a buffer load that returns
-the address it would read.  Widths of a row up to 2^27 elements, of which 16 rows have more bytes than a descriptor's
-offsets reach."""
+the address it would read, for rows up to the widest of which a descriptor's offsets reach 16; products over wider ones take
+other tiles."""
 import os
 import subprocess
 
