@@ -386,8 +386,8 @@ __global__ __launch_bounds__(64 * NW, sizeof(KV) <= 2 ? 4 : 1) void attn_decode_
 
 template <typename T, typename KV, int LPK, int DH, bool SELF>
 static void launch_nw(const AttnArgs& a, dim3 grid, hipStream_t s) {
-    if (a.wavefronts == 4) hipLaunchKernelGGL((attn_decode_kernel<T, KV, LPK, DH, SELF, 4>), grid, dim3(256), 0, s, a);
-    else hipLaunchKernelGGL((attn_decode_kernel<T, KV, LPK, DH, SELF, 8>), grid, dim3(512), 0, s, a);
+    if (a.wavefronts == 8) hipLaunchKernelGGL((attn_decode_kernel<T, KV, LPK, DH, SELF, 8>), grid, dim3(512), 0, s, a);
+    else hipLaunchKernelGGL((attn_decode_kernel<T, KV, LPK, DH, SELF, 4>), grid, dim3(256), 0, s, a);
 }
 template <typename T, typename KV, int LPK, bool SELF>
 static hipError_t launch_kv(const AttnArgs& a, dim3 grid, hipStream_t s) {
