@@ -12,6 +12,7 @@ SOURCES = ("aed_api.hip", "gemm_decode.hip", "gemm_tiled.hip", "gemm_dma.hip", "
 HOST_SOURCES = ("batching.cpp",)
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
+         "-mllvm", "-amdgpu-kernarg-preload-count=14",
          "-Wall", "-Wno-unused-function", "-Wno-pass-failed"]
 
 

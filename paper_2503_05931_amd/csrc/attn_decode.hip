@@ -29,6 +29,7 @@
 // workgroups, and the last workgroup of a (sequence, head) to finish
 // combines the partial (max, sum, values) triples in chunk order.
 #include "common.h"
+#include "kernel_tail.h"
 #include "kernels.h"
 
 namespace aed {
@@ -102,13 +103,29 @@ template <int LPK> __device__ __forceinline__ float keys_max(float v) {
 // LPK: lanes that share a key row.
 // (bfloat16 and 8-bit caches: at least four wavefronts per SIMD, i.e. at most 128 registers, so that two workgroups of
 // eight wavefronts share a CU -- with one, half as many bytes are in flight and the launch takes a quarter longer)
+template <bool SELF> struct AttnFields {
+    template <typename F> __host__ __device__ __forceinline__ static void fields(AttnArgs& a, F f) {
+        f(a.out); f(a.part); f(a.counters);
+        if constexpr (!SELF) { f(a.q_stats); f(a.q_mu_hat); f(a.q_c1); f(a.q_c2); }
+        f(a.scale_log2e); f(a.max_chunks);
+        if constexpr (!SELF) { f(a.q_eps); f(a.q_stat_tiles); f(a.q_rms); }
+    }
+    static constexpr int words() { return SELF ? 8 : 19; }
+};
+
+// list: page table (self) or work items (cross); rows: its pages a sequence (self) or the caches' frames a head (cross);
+// chunk_heads: AttnArgs::chunk | n_heads.  The rest in a tail (kernel_tail.h).
 template <typename T, typename KV, int LPK, int DH, bool SELF, int NW>
-__global__ __launch_bounds__(64 * NW, sizeof(KV) <= 2 ? 4 : 1) void attn_decode_kernel(AttnArgs a) {
+__global__ __launch_bounds__(64 * NW, sizeof(KV) <= 2 ? 4 : 1) void attn_decode_kernel(const void* K, const void* V, const float* Q, const void* list,
+                                                                                         const int* finished, const int* seq_len, int rows,
+                                                                                         int chunk_heads, ArgTail) {
+    TailLoad<AttnFields<SELF>, AttnArgs> rest(tail_at(56));
+    AttnArgs a;
     constexpr int EPL = DH / LPK;   // head_dim elements per lane
     constexpr int KPI = 64 / LPK;   // keys per load instruction
     constexpr int NI = 16 / KPI;    // load instructions per 16-key block
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, r = lane % LPK, g = lane / LPK;
-    const int h = blockIdx.x, H = a.n_heads;
+    const int h = blockIdx.x, H = chunk_heads & 63, chunk = chunk_heads & ~63;
 
     // Work item.  Cross-attention: from the host-built list (cut sequences, then longest first, so the long sequences
     // start early and the short ones fill the tail); the item carries everything needed to address
@@ -122,20 +139,25 @@ __global__ __launch_bounds__(64 * NW, sizeof(KV) <= 2 ? 4 : 1) void attn_decode_
     int last_page = 0;
     if constexpr (SELF) {
         b = blockIdx.y;
-        const int fin = a.finished[b];
-        const int total = a.seq_len[b] + 1;
-        pages = a.page_table + (size_t)b * a.max_pages + (blockIdx.z * a.chunk >> 4);
-        last_page = a.max_pages - 1 - (int)(blockIdx.z * a.chunk >> 4);
+        int fin = finished[b], len = seq_len[b];
+        pages = static_cast<const int*>(list) + (size_t)b * rows + (blockIdx.z * chunk >> 4);
+        last_page = rows - 1 - (int)(blockIdx.z * chunk >> 4);
         page0 = pages[min(wave, last_page)];
         page1 = pages[min(wave + NW, last_page)];
+        // one trip for all of them: left to itself the compiler asks for the others behind the exit
+        settle(fin); settle(len); settle(page0); settle(page1);
+        rest.get(a);
         if (fin) return;
-        n_chunks = (total + a.chunk - 1) / a.chunk;
+        const int total = len + 1;
         chunk_idx = blockIdx.z;
-        if (chunk_idx >= n_chunks) return;
-        start = chunk_idx * a.chunk;
-        n = min(a.chunk, total - start);
+        start = chunk_idx * chunk;
+        if (start >= total) return;
+        n = min(chunk, total - start);
+        n_chunks = total <= chunk ? 1 : (total + chunk - 1) / chunk;
     } else {
-        const int4 it = a.items[blockIdx.y];
+        int4 it = static_cast<const int4*>(list)[blockIdx.y];
+        settle(it.x); settle(it.y); settle(it.z); settle(it.w);  // the same
+        rest.get(a);
         b = it.x;
         if (b < 0) return;  // the sequence has finished (kItemOff)
         start = it.y & 0xFFFF;
@@ -156,7 +178,7 @@ __global__ __launch_bounds__(64 * NW, sizeof(KV) <= 2 ? 4 : 1) void attn_decode_
     bool q_fix = false;
     {
         const size_t qo = (size_t)b * H * DH + h * DH + r * EPL;
-        load_f32<EPL>(a.q + qo, q);
+        load_f32<EPL>(Q + qo, q);
         if constexpr (!SELF) {
             q_fix = a.q_stats != nullptr;
             // Only the first wavefront fetches what finishes the query (the row's tile statistics -- at most 64, one
@@ -178,8 +200,8 @@ __global__ __launch_bounds__(64 * NW, sizeof(KV) <= 2 ? 4 : 1) void attn_decode_
     auto fetch = [&](int kb, int page, Raw* kf, Raw* vf) {
         size_t at;
         if constexpr (SELF) at = ((size_t)page * H + h) * BLOCK;
-        else at = ((size_t)h * a.t_cap + row0) * ROW + (size_t)kb * BLOCK;
-        const char *kp = static_cast<const char*>(a.K) + at, *vp = static_cast<const char*>(a.V) + at;
+        else at = ((size_t)h * rows + row0) * ROW + (size_t)kb * BLOCK;
+        const char *kp = static_cast<const char*>(K) + at, *vp = static_cast<const char*>(V) + at;
         const int last = n - 1 - kb * 16;
 #pragma unroll
         for (int i = 0; i < NI; ++i) {
@@ -386,8 +408,15 @@ __global__ __launch_bounds__(64 * NW, sizeof(KV) <= 2 ? 4 : 1) void attn_decode_
 
 template <typename T, typename KV, int LPK, int DH, bool SELF>
 static void launch_nw(const AttnArgs& a, dim3 grid, hipStream_t s) {
-    if (a.wavefronts == 8) hipLaunchKernelGGL((attn_decode_kernel<T, KV, LPK, DH, SELF, 8>), grid, dim3(512), 0, s, a);
-    else hipLaunchKernelGGL((attn_decode_kernel<T, KV, LPK, DH, SELF, 4>), grid, dim3(256), 0, s, a);
+    const void* list = SELF ? static_cast<const void*>(a.page_table) : a.items;
+    const int rows = SELF ? a.max_pages : (int)a.t_cap, chunk_heads = (SELF ? a.chunk : 0) | a.n_heads;
+    const ArgTail tail = make_tail<AttnFields<SELF>>(a);
+    if (a.wavefronts == 8)
+        hipLaunchKernelGGL((attn_decode_kernel<T, KV, LPK, DH, SELF, 8>), grid, dim3(512), 0, s, a.K, a.V, a.q, list, a.finished, a.seq_len,
+                           rows, chunk_heads, tail);
+    else
+        hipLaunchKernelGGL((attn_decode_kernel<T, KV, LPK, DH, SELF, 4>), grid, dim3(256), 0, s, a.K, a.V, a.q, list, a.finished, a.seq_len,
+                           rows, chunk_heads, tail);
 }
 template <typename T, typename KV, int LPK, bool SELF>
 static hipError_t launch_kv(const AttnArgs& a, dim3 grid, hipStream_t s) {
@@ -406,14 +435,14 @@ static hipError_t launch_dh(const AttnArgs& a, dim3 grid, hipStream_t s) {
 }
 
 hipError_t launch_attn_self(Dtype dt, const AttnArgs& a, hipStream_t s) {
-    if (a.chunk < 64 || a.chunk % 64 != 0 || a.n_chunks_max < 1 || a.n_chunks_max > a.max_chunks || (a.wavefronts != 4 && a.wavefronts != 8))
+    if (a.chunk < 64 || a.chunk % 64 != 0 || a.n_heads < 1 || a.n_heads > 63 || a.n_chunks_max < 1 || a.n_chunks_max > a.max_chunks || (a.wavefronts != 4 && a.wavefronts != 8))
         return hipErrorInvalidValue;
     dim3 grid(a.n_heads, a.batch, a.n_chunks_max);
     return dt == kBF16 ? launch_dh<bf16_t, true>(a, grid, s) : launch_dh<float, true>(a, grid, s);
 }
 
 hipError_t launch_attn_cross(Dtype dt, const AttnArgs& a, hipStream_t s) {
-    if (!a.items || a.n_items < 1 || (a.wavefronts != 4 && a.wavefronts != 8)) return hipErrorInvalidValue;
+    if (!a.items || a.n_items < 1 || a.n_heads < 1 || a.n_heads > 63 || a.t_cap > INT_MAX || (a.wavefronts != 4 && a.wavefronts != 8)) return hipErrorInvalidValue;
     dim3 grid(a.n_heads, a.n_items);
     return dt == kBF16 ? launch_dh<bf16_t, false>(a, grid, s) : launch_dh<float, false>(a, grid, s);
 }

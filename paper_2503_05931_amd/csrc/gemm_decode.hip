@@ -30,13 +30,42 @@
 #include "common.h"
 #include "device_once.h"
 #include "gemm_common.h"
+#include "kernel_tail.h"
 #include "kernels.h"
 
 namespace aed {
 
 constexpr int kMaxLnBlocks = 4;  // PRO_LN: K <= 4 waves * 4 blocks * 64 = 1024
 
-// One output tile (column tile bx, row tile by) of the product described by a.
+// What a workgroup needs before its first request to memory: leading scalar arguments; the rest comes in a tail (kernel_tail.h)
+struct GemmStart { const void *W, *A; const float2* stats_in; int M, K, stat_tiles; };
+template <int PRO, int EPI> struct GemmFields {
+    static constexpr bool LNS = PRO == PRO_LNS, LN = PRO == PRO_LN, RS = EPI == EPI_RESID_S, QKV = EPI == EPI_QKV, CKV = EPI == EPI_CROSSKV,
+                          ADD = EPI == EPI_F32 && PRO == PRO_T;
+    template <typename F> __host__ __device__ __forceinline__ static void fields(GemmArgs& a, F f) {
+        f(a.out);
+        if constexpr (LNS) { f(a.ln_c1); f(a.ln_c2); f(a.mu_hat_out); } else f(a.bias);
+        if constexpr (LNS && QKV) { f(a.out2); f(a.raw_bias); }
+        if constexpr (LNS || RS) f(a.mu_hat_in);
+        if constexpr (LN) { f(a.ln_g); f(a.ln_b); }
+        if constexpr (RS) { f(a.shadow_out); f(a.stats_out); }
+        if constexpr (ADD) f(a.addend);
+        if constexpr (QKV) { f(a.kv_slot); f(a.k_pool); f(a.v_pool); }
+        if constexpr (CKV) { f(a.out_row_map); f(a.kc); f(a.vc); f(a.t_cap); }
+        f(a.N);
+        if constexpr (LNS || LN) { f(a.rms); f(a.ln_eps); }
+        if constexpr (LNS && QKV) f(a.n_raw);
+        if constexpr (RS) f(a.stat_tiles);
+        if constexpr (QKV) f(a.n_heads);
+        if constexpr (QKV || CKV) { f(a.kv_fp8); f(a.head_dim); f(a.d_model); }
+    }
+    static constexpr int words() {
+        return 2 * (1 + (LNS ? 3 : 1) + (LNS && QKV ? 2 : 0) + (LNS || RS) + 2 * LN + 2 * RS + ADD + 3 * QKV + 4 * CKV) +
+               1 + (LNS || LN ? 2 : 0) + (LNS && QKV) + RS + QKV + (QKV || CKV ? 3 : 0);
+    }
+};
+
+// One output tile (column tile bx, row tile by) of the product described by st and tail.
 // WNT: W is loaded with the non-temporal hint (GemmArgs::w_nt)
 // NB: 64-wide k blocks per wavefront, K = 64 NW NB, known at compile time; 0: any K.  NW: wavefronts
 //
@@ -50,17 +79,19 @@ constexpr int kMaxLnBlocks = 4;  // PRO_LN: K <= 4 waves * 4 blocks * 64 = 1024
 //  * with NB known the k loop is straight-line code and each block is waited for on its own; with a run-time k loop
 //    around conditional loads the compiler waited for the blocks just requested.
 template <typename T, int PRO, int EPI, int MT, int NT, bool WNT, int NB, int NW = 4>
-__device__ __forceinline__ void gemm_decode_body(const GemmArgs& a, const int bx, const int by) {
+__device__ __forceinline__ void gemm_decode_body(const GemmStart& st, TailPtr tail, const int bx, const int by) {
+    TailLoad<GemmFields<PRO, EPI>, GemmArgs> rest(tail);
+    GemmArgs a;
     constexpr int BM = 16 * MT, BN = 16 * NT;
     constexpr int EP = (MT * NT * 64 + 255) / 256;  // output 4-vectors per thread in the epilogue
     constexpr int ES = sizeof(T);
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, r = lane & 15, g = lane >> 4;
     const int m0 = by * BM, n0 = bx * BN;
-    const int K = NB > 0 ? NB * NW * 64 : a.K, M = a.M;
+    const int K = NB > 0 ? NB * NW * 64 : st.K, M = st.M;
     static_assert(NW == 4 || (PRO == PRO_T && MT * NT == 1 && NB > 0), "more wavefronts: one 16 x 16 tile, known K");
     const int nblk = K >> 8;  // 64-wide k blocks per wavefront
-    const char* __restrict__ W = static_cast<const char*>(a.W);
-    const char* __restrict__ A = static_cast<const char*>(a.A);
+    const char* __restrict__ W = static_cast<const char*>(st.W);
+    const char* __restrict__ A = static_cast<const char*>(st.A);
 
     constexpr bool LNS = PRO == PRO_LNS;         // LayerNorm folded around the product (see kernels.h)
     constexpr bool RS = EPI == EPI_RESID_S;      // residual update that also writes shadow and statistics
@@ -118,8 +149,8 @@ __device__ __forceinline__ void gemm_decode_body(const GemmArgs& a, const int bx
     auto fetch_stats = [&]() {
 #pragma unroll
         for (int p = 0; p < SP; ++p) {
-            const f32x4* sp = reinterpret_cast<const f32x4*>(a.stats_in + (size_t)(m0 + 16 * p + (tid >> 4)) * a.stat_tiles +
-                                                             min(4 * (tid & 15), a.stat_tiles - 4));
+            const f32x4* sp = reinterpret_cast<const f32x4*>(st.stats_in + (size_t)(m0 + 16 * p + (tid >> 4)) * st.stat_tiles +
+                                                             min(4 * (tid & 15), st.stat_tiles - 4));
             sv[p][0] = sp[0];
             sv[p][1] = sp[1];
         }
@@ -127,10 +158,10 @@ __device__ __forceinline__ void gemm_decode_body(const GemmArgs& a, const int bx
     auto combine_stats = [&]() {
 #pragma unroll
         for (int p = 0; p < SP; ++p) {
-            float2 st = combine_tile_stats(sv[p][0], sv[p][1], 4 * (tid & 15) < a.stat_tiles, a.stat_tiles);
-            const float rstd = fold_norm(a.rms, (float)K, a.ln_eps, st.y, st.x);
+            float2 rs = combine_tile_stats(sv[p][0], sv[p][1], 4 * (tid & 15) < st.stat_tiles, st.stat_tiles);
+            const float rstd = fold_norm(a.rms, (float)K, a.ln_eps, rs.y, rs.x);
             if ((tid & 15) == 0) {
-                red[0][0][16 * p + (tid >> 4)] = st.x;
+                red[0][0][16 * p + (tid >> 4)] = rs.x;
                 red[1][0][16 * p + (tid >> 4)] = rstd;
             }
         }
@@ -156,11 +187,11 @@ __device__ __forceinline__ void gemm_decode_body(const GemmArgs& a, const int bx
         __builtin_amdgcn_sched_barrier(0);
     };
 
-    // ---- epilogue operands (they do not depend on the product), requested behind the stream's first blocks (in front of
+    // ---- epilogue operands (they do not depend on the product), requested behind the stream's first blocks (behind
     // the rows and weights where the fused LayerNorm reads them, which has no ring)
-    const T* __restrict__ bias = static_cast<const T*>(a.bias);
+    const T* __restrict__ bias = nullptr;
     // columns from n_raw on are not normalised here (n_raw is a multiple of every tile width: uniform)
-    const bool raw = LNS && a.n_raw > 0 && n0 >= a.n_raw;
+    bool raw = false;
     // kept as loaded (null bias / addend: whatever W holds there) until the epilogue uses them: a conversion or a select
     // here would wait for everything requested so far
     f32x4 e_bias[EP], e_res[EP], e_aux[EP];  // e_aux: c1 (LNS)
@@ -171,13 +202,20 @@ __device__ __forceinline__ void gemm_decode_body(const GemmArgs& a, const int bx
     auto tile_row = [&](int t, int l) { return m0 + (t / NT) * 16 + (l & 15); };
     auto tile_col = [&](int t, int l) { return n0 + (t % NT) * 16 + (l >> 4) * 4; };
     auto request_epilogue = [&]() {
+        rest.get(a);
+        bias = static_cast<const T*>(a.bias);
+        if constexpr (LNS && EPI == EPI_QKV) raw = a.n_raw > 0 && n0 >= a.n_raw;
 #pragma unroll
         for (int j = 0; j < EP; ++j) {
             const int t = MT * NT < 4 ? min(wave, MT * NT - 1) : wave + 4 * j;
             const int m = tile_row(t, lane), n = tile_col(t, lane), mc = min(m, M - 1);
             if constexpr (LNS) {
-                e_bias[j] = load_global<f32x4>(raw ? a.raw_bias + (n - a.n_raw) : a.ln_c2 + n);
-                e_aux[j] = *reinterpret_cast<const f32x4*>(a.ln_c1 + (raw ? n - a.n_raw : n));
+                const float* c2 = a.ln_c2 + n;
+                if constexpr (EPI == EPI_QKV) c2 = raw ? a.raw_bias + (n - a.n_raw) : c2;
+                e_bias[j] = load_global<f32x4>(c2);
+                int n_c1 = n;
+                if constexpr (EPI == EPI_QKV) n_c1 = raw ? n - a.n_raw : n;
+                e_aux[j] = *reinterpret_cast<const f32x4*>(a.ln_c1 + n_c1);
             } else {
                 e_rbias[j] = load_global<typename Raw4<T>::type>(bias ? static_cast<const void*>(bias + n) : W);
             }
@@ -189,19 +227,12 @@ __device__ __forceinline__ void gemm_decode_body(const GemmArgs& a, const int bx
             if constexpr (EPI == EPI_CROSSKV) e_slot[j] = load_global<int>(a.out_row_map ? static_cast<const void*>(a.out_row_map + mc) : W);
         }
         if constexpr (LNS && !ST_FIRST) fetch_stats();
-        // the arguments that only the epilogue uses, into scalar registers now: read there, they are one more round trip
-        asm volatile("" ::"s"(a.out));
-        if constexpr (RS) asm volatile("" ::"s"(a.shadow_out), "s"(a.stats_out), "s"(a.N), "s"(a.stat_tiles));
-        if constexpr (EPI == EPI_QKV) asm volatile("" ::"s"(a.k_pool), "s"(a.v_pool), "s"(a.kv_fp8), "s"(a.n_heads), "s"(a.head_dim), "s"(a.d_model));
-        if constexpr (EPI == EPI_CROSSKV) asm volatile("" ::"s"(a.kc), "s"(a.vc), "s"(a.kv_fp8), "s"(a.t_cap), "s"(a.head_dim), "s"(a.d_model));
-        if constexpr (LNS) asm volatile("" ::"s"(a.mu_hat_out), "s"(a.rms), "s"(a.ln_eps), "s"(a.stat_tiles), "s"(a.N));
         __builtin_amdgcn_sched_barrier(0);
         if constexpr (LNS && ST_FIRST) combine_stats();
     };
 
     if constexpr (PRO == PRO_LN) {
-        request_epilogue();
-        const char* __restrict__ X = static_cast<const char*>(a.A);
+        const char* __restrict__ X = A;
         constexpr int NL = NB > 0 ? NB : kMaxLnBlocks;
         Frag16<float> xs[MT][NL];
         // the rows first (their statistics are needed first), then the weights; with NB known no block is conditional
@@ -219,6 +250,8 @@ __device__ __forceinline__ void gemm_decode_body(const GemmArgs& a, const int bx
             if (NB > 0 || i < nblk)
 #pragma unroll
                 for (int nt = 0; nt < NT; ++nt) wl[nt][i] = WNT ? load_frag_nt(wblk(nt, i), lane) : load_frag(wblk(nt, i), lane);
+        __builtin_amdgcn_sched_barrier(0);
+        request_epilogue();
         // LayerNorm gain/shift for this lane's k values, fetched before the statistics are known
         const T* __restrict__ G = static_cast<const T*>(a.ln_g);
         const T* __restrict__ Bt = static_cast<const T*>(a.ln_b);
@@ -357,12 +390,13 @@ __device__ __forceinline__ void gemm_decode_body(const GemmArgs& a, const int bx
         if constexpr (LNS) {
             const int rl = m - m0;
             const float mu = red[0][0][rl], rstd = red[1][0][rl], shift = mu - e_mu[j];
-            if (raw) {
-                // a product that belongs to a later normalisation of these rows (kernels.h, "merged products"):
-                // the bare sums (plus raw_bias) go to out2, whoever reads them finishes them
-                store4(a.out2 + (size_t)m * (a.N - a.n_raw) + (n - a.n_raw), s + e_bias[j]);
-                continue;
-            }
+            if constexpr (EPI == EPI_QKV)
+                if (raw) {
+                    // a product that belongs to a later normalisation of these rows (kernels.h, "merged products"):
+                    // the bare sums (plus raw_bias) go to out2, whoever reads them finishes them
+                    store4(a.out2 + (size_t)m * (a.N - a.n_raw) + (n - a.n_raw), s + e_bias[j]);
+                    continue;
+                }
             s = (s - shift * e_aux[j]) * rstd + e_bias[j];
             gemm_epilogue<T, EPI>(a, m, n, s, e_res[j], e_slot[j]);
             if (n == 0 && a.mu_hat_out) a.mu_hat_out[m] = mu;  // the layer's residual updates shift their shadows by this
@@ -385,23 +419,20 @@ __device__ __forceinline__ void gemm_decode_body(const GemmArgs& a, const int bx
 }
 
 template <typename T, int PRO, int EPI, int MT, int NT, bool WNT, int NB, int NW = 4>
-__global__ __launch_bounds__(64 * NW) void gemm_decode_kernel(GemmArgs a) {
-    gemm_decode_body<T, PRO, EPI, MT, NT, WNT, NB, NW>(a, blockIdx.x, blockIdx.y);
+__global__ __launch_bounds__(64 * NW) void gemm_decode_kernel(const void* W, const void* A, const float2* stats_in, int M, int K,
+                                                              int stat_tiles, ArgTail) {
+    gemm_decode_body<T, PRO, EPI, MT, NT, WNT, NB, NW>(GemmStart{W, A, stats_in, M, K, stat_tiles}, tail_at(40), blockIdx.x, blockIdx.y);
 }
 
-// Two products of the same operand in one launch: the first n0 workgroups are the tiles of a0 (a residual update,
-// EPI_RESID_S), the others the tiles of a1 (kernels.h, "merged products").  Neither reads what the other writes.
+// Two products of the same operand A in one launch: the workgroups of z = 0 are the tiles of a0 (a residual update,
+// EPI_RESID_S), those of z = 1 the tiles of a1 (kernels.h, "merged products").  Neither reads what the other writes.
 template <typename T, int MT, int NT, int EPI1, bool WNT, int NB>
-__global__ __launch_bounds__(256) void gemm_decode_pair_kernel(GemmArgs a0, GemmArgs a1, int n0) {
-    int b = blockIdx.x;
-    if (b < n0) {
-        const int nx = a0.N / (16 * NT);
-        gemm_decode_body<T, PRO_T, EPI_RESID_S, MT, NT, WNT, NB>(a0, b % nx, b / nx);
-    } else {
-        b -= n0;
-        const int nx = a1.N / (16 * NT);
-        gemm_decode_body<T, PRO_T, EPI1, MT, NT, WNT, NB>(a1, b % nx, b / nx);
-    }
+__global__ __launch_bounds__(256) void gemm_decode_pair_kernel(const void* W0, const void* W1, const void* A, int M, int K,
+                                                               ArgTail, ArgTail) {
+    if (blockIdx.z == 0)
+        gemm_decode_body<T, PRO_T, EPI_RESID_S, MT, NT, WNT, NB>(GemmStart{W0, A, nullptr, M, K, 0}, tail_at(32), blockIdx.x, blockIdx.y);
+    else
+        gemm_decode_body<T, PRO_T, EPI1, MT, NT, WNT, NB>(GemmStart{W1, A, nullptr, M, K, 0}, tail_at(32 + sizeof(ArgTail)), blockIdx.x, blockIdx.y);
 }
 
 // ---------------------------------------------------------------- LayerNorm to fragment order
@@ -486,6 +517,7 @@ template <typename T, int PRO, int EPI, int MT, int NT, int NB>
 static hipError_t launch_nb(const GemmArgs& a, hipStream_t s) {
     dim3 grid(a.N / (16 * NT), (a.M + 16 * MT - 1) / (16 * MT));
     const long wgs = (long)grid.x * grid.y;
+    const ArgTail tail = make_tail<GemmFields<PRO, EPI>>(a);
     unsigned lds = 0;
     // K = 4096 on 16 x 16 tiles: eight wavefronts have a workgroup's whole share of both operands under way at once, four half
     // of it.  24 layers: batch 64, 131 positions 124.1 -> 122.9 ms, batch 16, 24 positions 22.6 -> 22.3; one row 84.6 and 84.7;
@@ -493,8 +525,8 @@ static hipError_t launch_nb(const GemmArgs& a, hipStream_t s) {
     // 10.26 ms with eight, 10.99 with sixteen: four.)
     if constexpr (sizeof(T) == 2 && PRO == PRO_T && MT * NT == 1 && NB == 16) {
         if (wgs <= kCus) {
-            if (hint_w(a, wgs, grid.y)) hipLaunchKernelGGL((gemm_decode_kernel<T, PRO, EPI, MT, NT, true, NB / 2, 8>), grid, dim3(512), 0, s, a);
-            else hipLaunchKernelGGL((gemm_decode_kernel<T, PRO, EPI, MT, NT, false, NB / 2, 8>), grid, dim3(512), 0, s, a);
+            if (hint_w(a, wgs, grid.y)) hipLaunchKernelGGL((gemm_decode_kernel<T, PRO, EPI, MT, NT, true, NB / 2, 8>), grid, dim3(512), 0, s, a.W, a.A, a.stats_in, a.M, a.K, a.stat_tiles, tail);
+            else hipLaunchKernelGGL((gemm_decode_kernel<T, PRO, EPI, MT, NT, false, NB / 2, 8>), grid, dim3(512), 0, s, a.W, a.A, a.stats_in, a.M, a.K, a.stat_tiles, tail);
             return hipGetLastError();
         }
     }
@@ -511,11 +543,11 @@ static hipError_t launch_nb(const GemmArgs& a, hipStream_t s) {
     }
     if constexpr (sizeof(T) == 2) {  // float32 W is loaded the same way in both
         if (hint_w(a, wgs, grid.y)) {
-            hipLaunchKernelGGL((gemm_decode_kernel<T, PRO, EPI, MT, NT, true, NB>), grid, dim3(256), 0, s, a);
+            hipLaunchKernelGGL((gemm_decode_kernel<T, PRO, EPI, MT, NT, true, NB>), grid, dim3(256), 0, s, a.W, a.A, a.stats_in, a.M, a.K, a.stat_tiles, tail);
             return hipGetLastError();
         }
     }
-    hipLaunchKernelGGL((gemm_decode_kernel<T, PRO, EPI, MT, NT, false, NB>), grid, dim3(256), lds, s, a);
+    hipLaunchKernelGGL((gemm_decode_kernel<T, PRO, EPI, MT, NT, false, NB>), grid, dim3(256), lds, s, a.W, a.A, a.stats_in, a.M, a.K, a.stat_tiles, tail);
     return hipGetLastError();
 }
 // K = 1024 and, for the second FFN product, K = 4096 are unrolled; every other K runs the loop
@@ -666,11 +698,12 @@ static hipError_t launch_f32(GemmPro pro, GemmEpi epi, const GemmArgs& a0, hipSt
 template <typename T, int MT, int NT, int EPI1, int NB>
 static hipError_t launch_pair_nb(const GemmArgs& a0, const GemmArgs& a1, hipStream_t s) {
     const int rows = (a0.M + 16 * MT - 1) / (16 * MT);
-    const int n0 = a0.N / (16 * NT) * rows, n1 = a1.N / (16 * NT) * rows;
-    if (hint_w(a0, n0 + n1, rows))
-        hipLaunchKernelGGL((gemm_decode_pair_kernel<T, MT, NT, EPI1, true, NB>), dim3(n0 + n1), dim3(256), 0, s, a0, a1, n0);
+    const dim3 grid(a0.N / (16 * NT), rows, 2);
+    const ArgTail t0 = make_tail<GemmFields<PRO_T, EPI_RESID_S>>(a0), t1 = make_tail<GemmFields<PRO_T, EPI1>>(a1);
+    if (hint_w(a0, 2l * grid.x * rows, rows))
+        hipLaunchKernelGGL((gemm_decode_pair_kernel<T, MT, NT, EPI1, true, NB>), grid, dim3(256), 0, s, a0.W, a1.W, a0.A, a0.M, a0.K, t0, t1);
     else
-        hipLaunchKernelGGL((gemm_decode_pair_kernel<T, MT, NT, EPI1, false, NB>), dim3(n0 + n1), dim3(256), 0, s, a0, a1, n0);
+        hipLaunchKernelGGL((gemm_decode_pair_kernel<T, MT, NT, EPI1, false, NB>), grid, dim3(256), 0, s, a0.W, a1.W, a0.A, a0.M, a0.K, t0, t1);
     return hipGetLastError();
 }
 template <typename T, int EPI1, int NB>
@@ -684,7 +717,7 @@ static hipError_t launch_pair_tiles(const GemmArgs& a0, const GemmArgs& a1, hipS
 }
 
 hipError_t launch_gemm_pair(Dtype dt, const GemmArgs& a0, GemmEpi epi1, const GemmArgs& a1, hipStream_t s) {
-    if (dt != kBF16 || a0.M < 1 || a0.M != a1.M || a0.M > 256 || a0.K % 256 != 0 || a1.K != a0.K || a1.N != a0.N || a0.N % 32 != 0)
+    if (dt != kBF16 || a0.M < 1 || a0.M != a1.M || a0.M > 256 || a0.K % 256 != 0 || a1.A != a0.A || a1.K != a0.K || a1.N != a0.N || a0.N % 32 != 0)
         return hipErrorInvalidValue;
     if (!a0.stats_out || !a0.mu_hat_in || !a0.shadow_out || !stat_tiles_ok(a0.stat_tiles) || a0.stat_tiles * 16 != a0.N)
         return hipErrorInvalidValue;
