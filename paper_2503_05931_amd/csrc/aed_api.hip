@@ -79,6 +79,7 @@ struct Layout {
     int act_rows;  // rows the activation buffers hold: max(max_batch, prefill_rows)
     size_t k_pool, v_pool, kc, vc, w_frag, enc_frag;
     size_t w_merge, merge_vec;  // bfloat16 mode: the merged products' matrices and bias vectors (kernels.h)
+    size_t wk_t, q_frames, u_frames;  // cross-attention over the frames (frames_possible)
     size_t total;
     int max_pages, n_pages, max_items;
     size_t pool_layer_elems, cross_layer_elems;
@@ -110,6 +111,11 @@ aed_status check_config(const aed_config* c, std::string& err) {
     if (c->kv_fp8 != 0 && c->kv_fp8 != 1) return bad("kv_fp8 must be 0 or 1");
     if (c->kv_fp8 && c->dtype != 1) return unsup("8-bit key / value caches go with bfloat16 models only");
     return AED_OK;
+}
+
+// A decoder some of whose batches cross-attention may take over the frames (frames_attention)
+bool frames_possible(const aed_config* c) {
+    return c->dtype == 1 && !c->kv_fp8 && c->d_model == 1024 && c->head_dim == 128 && c->max_batch >= kFramesMinBatch;
 }
 
 void make_layout(const aed_config* c, Layout* L) {
@@ -178,6 +184,10 @@ void make_layout(const aed_config* c, Layout* L) {
     // merged products (bfloat16 mode): per layer Wcq.g . Wo and the vector Wcq.g . bo
     L->w_merge = take(c->dtype == 1 ? (size_t)c->n_layers * (d * d) * e : 0);
     L->merge_vec = take(c->dtype == 1 ? (size_t)c->n_layers * d * 4 : 0);
+    const bool frames = frames_possible(c);
+    L->wk_t = take(frames ? (size_t)c->n_layers * d * d * e : 0);
+    L->q_frames = take(frames ? Ba * 16 * d * e : 0);
+    L->u_frames = take(frames ? Ba * 16 * d * e : 0);
     // the batch's encoder states in fragment order (A operand of the cross K/V GEMMs), whole 256-row tiles
     L->enc_frag = take(align_up((size_t)c->max_total_enc_frames, 256) * d * e);
     L->total = off;
@@ -194,9 +204,13 @@ constexpr double kResidentLayerBytes = 220e6;
 // What the launches of a captured step or prompt pass depend on; everything else they read from device memory.
 struct GraphKey {
     int batch = -1, n_items = 0, cross_wavefronts = 0, self_chunk = 0, self_nchunks = 0, prompt_len = 0, max_new = 0;
+    int positions = 1;
+    bool frames = false;
     bool operator==(const GraphKey& o) const {
         return batch == o.batch && n_items == o.n_items && cross_wavefronts == o.cross_wavefronts &&
-               self_chunk == o.self_chunk && self_nchunks == o.self_nchunks && prompt_len == o.prompt_len && max_new == o.max_new;
+               self_chunk == o.self_chunk && self_nchunks == o.self_nchunks && prompt_len == o.prompt_len && max_new == o.max_new &&
+               frames == o.frames &&
+               positions == o.positions;
     }
 };
 // The graphs of the last few shapes (24 layers, three utterances of other lengths in turn 87.5 -> 84.9 ms); the one unused for
@@ -248,6 +262,8 @@ struct aed_decoder {
     int self_chunk = 64, self_nchunks = 1;
     int cross_keys = 0;                         // most keys of a cross-attention item
     bool cross_long = false, cross_even = false;  // see attn_wavefronts
+    int positions = 1;                            // of every sequence in the rows: a prompt pass's, else one
+    bool frames = false;                          // this batch's cross-attention reads the frames (attn_frames.hip)
     int last_prompt_len = 0, last_max_new = 0;
     long long total_enc = 0;
     const void* last_enc = nullptr;
@@ -367,6 +383,7 @@ void ln_consumer(const aed_decoder* d, GemmArgs& g, const float* c1, const float
 // Small batches in bfloat16 mode: the cross-attention query product is split over the QKV launch and the launch of the
 // self-attention output projection (kernels.h, "merged products"): one launch fewer per layer.
 constexpr int kMergeMaxRows = 256;
+static_assert(kMergeMaxRows < kFramesMinBatch, "cross-attention over the frames does not finish a merged query product");
 bool merged_products(const aed_decoder* d) { return folded_ln(d) && d->batch <= kMergeMaxRows; }
 
 hipError_t k_ln_qkv(aed_decoder* d, int l) {
@@ -480,7 +497,27 @@ int cross_wavefronts(const aed_decoder* d) {
     return attn_wavefronts((long long)d->n_items * H, (long long)d->batch * H, (int)d->kv_esz, d->cross_keys, d->cross_long, d->cross_even);
 }
 
+hipError_t k_cross_frames(aed_decoder* d, int l) {
+    FramesArgs a;
+    const size_t dm = d->cfg.d_model;
+    a.q = d->act_at<float>(d->lay.q);
+    a.wk_t = d->ws + d->lay.wk_t + (size_t)l * dm * dm * d->esz;
+    a.wv = static_cast<const char*>(d->fw[l].w_ckv) + dm * dm * d->esz;
+    a.bv = d->layers[l].b_ckv ? static_cast<const char*>(d->layers[l].b_ckv) + dm * d->esz : nullptr;
+    a.frames = d->ws + d->lay.enc_frag;
+    a.q_frames = d->ws + d->lay.q_frames;
+    a.u_frames = d->ws + d->lay.u_frames;
+    a.out = d->act + d->lay.attn_out;
+    a.items = d->at<int4>(d->lay.items);
+    a.n_items = d->n_items;
+    a.rows = d->batch;
+    a.positions = d->positions;
+    a.scale_log2e = (float)(1.4426950408889634 / sqrt((double)d->cfg.head_dim));
+    return launch_attn_frames(a, d->stream);
+}
+
 hipError_t k_cross_attn(aed_decoder* d, int l) {
+    if (d->frames) return k_cross_frames(d, l);
     AttnArgs a = attn_base(d);
     a.K = d->ws + d->lay.kc + (size_t)l * d->lay.cross_layer_elems * d->kv_esz;
     a.V = d->ws + d->lay.vc + (size_t)l * d->lay.cross_layer_elems * d->kv_esz;
@@ -635,7 +672,8 @@ aed_status start_batch(aed_decoder* d, const void* enc, bool padded, int t_max, 
     std::vector<int> off(batch + 1, 0);
     for (int b = 0; b < batch; ++b) off[b + 1] = off[b] + enc_lens[b];
     const int longest = *std::max_element(enc_lens, enc_lens + batch);
-    const CrossCut cut = cross_cut(total, longest, batch, d->cfg.n_heads, (int)d->kv_esz);
+    const bool frames = frames_possible(&d->cfg) && frames_attention(total, longest, batch);
+    const CrossCut cut = frames ? kWhole : cross_cut(total, longest, batch, d->cfg.n_heads, (int)d->kv_esz);
     std::vector<int4> items;
     for (int b = 0; b < batch; ++b) add_items(items, b, enc_lens[b], off[b], cut);
     if ((int)items.size() > d->lay.max_items) return fail(d, AED_ECAPACITY, "cross-attention work list overflow");
@@ -654,6 +692,7 @@ aed_status start_batch(aed_decoder* d, const void* enc, bool padded, int t_max, 
     for (const int4& it : items) d->cross_keys = std::max(d->cross_keys, it.z & 0xFFFF);
     d->cross_long = total >= (long long)kLongItem * d->n_items;
     d->cross_even = even_lengths(total, longest, batch);
+    d->frames = frames;
     d->items_host = items;
     d->total_enc = total;
     d->last_enc = enc;
@@ -684,6 +723,7 @@ GraphKey graph_key(const aed_decoder* d) {
     key.batch = d->batch; key.n_items = d->n_items;
     key.cross_wavefronts = cross_wavefronts(d);
     key.self_chunk = d->self_chunk; key.self_nchunks = d->self_nchunks;
+    key.frames = d->frames; key.positions = d->positions;
     return key;
 }
 // Capture what enqueue launches into a launch graph; a graph of the same shape that the pool still has is taken.
@@ -763,6 +803,7 @@ aed_status prefill_pass(aed_decoder* d, const std::vector<int>& prompt_host, int
     d->lay.items = saved.v_items;
     d->batch = R;
     d->n_items = (int)items.size();
+    d->positions = np;
     d->self_chunk = std::max(64, (p1 + 63) / 64 * 64);  // a position sees at most p1 keys: one work item each
     d->self_nchunks = 1;
     const StateArgs st = d->state_args(0, 0);
@@ -788,6 +829,7 @@ aed_status prefill_pass(aed_decoder* d, const std::vector<int>& prompt_host, int
     d->lay = saved;
     d->batch = saved_batch;
     d->n_items = saved_items;
+    d->positions = 1;
     d->self_chunk = saved_chunk;
     d->self_nchunks = saved_nch;
     if (grc != AED_OK) return grc;
@@ -931,6 +973,13 @@ aed_status aed_decoder_create(const aed_config* cfg, const aed_weights* weights,
             v += dm;
         }
         if (e != hipSuccess) return cleanup(e, "forming the merged products' matrices");
+    }
+    if (frames_possible(cfg)) {
+        const size_t bytes = (size_t)cfg->d_model * cfg->d_model * d->esz;
+        e = hipSuccess;
+        for (int l = 0; l < cfg->n_layers && e == hipSuccess; ++l)
+            e = launch_frames_weight(d->layers[l].w_ckv, d->ws + L.wk_t + l * bytes, d->stream);
+        if (e != hipSuccess) return cleanup(e, "transposing the cross-attention key matrices");
     }
     if ((e = hipStreamSynchronize(d->stream)) != hipSuccess) return cleanup(e, "hipStreamSynchronize");
     *out = d;
@@ -1208,6 +1257,7 @@ extern "C" aed_status aed_greedy_decode_queue(aed_decoder* d, const void* enc_st
     }
     d->cross_long = in_slots >= (long long)kLongItem * d->n_items;
     d->cross_even = even_lengths(in_slots, longest, B);
+    d->frames = false;  // the slots' frames are kept as keys and values only
     d->total_enc = -1;
     d->page_table.assign((size_t)B * MP, 0);
     for (int b = 0; b < B; ++b)

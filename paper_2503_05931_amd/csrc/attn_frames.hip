@@ -1,0 +1,377 @@
+// Cross-attention over the encoder frames themselves (bfloat16, d_model 1024, 8 heads of 128), for large batches.
+//
+// With keys K = E Wk^T + bk and values V = E Wv^T + bv of the frames E, a head's scores and output are
+//   q . K_t        = (Wk^T q) . E_t + q . bk       (the last term is the same for every frame: the softmax drops it)
+//   sum_t p_t V_t  = Wv (sum_t p_t E_t) + bv       (the p_t add up to 1)
+// so a step can read the frames, 2 KB each and the same for all heads, where it reads 4 KB of keys and values per frame.  At
+// large batches that stream is what bounds cross-attention; the price are two small products per row and layer
+// (frames_query_kernel, frames_out_kernel) and 8 times the multiplications of one query row, which go to the matrix cores.
+//
+// The matrix cores take bfloat16.  The frames are bfloat16; what is float32 goes in as two of them, high and low
+// (x = hi + lo up to 2^-17): the 8 heads' queries Wk^T q fill the 16 columns of a 16 x 16 tile as 8 high and 8 low parts, the
+// probabilities likewise, and the frames' weighted sums enter the last product as high and low parts.  Sums are float32.
+// The rounding of keys and values to bfloat16 is gone.
+#include <algorithm>
+
+#include "common.h"
+#include "gemm_common.h"
+#include "kernels.h"
+#include "device_once.h"
+
+namespace aed {
+
+namespace {
+
+constexpr int kD = 1024, kH = 8, kDh = 128, kCols = 16;
+constexpr int kSlab = 16384, kPart = 8192;               // bytes of LDS: a wavefront's part of 32 frames; all wavefronts' partial scores of a position
+constexpr int kNonTemporal = 2;  // a buffer load's nt bit: the frames are read once and should not push other data out of the caches
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+
+__device__ __forceinline__ void split(float x, bf16_t& hi, bf16_t& lo) {
+    hi = (bf16_t)x;
+    lo = (bf16_t)(x - (float)hi);
+}
+__device__ __forceinline__ float other_half(float v) { return dpp_mov<0x128>(v); }  // of lane l ^ 8 (row_ror 8)
+
+}  // namespace
+
+// ---------------------------------------------------------------- Wk^T q
+// Q[b][c][k], 16 x 1024 a row: for head h the high (c = h) and low (c = 8 + h) parts of scale * sum_e q[b][128 h + e] Wk[128 h + e][k].
+// A workgroup takes 32 rows, 256 of the 1024 columns k and one head; the products are short (K = 128), so what counts is the
+// 32 KB a row that are written: row i = 4 g + e of a wavefront's weight tile t is column 16 g + 4 t + e of its 64, so that a lane
+// ends with 16 consecutive columns and four lanes write whole lines.  Heads are dealt to the XCDs (x = 8 heads).
+// Wt: per head [1024][128] in fragment order (launch_frames_weight).
+__global__ __launch_bounds__(256) void frames_query_kernel(const float* __restrict__ q, const char* __restrict__ Wt, bf16_t* __restrict__ Q,
+                                                           int M, float scale) {
+    constexpr int MT = 2, NT = 4;
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, r = lane & 15, g = lane >> 4;
+    const int h = blockIdx.x, n0 = blockIdx.y * 256 + wave * 64, m0 = blockIdx.z * 32;
+    Frag16<bf16_t> w[NT][2];
+    const char* wp = Wt + (size_t)h * kD * kDh * 2 + frag_block_off<2>((n0 >> 4) + (r >> 2), 0, kDh);
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+        for (int kb = 0; kb < 2; ++kb) w[nt][kb] = load_frag(reinterpret_cast<const bf16_t*>(wp + kb * 2048), g * 16 + 4 * nt + (r & 3));
+    f32x4 acc[MT][NT];
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) {
+        const float* p = q + (size_t)min(m0 + mt * 16 + r, M - 1) * kD + h * kDh + g * 16;
+        float x[2][16];
+        load_f32<16>(p, x[0]);
+        load_f32<16>(p + 64, x[1]);
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) acc[mt][nt] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int kb = 0; kb < 2; ++kb) {
+            Frag16<bf16_t> hi, lo;
+            float res[16];
+            pack_frag(x[kb], hi);
+            unpack_frag(hi, res);
+#pragma unroll
+            for (int e = 0; e < 16; ++e) res[e] = x[kb][e] - res[e];
+            pack_frag(res, lo);
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt) {
+                mma(acc[mt][nt], w[nt][kb], hi);
+                mma(acc[mt][nt], w[nt][kb], lo);
+            }
+        }
+    }
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) {
+        const int m = m0 + mt * 16 + r;
+        if (m >= M) continue;
+        bf16_t* out = Q + ((size_t)m * kCols + h) * kD + n0 + 16 * g;
+        bf16x8 hi[2], lo[2];
+#pragma unroll
+        for (int e = 0; e < 16; ++e) {
+            bf16_t a, b;
+            split(acc[mt][e >> 2][e & 3] * scale, a, b);
+            hi[e >> 3][e & 7] = a;
+            lo[e >> 3][e & 7] = b;
+        }
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            *reinterpret_cast<bf16x8*>(out + 8 * j) = hi[j];
+            *reinterpret_cast<bf16x8*>(out + kH * kD + 8 * j) = lo[j];
+        }
+    }
+}
+
+// ---------------------------------------------------------------- attention
+// One workgroup per sequence, all heads.  U[b][c][k]: high and low parts of head h's sum_t p_t E[t][k], as Q.
+// Bound by memory: a sequence's frames are read once, 2 KB each.  A step takes 32 frames; wavefront w has columns 256 w .. + 255
+// of them:
+//  * frames come from fragment order (the encoder states as the cross K/V product reads them, so a sequence's first and last
+//    16-row tile may hold its neighbours' frames, which are masked) straight into registers: rows of a tile = frames, the
+//    operand of the score product, Q's part staying in registers (32 of them);
+//  * the four wavefronts' partial scores are added through LDS (the step's only barrier; two buffers), every wavefront then
+//    has all 32 frames' scores and takes the softmax itself: lane (c, g) holds frames 4 g .. 4 g + 3 of either tile for column c,
+//    which is the operand layout of the second product;
+//  * the second product contracts over frames, so it needs them transposed: each wavefront puts its part into LDS and reads it
+//    back through the transposing read (ds_read_b64_tr_b16: 16 lanes read four 32-byte rows, lane i gets column i).  The
+//    16-byte pieces of odd k are stored 8 rows on, so that the four rows' pieces lie in different banks;
+//  * the next step's frames are requested as soon as this step's are in LDS: 64 KB a workgroup, 128 KB a CU under way.
+// A prompt pass has several positions of a sequence: NQ of them are taken at once, with one reading of the frames.
+template <int NQ>
+__global__ __launch_bounds__(256, NQ == 1 ? 2 : 1) void attn_frames_kernel(const void* E, const void* Q, const int4* items, void* U, int first, int stride) {
+    extern __shared__ __align__(16) char lds[];
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, r = lane & 15, g = lane >> 4;
+    const int4 it = items[blockIdx.x * stride + first];
+    int b[NQ];
+    b[0] = it.x;
+#pragma unroll
+    for (int i = 1; i < NQ; ++i) b[i] = items[blockIdx.x * stride + first + i].x;
+    if (b[0] < 0) return;  // the sequence has finished (kItemOff)
+    const int n = it.z & 0xFFFF, skip = it.w & 15;
+    const int tiles = (skip + n + 15) >> 4, steps = (tiles + 1) >> 1;
+    const char* src = static_cast<const char*>(E) + (size_t)(it.w >> 4) * (kD * 32) + wave * 8192;
+    char* slab = lds + wave * kSlab;
+    char* part = lds + 4 * kSlab;
+
+    bf16x8 x[2][8];  // a step's two tiles, 8 pieces of 16 bytes a lane each
+    // through a buffer descriptor: of a tile past the end, requested all the same so that no request sits behind a branch, the
+    // lanes ask beyond the descriptor's end and nothing is fetched (65535 frames are 128 MB)
+    const __amdgpu_buffer_rsrc_t rsrc = __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(src), 0, 0x40000000, 0x20000);
+    auto fetch = [&](int s, int u) {
+        const int t = 2 * s + u, at = t < tiles ? t * (kD * 32) : 0, voff = t < tiles ? lane * 16 : 0x7ffffff0;
+#pragma unroll
+        for (int j = 0; j < 8; ++j)
+            x[u][j] = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(rsrc, voff, at + j * 1024, kNonTemporal));
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    bf16x8 qf[NQ][8];
+#pragma unroll
+    for (int i = 0; i < NQ; ++i) {
+        const bf16_t* p = static_cast<const bf16_t*>(Q) + ((size_t)b[i] * kCols + r) * kD + wave * 256 + 16 * g;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) qf[i][j] = *reinterpret_cast<const bf16x8*>(p + (j >> 1) * 64 + (j & 1) * 8);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    fetch(0, 0);
+    fetch(0, 1);
+    f32x4 acc[NQ][16];  // lane (c, g): columns 16 t + 4 g .. + 3 of this wavefront's 256, for column c of Q
+#pragma unroll
+    for (int i = 0; i < NQ; ++i)
+#pragma unroll
+        for (int t = 0; t < 16; ++t) acc[i][t] = f32x4{0.f, 0.f, 0.f, 0.f};
+    float m_run[NQ], l_run[NQ];
+#pragma unroll
+    for (int i = 0; i < NQ; ++i) { m_run[i] = -INFINITY; l_run[i] = 0.f; }
+    char* const put = slab + g * 256;
+    const int key = 4 * g + (r >> 2), odd = (r >> 1) & 1;
+    const auto get = (__attribute__((address_space(3))) char*)slab + odd * 1024 + ((key ^ (8 * odd)) * 16) + (r & 1) * 8;
+
+#pragma unroll 1
+    for (int s = 0; s < steps; ++s) {
+        char* const buf = part + (s & 1) * (NQ * kPart);
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            // scores of this wavefront's columns
+            f32x4 sc[NQ];
+#pragma unroll
+            for (int i = 0; i < NQ; ++i) sc[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int j = 0; j < 8; ++j)
+#pragma unroll
+                for (int i = 0; i < NQ; ++i) sc[i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(x[u][j], qf[i][j], sc[i], 0, 0, 0);
+            // the frames into LDS, zeros in the place of those that are not this sequence's (their probability is 0, but 0
+            // times an infinity is not); then the next step's are requested
+            const int t = (2 * s + u) * 16 + r - skip;
+            const bool own = t >= 0 && t < n;
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                u32x4 v = __builtin_bit_cast(u32x4, x[u][j]);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) v[e] = own ? v[e] : 0u;
+                *reinterpret_cast<u32x4*>(put + u * 8192 + j * 1024 + (r ^ (8 * (j & 1))) * 16) = v;
+            }
+            fetch(s + 1, u);
+#pragma unroll
+            for (int i = 0; i < NQ; ++i) *reinterpret_cast<f32x4*>(buf + i * kPart + wave * 2048 + u * 1024 + lane * 16) = sc[i];
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        lds_barrier();
+        bf16x8 pf[NQ];
+        float alpha[NQ];
+#pragma unroll
+        for (int i = 0; i < NQ; ++i) {
+            // all columns' scores; high and low part of the query together
+            float p[2][4], m_blk = -INFINITY;
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                f32x4 v[4];
+#pragma unroll
+                for (int w = 0; w < 4; ++w) v[w] = *reinterpret_cast<const f32x4*>(buf + i * kPart + w * 2048 + u * 1024 + lane * 16);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    float d = (v[0][e] + v[1][e]) + (v[2][e] + v[3][e]);
+                    d += other_half(d);
+                    const int t = (2 * s + u) * 16 + 4 * g + e - skip;
+                    p[u][e] = t >= 0 && t < n ? d : -INFINITY;
+                    m_blk = fmaxf(m_blk, p[u][e]);
+                }
+            }
+            m_blk = rows4_max(m_blk);
+            const float m_new = fmaxf(m_run[i], m_blk);
+            alpha[i] = __builtin_amdgcn_exp2f(m_run[i] - m_new);  // first step: exp2(-inf) = 0
+            m_run[i] = m_new;
+            l_run[i] *= alpha[i];
+#pragma unroll
+            for (int u = 0; u < 2; ++u)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const float v = __builtin_amdgcn_exp2f(p[u][e] - m_new);
+                    l_run[i] += v;
+                    bf16_t hi, lo;
+                    split(v, hi, lo);
+                    pf[i][4 * u + e] = r < kH ? hi : lo;
+                }
+        }
+#pragma unroll
+        for (int t = 0; t < 16; ++t) {
+            // frames 4 g .. 4 g + 3 of both tiles, column 16 t + r: block t / 4 of the wavefront's part, its quarter t % 4
+            u32x2 a[2];
+#pragma unroll
+            for (int u = 0; u < 2; ++u)
+                a[u] = __builtin_bit_cast(u32x2, __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+                    (__attribute__((address_space(3))) s16x4*)(get + u * 8192 + (t >> 2) * 2048 + (t & 3) * 256)));
+            const bf16x8 e8 = __builtin_bit_cast(bf16x8, u32x4{a[0][0], a[0][1], a[1][0], a[1][1]});
+#pragma unroll
+            for (int i = 0; i < NQ; ++i) acc[i][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(e8, pf[i], acc[i][t] * alpha[i], 0, 0, 0);
+        }
+    }
+#pragma unroll
+    for (int i = 0; i < NQ; ++i) {
+        const float inv = 1.0f / rows4_sum(l_run[i]);
+        bf16_t* out = static_cast<bf16_t*>(U) + ((size_t)b[i] * kCols + r) * kD + wave * 256 + 4 * g;
+#pragma unroll
+        for (int t = 0; t < 16; ++t) {
+            bf16x4 o;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const float v = (acc[i][t][e] + other_half(acc[i][t][e])) * inv;
+                bf16_t hi, lo;
+                split(v, hi, lo);
+                o[e] = r < kH ? hi : lo;
+            }
+            *reinterpret_cast<bf16x4*>(out + t * 16) = o;
+        }
+    }
+}
+
+template <int NQ> static hipError_t launch_positions(const FramesArgs& a, int first, hipStream_t s) {
+    constexpr int kLds = 4 * kSlab + 2 * NQ * kPart;
+    static DeviceOnce once;
+    const hipError_t e = once.run([] {
+        return hipFuncSetAttribute(reinterpret_cast<const void*>(&attn_frames_kernel<NQ>), hipFuncAttributeMaxDynamicSharedMemorySize, kLds);
+    });
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(attn_frames_kernel<NQ>, dim3(a.n_items / a.positions), dim3(256), kLds, s, a.frames, a.q_frames, a.items, a.u_frames, first,
+                       a.positions);
+    return hipGetLastError();
+}
+
+// ---------------------------------------------------------------- Wv u + bv
+// out[b][128 h + e] (fragment order) = sum_k Wv[128 h + e][k] (U[b][h][k] + U[b][8 + h][k]) + bv.  A workgroup takes 32 rows and half a
+// head's 128 columns; the wavefronts split k and their sums meet in LDS, as in gemm_decode.hip.  U is read as it lies: 16 rows of
+// 64 contiguous bytes an instruction.
+__global__ __launch_bounds__(256, 2) void frames_out_kernel(const bf16_t* __restrict__ U, const char* __restrict__ Wv, const bf16_t* __restrict__ bias,
+                                                            char* __restrict__ out, int M) {
+    constexpr int MT = 2, NT = 4;
+    __shared__ f32x4 sum[4][MT * NT][64];
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, r = lane & 15, g = lane >> 4;
+    const int h = blockIdx.x, n0 = blockIdx.y * 64, m0 = blockIdx.z * 32;
+    f32x4 acc[MT][NT];
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) acc[mt][nt] = f32x4{0.f, 0.f, 0.f, 0.f};
+    // a 64-wide block's piece p is k = 32 p + 8 g .. + 7 here, which in the weights' fragment order is quarter 2 p + g / 2, half g % 2
+    bf16x8 af[2][MT][2][2], wf[2][NT][2];
+    auto fetch = [&](int slot, int i) {
+        const int kb = wave * 4 + i;
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+            for (int p = 0; p < 2; ++p)
+                wf[slot][nt][p] = *reinterpret_cast<const bf16x8*>(Wv + frag_block_off<2>(((h * kDh + n0) >> 4) + nt, kb, kD) + (g & 1) * 1024 +
+                                                                   ((2 * p + (g >> 1)) * 16 + r) * 16);
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+            for (int part = 0; part < 2; ++part)
+#pragma unroll
+                for (int p = 0; p < 2; ++p)
+                    af[slot][mt][part][p] = *reinterpret_cast<const bf16x8*>(
+                        U + ((size_t)min(m0 + mt * 16 + r, M - 1) * kCols + part * kH + h) * kD + kb * 64 + p * 32 + g * 8);
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    fetch(0, 0);
+    fetch(1, 1);
+    f32x4 bv[2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) bv[i] = bias ? load4(bias + h * kDh + n0 + ((wave + 4 * i) % NT) * 16 + 4 * g) : f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+#pragma unroll
+        for (int p = 0; p < 2; ++p)
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+                for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+                    for (int part = 0; part < 2; ++part)
+                        acc[mt][nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[i & 1][nt][p], af[i & 1][mt][part][p], acc[mt][nt], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+        if (i + 2 < 4) fetch(i & 1, i + 2);
+    }
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) sum[wave][mt * NT + nt][lane] = acc[mt][nt];
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const int t = wave + 4 * i, m = m0 + (t / NT) * 16 + r;
+        const f32x4 v = (sum[0][t][lane] + sum[1][t][lane]) + (sum[2][t][lane] + sum[3][t][lane]) + bv[i];
+        if (m < M) store4(reinterpret_cast<bf16_t*>(out + frag_elem_off<2>(m, h * kDh + n0 + (t % NT) * 16 + 4 * g, kD)), v);
+    }
+}
+
+// ---------------------------------------------------------------- Wk^T, once at create
+// dst: per head [1024][128] in fragment order <- W [1024 (h, e)][1024 k] row-major; one thread per 16-byte piece
+__global__ __launch_bounds__(256) void frames_weight_kernel(const bf16_t* __restrict__ W, char* __restrict__ dst) {
+    const int i = blockIdx.x * 256 + threadIdx.x, k = i & (kD - 1), e0 = (i >> 10) * 8;  // neighbours read neighbouring k
+    if (e0 >= kD) return;
+    bf16x8 v;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) v[e] = W[(size_t)(e0 + e) * kD + k];
+    const int h = e0 / kDh;
+    *reinterpret_cast<bf16x8*>(dst + (size_t)h * kD * kDh * 2 + frag_elem_off<2>(k, e0 % kDh, kDh)) = v;
+}
+
+hipError_t launch_frames_weight(const void* W, void* dst, hipStream_t s) {
+    hipLaunchKernelGGL(frames_weight_kernel, dim3(kD * kD / 8 / 256), dim3(256), 0, s, static_cast<const bf16_t*>(W), static_cast<char*>(dst));
+    return hipGetLastError();
+}
+
+hipError_t launch_attn_frames(const FramesArgs& a, hipStream_t s) {
+    if (a.rows < 1 || a.n_items < 1 || !a.items || a.positions < 1 || a.n_items % a.positions != 0) return hipErrorInvalidValue;
+    hipError_t e;
+    const unsigned rows = (a.rows + 31) / 32;
+    hipLaunchKernelGGL(frames_query_kernel, dim3(kH, kD / 256, rows), dim3(256), 0, s, a.q, static_cast<const char*>(a.wk_t), static_cast<bf16_t*>(a.q_frames),
+                       a.rows, a.scale_log2e);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+    for (int at = 0; at < a.positions;) {
+        const int nq = std::min(2, a.positions - at);  // of three the sums do not fit the registers
+        e = nq == 2 ? launch_positions<2>(a, at, s) : launch_positions<1>(a, at, s);
+        if (e != hipSuccess) return e;
+        at += nq;
+    }
+    hipLaunchKernelGGL(frames_out_kernel, dim3(kH, kDh / 64, rows), dim3(256), 0, s, static_cast<const bf16_t*>(a.u_frames), static_cast<const char*>(a.wv),
+                       static_cast<const bf16_t*>(a.bv), static_cast<char*>(a.out), a.rows);
+    return hipGetLastError();
+}
+
+}  // namespace aed

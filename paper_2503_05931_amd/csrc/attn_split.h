@@ -41,11 +41,11 @@ struct CrossCut { int longest, piece; };
 //    11.0 and 8.9; from batch 128 on little is cut (15.8 and 15.6).  Float32 is cut from 7/8 of two CUs' share up to kF32TwoRounds,
 //    of one beyond: log-normal lengths, from two / one CU's share, batch 80 25.1 and 18.9, 96 26.9 and 21.0, 128 30.3 and 28.7; 12 to
 //    500 keys, batch 40 22.4 and 25.9, 48 22.0 and 27.6, 64 29.9 and 32.3, 80 37.1 and 37.1.
+constexpr CrossCut kWhole{INT_MAX, INT_MAX};
 inline CrossCut cross_cut(long long total_keys, int longest_len, int batch, int n_heads, int kv_bytes) {
-    const CrossCut whole{INT_MAX, INT_MAX};
     const long long wgs = (long long)batch * n_heads;
-    if (batch > 4096) return whole;
-    if (kv_bytes <= 2 && wgs > 48 * kv_bytes && wgs <= 256 && even_lengths(total_keys, longest_len, batch)) return whole;
+    if (batch > 4096) return kWhole;
+    if (kv_bytes <= 2 && wgs > 48 * kv_bytes && wgs <= 256 && even_lengths(total_keys, longest_len, batch)) return kWhole;
     const long long share = total_keys * n_heads / 256 * (kv_bytes == 4 ? 2 : 1);
     CrossCut c;
     c.longest = (int)std::min<long long>(std::max<long long>(192, (kv_bytes == 4 && wgs > kF32TwoRounds ? share / 2 : share) * 7 / 8), INT_MAX);
@@ -77,6 +77,21 @@ inline void order_items(std::vector<int4>& items) {
         const bool pc = p.z >> 16 > 1, qc = q.z >> 16 > 1;
         return pc != qc ? pc : (p.z & 0xFFFF) > (q.z & 0xFFFF);
     });
+}
+
+// Whether cross-attention of a batch reads the frames (attn_frames.hip) instead of keys and values.
+// Half the bytes per frame against two products per sequence and what a workgroup needs to begin and end; one workgroup per
+// sequence, so the longest must not take longer than all together.  A whole step of 4 layers, us, keys and values / frames:
+//   sequences         260           300           400           512           600           700          1000
+//   100 frames     306   385    321   402    366   434    410   468    511   612    547   625    686    771
+//   200            375   427    395   451    464   488    534   531    658   695    715   724    928    905
+//   300            436   483    466   499    559   543    659   604    802   788    884   826   1168   1046
+//   500            564   572    614   594    751   646    906   733   1090   953   1217  1006   1644   1284
+//   12 to 500      414   459    433   485    518   538    617   593    748   734    814   774   1088    982
+//   log-normal     324   460    340   476    396   513    438   546    556   661    599   680    765    819
+constexpr int kFramesMinBatch = 288;
+inline bool frames_attention(long long total_keys, int longest_len, int batch) {
+    return batch >= kFramesMinBatch && total_keys >= 140ll * batch + 60000 && 256ll * longest_len <= total_keys;
 }
 
 // Wavefronts per workgroup, 4 or 8, of a launch of wgs workgroups over caches of kv_bytes an element.  What counts is that

@@ -154,6 +154,25 @@ struct AttnArgs {
 hipError_t launch_attn_self(Dtype dt, const AttnArgs& a, hipStream_t s);
 hipError_t launch_attn_cross(Dtype dt, const AttnArgs& a, hipStream_t s);
 
+// Cross-attention over the encoder frames themselves (attn_frames.hip): bfloat16, d_model 1024, 8 heads of 128
+struct FramesArgs {
+    const float* q;       // [rows, 1024]
+    const void* wk_t;     // this layer's Wk^T (launch_frames_weight)
+    const void* wv;       // rows [1024, 2048) of w_ckv in fragment order
+    const void* bv;       // [1024] or null
+    const void* frames;   // [.., 1024] in fragment order
+    void* q_frames;       // [rows][16][1024] scratch
+    void* u_frames;       // [rows][16][1024] scratch
+    void* out;            // [rows, 1024] in fragment order
+    const int4* items;    // AttnArgs::items, whole sequences
+    int n_items, rows;
+    int positions;        // items i * positions .. + positions - 1 are positions of one sequence (a prompt pass; else 1)
+    float scale_log2e;
+};
+hipError_t launch_attn_frames(const FramesArgs& a, hipStream_t s);
+// dst (2 MB): W [1024, 1024] row-major, transposed per head for launch_attn_frames
+hipError_t launch_frames_weight(const void* W, void* dst, hipStream_t s);
+
 // ---------------------------------------------------------------- small kernels
 struct StateArgs {
     int* seq_len; int* n_gen; int* finished; int* cur_tok; int* limit; int* n_finished;

@@ -1,0 +1,62 @@
+"""Cross-attention over the encoder frames (csrc/attn_frames.hip; bfloat16, d_model 1024, 8 heads of 128, large batches of long
+sequences): sequences that begin and end anywhere in a 16-row tile, steps of 32 frames with and without a
+remainder, one frame, padding rows of prompt passes, neighbours with infinite frames.  Logits against the oracle on
+sampled sequences, tolerance of the other bfloat16 tests."""
+import numpy as np
+import pytest
+
+from paper_2503_05931_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+EDGES = [1, 15, 16, 17, 31, 32, 33, 48, 63, 64, 65, 2, 127, 500]
+
+
+def workload(batch, seed, norm_type=0, prompt_len=1, max_new=3):
+    lens = (EDGES + [330 + (37 * i) % 171 for i in range(batch)])[:batch]
+    lens[-1] = 5  # the last rows of the last tile are past the end
+    cfg = W.DecoderConfig(name="frames", n_layers=2, d_model=1024, n_heads=8, head_dim=128, d_ffn=256, vocab=192, dtype="bf16",
+                          batch=batch, prompt_len=prompt_len, max_new=max_new, norm_type=norm_type)
+    assert batch >= 288 and sum(lens) >= 140 * batch + 60000 and 256 * max(lens) <= sum(lens)  # such a batch is taken over the frames
+    return W.custom(cfg, lens, seed, random_ln=True)
+
+
+@pytest.mark.parametrize("batch,norm_type", [(385, 0), (400, 1), (513, 0)])
+def test_frames_attention(oracle, batch, norm_type):
+    import torch
+    from tests import gpu_util as G
+    assert torch.cuda.is_available()
+    wl = workload(batch, batch, norm_type)
+    rows = list(range(len(EDGES))) + [batch // 2, batch - 2, batch - 1]
+    toks = np.random.default_rng(batch).integers(0, wl.cfg.vocab, size=(batch, 2)).astype(np.int32)
+    sub = wl.subset(rows)
+    ref = oracle.Model(wl.cfg, wl.weights).decode_forced(sub.enc, sub.enc_lens, toks[rows])
+    dec = G.make_decoder(wl)
+    glog, gids = G.forced_logits_gpu(dec, wl, toks, rows)
+    err, _ = G.check_forced(ref, glog, gids, G.TOL["bf16"])
+    print(f"batch {batch}: max |dlogit| = {err:.2e}")
+    # frames of another sequence count for nothing, whatever they hold
+    at = int(wl.enc_lens[:3].sum())
+    wl.enc[at:at + wl.enc_lens[3]] = np.inf
+    glog2, _ = G.forced_logits_gpu(dec, wl, toks, rows)
+    others = [i for i, b in enumerate(rows) if b != 3]
+    assert (glog2[others] == glog[others]).all()
+    dec.close()
+
+
+def test_frames_attention_in_a_prompt_pass():
+    import torch
+    from tests import gpu_util as G
+    batch, P = 389, 4
+    wl = workload(batch, 5, prompt_len=P, max_new=4)
+    kv = {}
+    for rows in (0, 2 * 400):  # position by position; two positions in a pass, each with 11 padding rows
+        dec = G.make_decoder(wl, prefill_rows=rows)
+        dec.aed_cross_kv_precompute(dec.to_device(wl.enc), wl.enc_lens)
+        toks, lens = dec.aed_greedy_decode(torch.from_numpy(wl.prompt).to(dec.device), 4)
+        assert (lens.cpu().numpy() == 4).all()
+        kv[rows] = [dec.aed_read_self_kv(1, b) for b in (0, 1, 13, batch - 1)]
+        dec.close()
+    for (k0, v0), (k1, v1) in zip(kv[0], kv[2 * 400]):
+        assert np.isfinite(k1[:P]).all() and np.isfinite(v1[:P]).all()
+        assert np.abs(k0[:P - 1] - k1[:P - 1]).max() <= 4e-2 and np.abs(v0[:P - 1] - v1[:P - 1]).max() <= 4e-2
