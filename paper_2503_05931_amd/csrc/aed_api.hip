@@ -196,10 +196,13 @@ void make_layout(const aed_config* c, Layout* L) {
 // The memory-side cache holds 256 MB; a decoder whose per-step weights stay well below that keeps them there from
 // one step to the next (the keys and values are streamed around the caches), a larger one cannot.
 constexpr double kCacheResidentWeightBytes = 192e6;
-// Of a larger decoder, the first layers whose weights add up to this much are loaded the ordinary way and so stay
-// cached from step to step; the rest is streamed with the non-temporal hint.  (24 layers of 29.4 MB: 7 or 8 resident
-// layers are the optimum, 1.195 -> 1.160 ms per step; from 9 on the cache thrashes and the gain is gone.)
-constexpr double kResidentLayerBytes = 220e6;
+// Of a larger decoder, weights that add up to this much are loaded the ordinary way and so stay cached from step to step; the
+// rest is streamed with the non-temporal hint.  The second FFN matrices come first, then whole layers: that product is 64
+// workgroups per 16 rows, so a few CUs take in all of it, and waits for memory longest (one row: 6.3 us from memory, 4.1 from
+// the cache, the other products 0.4 to 0.6 us less).  24 layers, us a step with the first 7 layers resident / with the 24
+// second FFN matrices: batch 1 628.9, 614.4; 4 640.7, 624.5; 16 663.4, 655.8; 32 734.6, 727.2; 64 841.0, 834.1; 128 1422.7,
+// 1417.9; 200 1548.4, 1551.1.  (Of whole layers 7 or 8 were the optimum; beyond 240 MB the cache thrashes.)
+constexpr double kResidentBytes = 220e6;
 
 // What the launches of a captured step or prompt pass depend on; everything else they read from device memory.
 struct GraphKey {
@@ -236,7 +239,8 @@ struct aed_decoder {
     size_t esz;
     size_t kv_esz;  // bytes per cached key / value element: esz, or 1 for E4M3 codes
     int w_nt = 0;   // the decode step's weights do not fit the memory-side cache: stream them with the non-temporal hint,
-    int resident_layers = 0;  // except those of the first resident_layers layers
+    int resident_layers = 0;  // except those of the first resident_layers layers and the second FFN matrix of the first
+    int resident_ffn2 = 0;    // resident_ffn2
     Layout lay;
     std::vector<aed_layer_weights> layers;  // caller's pointers (biases, LayerNorm, embeddings are used in place)
     aed_weights w;
@@ -442,6 +446,7 @@ hipError_t k_self_attn(aed_decoder* d, int l) {
 // x += A . W^T + bias
 hipError_t k_resid(aed_decoder* d, int l, const void* A, const void* W, const void* bias, int K) {
     GemmArgs g = gemm_base(d, l);
+    if (W == d->fw[l].w_ff2) g.w_nt = d->w_nt && l >= d->resident_ffn2;
     g.A = A; g.W = W; g.bias = bias;
     g.N = d->cfg.d_model; g.K = K;
     g.out = d->act_at<float>(d->lay.x);
@@ -878,7 +883,9 @@ aed_status aed_decoder_create(const aed_config* cfg, const aed_weights* weights,
         const double dm = cfg->d_model, step_w = ((double)cfg->n_layers * (6 * dm * dm + 2 * dm * cfg->d_ffn) + dm * cfg->vocab) * d->esz;
         d->w_nt = step_w > kCacheResidentWeightBytes;
         const double layer_w = (6 * dm * dm + 2 * dm * cfg->d_ffn) * d->esz;
-        d->resident_layers = d->w_nt ? std::min(cfg->n_layers, (int)(kResidentLayerBytes / layer_w)) : 0;
+        const double ffn2_w = dm * cfg->d_ffn * d->esz;
+        d->resident_ffn2 = d->w_nt ? (int)std::min<double>(cfg->n_layers, kResidentBytes / ffn2_w) : 0;
+        d->resident_layers = d->w_nt ? (int)std::min<double>(cfg->n_layers, (kResidentBytes - d->resident_ffn2 * ffn2_w) / (layer_w - ffn2_w)) : 0;
     }
     d->lay = L;
     d->layers.assign(weights->layers, weights->layers + cfg->n_layers);
