@@ -55,10 +55,17 @@ __global__ __launch_bounds__(256) void frames_query_kernel(const float* __restri
     f32x4 acc[MT][NT];
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt) {
-        const float* p = q + (size_t)min(m0 + mt * 16 + r, M - 1) * kD + h * kDh + g * 16;
+        // lane (r, g) takes elements 16 j + 4 g .. + 3 of a 64-wide block, so that four lanes read 64 bytes in a row; Wt is stored to match
+        const f32x4* p = reinterpret_cast<const f32x4*>(q + (size_t)min(m0 + mt * 16 + r, M - 1) * kD + h * kDh + g * 4);
         float x[2][16];
-        load_f32<16>(p, x[0]);
-        load_f32<16>(p + 64, x[1]);
+#pragma unroll
+        for (int kb = 0; kb < 2; ++kb)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const f32x4 v = p[kb * 16 + j * 4];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) x[kb][4 * j + e] = v[e];
+            }
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt) acc[mt][nt] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
@@ -109,8 +116,9 @@ __global__ __launch_bounds__(256) void frames_query_kernel(const float* __restri
 //    has all 32 frames' scores and takes the softmax itself: lane (c, g) holds frames 4 g .. 4 g + 3 of either tile for column c,
 //    which is the operand layout of the second product;
 //  * the second product contracts over frames, so it needs them transposed: each wavefront puts its part into LDS and reads it
-//    back through the transposing read (ds_read_b64_tr_b16: 16 lanes read four 32-byte rows, lane i gets column i).  The
-//    16-byte pieces of odd k are stored 8 rows on, so that the four rows' pieces lie in different banks;
+//    back through the transposing read (ds_read_b64_tr_b16: 16 lanes read four rows of four 8-byte pieces, lane i gets column i).
+//    Piece p of a tile's row is the 4 columns 16 p + 4 t of a 64-column block, so that a lane's sums are 16 consecutive columns
+//    after t = 0 .. 3; the quarters of a block are stored 4 rows apart from each other, so that the four pieces lie in different banks;
 //  * the next step's frames are requested as soon as this step's are in LDS: 64 KB a workgroup, 128 KB a CU under way.
 // A prompt pass has several positions of a sequence: NQ of them are taken at once, with one reading of the frames.
 template <int NQ>
@@ -150,17 +158,18 @@ __global__ __launch_bounds__(256, NQ == 1 ? 2 : 1) void attn_frames_kernel(const
     __builtin_amdgcn_sched_barrier(0);
     fetch(0, 0);
     fetch(0, 1);
-    f32x4 acc[NQ][16];  // lane (c, g): columns 16 t + 4 g .. + 3 of this wavefront's 256, for column c of Q
+    f32x4 acc[NQ][4][4];  // [.][m][t], lane (c, g): columns 64 m + 16 g + 4 t .. + 3 of this wavefront's 256, for column c of Q
 #pragma unroll
     for (int i = 0; i < NQ; ++i)
 #pragma unroll
-        for (int t = 0; t < 16; ++t) acc[i][t] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int m = 0; m < 4; ++m)
+#pragma unroll
+            for (int t = 0; t < 4; ++t) acc[i][m][t] = f32x4{0.f, 0.f, 0.f, 0.f};
     float m_run[NQ], l_run[NQ];
 #pragma unroll
     for (int i = 0; i < NQ; ++i) { m_run[i] = -INFINITY; l_run[i] = 0.f; }
-    char* const put = slab + g * 256;
-    const int key = 4 * g + (r >> 2), odd = (r >> 1) & 1;
-    const auto get = (__attribute__((address_space(3))) char*)slab + odd * 1024 + ((key ^ (8 * odd)) * 16) + (r & 1) * 8;
+    char* const put = slab + g * 256 + (r ^ (4 * g)) * 16;
+    const auto get = (__attribute__((address_space(3))) char*)slab + (r & 3) * 256 + ((4 * g + (r >> 2)) ^ (4 * (r & 3))) * 16;
 
 #pragma unroll 1
     for (int s = 0; s < steps; ++s) {
@@ -184,7 +193,7 @@ __global__ __launch_bounds__(256, NQ == 1 ? 2 : 1) void attn_frames_kernel(const
                 u32x4 v = __builtin_bit_cast(u32x4, x[u][j]);
 #pragma unroll
                 for (int e = 0; e < 4; ++e) v[e] = own ? v[e] : 0u;
-                *reinterpret_cast<u32x4*>(put + u * 8192 + j * 1024 + (r ^ (8 * (j & 1))) * 16) = v;
+                *reinterpret_cast<u32x4*>(put + u * 8192 + j * 1024) = v;
             }
             fetch(s + 1, u);
 #pragma unroll
@@ -229,34 +238,38 @@ __global__ __launch_bounds__(256, NQ == 1 ? 2 : 1) void attn_frames_kernel(const
                 }
         }
 #pragma unroll
-        for (int t = 0; t < 16; ++t) {
-            // frames 4 g .. 4 g + 3 of both tiles, column 16 t + r: block t / 4 of the wavefront's part, its quarter t % 4
-            u32x2 a[2];
+        for (int m = 0; m < 4; ++m)
 #pragma unroll
-            for (int u = 0; u < 2; ++u)
-                a[u] = __builtin_bit_cast(u32x2, __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-                    (__attribute__((address_space(3))) s16x4*)(get + u * 8192 + (t >> 2) * 2048 + (t & 3) * 256)));
-            const bf16x8 e8 = __builtin_bit_cast(bf16x8, u32x4{a[0][0], a[0][1], a[1][0], a[1][1]});
+            for (int t = 0; t < 4; ++t) {
+                // frames 4 g .. 4 g + 3 of both tiles, column 64 m + 16 (r / 4) + 4 t + r % 4
+                u32x2 a[2];
 #pragma unroll
-            for (int i = 0; i < NQ; ++i) acc[i][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(e8, pf[i], acc[i][t] * alpha[i], 0, 0, 0);
-        }
+                for (int u = 0; u < 2; ++u)
+                    a[u] = __builtin_bit_cast(u32x2, __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+                        (__attribute__((address_space(3))) s16x4*)(get + u * 8192 + m * 2048 + (t >> 1) * 1024 + (t & 1) * 8)));
+                const bf16x8 e8 = __builtin_bit_cast(bf16x8, u32x4{a[0][0], a[0][1], a[1][0], a[1][1]});
+#pragma unroll
+                for (int i = 0; i < NQ; ++i) acc[i][m][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(e8, pf[i], acc[i][m][t] * alpha[i], 0, 0, 0);
+            }
     }
 #pragma unroll
     for (int i = 0; i < NQ; ++i) {
         const float inv = 1.0f / rows4_sum(l_run[i]);
-        bf16_t* out = static_cast<bf16_t*>(U) + ((size_t)b[i] * kCols + r) * kD + wave * 256 + 4 * g;
+        bf16_t* out = static_cast<bf16_t*>(U) + ((size_t)b[i] * kCols + r) * kD + wave * 256 + 16 * g;
 #pragma unroll
-        for (int t = 0; t < 16; ++t) {
-            bf16x4 o;
+        for (int m = 0; m < 4; ++m)
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const float v = (acc[i][t][e] + other_half(acc[i][t][e])) * inv;
-                bf16_t hi, lo;
-                split(v, hi, lo);
-                o[e] = r < kH ? hi : lo;
+            for (int j = 0; j < 2; ++j) {
+                bf16x8 o;
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    const float a = acc[i][m][2 * j + (e >> 2)][e & 3], v = (a + other_half(a)) * inv;
+                    bf16_t hi, lo;
+                    split(v, hi, lo);
+                    o[e] = r < kH ? hi : lo;
+                }
+                *reinterpret_cast<bf16x8*>(out + m * 64 + j * 8) = o;
             }
-            *reinterpret_cast<bf16x4*>(out + t * 16) = o;
-        }
     }
 }
 
@@ -340,15 +353,19 @@ __global__ __launch_bounds__(256, 2) void frames_out_kernel(const bf16_t* __rest
 }
 
 // ---------------------------------------------------------------- Wk^T, once at create
-// dst: per head [1024][128] in fragment order <- W [1024 (h, e)][1024 k] row-major; one thread per 16-byte piece
+// dst: per head [1024][128] in fragment order, element 16 j + 4 g + e of a 64-wide block in the place of 16 g + 4 j + e (see
+// frames_query_kernel) <- W [1024 (h, e)][1024 k] row-major; one thread per 16-byte piece
 __global__ __launch_bounds__(256) void frames_weight_kernel(const bf16_t* __restrict__ W, char* __restrict__ dst) {
-    const int i = blockIdx.x * 256 + threadIdx.x, k = i & (kD - 1), e0 = (i >> 10) * 8;  // neighbours read neighbouring k
-    if (e0 >= kD) return;
+    const int i = blockIdx.x * 256 + threadIdx.x, k = i & (kD - 1), p0 = (i >> 10) * 8;  // neighbours read neighbouring k
+    if (p0 >= kD) return;
     bf16x8 v;
 #pragma unroll
-    for (int e = 0; e < 8; ++e) v[e] = W[(size_t)(e0 + e) * kD + k];
-    const int h = e0 / kDh;
-    *reinterpret_cast<bf16x8*>(dst + (size_t)h * kD * kDh * 2 + frag_elem_off<2>(k, e0 % kDh, kDh)) = v;
+    for (int e = 0; e < 8; ++e) {
+        const int p = p0 + e;
+        v[e] = W[(size_t)((p & ~63) + 16 * ((p & 15) >> 2) + 4 * ((p & 63) >> 4) + (p & 3)) * kD + k];
+    }
+    const int h = p0 / kDh;
+    *reinterpret_cast<bf16x8*>(dst + (size_t)h * kD * kDh * 2 + frag_elem_off<2>(k, p0 % kDh, kDh)) = v;
 }
 
 hipError_t launch_frames_weight(const void* W, void* dst, hipStream_t s) {
