@@ -59,6 +59,9 @@ typedef bf16_t bf16x4 __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ void load_to_lds16(const void* g, unsigned lds_base) {
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off\n" ::"s"(lds_base), "v"(g) : "memory");
 }
+// Between LDS writes and reads of one wavefront, which the hardware keeps in order: the compiler, which looks at one lane at a
+// time, must not take what a lane has read before for what it would read now.
+__device__ __forceinline__ void other_lanes_wrote() { asm volatile("" ::: "memory"); }
 // At most N of this wavefront's memory operations still in flight, its LDS reads done, then the barrier.
 template <int N> __device__ __forceinline__ void wait_loads_barrier() {
     asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(N) : "memory");
@@ -227,6 +230,7 @@ __global__ __launch_bounds__(512) void gemm_dma_crosskv_kernel(GemmArgs a) {
                         for (int e = 0; e < 4; ++e) o[e] = (bf16_t)acc[mt][nt][4 * q + e];
                         *reinterpret_cast<bf16x4*>(scr + r32 * 128 + ((c ^ (r32 & 7)) * 16) + hh * 8) = o;
                     }
+                other_lanes_wrote();
 #pragma unroll
                 for (int p = 0; p < 4; ++p) {
                     const int row = p * 8 + (lane >> 3), c = lane & 7;
@@ -237,6 +241,7 @@ __global__ __launch_bounds__(512) void gemm_dma_crosskv_kernel(GemmArgs a) {
                         *reinterpret_cast<f32x4*>(dst + frame * a.head_dim + c * 8) = v;
                     }
                 }
+                other_lanes_wrote();
             }
         } else {
             // one byte per element: the wavefront's 32 x 64 block is 32 rows of 64 bytes = four 16-byte chunks
@@ -254,6 +259,7 @@ __global__ __launch_bounds__(512) void gemm_dma_crosskv_kernel(GemmArgs a) {
                         for (int e = 0; e < 4; ++e) o[e] = acc[mt][nt][4 * q + e];
                         store4_fp8(reinterpret_cast<unsigned char*>(scr) + r32 * 64 + ((c ^ (r32 & 3)) * 16) + (q & 1) * 8 + hh * 4, o);
                     }
+                other_lanes_wrote();
 #pragma unroll
                 for (int p = 0; p < 2; ++p) {
                     const int row = p * 16 + (lane >> 2), c = lane & 3;
@@ -264,6 +270,7 @@ __global__ __launch_bounds__(512) void gemm_dma_crosskv_kernel(GemmArgs a) {
                         *reinterpret_cast<f32x4*>(dst + frame * a.head_dim + c * 16) = v;
                     }
                 }
+                other_lanes_wrote();
             }
         }
         init_acc();
