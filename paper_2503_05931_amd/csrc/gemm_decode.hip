@@ -83,12 +83,12 @@ __device__ __forceinline__ void gemm_decode_body(const GemmStart& st, TailPtr ta
     TailLoad<GemmFields<PRO, EPI>, GemmArgs> rest(tail);
     GemmArgs a;
     constexpr int BM = 16 * MT, BN = 16 * NT;
-    constexpr int EP = (MT * NT * 64 + 255) / 256;  // output 4-vectors per thread in the epilogue
+    constexpr int EP = (MT * NT + NW - 1) / NW;  // output 4-vectors per thread in the epilogue
     constexpr int ES = sizeof(T);
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, r = lane & 15, g = lane >> 4;
     const int m0 = by * BM, n0 = bx * BN;
     const int K = NB > 0 ? NB * NW * 64 : st.K, M = st.M;
-    static_assert(NW == 4 || (PRO == PRO_T && MT * NT == 1 && NB > 0), "more wavefronts: one 16 x 16 tile, known K");
+    static_assert(NW == 4 || (PRO != PRO_LN && NB > 0), "more wavefronts: known K, no LayerNorm in front");
     const int nblk = K >> 8;  // 64-wide k blocks per wavefront
     const char* __restrict__ W = static_cast<const char*>(st.W);
     const char* __restrict__ A = static_cast<const char*>(st.A);
@@ -143,13 +143,13 @@ __device__ __forceinline__ void gemm_decode_body(const GemmStart& st, TailPtr ta
     // LNS: tile statistics of the rows being multiplied, 16 lanes per row, four 16-column tiles per lane.  Of 16 rows they
     // are requested in front of the stream and combined while it is on its way (4.13 -> 3.96 us for the QKV product of one
     // row); of more rows they would hold it back (8.2 -> 8.9 us at 256 rows) and are requested behind its first blocks.
-    constexpr int SP = LNS ? MT : 1;
+    constexpr int SR = 4 * NW, SP = LNS ? (BM + SR - 1) / SR : 1;  // rows a pass, passes
     constexpr bool ST_FIRST = MT == 1;
     f32x4 sv[SP][2];
     auto fetch_stats = [&]() {
 #pragma unroll
         for (int p = 0; p < SP; ++p) {
-            const f32x4* sp = reinterpret_cast<const f32x4*>(st.stats_in + (size_t)(m0 + 16 * p + (tid >> 4)) * st.stat_tiles +
+            const f32x4* sp = reinterpret_cast<const f32x4*>(st.stats_in + (size_t)(m0 + min(SR * p + (tid >> 4), BM - 1)) * st.stat_tiles +
                                                              min(4 * (tid & 15), st.stat_tiles - 4));
             sv[p][0] = sp[0];
             sv[p][1] = sp[1];
@@ -160,9 +160,10 @@ __device__ __forceinline__ void gemm_decode_body(const GemmStart& st, TailPtr ta
         for (int p = 0; p < SP; ++p) {
             float2 rs = combine_tile_stats(sv[p][0], sv[p][1], 4 * (tid & 15) < st.stat_tiles, st.stat_tiles);
             const float rstd = fold_norm(a.rms, (float)K, a.ln_eps, rs.y, rs.x);
-            if ((tid & 15) == 0) {
-                red[0][0][16 * p + (tid >> 4)] = rs.x;
-                red[1][0][16 * p + (tid >> 4)] = rstd;
+            const int row = SR * p + (tid >> 4);
+            if ((tid & 15) == 0 && row < BM) {
+                red[0][0][row] = rs.x;
+                red[1][0][row] = rstd;
             }
         }
     };
@@ -207,7 +208,7 @@ __device__ __forceinline__ void gemm_decode_body(const GemmStart& st, TailPtr ta
         if constexpr (LNS && EPI == EPI_QKV) raw = a.n_raw > 0 && n0 >= a.n_raw;
 #pragma unroll
         for (int j = 0; j < EP; ++j) {
-            const int t = MT * NT < 4 ? min(wave, MT * NT - 1) : wave + 4 * j;
+            const int t = MT * NT < NW ? min(wave, MT * NT - 1) : wave + NW * j;
             const int m = tile_row(t, lane), n = tile_col(t, lane), mc = min(m, M - 1);
             if constexpr (LNS) {
                 const float* c2 = a.ln_c2 + n;
@@ -374,8 +375,8 @@ __device__ __forceinline__ void gemm_decode_body(const GemmStart& st, TailPtr ta
 
 #pragma unroll
     for (int j = 0; j < EP; ++j) {
-        const int t = wave + 4 * j, l = lane;
-        if (MT * NT < 4 && t >= MT * NT) continue;
+        const int t = wave + NW * j, l = lane;
+        if (MT * NT < NW && t >= MT * NT) continue;
         f32x4 s = part[0][t][l];
 #pragma unroll
         for (int w = 1; w < NW; ++w) s += part[w][t][l];
@@ -426,13 +427,13 @@ __global__ __launch_bounds__(64 * NW) void gemm_decode_kernel(const void* W, con
 
 // Two products of the same operand A in one launch: the workgroups of z = 0 are the tiles of a0 (a residual update,
 // EPI_RESID_S), those of z = 1 the tiles of a1 (kernels.h, "merged products").  Neither reads what the other writes.
-template <typename T, int MT, int NT, int EPI1, bool WNT, int NB>
-__global__ __launch_bounds__(256) void gemm_decode_pair_kernel(const void* W0, const void* W1, const void* A, int M, int K,
+template <typename T, int MT, int NT, int EPI1, bool WNT, int NB, int NW = 4>
+__global__ __launch_bounds__(64 * NW) void gemm_decode_pair_kernel(const void* W0, const void* W1, const void* A, int M, int K,
                                                                ArgTail, ArgTail) {
     if (blockIdx.z == 0)
-        gemm_decode_body<T, PRO_T, EPI_RESID_S, MT, NT, WNT, NB>(GemmStart{W0, A, nullptr, M, K, 0}, tail_at(32), blockIdx.x, blockIdx.y);
+        gemm_decode_body<T, PRO_T, EPI_RESID_S, MT, NT, WNT, NB, NW>(GemmStart{W0, A, nullptr, M, K, 0}, tail_at(32), blockIdx.x, blockIdx.y);
     else
-        gemm_decode_body<T, PRO_T, EPI1, MT, NT, WNT, NB>(GemmStart{W1, A, nullptr, M, K, 0}, tail_at(32 + sizeof(ArgTail)), blockIdx.x, blockIdx.y);
+        gemm_decode_body<T, PRO_T, EPI1, MT, NT, WNT, NB, NW>(GemmStart{W1, A, nullptr, M, K, 0}, tail_at(32 + sizeof(ArgTail)), blockIdx.x, blockIdx.y);
 }
 
 // ---------------------------------------------------------------- LayerNorm to fragment order
@@ -513,23 +514,32 @@ static bool hint_w(const GemmArgs& a, long wgs, int row_tiles) { return a.w_nt &
 // launch of one round does not need it (130 rows, K = 4096: 17.9 us without, 19.0 with).
 constexpr unsigned kOneWgLds = 66 << 10;
 
+// Eight wavefronts a workgroup instead of four, of bfloat16 products over K = 1024 (nb = 4 blocks a wavefront) or 4096 (16):
+// tiles of 512 outputs and more, and over 4096 the smallest, up to a workgroup a CU; 64 x 64 over 1024 always (one fits a CU either
+// way).  Their operands are under way sooner, and a wavefront has half the matrix instructions behind them.  us a launch, four /
+// eight wavefronts (weights of 24 layers in turn): N = 4096, K = 1024 on 32 x 64, 80 to 128 rows 4.42 to 4.53 / 4.18 to 4.29, from
+// memory with the hint on 64 x 32 5.99 / 5.28; on 64 x 64, 256 rows 6.43 / 5.88, 512 10.98 / 10.00; N = 1024 on 32 x 64, 512 rows 4.58 /
+// 4.43, on 64 x 64, 1024 rows 6.58 / 6.20; N = 1024, K = 4096 on 16 x 16, 64 rows 4.53 / 4.38 (24 layers, batch 64, 131 positions 124.1 ->
+// 122.9 ms), on 32 x 16, 128 rows 5.60 / 5.50, from memory 7.50 / 7.27.  But 16 x 16 to 32 x 32 over 1024 4 to 8 % slower, 32 x 32 over 4096 1 %
+// slower, 64 x 64 over 4096, 1024 rows 15.4 / 15.6; sixteen nowhere faster; 32 x 64, 256 rows, two a CU 6.42 / 6.92.
+constexpr bool eight_wavefronts(int tiles, int nb) { return (nb == 4 && tiles >= 8) || (nb == 16 && (tiles <= 2 || tiles == 8)); }
+constexpr bool always_eight(int tiles, int nb) { return nb == 4 && tiles == 16; }
+
 template <typename T, int PRO, int EPI, int MT, int NT, int NB>
 static hipError_t launch_nb(const GemmArgs& a, hipStream_t s) {
     dim3 grid(a.N / (16 * NT), (a.M + 16 * MT - 1) / (16 * MT));
     const long wgs = (long)grid.x * grid.y;
     const ArgTail tail = make_tail<GemmFields<PRO, EPI>>(a);
     unsigned lds = 0;
-    // K = 4096 on 16 x 16 tiles: eight wavefronts have a workgroup's whole share of both operands under way at once, four half
-    // of it.  24 layers: batch 64, 131 positions 124.1 -> 122.9 ms, batch 16, 24 positions 22.6 -> 22.3; one row 84.6 and 84.7;
-    // sixteen: batch 16 22.7, one row 85.2.  Beyond one workgroup per CU two of four share it.  (float32, batch 32: 10.27 and
-    // 10.26 ms with eight, 10.99 with sixteen: four.)
-    if constexpr (sizeof(T) == 2 && PRO == PRO_T && MT * NT == 1 && NB == 16) {
-        if (wgs <= kCus) {
+    // Where one workgroup has a CU to itself, eight wavefronts have its operands under way sooner than four.
+    if constexpr (sizeof(T) == 2 && eight_wavefronts(MT * NT, NB)) {
+        if (wgs <= kCus || always_eight(MT * NT, NB)) {
             if (hint_w(a, wgs, grid.y)) hipLaunchKernelGGL((gemm_decode_kernel<T, PRO, EPI, MT, NT, true, NB / 2, 8>), grid, dim3(512), 0, s, a.W, a.A, a.stats_in, a.M, a.K, a.stat_tiles, tail);
             else hipLaunchKernelGGL((gemm_decode_kernel<T, PRO, EPI, MT, NT, false, NB / 2, 8>), grid, dim3(512), 0, s, a.W, a.A, a.stats_in, a.M, a.K, a.stat_tiles, tail);
             return hipGetLastError();
         }
     }
+    if constexpr (!(sizeof(T) == 2 && always_eight(MT * NT, NB))) {
     if constexpr (sizeof(T) == 4 && PRO == PRO_T && MT * NT >= 4 && MT * NT <= 8) {
         if (wgs > kCus) {
             static DeviceOnce once;
@@ -548,6 +558,7 @@ static hipError_t launch_nb(const GemmArgs& a, hipStream_t s) {
         }
     }
     hipLaunchKernelGGL((gemm_decode_kernel<T, PRO, EPI, MT, NT, false, NB>), grid, dim3(256), lds, s, a.W, a.A, a.stats_in, a.M, a.K, a.stat_tiles, tail);
+    }
     return hipGetLastError();
 }
 // K = 1024 and, for the second FFN product, K = 4096 are unrolled; every other K runs the loop
@@ -566,9 +577,11 @@ static hipError_t launch_one(const GemmArgs& a, hipStream_t s) {
 // workgroups are spread over the 256 CUs.  W mostly comes from memory, A from the caches; the folded LayerNorm reads 512
 // bytes of statistics per row of 2 KB.  Workgroups of the smaller tiles share a CU (two or three fit by registers), so
 // beyond 256 workgroups the bytes through a CU grow in proportion, not in whole rounds.  The 64 x 64 tile runs one workgroup
-// per CU and its stream costs about half more than its bytes say when K is short (measured at M = 256, K = 1024: 9.7 us
-// against 8.2 us for the 32 x 64 tile on the QKV product); over K = 4096 the start-up is a smaller part and the bytes decide
-// (second FFN product at M = 1024: 18.1 us against 19.4 us for 32 x 64).
+// per CU; up to a workgroup a CU, on eight wavefronts, it costs less than its bytes say (K = 1024, N = 4096, us on 32 x 64 / 64 x 64: 160
+// rows 5.92 / 5.63, 256 6.42 / 5.88; N = 1024, 700 rows 5.98 / 5.63), in several rounds half more (320 rows 7.98 and over 8.93, 700 13.6 /
+// 14.5); over K = 4096 the start-up is a smaller part and the bytes decide (1024 rows 17.9 / 15.4).  The wider
+// tile reads a weight panel more often: where weights come from memory, 64 x 32 is better than 32 x 64 (N = 4096, 128 rows 5.31 / 5.59,
+// from the caches 4.62 / 4.29).
 //
 // float32: whole rounds of 256 workgroups, because workgroups that share a CU gain little or lose (kOneWgLds; the fused
 // LayerNorm keeps its rows in registers, small tiles only, one workgroup per CU).  A round costs
@@ -602,7 +615,10 @@ static TileId choose_tile(const GemmArgs& a, int n_out) {
             cost = rounds * (PRO == PRO_LN ? bm + bn : (double)a.K * std::max(bm * bn, 14 * (bm + bn)) + 450.0 * 1024);
         } else {
             const double rounds = wgs > kCus ? (double)wgs / kCus : 1.0;
-            cost = rounds * (bm * a_bytes + bn * w_bytes) * (c == T44 && a.K < 4096 ? 1.6 : 1.0);
+            double factor = 1.0;
+            if (c == T44 && a.K < 4096) factor = a.K == 1024 && wgs <= kCus ? 0.92 : 1.6;
+            if (c == T24 && hint_w(a, wgs, (a.M + bm - 1) / bm)) factor = 1.05;
+            cost = rounds * (bm * a_bytes + bn * w_bytes) * factor;
         }
         if (cost < best_cost || (cost == best_cost && wgs < best_wgs)) { best = c; best_cost = cost; best_wgs = wgs; }
     }
@@ -624,12 +640,16 @@ static hipError_t launch_tiles(const GemmArgs& a, hipStream_t s) {
 }
 
 constexpr int kLnFusedMaxM = 128;
-// The LDS-tiled kernel (bf16, 128 x 128 tiles) takes over once its tiles fill the GPU; below that
-// the streaming kernel's 256+ small workgroups are faster (measured at M = 1024: N = 1024 gives 64
-// tiles and 17.8 us against 7.6 us streamed; N = 4096 gives 256 tiles and 23.8 us against 28.4 us).
+// The LDS-tiled kernel (bf16, 128 x 128 tiles, one workgroup a CU) takes as long for a few tiles as for 256 of them (K = 1024:
+// 14 to 15 us a round), the streaming kernel's time goes with the rows: the first is faster where its rounds are full to
+// more than 5/6.  K = 1024, us tiled / streamed: N = 4096, 700 rows (192 tiles) 14.4 / 13.7, 896 (224) 14.6 / 15.7, 1024 (256) 14.9 / 17.5,
+// 1536 (384) 26.6 / 25.1, 2048 (512) 28.0 / 32.2; N = 3072, 1024 rows (192) 15.8 / 15.1, 2048 (384) 30.1 / 27.4, 3072 (576) 43.8 / 39.1.
+// Over another K the streaming kernel loops and is slower: from 160 tiles on.
 constexpr int kTiledMinTiles = 160;
 static bool use_tiled(const GemmArgs& a) {
-    return a.N % 128 == 0 && (long)((a.M + 127) / 128) * (a.N / 128) >= kTiledMinTiles;
+    if (a.N % 128 != 0) return false;
+    const long tiles = (long)((a.M + 127) / 128) * (a.N / 128), rounds = (tiles + kCus - 1) / kCus;
+    return a.K == 1024 ? 6 * tiles > 5 * kCus * rounds : tiles >= kTiledMinTiles;
 }
 
 // The 256 x 256 direct-to-LDS kernel (cross K/V product only) needs whole 256-row tiles in A and enough
@@ -699,8 +719,18 @@ template <typename T, int MT, int NT, int EPI1, int NB>
 static hipError_t launch_pair_nb(const GemmArgs& a0, const GemmArgs& a1, hipStream_t s) {
     const int rows = (a0.M + 16 * MT - 1) / (16 * MT);
     const dim3 grid(a0.N / (16 * NT), rows, 2);
+    const long wgs = 2l * grid.x * rows;
     const ArgTail t0 = make_tail<GemmFields<PRO_T, EPI_RESID_S>>(a0), t1 = make_tail<GemmFields<PRO_T, EPI1>>(a1);
-    if (hint_w(a0, 2l * grid.x * rows, rows))
+    if constexpr (eight_wavefronts(MT * NT, NB)) {
+        if (wgs <= kCus) {
+            if (hint_w(a0, wgs, rows))
+                hipLaunchKernelGGL((gemm_decode_pair_kernel<T, MT, NT, EPI1, true, NB / 2, 8>), grid, dim3(512), 0, s, a0.W, a1.W, a0.A, a0.M, a0.K, t0, t1);
+            else
+                hipLaunchKernelGGL((gemm_decode_pair_kernel<T, MT, NT, EPI1, false, NB / 2, 8>), grid, dim3(512), 0, s, a0.W, a1.W, a0.A, a0.M, a0.K, t0, t1);
+            return hipGetLastError();
+        }
+    }
+    if (hint_w(a0, wgs, rows))
         hipLaunchKernelGGL((gemm_decode_pair_kernel<T, MT, NT, EPI1, true, NB>), grid, dim3(256), 0, s, a0.W, a1.W, a0.A, a0.M, a0.K, t0, t1);
     else
         hipLaunchKernelGGL((gemm_decode_pair_kernel<T, MT, NT, EPI1, false, NB>), grid, dim3(256), 0, s, a0.W, a1.W, a0.A, a0.M, a0.K, t0, t1);
