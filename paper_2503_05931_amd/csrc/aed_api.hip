@@ -274,7 +274,9 @@ struct aed_decoder {
     bool last_enc_padded = false;
     std::vector<int> enc_lens, enc_off, page_table;
     std::vector<int4> items_host;  // the cross-attention work list of the batch (a prefill pass repeats it per position)
-    int* pin_poll = nullptr;  // pinned host memory for the finished-count poll
+    int* pin_poll = nullptr;  // pinned host memory: poll words of the finished count, the queue's flags, then the next two
+    int* pin_off = nullptr;   // frame offsets and work list of the batch being started
+    int4* pin_items = nullptr;
     hipEvent_t poll_event[2] = {nullptr, nullptr};
     hipEvent_t t0 = nullptr, t1 = nullptr;
     GraphPool greedy_graphs;  // one greedy step (prompt feeding, EOS rules, output writes)
@@ -685,12 +687,6 @@ aed_status start_batch(aed_decoder* d, const void* enc, bool padded, int t_max, 
     order_items(items);
 
     HIP_TRY(d, hipStreamSynchronize(d->stream));  // the previous batch's work is done with the old tables
-    // the chunk merge's arrival counters return to zero by themselves after every launch; a batch still starts
-    // from zero, whatever an earlier launch that ended abnormally may have left
-    HIP_TRY(d, hipMemsetAsync(d->ws + d->lay.counters, 0, (size_t)d->lay.act_rows * d->cfg.n_heads * 4, d->stream));
-    HIP_TRY(d, hipMemcpyAsync(d->at<int>(d->lay.enc_off), off.data(), off.size() * 4, hipMemcpyHostToDevice, d->stream));
-    HIP_TRY(d, hipMemcpyAsync(d->at<int4>(d->lay.items), items.data(), items.size() * 16, hipMemcpyHostToDevice, d->stream));
-    if (padded) HIP_TRY(d, launch_padded_row_map(d->at<int>(d->lay.enc_off), d->at<int>(d->lay.row_map), t_max, batch, d->stream));
     d->batch = batch;
     d->n_items = (int)items.size();
     d->cross_keys = 0;
@@ -711,8 +707,18 @@ aed_status start_batch(aed_decoder* d, const void* enc, bool padded, int t_max, 
     d->self_nchunks = (d->cfg.max_dec_len + d->self_chunk - 1) / d->self_chunk;
     d->state = aed_decoder::NO_BATCH;
 
-    StateArgs st = d->state_args(0, 0);
-    HIP_TRY(d, launch_reset(st, nullptr, 0, 0, d->stream));
+    // Tables by way of pinned memory, which the kernel reads itself.  The chunk merge's arrival counters return to zero by
+    // themselves after every launch; a batch still starts from zero, whatever an earlier launch that ended abnormally may have left.
+    StartArgs sa;
+    memcpy(d->pin_off, off.data(), off.size() * 4);
+    memcpy(d->pin_items, items.data(), items.size() * 16);
+    sa.src_off = d->pin_off; sa.src_items = d->pin_items;
+    sa.enc_off = d->at<int>(d->lay.enc_off);
+    sa.counters = d->at<int>(d->lay.counters);
+    sa.n_counters = d->lay.act_rows * d->cfg.n_heads;
+    sa.row_map = padded ? d->at<int>(d->lay.row_map) : nullptr;
+    sa.t_max = t_max;
+    HIP_TRY(d, launch_start_batch(sa, d->state_args(0, 0), d->stream));
     // encoder frames -> fragment order once (gathering the valid rows of a padded tensor), then one GEMM per layer
     HIP_TRY(d, launch_reorder_rows(d->dt, enc, padded ? d->at<int>(d->lay.row_map) : nullptr, d->ws + d->lay.enc_frag,
                                    (int)total, d->cfg.d_model, d->stream));
@@ -901,10 +907,12 @@ aed_status aed_decoder_create(const aed_config* cfg, const aed_weights* weights,
     };
     hipError_t e;
     if ((e = scratch_of_current_device(&d->static_scratch)) != hipSuccess) return cleanup(e, "hipGetSymbolAddress(scratch)");
-    // two poll words, then (from word 64) one finished flag per sequence for the request queue
-    if ((e = hipHostMalloc(reinterpret_cast<void**>(&d->pin_poll), 256 + (size_t)cfg->max_batch * 4,
-                           hipHostMallocDefault)) != hipSuccess)
+    // two poll words, then (from word 64) one finished flag per sequence for the request queue, then a batch's tables
+    const size_t flags_end = align_up(256 + (size_t)cfg->max_batch * 4, 256), off_end = align_up(flags_end + ((size_t)cfg->max_batch + 1) * 4, 256);
+    if ((e = hipHostMalloc(reinterpret_cast<void**>(&d->pin_poll), off_end + (size_t)L.max_items * 16, hipHostMallocDefault)) != hipSuccess)
         return cleanup(e, "hipHostMalloc");
+    d->pin_off = reinterpret_cast<int*>(reinterpret_cast<char*>(d->pin_poll) + flags_end);
+    d->pin_items = reinterpret_cast<int4*>(reinterpret_cast<char*>(d->pin_poll) + off_end);
     d->pin_poll[0] = d->pin_poll[1] = 0;
     for (int i = 0; i < 2; ++i)
         if ((e = hipEventCreateWithFlags(&d->poll_event[i], hipEventDisableTiming)) != hipSuccess)
@@ -1031,9 +1039,8 @@ aed_status aed_decode_step(aed_decoder* d, const int32_t* tokens_in, int32_t* to
         if (d->pages_used + d->batch > d->lay.n_pages)
             return fail(d, AED_ECAPACITY, "self-attention page pool exhausted (%d pages)", d->lay.n_pages);
         const int blk = d->host_pos / kPage;
+        HIP_TRY(d, launch_assign_pages(d->at<int>(d->lay.page_table), d->lay.max_pages, blk, d->pages_used, d->batch, d->stream));
         for (int b = 0; b < d->batch; ++b) d->page_table[(size_t)b * d->lay.max_pages + blk] = d->pages_used++;
-        aed_status st = upload_page_table(d);
-        if (st != AED_OK) return st;
     }
     StateArgs st = d->state_args(0, 0);
     HIP_TRY(d, launch_set_tokens(st.cur_tok, tokens_in, 1, d->batch, d->stream));
@@ -1044,15 +1051,16 @@ aed_status aed_decode_step(aed_decoder* d, const int32_t* tokens_in, int32_t* to
         aed_status grc = ensure_graph(d, st, 0, d->at<int>(d->lay.step_tok), graph_key(d), &d->step_graphs, &g);
         if (grc != AED_OK) return grc;
         HIP_TRY(d, hipGraphLaunch(g, d->stream));
-        if (tokens_out)
-            HIP_TRY(d, hipMemcpyAsync(tokens_out, d->at<int>(d->lay.step_tok), (size_t)d->batch * 4,
-                                      hipMemcpyDeviceToDevice, d->stream));
     } else {
-        HIP_TRY(d, enqueue_step(d, st, 0, tokens_out));
+        HIP_TRY(d, enqueue_step(d, st, 0, d->at<int>(d->lay.step_tok)));
     }
-    if (logits_out)
-        HIP_TRY(d, hipMemcpyAsync(logits_out, d->act_at<float>(d->lay.logits), (size_t)d->batch * d->cfg.vocab * 4,
-                                  hipMemcpyDeviceToDevice, d->stream));
+    const size_t n = (size_t)d->batch * d->cfg.vocab;
+    if (logits_out && (uintptr_t)logits_out % 16 != 0) {
+        HIP_TRY(d, hipMemcpyAsync(logits_out, d->act_at<float>(d->lay.logits), n * 4, hipMemcpyDeviceToDevice, d->stream));
+        logits_out = nullptr;
+    }
+    if (tokens_out || logits_out)
+        HIP_TRY(d, launch_hand_out(d->at<int>(d->lay.step_tok), tokens_out, d->batch, d->act_at<float>(d->lay.logits), logits_out, n, d->stream));
     d->host_pos += 1;
     return AED_OK;
 }

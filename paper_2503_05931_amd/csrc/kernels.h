@@ -211,8 +211,17 @@ hipError_t launch_sample_embed(Dtype dt, const float* logits, const StateArgs& s
 // seq_len = start_pos, cur_tok = prompt[b][start_pos], n_gen = finished = 0, n_finished = 0,
 // limit = limits ? limits[b] : INT_MAX, out_tokens = pad (fill_out)
 hipError_t launch_reset(const StateArgs& st, const int* limits_dev, int fill_out, int start_pos, hipStream_t s);
-// row_map[enc_off[b] + t] = b * t_max + t: where the frames of a padded tensor are
-hipError_t launch_padded_row_map(const int* enc_off, int* row_map, int t_max, int batch, hipStream_t s);
+// The start of a batch: enc_off[b] = src_off[b], items = src_items (state: n_items of them), counters = 0, state as launch_reset leaves
+// it at position 0 without a prompt; with row_map: row_map[enc_off[b] + t] = b * t_max + t, where the frames of a padded tensor are.
+struct StartArgs {
+    const int* src_off;     // [batch + 1] pinned host memory
+    const int4* src_items;  // pinned host memory
+    int *enc_off, *counters, *row_map;
+    int n_counters, t_max;
+};
+hipError_t launch_start_batch(const StartArgs& a, const StateArgs& st, hipStream_t s);
+// ids_out[b] = ids[b], logits_out[i] = logits[i] (i < n, n % 4 == 0); either output may be null, logits_out 16-byte aligned
+hipError_t launch_hand_out(const int* ids, int* ids_out, int batch, const float* logits, float* logits_out, size_t n, hipStream_t s);
 // cur_tok[b] = src[b * stride]
 hipError_t launch_set_tokens(int* cur_tok, const int* src, int stride, int batch, hipStream_t s);
 // out[b] = n_gen[b]; dst[b, t] = out_tokens[b, t]

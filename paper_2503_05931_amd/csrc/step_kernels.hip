@@ -7,6 +7,8 @@
 // every step without touching its arguments.
 #include <limits.h>
 
+#include <algorithm>
+
 #include "common.h"
 #include "kernels.h"
 
@@ -233,15 +235,48 @@ hipError_t launch_reset(const StateArgs& st, const int* limits_dev, int fill_out
     return hipGetLastError();
 }
 
-// On the device, because 65 thousand entries built on the host and uploaded kept the GPU waiting: a padded batch of 256 taken in
-// by 4 layers, with its 4 prompt steps, 2.91 -> 2.85 ms.
-__global__ void padded_row_map_kernel(const int* __restrict__ enc_off, int* __restrict__ row_map, int t_max) {
-    const int b = blockIdx.x, at = enc_off[b], n = enc_off[b + 1] - at;
-    for (int t = threadIdx.x; t < n; t += blockDim.x) row_map[at + t] = b * t_max + t;
+// A batch's start in one launch: the host's tables out of pinned memory into their places, the padded tensor's row map (65
+// thousand entries built on the host and uploaded kept the GPU waiting), arrival counters and sequence state cleared.  As two
+// uploads, a memset and two kernels the GPU waited 9 to 18 us in front of each.
+__global__ __launch_bounds__(256) void start_batch_kernel(StartArgs a, StateArgs st) {
+    const int b = blockIdx.x, tid = threadIdx.x, at = b * blockDim.x + tid, all = gridDim.x * blockDim.x;
+    const int first = a.src_off[b], n = a.src_off[b + 1] - first;
+    if (tid == 0) {
+        a.enc_off[b] = first;
+        if (b + 1 == st.batch) a.enc_off[b + 1] = first + n;
+        st.seq_len[b] = 0;
+        st.n_gen[b] = 0;
+        st.finished[b] = 0;
+        st.cur_tok[b] = 0;
+        st.limit[b] = INT_MAX;
+        if (b == 0) *st.n_finished = 0;
+    }
+    for (int i = at; i < st.n_items; i += all) st.items[i] = a.src_items[i];
+    for (int i = at; i < a.n_counters; i += all) a.counters[i] = 0;
+    if (a.row_map)
+        for (int t = tid; t < n; t += blockDim.x) a.row_map[first + t] = b * a.t_max + t;
 }
 
-hipError_t launch_padded_row_map(const int* enc_off, int* row_map, int t_max, int batch, hipStream_t s) {
-    hipLaunchKernelGGL(padded_row_map_kernel, dim3(batch), dim3(256), 0, s, enc_off, row_map, t_max);
+hipError_t launch_start_batch(const StartArgs& a, const StateArgs& st, hipStream_t s) {
+    hipLaunchKernelGGL(start_batch_kernel, dim3(st.batch), dim3(256), 0, s, a, st);
+    return hipGetLastError();
+}
+
+// A step's results to the caller's buffers: one launch where two copies were two, each with the GPU idle in front of it.
+__global__ __launch_bounds__(256) void hand_out_kernel(const int* __restrict__ ids, int* __restrict__ ids_out, int batch,
+                                                       const f32x4* __restrict__ logits, f32x4* __restrict__ logits_out, size_t n4) {
+    const size_t at = (size_t)blockIdx.x * 256 + threadIdx.x;
+    if (ids_out)
+        for (size_t i = at; i < (size_t)batch; i += (size_t)gridDim.x * 256) ids_out[i] = ids[i];
+    if (logits_out)
+        for (size_t i = at; i < n4; i += (size_t)gridDim.x * 256) logits_out[i] = logits[i];
+}
+
+hipError_t launch_hand_out(const int* ids, int* ids_out, int batch, const float* logits, float* logits_out, size_t n, hipStream_t s) {
+    if (n % 4 != 0 || (uintptr_t)logits_out % 16 != 0) return hipErrorInvalidValue;
+    const size_t blocks = std::min<size_t>(2048, ((logits_out ? n / 4 : batch) + 255) / 256);
+    hipLaunchKernelGGL(hand_out_kernel, dim3((unsigned)blocks), dim3(256), 0, s, ids, ids_out, batch, reinterpret_cast<const f32x4*>(logits),
+                       reinterpret_cast<f32x4*>(logits_out), n / 4);
     return hipGetLastError();
 }
 
