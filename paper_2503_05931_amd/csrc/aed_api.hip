@@ -69,7 +69,7 @@ size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
 // Offsets (bytes) of everything carved from the caller's workspace.
 struct Layout {
-    size_t x, q, q_aux, logits, attn_out, ffn_h, ln_h, x_shadow, ln_stats, mu_hat, ln_fold;
+    size_t x, q, q_aux, logits, attn_out, ffn_h, x_shadow, ln_stats, mu_hat, ln_fold;
     size_t stats_elems;  // float2 per statistics buffer
     size_t shadow_bytes; // bytes per shadow buffer
     size_t act_bytes;    // [0, act_bytes): the step's activations and attention partials (x ... counters)
@@ -138,8 +138,8 @@ void make_layout(const aed_config* c, Layout* L) {
     L->logits = take(B * (size_t)c->vocab * 4);
     L->attn_out = take(Bp * d * e);
     L->ffn_h = take(Bp * (size_t)c->d_ffn * e);
-    L->ln_h = take(Bp * d * e);
-    // bfloat16 mode: LayerNorm folded around the products (shadow of the residual rows, tile statistics in two
+    take(Bp * d * e);  // not used: what aed_decode_step_noalloc takes and refuses (act_bytes) stays as it has been
+    // LayerNorm folded around the products (shadow of the residual rows, tile statistics in two
     // buffers that alternate from one residual update to the next, row shifts, folded gain/shift vectors)
     L->x_shadow = take(2 * Bp * d * e);  // two buffers, alternating like the statistics
     L->shadow_bytes = Bp * d * e;
@@ -247,7 +247,7 @@ struct aed_decoder {
     struct FragWeights { const void *w_qkv, *w_o, *w_cq, *w_ckv, *w_co, *w_ff1, *w_ff2; };
     std::vector<FragWeights> fw;            // the matrices re-ordered into fragment order (workspace)
     struct LnFold { const float *qkv_c1, *qkv_c2, *cq_c1, *cq_c2, *ff1_c1, *ff1_c2; };
-    std::vector<LnFold> fold;               // bfloat16 mode: W . g and W . b + bias of every LayerNorm product
+    std::vector<LnFold> fold;               // W . g and W . b + bias of every LayerNorm product
     const float *out_c1 = nullptr, *out_c2 = nullptr;
     struct Merged { const void* w_p2; const float* cb_cq; };  // Wcq.g . Wo (fragment order), Wcq.g . bo
     std::vector<Merged> mw;
@@ -350,7 +350,6 @@ GemmArgs gemm_base(const aed_decoder* d, int layer) {
     GemmArgs g;
     memset(&g, 0, sizeof g);
     g.ln_eps = d->cfg.ln_eps;
-    g.ln_scratch = d->act + d->lay.ln_h;
     g.M = d->batch;
     g.n_heads = d->cfg.n_heads;
     g.head_dim = d->cfg.head_dim;
@@ -361,8 +360,7 @@ GemmArgs gemm_base(const aed_decoder* d, int layer) {
     return g;
 }
 
-// bfloat16 mode: the LayerNorm products read the shadow of the residual rows and their statistics
-bool folded_ln(const aed_decoder* d) { return d->dt == kBF16; }
+// The LayerNorm products read the shadow of the residual rows and their statistics
 float2* stats_buf(const aed_decoder* d, int par) {
     return reinterpret_cast<float2*>(d->act + d->lay.ln_stats) + (size_t)par * d->lay.stats_elems;
 }
@@ -390,29 +388,24 @@ void ln_consumer(const aed_decoder* d, GemmArgs& g, const float* c1, const float
 // self-attention output projection (kernels.h, "merged products"): one launch fewer per layer.
 constexpr int kMergeMaxRows = 256;
 static_assert(kMergeMaxRows < kFramesMinBatch, "cross-attention over the frames does not finish a merged query product");
-bool merged_products(const aed_decoder* d) { return folded_ln(d) && d->batch <= kMergeMaxRows; }
+bool merged_products(const aed_decoder* d) { return d->dt == kBF16 && d->batch <= kMergeMaxRows; }
 
 hipError_t k_ln_qkv(aed_decoder* d, int l) {
-    const aed_layer_weights& w = d->layers[l];
     GemmArgs g = gemm_base(d, l);
-    g.A = d->act_at<float>(d->lay.x);
-    g.W = d->fw[l].w_qkv; g.bias = w.b_qkv; g.ln_g = w.ln1_g; g.ln_b = w.ln1_b;
+    g.W = d->fw[l].w_qkv;
     g.N = 3 * d->cfg.d_model; g.K = d->cfg.d_model;
     g.out = d->act_at<float>(d->lay.q);
     g.k_pool = d->ws + d->lay.k_pool + (size_t)l * d->lay.pool_layer_elems * d->kv_esz;
     g.v_pool = d->ws + d->lay.v_pool + (size_t)l * d->lay.pool_layer_elems * d->kv_esz;
     g.kv_slot = d->at<int>(d->lay.kv_slot);
-    if (folded_ln(d)) {
-        ln_consumer(d, g, d->fold[l].qkv_c1, d->fold[l].qkv_c2, l, true);
-        if (merged_products(d)) {  // the stored matrix is [Wqkv.g1 ; Wcq.g2]: the last d columns are P1 of the merged products
-            g.N = 4 * d->cfg.d_model;
-            g.n_raw = 3 * d->cfg.d_model;
-            g.out2 = d->act_at<float>(d->lay.q_aux);
-            g.raw_bias = d->mw[l].cb_cq;
-        }
-        return launch_gemm(d->dt, PRO_LNS, EPI_QKV, g, d->stream);
+    ln_consumer(d, g, d->fold[l].qkv_c1, d->fold[l].qkv_c2, l, true);
+    if (merged_products(d)) {  // the stored matrix is [Wqkv.g1 ; Wcq.g2]: the last d columns are P1 of the merged products
+        g.N = 4 * d->cfg.d_model;
+        g.n_raw = 3 * d->cfg.d_model;
+        g.out2 = d->act_at<float>(d->lay.q_aux);
+        g.raw_bias = d->mw[l].cb_cq;
     }
-    return launch_gemm(d->dt, PRO_LN, EPI_QKV, g, d->stream);
+    return launch_gemm(d->dt, PRO_LNS, EPI_QKV, g, d->stream);
 }
 
 AttnArgs attn_base(const aed_decoder* d) {
@@ -452,15 +445,12 @@ hipError_t k_resid(aed_decoder* d, int l, const void* A, const void* W, const vo
     g.A = A; g.W = W; g.bias = bias;
     g.N = d->cfg.d_model; g.K = K;
     g.out = d->act_at<float>(d->lay.x);
-    if (folded_ln(d)) {
-        g.stats_out = stats_buf(d, d->x_par ^ 1);
-        g.mu_hat_in = shift_buf(d, l & 1);  // the mean of the rows that entered the layer
-        g.shadow_out = shadow_buf(d, d->x_par ^ 1);
-        g.stat_tiles = d->cfg.d_model / 16;
-        d->x_par ^= 1;
-        return launch_gemm(d->dt, PRO_T, EPI_RESID_S, g, d->stream);
-    }
-    return launch_gemm(d->dt, PRO_T, EPI_RESID, g, d->stream);
+    g.stats_out = stats_buf(d, d->x_par ^ 1);
+    g.mu_hat_in = shift_buf(d, l & 1);  // the mean of the rows that entered the layer
+    g.shadow_out = shadow_buf(d, d->x_par ^ 1);
+    g.stat_tiles = d->cfg.d_model / 16;
+    d->x_par ^= 1;
+    return launch_gemm(d->dt, PRO_T, EPI_RESID_S, g, d->stream);
 }
 
 // x += Wo . o + bo and, in the same launch, P2 = (Wcq.g . Wo) . o -> q (finished by cross-attention)
@@ -486,17 +476,12 @@ hipError_t k_self_out_crossq(aed_decoder* d, int l) {
 }
 
 hipError_t k_ln_crossq(aed_decoder* d, int l) {
-    const aed_layer_weights& w = d->layers[l];
     GemmArgs g = gemm_base(d, l);
-    g.A = d->act_at<float>(d->lay.x);
-    g.W = d->fw[l].w_cq; g.bias = w.b_cq; g.ln_g = w.ln2_g; g.ln_b = w.ln2_b;
+    g.W = d->fw[l].w_cq;
     g.N = d->cfg.d_model; g.K = d->cfg.d_model;
     g.out = d->act_at<float>(d->lay.q);
-    if (folded_ln(d)) {
-        ln_consumer(d, g, d->fold[l].cq_c1, d->fold[l].cq_c2, l, false);
-        return launch_gemm(d->dt, PRO_LNS, EPI_F32, g, d->stream);
-    }
-    return launch_gemm(d->dt, PRO_LN, EPI_F32, g, d->stream);
+    ln_consumer(d, g, d->fold[l].cq_c1, d->fold[l].cq_c2, l, false);
+    return launch_gemm(d->dt, PRO_LNS, EPI_F32, g, d->stream);
 }
 
 int cross_wavefronts(const aed_decoder* d) {
@@ -546,30 +531,21 @@ hipError_t k_cross_attn(aed_decoder* d, int l) {
 }
 
 hipError_t k_ln_ffn1(aed_decoder* d, int l) {
-    const aed_layer_weights& w = d->layers[l];
     GemmArgs g = gemm_base(d, l);
-    g.A = d->act_at<float>(d->lay.x);
-    g.W = d->fw[l].w_ff1; g.bias = w.b_ff1; g.ln_g = w.ln3_g; g.ln_b = w.ln3_b;
+    g.W = d->fw[l].w_ff1;
     g.N = d->cfg.d_ffn; g.K = d->cfg.d_model;
     g.out = d->act + d->lay.ffn_h;
-    if (folded_ln(d)) {
-        ln_consumer(d, g, d->fold[l].ff1_c1, d->fold[l].ff1_c2, l, false);
-        return launch_gemm(d->dt, PRO_LNS, EPI_RELU_T, g, d->stream);
-    }
-    return launch_gemm(d->dt, PRO_LN, EPI_RELU_T, g, d->stream);
+    ln_consumer(d, g, d->fold[l].ff1_c1, d->fold[l].ff1_c2, l, false);
+    return launch_gemm(d->dt, PRO_LNS, EPI_RELU_T, g, d->stream);
 }
 
 hipError_t k_ln_vocab(aed_decoder* d) {
     GemmArgs g = gemm_base(d, d->cfg.n_layers);
-    g.A = d->act_at<float>(d->lay.x);
-    g.W = d->fw_out; g.bias = d->w.b_out; g.ln_g = d->w.lnf_g; g.ln_b = d->w.lnf_b;
+    g.W = d->fw_out;
     g.N = d->cfg.vocab; g.K = d->cfg.d_model;
     g.out = d->act_at<float>(d->lay.logits);
-    if (folded_ln(d)) {
-        ln_consumer(d, g, d->out_c1, d->out_c2, d->cfg.n_layers, true);
-        return launch_gemm(d->dt, PRO_LNS, EPI_F32, g, d->stream);
-    }
-    return launch_gemm(d->dt, PRO_LN, EPI_F32, g, d->stream);
+    ln_consumer(d, g, d->out_c1, d->out_c2, d->cfg.n_layers, true);
+    return launch_gemm(d->dt, PRO_LNS, EPI_F32, g, d->stream);
 }
 
 // K/V of rows [0, rows) of the fragment-ordered encoder frames; frame_map (may be null) names the frame slot of
@@ -621,12 +597,10 @@ EmbedArgs embed_args(const aed_decoder* d) {
     ea.x = d->act_at<float>(d->lay.x);
     ea.tok_emb = d->w.tok_emb; ea.pos_emb = d->w.pos_emb;
     ea.d = d->cfg.d_model; ea.max_positions = d->cfg.max_positions; ea.emb_scale = d->cfg.emb_scale;
-    if (folded_ln(d)) {
-        ea.sh.shadow = shadow_buf(d, 0);
-        ea.sh.stats = stats_buf(d, 0);
-        ea.sh.mu_hat = shift_buf(d, 1);  // read as the shift of the rows entering layer 0
-        ea.sh.rms = d->cfg.norm_type == 1;
-    }
+    ea.sh.shadow = shadow_buf(d, 0);
+    ea.sh.stats = stats_buf(d, 0);
+    ea.sh.mu_hat = shift_buf(d, 1);  // read as the shift of the rows entering layer 0
+    ea.sh.rms = d->cfg.norm_type == 1;
     return ea;
 }
 hipError_t k_embed(aed_decoder* d, const StateArgs& st) { return launch_embed(d->dt, embed_args(d), st, d->stream); }
@@ -927,11 +901,11 @@ aed_status aed_decoder_create(const aed_config* cfg, const aed_weights* weights,
     {
         char* p = d->ws + L.w_frag;
         const int dm = cfg->d_model, F = cfg->d_ffn;
-        // bfloat16 mode: a matrix that follows a LayerNorm is stored with that LayerNorm's gain multiplied into its
-        // columns (the folded LayerNorm, kernels.h); float32 mode applies the gain to the rows instead
+        // a matrix that follows a LayerNorm is stored with that LayerNorm's gain multiplied into its columns (the folded
+        // LayerNorm, kernels.h)
         auto put = [&](const void* src, int N, int K, const void* gain = nullptr) -> const void* {
             void* dst = p;
-            if (e == hipSuccess) e = launch_reorder_weight(d->dt, src, folded_ln(d) ? gain : nullptr, dst, N, K, d->stream);
+            if (e == hipSuccess) e = launch_reorder_weight(d->dt, src, gain, dst, N, K, d->stream);
             p += (size_t)N * K * d->esz;
             return dst;
         };
@@ -951,7 +925,7 @@ aed_status aed_decoder_create(const aed_config* cfg, const aed_weights* weights,
         d->fw_out = put(d->w.w_out, cfg->vocab, dm, d->w.lnf_g);
         if (e != hipSuccess) return cleanup(e, "weight re-ordering");
     }
-    if (folded_ln(d)) {  // W . g and W . b + bias of every product that follows a LayerNorm
+    {   // W . g and W . b + bias of every product that follows a LayerNorm
         float* p = reinterpret_cast<float*>(d->ws + L.ln_fold);
         const int dm = cfg->d_model, F = cfg->d_ffn;
         e = hipSuccess;
@@ -972,7 +946,7 @@ aed_status aed_decoder_create(const aed_config* cfg, const aed_weights* weights,
         fold(d->w.w_out, d->w.lnf_g, d->w.lnf_b, d->w.b_out, cfg->vocab, &d->out_c1, &d->out_c2);
         if (e != hipSuccess) return cleanup(e, "folding LayerNorm gain and shift into the products");
     }
-    if (folded_ln(d)) {  // merged products: Wcq.g . Wo and Wcq.g . bo per layer
+    if (d->dt == kBF16) {  // merged products: Wcq.g . Wo and Wcq.g . bo per layer
         const int dm = cfg->d_model;
         char* p = d->ws + L.w_merge;
         float* v = reinterpret_cast<float*>(d->ws + L.merge_vec);
@@ -1523,22 +1497,19 @@ aed_status aed_kernel_work(aed_decoder* d, int32_t cls, double* bytes, double* f
     if (!bytes || !flops) return fail(d, AED_EINVAL, "NULL output");
     HIP_TRY(d, hipStreamSynchronize(d->stream));
     const double e = (double)d->esz, ekv = (double)d->kv_esz, B = d->batch, dm = d->cfg.d_model, F = d->cfg.d_ffn, V = d->cfg.vocab;
-    // ln: the product follows a LayerNorm.  float32 mode reads the float32 rows and the gain / shift vectors;
-    // bfloat16 mode reads the rows' shadow, their tile statistics and shifts, and the folded vectors c1, c2.
-    // resid: a residual update (float32 rows read and written); bfloat16 mode also writes shadow and statistics.
-    const bool folded = folded_ln(d);
+    // ln: the product follows a LayerNorm: the rows' shadow, their tile statistics and shifts, the folded vectors c1, c2.
+    // resid: a residual update (float32 rows read and written, shadow and statistics written).
     const double stats = (dm / 16) * B * 8;
-    auto gemm = [&](double M, double N, double K, double a_bytes, double out_bytes, bool ln, bool resid) {
-        *bytes = N * K * e + M * N * out_bytes;
-        if (!ln) *bytes += N * e + M * K * a_bytes;
-        else if (folded) *bytes += M * K * e + stats + M * 4 + 2 * N * 4;
-        else *bytes += N * e + M * K * 4 + 2 * K * e;
-        if (resid && folded) *bytes += M * N * e + 2 * stats + M * 4 + N * e;
+    auto gemm = [&](double M, double N, double K, double out_bytes, bool ln, bool resid) {
+        *bytes = N * K * e + M * N * out_bytes + M * K * e;
+        if (ln) *bytes += stats + M * 4 + 2 * N * 4;
+        else *bytes += N * e;
+        if (resid) *bytes += M * N * e + 2 * stats + M * 4 + N * e;
         *flops = 2 * M * N * K;
     };
     switch (cls) {
         case AED_K_LN_QKV:
-            gemm(B, 3 * dm, dm, 4, 0, true, false);
+            gemm(B, 3 * dm, dm, 0, true, false);
             *bytes += B * dm * 4 + 2 * B * dm * ekv;
             if (merged_products(d)) {  // the part of the cross-attention query product that reads the same rows rides along
                 *bytes += dm * dm * e + B * dm * 4;
@@ -1546,21 +1517,21 @@ aed_status aed_kernel_work(aed_decoder* d, int32_t cls, double* bytes, double* f
             }
             break;
         case AED_K_SELF_OUT:
-            gemm(B, dm, dm, e, 8, false, true);
+            gemm(B, dm, dm, 8, false, true);
             if (merged_products(d)) {  // the part of the cross-attention query product that reads o rides along
                 *bytes += dm * dm * e + B * dm * 4;
                 *flops += 2 * B * dm * dm;
             }
             break;
-        case AED_K_CROSS_OUT: gemm(B, dm, dm, e, 8, false, true); break;
+        case AED_K_CROSS_OUT: gemm(B, dm, dm, 8, false, true); break;
         case AED_K_LN_CROSSQ:
             if (merged_products(d)) { *bytes = 0; *flops = 0; break; }
-            gemm(B, dm, dm, 4, 4, true, false);
+            gemm(B, dm, dm, 4, true, false);
             break;
-        case AED_K_LN_FFN1: gemm(B, F, dm, 4, e, true, false); break;
-        case AED_K_FFN2: gemm(B, dm, F, e, 8, false, true); break;
-        case AED_K_LN_VOCAB: gemm(B, V, dm, 4, 4, true, false); break;
-        case AED_K_CROSS_KV: gemm((double)d->total_enc, 2 * dm, dm, e, ekv, false, false); break;
+        case AED_K_LN_FFN1: gemm(B, F, dm, e, true, false); break;
+        case AED_K_FFN2: gemm(B, dm, F, 8, false, true); break;
+        case AED_K_LN_VOCAB: gemm(B, V, dm, 4, true, false); break;
+        case AED_K_CROSS_KV: gemm((double)d->total_enc, 2 * dm, dm, ekv, false, false); break;
         case AED_K_SELF_ATTN: case AED_K_CROSS_ATTN: {
             double keys = 0;
             if (cls == AED_K_CROSS_ATTN) keys = (double)d->total_enc;

@@ -103,11 +103,6 @@ __device__ __forceinline__ void mma(f32x4& acc, const Frag16<bf16_t>& w, const F
     acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w.lo, a.lo, acc, 0, 0, 0);
     acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w.hi, a.hi, acc, 0, 0, 0);
 }
-__device__ __forceinline__ void mma(f32x4& acc, const Frag16<float>& w, const Frag16<float>& a) {
-#pragma unroll
-    for (int i = 0; i < 16; ++i) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(w.v[i], a.v[i], acc, 0, 0, 0);
-}
-
 // Four consecutive cache elements as 8-bit E4M3 codes (OCP 8-bit floating point: bias 7, no infinities, largest
 // magnitude 448): round to nearest even, done by the conversion instruction; saturation is done here.
 __device__ __forceinline__ void store4_fp8(unsigned char* p, f32x4 s) {
@@ -155,14 +150,12 @@ template <int EPI> __device__ __forceinline__ int row_slot(const GemmArgs& a, in
 }
 
 // One lane's four consecutive outputs C[m][n .. n+3] (bias already added) go where the epilogue says.
-// res: the residual read earlier from the same place (EPI_RESID only); slot: EPI_QKV: kv_slot[m], EPI_CROSSKV: the frame
+// slot: EPI_QKV: kv_slot[m], EPI_CROSSKV: the frame
 // of row m -- read by the caller once per row, ahead of the stores.
 template <typename T, int EPI>
-__device__ __forceinline__ void gemm_epilogue(const GemmArgs& a, int m, int n, f32x4 s, f32x4 res, int slot) {
+__device__ __forceinline__ void gemm_epilogue(const GemmArgs& a, int m, int n, f32x4 s, int slot) {
     constexpr int ES = sizeof(T);
-    if constexpr (EPI == EPI_RESID) {
-        *reinterpret_cast<f32x4*>(static_cast<char*>(a.out) + frag_elem_off<4>(m, n, a.N)) = res + s;
-    } else if constexpr (EPI == EPI_F32) {
+    if constexpr (EPI == EPI_F32) {
         store4(static_cast<float*>(a.out) + (size_t)m * a.N + n, s);
     } else if constexpr (EPI == EPI_RELU_T) {
         s[0] = fmaxf(s[0], 0.f); s[1] = fmaxf(s[1], 0.f); s[2] = fmaxf(s[2], 0.f); s[3] = fmaxf(s[3], 0.f);

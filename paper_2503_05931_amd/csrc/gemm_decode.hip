@@ -20,11 +20,10 @@
 //   * the weight fragment is the first MFMA operand: lane (r, g) then holds
 //     C[m = r][n = 4 g .. 4 g + 3], four consecutive outputs of one row, which
 //     is one 16-byte (fp32) or 8-byte (bf16) store, also into fragment order.
-// The LayerNorm prologue (batches up to 128 rows) keeps a wavefront's slice of
-// the fp32 residual rows in registers, gets the row statistics with two LDS
-// exchanges (mean, then centred sum of squares) and normalises in place, so the
-// rows are read once per workgroup.  Larger batches normalise once in a
-// separate small kernel (layernorm_frag_kernel) and stream the result.
+// A LayerNorm before a product is folded around it (kernels.h) in both storage types.  In float32 it was a prologue that
+// read, normalised and kept the rows before the first multiplication (up to 128 rows), or a launch of its own:
+// us a step of 4 layers of d_model 1024 with it / folded: batch 1 215 / 172, 32 247 / 202, 128 429 / 356, 256 588 / 543,
+// 900 1720 / 1691.
 #include <algorithm>
 
 #include "common.h"
@@ -35,33 +34,30 @@
 
 namespace aed {
 
-constexpr int kMaxLnBlocks = 4;  // PRO_LN: K <= 4 waves * 4 blocks * 64 = 1024
-
 // What a workgroup needs before its first request to memory: leading scalar arguments; the rest comes in a tail (kernel_tail.h)
 struct GemmStart { const void *W, *A; const float2* stats_in; int M, K, stat_tiles; };
 template <int PRO, int EPI> struct GemmFields {
-    static constexpr bool LNS = PRO == PRO_LNS, LN = PRO == PRO_LN, RS = EPI == EPI_RESID_S, QKV = EPI == EPI_QKV, CKV = EPI == EPI_CROSSKV,
+    static constexpr bool LNS = PRO == PRO_LNS, RS = EPI == EPI_RESID_S, QKV = EPI == EPI_QKV, CKV = EPI == EPI_CROSSKV,
                           ADD = EPI == EPI_F32 && PRO == PRO_T;
     template <typename F> __host__ __device__ __forceinline__ static void fields(GemmArgs& a, F f) {
         f(a.out);
         if constexpr (LNS) { f(a.ln_c1); f(a.ln_c2); f(a.mu_hat_out); } else f(a.bias);
         if constexpr (LNS && QKV) { f(a.out2); f(a.raw_bias); }
         if constexpr (LNS || RS) f(a.mu_hat_in);
-        if constexpr (LN) { f(a.ln_g); f(a.ln_b); }
         if constexpr (RS) { f(a.shadow_out); f(a.stats_out); }
         if constexpr (ADD) f(a.addend);
         if constexpr (QKV) { f(a.kv_slot); f(a.k_pool); f(a.v_pool); }
         if constexpr (CKV) { f(a.out_row_map); f(a.kc); f(a.vc); f(a.t_cap); }
         f(a.N);
-        if constexpr (LNS || LN) { f(a.rms); f(a.ln_eps); }
+        if constexpr (LNS) { f(a.rms); f(a.ln_eps); }
         if constexpr (LNS && QKV) f(a.n_raw);
         if constexpr (RS) f(a.stat_tiles);
         if constexpr (QKV) f(a.n_heads);
         if constexpr (QKV || CKV) { f(a.kv_fp8); f(a.head_dim); f(a.d_model); }
     }
     static constexpr int words() {
-        return 2 * (1 + (LNS ? 3 : 1) + (LNS && QKV ? 2 : 0) + (LNS || RS) + 2 * LN + 2 * RS + ADD + 3 * QKV + 4 * CKV) +
-               1 + (LNS || LN ? 2 : 0) + (LNS && QKV) + RS + QKV + (QKV || CKV ? 3 : 0);
+        return 2 * (1 + (LNS ? 3 : 1) + (LNS && QKV ? 2 : 0) + (LNS || RS) + 2 * RS + ADD + 3 * QKV + 4 * CKV) +
+               1 + (LNS ? 2 : 0) + (LNS && QKV) + RS + QKV + (QKV || CKV ? 3 : 0);
     }
 };
 
@@ -74,8 +70,7 @@ template <int PRO, int EPI> struct GemmFields {
 //  * everything a workgroup reads -- the first blocks of both operands, then row statistics, vectors, residual tile,
 //    cache slots -- is requested before anything is waited for.  The memory counter is in order and a load behind a
 //    branch makes the compiler wait for all loads before it, so no load sits behind one: indices are clamped instead
-//    (buffers of fragment order are padded to whole tiles), null operands are read from W and replaced by zero
-//    (the loads of the fused LayerNorm over a K that is not 1024 are the exception);
+//    (buffers of fragment order are padded to whole tiles), null operands are read from W and replaced by zero;
 //  * with NB known the k loop is straight-line code and each block is waited for on its own; with a run-time k loop
 //    around conditional loads the compiler waited for the blocks just requested.
 template <typename T, int PRO, int EPI, int MT, int NT, bool WNT, int NB, int NW = 4>
@@ -85,36 +80,42 @@ __device__ __forceinline__ void gemm_decode_body(const GemmStart& st, TailPtr ta
     constexpr int BM = 16 * MT, BN = 16 * NT;
     constexpr int EP = (MT * NT + NW - 1) / NW;  // output 4-vectors per thread in the epilogue
     constexpr int ES = sizeof(T);
-    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, r = lane & 15, g = lane >> 4;
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
     const int m0 = by * BM, n0 = bx * BN;
     const int K = NB > 0 ? NB * NW * 64 : st.K, M = st.M;
-    static_assert(NW == 4 || (PRO != PRO_LN && NB > 0), "more wavefronts: known K, no LayerNorm in front");
+    static_assert(NW == 4 || NB > 0, "more wavefronts: known K");
     const int nblk = K >> 8;  // 64-wide k blocks per wavefront
     const char* __restrict__ W = static_cast<const char*>(st.W);
     const char* __restrict__ A = static_cast<const char*>(st.A);
 
     constexpr bool LNS = PRO == PRO_LNS;         // LayerNorm folded around the product (see kernels.h)
     constexpr bool RS = EPI == EPI_RESID_S;      // residual update that also writes shadow and statistics
-    constexpr bool RES = EPI == EPI_RESID || RS;
 
     __shared__ f32x4 part[NW][MT * NT][64];
-    __shared__ float red[2][4][BM];
+    __shared__ float red[2][BM];  // LNS: the rows' means, the factors their products are scaled with
 
-    f32x4 acc[MT][NT];
+    // float32: either half of every block's products has its own sum.  A float32 decoder's error is made of the roundings along
+    // such sums, and two of half the length have fewer large ones (relative error of the logits against float64, one sum and a
+    // LayerNorm before the product / this: 4 layers of d_model 1024 4.07e-7 / 3.14e-7, 2 of 256 1.59e-7 / 1.44e-7; where every
+    // update moves a row's mean by three times its spread, 4.2e-6 / 5.2e-6: the shadow then carries that offset).
+    constexpr int SUMS = ES == 4 ? 2 : 1;
+    f32x4 acc[SUMS][MT][NT];
 #pragma unroll
-    for (int mt = 0; mt < MT; ++mt)
+    for (int i = 0; i < SUMS; ++i)
 #pragma unroll
-        for (int nt = 0; nt < NT; ++nt) acc[mt][nt] = f32x4{0.f, 0.f, 0.f, 0.f};
+        for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt) acc[i][mt][nt] = f32x4{0.f, 0.f, 0.f, 0.f};
 
     // block (n tile, k block i*4 + wave) of the re-ordered weights
     auto wblk = [&](int nt, int i) {
         return reinterpret_cast<const T*>(W + frag_block_off<ES>((n0 >> 4) + nt, i * NW + wave, K));
     };
 
-    // ---- the operand stream (everything but the float32-mode LayerNorm prologue): ring of D blocks in registers
+    // ---- the operand stream: ring of D blocks in registers
     constexpr int D0 = (MT + NT) <= 2 ? 8 : (MT + NT) <= 4 ? 4 : 2;
     constexpr int DMAX = ES == 4 && D0 > 2 ? D0 / 2 : D0;
-    constexpr int D = PRO == PRO_LN ? 1 : (NB > 0 && NB < DMAX ? NB : DMAX);
+    constexpr int D = NB > 0 && NB < DMAX ? NB : DMAX;
     Frag16<T> af[D][MT], wf[D][NT];
     // 16-row tiles: A through a buffer descriptor; the lanes of rows from M on ask beyond its end and get zeros without a
     // request.  One row, 24 layers: 97.5 -> 95.3 ms for three utterances of 40 tokens.  Larger tiles have few such rows.
@@ -138,7 +139,17 @@ __device__ __forceinline__ void gemm_decode_body(const GemmStart& st, TailPtr ta
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
-            for (int mt = 0; mt < MT; ++mt) mma(acc[mt][nt], wf[slot][nt], af[slot][mt]);
+            for (int mt = 0; mt < MT; ++mt) {
+                if constexpr (ES == 4) {
+#pragma unroll
+                    for (int i = 0; i < 16; ++i) {
+                        f32x4& sum = acc[i / 8][mt][nt];
+                        sum = __builtin_amdgcn_mfma_f32_16x16x4f32(wf[slot][nt].v[i], af[slot][mt].v[i], sum, 0, 0, 0);
+                    }
+                } else {
+                    mma(acc[0][mt][nt], wf[slot][nt], af[slot][mt]);
+                }
+            }
     };
     // LNS: tile statistics of the rows being multiplied, 16 lanes per row, four 16-column tiles per lane.  Of 16 rows they
     // are requested in front of the stream and combined while it is on its way (4.13 -> 3.96 us for the QKV product of one
@@ -162,8 +173,8 @@ __device__ __forceinline__ void gemm_decode_body(const GemmStart& st, TailPtr ta
             const float rstd = fold_norm(a.rms, (float)K, a.ln_eps, rs.y, rs.x);
             const int row = SR * p + (tid >> 4);
             if ((tid & 15) == 0 && row < BM) {
-                red[0][0][row] = rs.x;
-                red[1][0][row] = rstd;
+                red[0][row] = rs.x;
+                red[1][row] = rstd;
             }
         }
     };
@@ -188,8 +199,7 @@ __device__ __forceinline__ void gemm_decode_body(const GemmStart& st, TailPtr ta
         __builtin_amdgcn_sched_barrier(0);
     };
 
-    // ---- epilogue operands (they do not depend on the product), requested behind the stream's first blocks (behind
-    // the rows and weights where the fused LayerNorm reads them, which has no ring)
+    // ---- epilogue operands (they do not depend on the product), requested behind the stream's first blocks
     const T* __restrict__ bias = nullptr;
     // columns from n_raw on are not normalised here (n_raw is a multiple of every tile width: uniform)
     bool raw = false;
@@ -221,7 +231,7 @@ __device__ __forceinline__ void gemm_decode_body(const GemmStart& st, TailPtr ta
                 e_rbias[j] = load_global<typename Raw4<T>::type>(bias ? static_cast<const void*>(bias + n) : W);
             }
             if constexpr (LNS || RS) e_mu[j] = a.mu_hat_in[m];
-            if constexpr (RES) e_res[j] = *reinterpret_cast<const f32x4*>(static_cast<const char*>(a.out) + frag_elem_off<4>(m, n, a.N));
+            if constexpr (RS) e_res[j] = *reinterpret_cast<const f32x4*>(static_cast<const char*>(a.out) + frag_elem_off<4>(m, n, a.N));
             if constexpr (EPI == EPI_F32 && PRO == PRO_T)  // optional addend, float [M,N] row-major like the output
                 e_res[j] = load_global<f32x4>(a.addend ? static_cast<const void*>(a.addend + (size_t)mc * a.N + n) : W);
             if constexpr (EPI == EPI_QKV) e_slot[j] = a.kv_slot[mc];
@@ -232,97 +242,7 @@ __device__ __forceinline__ void gemm_decode_body(const GemmStart& st, TailPtr ta
         if constexpr (LNS && ST_FIRST) combine_stats();
     };
 
-    if constexpr (PRO == PRO_LN) {
-        const char* __restrict__ X = A;
-        constexpr int NL = NB > 0 ? NB : kMaxLnBlocks;
-        Frag16<float> xs[MT][NL];
-        // the rows first (their statistics are needed first), then the weights; with NB known no block is conditional
-#pragma unroll
-        for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-            for (int i = 0; i < NL; ++i)
-                if (NB > 0 || i < nblk)
-                    xs[mt][i] = load_frag(
-                        reinterpret_cast<const float*>(X + frag_block_off<4>((m0 >> 4) + mt, i * 4 + wave, K)), lane);
-        // the weight stream starts before the statistics are known
-        Frag16<T> wl[NT][NL];
-#pragma unroll
-        for (int i = 0; i < NL; ++i)
-            if (NB > 0 || i < nblk)
-#pragma unroll
-                for (int nt = 0; nt < NT; ++nt) wl[nt][i] = WNT ? load_frag_nt(wblk(nt, i), lane) : load_frag(wblk(nt, i), lane);
-        __builtin_amdgcn_sched_barrier(0);
-        request_epilogue();
-        // LayerNorm gain/shift for this lane's k values, fetched before the statistics are known
-        const T* __restrict__ G = static_cast<const T*>(a.ln_g);
-        const T* __restrict__ Bt = static_cast<const T*>(a.ln_b);
-        Frag16<T> gam_f[NL], bet_f[NL];
-#pragma unroll
-        for (int i = 0; i < NL; ++i)
-            if (NB > 0 || i < nblk) {
-                gam_f[i] = load_frag_rm(G + (i * 4 + wave) * 64 + g * 16);
-                bet_f[i] = load_frag_rm((Bt ? Bt : G) + (i * 4 + wave) * 64 + g * 16);
-            }
-        // row mean
-        float mean[MT], rstd[MT];
-#pragma unroll
-        for (int mt = 0; mt < MT; ++mt) {
-            float s = 0.f;
-#pragma unroll
-            for (int i = 0; i < NL; ++i)
-                if (NB > 0 || i < nblk)
-#pragma unroll
-                    for (int e = 0; e < 16; ++e) s += xs[mt][i].v[e];
-            s = rows4_sum(s);
-            if (g == 0) red[0][wave][mt * 16 + r] = s;
-        }
-        lds_barrier();  // the weights stay in flight
-#pragma unroll
-        for (int mt = 0; mt < MT; ++mt) {
-            int i = mt * 16 + r;
-            mean[mt] = a.rms ? 0.f : (red[0][0][i] + red[0][1][i] + red[0][2][i] + red[0][3][i]) / (float)K;
-            float s = 0.f;
-#pragma unroll
-            for (int b = 0; b < NL; ++b)
-                if (NB > 0 || b < nblk)
-#pragma unroll
-                    for (int e = 0; e < 16; ++e) {
-                        float c = xs[mt][b].v[e] - mean[mt];
-                        s += c * c;
-                    }
-            s = rows4_sum(s);
-            if (g == 0) red[1][wave][i] = s;
-        }
-        lds_barrier();
-#pragma unroll
-        for (int mt = 0; mt < MT; ++mt) {
-            int i = mt * 16 + r;
-            float var = (red[1][0][i] + red[1][1][i] + red[1][2][i] + red[1][3][i]) / (float)K;
-            rstd[mt] = 1.0f / sqrtf(var + a.ln_eps);
-        }
-#pragma unroll
-        for (int i = 0; i < NL; ++i) {
-            if (NB > 0 || i < nblk) {
-                float gam[16], bet[16];
-                unpack_frag(gam_f[i], gam);
-                unpack_frag(bet_f[i], bet);
-#pragma unroll
-                for (int e = 0; e < 16; ++e) bet[e] = Bt ? bet[e] : 0.f;
-                Frag16<T> al[MT];
-#pragma unroll
-                for (int mt = 0; mt < MT; ++mt) {
-                    float y[16];
-#pragma unroll
-                    for (int e = 0; e < 16; ++e) y[e] = (xs[mt][i].v[e] - mean[mt]) * rstd[mt] * gam[e] + bet[e];
-                    pack_frag(y, al[mt]);
-                }
-#pragma unroll
-                for (int nt = 0; nt < NT; ++nt)
-#pragma unroll
-                    for (int mt = 0; mt < MT; ++mt) mma(acc[mt][nt], wl[nt][i], al[mt]);
-            }
-        }
-    } else if constexpr (NB > 0) {
+    if constexpr (NB > 0) {
         start_ring();
         request_epilogue();
 #pragma unroll
@@ -370,7 +290,7 @@ __device__ __forceinline__ void gemm_decode_body(const GemmStart& st, TailPtr ta
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
-        for (int nt = 0; nt < NT; ++nt) part[wave][mt * NT + nt][lane] = acc[mt][nt];
+        for (int nt = 0; nt < NT; ++nt) part[wave][mt * NT + nt][lane] = SUMS == 2 ? acc[0][mt][nt] + acc[SUMS - 1][mt][nt] : acc[0][mt][nt];
     __syncthreads();
 
 #pragma unroll
@@ -390,7 +310,7 @@ __device__ __forceinline__ void gemm_decode_body(const GemmStart& st, TailPtr ta
         if constexpr (EPI == EPI_CROSSKV) e_slot[j] = a.out_row_map ? e_slot[j] : m;
         if constexpr (LNS) {
             const int rl = m - m0;
-            const float mu = red[0][0][rl], rstd = red[1][0][rl], shift = mu - e_mu[j];
+            const float mu = red[0][rl], rstd = red[1][rl], shift = mu - e_mu[j];
             if constexpr (EPI == EPI_QKV)
                 if (raw) {
                     // a product that belongs to a later normalisation of these rows (kernels.h, "merged products"):
@@ -399,7 +319,7 @@ __device__ __forceinline__ void gemm_decode_body(const GemmStart& st, TailPtr ta
                     continue;
                 }
             s = (s - shift * e_aux[j]) * rstd + e_bias[j];
-            gemm_epilogue<T, EPI>(a, m, n, s, e_res[j], e_slot[j]);
+            gemm_epilogue<T, EPI>(a, m, n, s, e_slot[j]);
             if (n == 0 && a.mu_hat_out) a.mu_hat_out[m] = mu;  // the layer's residual updates shift their shadows by this
         } else if constexpr (RS) {
             const float mu_old = e_mu[j];
@@ -414,7 +334,7 @@ __device__ __forceinline__ void gemm_decode_body(const GemmStart& st, TailPtr ta
         } else {
             s += e_bias[j];
             if constexpr (EPI == EPI_F32 && PRO == PRO_T) { if (a.addend) s += e_res[j]; }
-            gemm_epilogue<T, EPI>(a, m, n, s, e_res[j], e_slot[j]);
+            gemm_epilogue<T, EPI>(a, m, n, s, e_slot[j]);
         }
     }
 }
@@ -434,71 +354,6 @@ __global__ __launch_bounds__(64 * NW) void gemm_decode_pair_kernel(const void* W
         gemm_decode_body<T, PRO_T, EPI_RESID_S, MT, NT, WNT, NB, NW>(GemmStart{W0, A, nullptr, M, K, 0}, tail_at(32), blockIdx.x, blockIdx.y);
     else
         gemm_decode_body<T, PRO_T, EPI1, MT, NT, WNT, NB, NW>(GemmStart{W1, A, nullptr, M, K, 0}, tail_at(32 + sizeof(ArgTail)), blockIdx.x, blockIdx.y);
-}
-
-// ---------------------------------------------------------------- LayerNorm to fragment order
-// For larger batches the LayerNorm is not fused into the GEMM (every n-tile workgroup would re-read
-// and re-normalise all fp32 rows, and the resident rows starve the big tiles of registers): this
-// kernel writes h = LN(x) once, in the storage type and fragment order, and the GEMM streams it like
-// any other activation.  One wavefront per row: lane l holds the 16 k values of k-group l (block
-// l / 4, quarter l % 4), the statistics are two wavefront reductions -- no LDS, no barrier -- and
-// M / 4 workgroups spread the rows over the GPU.
-template <typename T>
-__global__ __launch_bounds__(256) void layernorm_frag_kernel(const char* __restrict__ X, const T* __restrict__ G,
-                                                             const T* __restrict__ Bt, char* __restrict__ Hout, int M,
-                                                             int K, float eps, int rms) {
-    constexpr int ES = sizeof(T);
-    const int lane = threadIdx.x & 63;
-    const int row = blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (row >= M) return;
-    const int n_groups = K >> 4;  // 16-wide k groups in a row (K <= 1024: at most 64, one per lane)
-    const bool live = lane < n_groups;
-    const int kb = lane >> 2, q = lane & 3;
-    const int frag_lane = q * 16 + (row & 15);
-    float x[16];
-    if (live) {
-        const f32x4* p = reinterpret_cast<const f32x4*>(X + frag_block_off<4>(row >> 4, kb, K)) + frag_lane;
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const f32x4 v = p[64 * j];
-            x[4 * j] = v[0]; x[4 * j + 1] = v[1]; x[4 * j + 2] = v[2]; x[4 * j + 3] = v[3];
-        }
-    } else {
-#pragma unroll
-        for (int e = 0; e < 16; ++e) x[e] = 0.f;
-    }
-    float s = 0.f;
-#pragma unroll
-    for (int e = 0; e < 16; ++e) s += x[e];
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) s += __shfl_xor(s, off);
-    const float mean = rms ? 0.f : s / (float)K;  // RMSNorm: no mean subtraction
-    float m2 = 0.f;
-    if (live) {
-#pragma unroll
-        for (int e = 0; e < 16; ++e) {
-            const float c = x[e] - mean;
-            m2 += c * c;
-        }
-    }
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) m2 += __shfl_xor(m2, off);
-    const float rstd = 1.0f / sqrtf(m2 / (float)K + eps);
-    if (!live) return;
-    const int k0 = lane * 16;
-    float gam[16], bet[16], y[16];
-    unpack_frag(load_frag_rm(G + k0), gam);
-    if (Bt) {
-        unpack_frag(load_frag_rm(Bt + k0), bet);
-    } else {
-#pragma unroll
-        for (int e = 0; e < 16; ++e) bet[e] = 0.f;
-    }
-#pragma unroll
-    for (int e = 0; e < 16; ++e) y[e] = (x[e] - mean) * rstd * gam[e] + bet[e];
-    Frag16<T> f;
-    pack_frag(y, f);
-    store_frag(reinterpret_cast<T*>(Hout + frag_block_off<ES>(row >> 4, kb, K)), frag_lane, f);
 }
 
 // The non-temporal hint for W (GemmArgs::w_nt) goes with launches of one workgroup per CU in at most four row tiles: the
@@ -540,7 +395,7 @@ static hipError_t launch_nb(const GemmArgs& a, hipStream_t s) {
         }
     }
     if constexpr (!(sizeof(T) == 2 && always_eight(MT * NT, NB))) {
-    if constexpr (sizeof(T) == 4 && PRO == PRO_T && MT * NT >= 4 && MT * NT <= 8) {
+    if constexpr (sizeof(T) == 4 && MT * NT >= 4 && MT * NT <= 8) {
         if (wgs > kCus) {
             static DeviceOnce once;
             hipError_t e = once.run([] {
@@ -565,7 +420,7 @@ static hipError_t launch_nb(const GemmArgs& a, hipStream_t s) {
 template <typename T, int PRO, int EPI, int MT, int NT>
 static hipError_t launch_one(const GemmArgs& a, hipStream_t s) {
     if (a.K == 1024) return launch_nb<T, PRO, EPI, MT, NT, 4>(a, s);
-    if constexpr (EPI == EPI_RESID || EPI == EPI_RESID_S)
+    if constexpr (EPI == EPI_RESID_S)
         if (a.K == 4096) return launch_nb<T, PRO, EPI, MT, NT, 16>(a, s);
     return launch_nb<T, PRO, EPI, MT, NT, 0>(a, s);
 }
@@ -583,12 +438,10 @@ static hipError_t launch_one(const GemmArgs& a, hipStream_t s) {
 // tile reads a weight panel more often: where weights come from memory, 64 x 32 is better than 32 x 64 (N = 4096, 128 rows 5.31 / 5.59,
 // from the caches 4.62 / 4.29).
 //
-// float32: whole rounds of 256 workgroups, because workgroups that share a CU gain little or lose (kOneWgLds; the fused
-// LayerNorm keeps its rows in registers, small tiles only, one workgroup per CU).  A round costs
-//  * behind the fused LayerNorm in proportion to BM + BN (K = 1024: 16 x 16 4.8 us, 32 x 16 7.0, 32 x 32 9.0, and 2.3 a launch);
-//  * else per k the larger of the matrix instructions (BM * BN at 154 TFLOP/s) and what the CU takes in, and 2.5 us of
-//    start-up.  Measured at K = 1024 / 4096, us a round: 16 x 16 2.8 / 7.5, 32 x 16 4.2 / 10.3, 32 x 32 6.4 / 17.5, 32 x 64 and
-//    64 x 32 11 / 33.5, 64 x 64 19.5 / 65.
+// float32: whole rounds of 256 workgroups, because workgroups that share a CU gain little or lose (kOneWgLds).  A round
+// costs per k the larger of the matrix instructions (BM * BN at 154 TFLOP/s) and what the CU takes in, and 2.5 us of
+// start-up.  Measured at K = 1024 / 4096, us a round: 16 x 16 2.8 / 7.5, 32 x 16 4.2 / 10.3, 32 x 32 6.4 / 17.5, 32 x 64 and
+// 64 x 32 11 / 33.5, 64 x 64 19.5 / 65.
 // Over 9 row counts from 65 to 1000 and the seven products of a 4-layer decoder (d_model 1024, FFN 4096, the cross K/V
 // product on four times the rows) this choice is on average 0.6 % slower than the fastest tile and nowhere more than 6 %;
 // choosing by bytes among all tiles was 20 % slower (130 rows: cross-attention query 15.0 us on 32 x 16, 10.2 on 32 x 32; FFN1
@@ -602,17 +455,14 @@ static TileId choose_tile(const GemmArgs& a, int n_out) {
     int best = 0;
     double best_cost = 1e300;
     long best_wgs = 0;
-    const int n_cands = PRO == PRO_LN ? 3 : 6;
-    static_assert(PRO != PRO_LNS || sizeof(T) == 2, "the folded LayerNorm is a bfloat16-mode path");
-    static_assert(PRO != PRO_LN || sizeof(T) == 4, "the fused LayerNorm is a float32-mode path");
-    for (int c = 0; c < n_cands; ++c) {
+    for (int c = 0; c < 6; ++c) {
         const int bm = 16 * cands[c].mt, bn = 16 * cands[c].nt;
         if (a.N % bn != 0 || (cands[c].mt == 1 && a.K > FragRows<sizeof(T)>::kMaxK)) continue;
         const long wgs = (long)((a.M + bm - 1) / bm) * (n_out / bn);
         double cost;
         if constexpr (sizeof(T) == 4) {
             const double rounds = (double)((wgs + kCus - 1) / kCus);
-            cost = rounds * (PRO == PRO_LN ? bm + bn : (double)a.K * std::max(bm * bn, 14 * (bm + bn)) + 450.0 * 1024);
+            cost = rounds * ((double)a.K * std::max(bm * bn, 14 * (bm + bn)) + 450.0 * 1024);
         } else {
             const double rounds = wgs > kCus ? (double)wgs / kCus : 1.0;
             double factor = 1.0;
@@ -631,15 +481,11 @@ static hipError_t launch_tiles(const GemmArgs& a, hipStream_t s) {
     if (best == T11) return launch_one<T, PRO, EPI, 1, 1>(a, s);
     if (best == T22) return launch_one<T, PRO, EPI, 2, 2>(a, s);
     if (best == T21) return launch_one<T, PRO, EPI, 2, 1>(a, s);
-    if constexpr (PRO != PRO_LN) {
-        if (best == T24) return launch_one<T, PRO, EPI, 2, 4>(a, s);
-        if (best == T42) return launch_one<T, PRO, EPI, 4, 2>(a, s);
-        return launch_one<T, PRO, EPI, 4, 4>(a, s);
-    }
-    return hipErrorInvalidValue;
+    if (best == T24) return launch_one<T, PRO, EPI, 2, 4>(a, s);
+    if (best == T42) return launch_one<T, PRO, EPI, 4, 2>(a, s);
+    return launch_one<T, PRO, EPI, 4, 4>(a, s);
 }
 
-constexpr int kLnFusedMaxM = 128;
 // The LDS-tiled kernel (bf16, 128 x 128 tiles, one workgroup a CU) takes as long for a few tiles as for 256 of them (K = 1024:
 // 14 to 15 us a round), the streaming kernel's time goes with the rows: the first is faster where its rounds are full to
 // more than 5/6.  K = 1024, us tiled / streamed: N = 4096, 700 rows (192 tiles) 14.4 / 13.7, 896 (224) 14.6 / 15.7, 1024 (256) 14.9 / 17.5,
@@ -663,13 +509,12 @@ static bool use_dma_crosskv(const GemmArgs& a) {
 // The row statistics behind a folded LayerNorm: 16 lanes share a row of at most 64 tiles (d_model <= 1024)
 static bool stat_tiles_ok(int n) { return n >= 4 && n % 4 == 0 && n <= 64; }
 
-// bfloat16: the LayerNorm is always folded around the product (PRO_LNS)
-static hipError_t launch_bf16(GemmPro pro, GemmEpi epi, const GemmArgs& a, hipStream_t s) {
-    typedef bf16_t T;
+template <typename T> static hipError_t launch_typed(GemmPro pro, GemmEpi epi, const GemmArgs& a, hipStream_t s) {
+    constexpr bool tiled = sizeof(T) == 2;  // the kernels with operands in LDS take bfloat16
     if (pro == PRO_LNS) {
         if (!a.stats_in || !a.mu_hat_in || !a.ln_c1 || !a.ln_c2 || !stat_tiles_ok(a.stat_tiles)) return hipErrorInvalidValue;
         if (epi == EPI_QKV && !a.kv_slot) return hipErrorInvalidValue;
-        if (use_tiled(a)) return launch_gemm_tiled(epi, a, s);
+        if (tiled && use_tiled(a)) return launch_gemm_tiled(epi, a, s);
         if (epi == EPI_QKV) return launch_tiles<T, PRO_LNS, EPI_QKV>(a, s);
         if (epi == EPI_F32) return launch_tiles<T, PRO_LNS, EPI_F32>(a, s);
         if (epi == EPI_RELU_T) return launch_tiles<T, PRO_LNS, EPI_RELU_T>(a, s);
@@ -680,37 +525,10 @@ static hipError_t launch_bf16(GemmPro pro, GemmEpi epi, const GemmArgs& a, hipSt
         return launch_tiles<T, PRO_T, EPI_RESID_S>(a, s);
     }
     if (pro == PRO_T && epi == EPI_CROSSKV) {
-        if (use_dma_crosskv(a)) return launch_gemm_dma_crosskv(a, s);
-        if (use_tiled(a)) return launch_gemm_tiled(epi, a, s);
+        if (tiled && use_dma_crosskv(a)) return launch_gemm_dma_crosskv(a, s);
+        if (tiled && use_tiled(a)) return launch_gemm_tiled(epi, a, s);
         return launch_tiles<T, PRO_T, EPI_CROSSKV>(a, s);
     }
-    return hipErrorInvalidValue;
-}
-
-static hipError_t launch_f32(GemmPro pro, GemmEpi epi, const GemmArgs& a0, hipStream_t s) {
-    typedef float T;
-    GemmArgs a = a0;
-    if (epi == EPI_QKV && !a.kv_slot) return hipErrorInvalidValue;
-    // fused LayerNorm while one round of 32x32 tiles covers the product; else LayerNorm once, separately
-    if (pro == PRO_LN && a.M > kLnFusedMaxM && (long)((a.M + 31) / 32) * (a.N / 32) > 256) {
-        // two launches: h = LN(x) in fragment order, then the plain streaming GEMM on h
-        if (!a.ln_scratch) return hipErrorInvalidValue;
-        hipLaunchKernelGGL(layernorm_frag_kernel<T>, dim3((a.M + 3) / 4), dim3(256), 0, s,
-                           static_cast<const char*>(a.A), static_cast<const T*>(a.ln_g), static_cast<const T*>(a.ln_b),
-                           static_cast<char*>(a.ln_scratch), a.M, a.K, a.ln_eps, a.rms);
-        hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
-        a.A = a.ln_scratch;
-        if (epi == EPI_QKV) return launch_tiles<T, PRO_T, EPI_QKV>(a, s);
-        if (epi == EPI_F32) return launch_tiles<T, PRO_T, EPI_F32>(a, s);
-        if (epi == EPI_RELU_T) return launch_tiles<T, PRO_T, EPI_RELU_T>(a, s);
-        return hipErrorInvalidValue;
-    }
-    if (pro == PRO_LN && epi == EPI_QKV) return launch_tiles<T, PRO_LN, EPI_QKV>(a, s);
-    if (pro == PRO_LN && epi == EPI_F32) return launch_tiles<T, PRO_LN, EPI_F32>(a, s);
-    if (pro == PRO_LN && epi == EPI_RELU_T) return launch_tiles<T, PRO_LN, EPI_RELU_T>(a, s);
-    if (pro == PRO_T && epi == EPI_RESID) return launch_tiles<T, PRO_T, EPI_RESID>(a, s);
-    if (pro == PRO_T && epi == EPI_CROSSKV) return launch_tiles<T, PRO_T, EPI_CROSSKV>(a, s);
     return hipErrorInvalidValue;
 }
 
@@ -758,8 +576,7 @@ hipError_t launch_gemm_pair(Dtype dt, const GemmArgs& a0, GemmEpi epi1, const Ge
 
 hipError_t launch_gemm(Dtype dt, GemmPro pro, GemmEpi epi, const GemmArgs& a, hipStream_t s) {
     if (a.M < 1 || a.K % 256 != 0 || a.N % 64 != 0) return hipErrorInvalidValue;
-    if (pro == PRO_LN && a.K > 256 * kMaxLnBlocks) return hipErrorInvalidValue;
-    return dt == kBF16 ? launch_bf16(pro, epi, a, s) : launch_f32(pro, epi, a, s);
+    return dt == kBF16 ? launch_typed<bf16_t>(pro, epi, a, s) : launch_typed<float>(pro, epi, a, s);
 }
 
 // ---------------------------------------------------------------- LayerNorm folding (once, at create)

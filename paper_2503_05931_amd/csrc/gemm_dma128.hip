@@ -239,7 +239,7 @@ __global__ __launch_bounds__(256) void gemm_dma128_kernel(GemmArgs a) {
                     if (m >= a.M) continue;
                     if constexpr (LNS) v = (v - shift[mt] * c1) * rstd[mt] + bv;
                     else v += bv;
-                    gemm_epilogue<T, EPI>(a, m, n, v, f32x4{0.f, 0.f, 0.f, 0.f}, slot_of_row[mt]);
+                    gemm_epilogue<T, EPI>(a, m, n, v, slot_of_row[mt]);
                 }
             }
         zero_acc();

@@ -165,11 +165,8 @@ __global__ __launch_bounds__(256) void gemm_tiled_kernel(GemmArgs a) {
         for (int i = 0; i < WM; ++i) {
             const int m = m0 + (wm * WM + i) * 16 + r;
             if (m >= a.M) continue;
-            f32x4 res = f32x4{0.f, 0.f, 0.f, 0.f};
-            if constexpr (EPI == EPI_RESID)
-                res = *reinterpret_cast<const f32x4*>(static_cast<const char*>(a.out) + frag_elem_off<4>(m, n, a.N));
-            if constexpr (LNS) gemm_epilogue<T, EPI>(a, m, n, (acc[i][j] - shift[i] * c1) * rstd[i] + bv, res, slot[i]);
-            else gemm_epilogue<T, EPI>(a, m, n, acc[i][j] + bv, res, slot[i]);
+            if constexpr (LNS) gemm_epilogue<T, EPI>(a, m, n, (acc[i][j] - shift[i] * c1) * rstd[i] + bv, slot[i]);
+            else gemm_epilogue<T, EPI>(a, m, n, acc[i][j] + bv, slot[i]);
         }
     }
 }
@@ -194,7 +191,7 @@ static hipError_t launch_tiled_one(const GemmArgs& a, hipStream_t s) {
 hipError_t launch_gemm_tiled(GemmEpi epi, const GemmArgs& a, hipStream_t s) {
     if (a.M < 1 || a.N % 128 != 0 || a.K % 64 != 0) return hipErrorInvalidValue;
     // from 8 k-blocks on, the same tile fed by direct-to-LDS loads (several k-steps in flight) is used instead
-    if (a.K >= 512 && epi != EPI_RESID) return launch_gemm_dma128(epi, a, s);
+    if (a.K >= 512) return launch_gemm_dma128(epi, a, s);
     // Measured on MI355X for the cross K/V GEMM (K = 1024, N = 2048, bf16), TFLOP/s at M = 7 217 / 512 000:
     //   128x128 tile, D = 1: 627 / 684      256x128, D = 1: 485 / 529      128x64, D = 1: 567 / 621
     //   128x128, D = 2: 410 / 419 (one workgroup per CU instead of two: registers)
@@ -213,7 +210,6 @@ hipError_t launch_gemm_tiled(GemmEpi epi, const GemmArgs& a, hipStream_t s) {
     switch (epi) {
         case EPI_CROSSKV: return launch_tiled_one<EPI_CROSSKV, 4, 4, 1, false>(a, s);
         case EPI_QKV: return launch_tiled_one<EPI_QKV, 4, 4, 1, false>(a, s);
-        case EPI_RESID: return launch_tiled_one<EPI_RESID, 4, 4, 1, false>(a, s);
         case EPI_F32: return launch_tiled_one<EPI_F32, 4, 4, 1, false>(a, s);
         case EPI_RELU_T: return launch_tiled_one<EPI_RELU_T, 4, 4, 1, false>(a, s);
         default: break;

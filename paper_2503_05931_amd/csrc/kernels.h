@@ -12,7 +12,7 @@ constexpr int kPage = 16;  // tokens per self-attention KV page
 
 // ---------------------------------------------------------------- decode GEMM
 // C[M,N] = prologue(A)[M,K] . W[N,K]^T (+bias), then an epilogue.
-// PRO_LNS (bfloat16 mode): the LayerNorm is folded around the product instead of being applied to the operand.
+// PRO_LNS: the LayerNorm is folded around the product instead of being applied to the operand.
 // Whoever writes the residual rows x (embedding, EPI_RESID_S) also writes their "shadow" x - mu_hat in the
 // storage type and fragment order (mu_hat: the row mean before the update, so the shadow has no large common
 // offset) and per-row statistics of x; the gain g of the LayerNorm is multiplied into the matrix once, when the
@@ -20,24 +20,21 @@ constexpr int kPage = 16;  // tokens per self-attention KV page
 //   W . LN(x) + bias = rstd * (Wg . shadow - (mu - mu_hat) * c1) + c2,  c1 = Wg . 1,  c2 = W . b + bias,
 // so the product streams half the bytes of the float32 rows and needs no pass over them first, and one shadow
 // serves every product that reads the rows.
-enum GemmPro { PRO_LN = 0, PRO_T = 1, PRO_LNS = 2 };
-// EPI_RESID_S: EPI_RESID that also writes the shadow and the statistics of the updated rows.
-enum GemmEpi { EPI_QKV = 0, EPI_RESID = 1, EPI_F32 = 2, EPI_RELU_T = 3, EPI_CROSSKV = 4, EPI_RESID_S = 5 };
+enum GemmPro { PRO_T, PRO_LNS };
+// EPI_RESID_S: residual update that also writes the shadow and the statistics of the updated rows.
+enum GemmEpi { EPI_QKV, EPI_F32, EPI_RELU_T, EPI_CROSSKV, EPI_RESID_S };
 
 struct GemmArgs {
-    const void* A;        // PRO_LN: float [M,K] (residual stream); PRO_T: T [M,K]; both in fragment order
+    const void* A;        // T [M,K] in fragment order (PRO_LNS: the rows' shadow)
     int n_raw;            // PRO_LNS + EPI_QKV, streaming kernel: columns [n_raw, N) (n_raw = 3 d_model) are not normalised and not
     float* out2;          // part of q/k/v: their bare sums plus raw_bias go to out2, float [M, N - n_raw] row-major.  0: no such columns
     const float* raw_bias;  // [N - n_raw]
     const float* addend;  // PRO_T + EPI_F32, streaming kernel, may be null: float [M,N] row-major added to the result
     const void* W;        // T [N,K] in fragment order (launch_reorder_weight)
     const void* bias;     // T [N] or null
-    const void* ln_g;     // T [K]  (PRO_LN)
-    const void* ln_b;     // T [K]
     float ln_eps;
-    void* ln_scratch;     // T [M,K] fragment order: LN(x) when the LayerNorm runs as its own launch (M > 128)
     int M, N, K;
-    void* out;            // EPI_RESID: float [M,N] fragment order, += ; EPI_F32: float [M,N] row-major;
+    void* out;            // EPI_RESID_S: float [M,N] fragment order, += ; EPI_F32: float [M,N] row-major;
                           // EPI_RELU_T: T [M,N] fragment order; EPI_QKV: float q [M,d_model] row-major
     // EPI_QKV: columns [d,2d) and [2d,3d) go to the paged self-attention cache of this layer
     void* k_pool;         // T (or E4M3 codes, kv_fp8) [pages][H][16][Dh]
@@ -64,19 +61,19 @@ struct GemmArgs {
     void* shadow_out;        // EPI_RESID_S: T [M,N] fragment order
     int stat_tiles;
     int kv_fp8;              // EPI_QKV / EPI_CROSSKV: the caches hold 8-bit E4M3 codes instead of T
-    int rms;                 // the normalisation is RMSNorm (no mean subtraction; ln_b may be null) instead of LayerNorm:
-                             // PRO_LN normalises that way, PRO_LNS reads the statistics that way (see fold_norm)
+    int rms;                 // the normalisation is RMSNorm (no mean subtraction) instead of LayerNorm: PRO_LNS reads the
+                             // statistics that way (see fold_norm)
     int w_nt;                // streaming kernel: load W with the non-temporal hint (weights that are not expected to
                              // survive in the caches until the next step anyway, and should not push other data out)
 };
 
 // Buffers in fragment order must hold a multiple of 128 rows (rows >= M are read, never written).
 // Returns hipSuccess or the launch error.  Requirements (checked by the caller):
-// K % 256 == 0, N % 64 == 0, PRO_LN: K <= 1024.
+// K % 256 == 0, N % 64 == 0.
 hipError_t launch_gemm(Dtype dt, GemmPro pro, GemmEpi epi, const GemmArgs& a, hipStream_t s);
 // LDS-tiled MFMA GEMM for large M (bf16 only; fragment-order A padded to a multiple of 128 rows, N % 128 == 0)
 hipError_t launch_gemm_tiled(GemmEpi epi, const GemmArgs& a, hipStream_t s);
-// the same 128 x 128 tile fed by direct-to-LDS loads (bf16, K >= 512, not EPI_RESID); a.ln_c1 != null: PRO_LNS
+// the same 128 x 128 tile fed by direct-to-LDS loads (bf16, K >= 512); a.ln_c1 != null: PRO_LNS
 hipError_t launch_gemm_dma128(GemmEpi epi, const GemmArgs& a, hipStream_t s);
 // bf16 cross K/V product with 256 x 256 tiles fed by direct-to-LDS loads; A must hold whole 256-row tiles
 hipError_t launch_gemm_dma_crosskv(const GemmArgs& a, hipStream_t s);
@@ -186,8 +183,7 @@ struct StateArgs {
     int4* items;      // [n_items] cross-attention work list (AttnArgs::items): the sampler marks a finished sequence's
     int n_items;      // items with kItemOff, launch_reset and launch_prepare_timing take the marks off
 };
-// What the folded LayerNorm of the first layer needs beside the rows themselves (bfloat16 mode; see PRO_LNS).
-// shadow == null: not written.
+// What the folded LayerNorm of the first layer needs beside the rows themselves (see PRO_LNS).  shadow == null: not written.
 struct ShadowArgs {
     void* shadow;       // T [B, d] fragment order: x - row mean
     float2* stats;      // [B][d / 16]: mean and sum of squared deviations of every 16-column tile
