@@ -1542,6 +1542,10 @@ aed_status aed_kernel_work(aed_decoder* d, int32_t cls, double* bytes, double* f
             }
             *bytes = keys * 2 * dm * ekv + B * dm * 4 + B * dm * e;
             *flops = keys * 4 * dm;
+            if (cls == AED_K_CROSS_ATTN && d->frames) {  // one copy of the frames for all heads; Wk and Wv
+                *bytes = keys * dm * e + 2 * dm * dm * e + B * dm * 4 + B * dm * e;
+                *flops = keys * 4 * dm * d->cfg.n_heads + 4 * B * dm * dm;
+            }
             break;
         }
         default: return fail(d, AED_EINVAL, "unknown kernel class");

@@ -5,7 +5,7 @@ sampled sequences, tolerance of the other bfloat16 tests."""
 import numpy as np
 import pytest
 
-from paper_2503_05931_amd import workloads as W
+from paper_2503_05931_amd import binding, workloads as W
 
 pytestmark = pytest.mark.gpu
 
@@ -35,6 +35,8 @@ def test_frames_attention(oracle, batch, norm_type):
     glog, gids = G.forced_logits_gpu(dec, wl, toks, rows)
     err, _ = G.check_forced(ref, glog, gids, G.TOL["bf16"])
     print(f"batch {batch}: max |dlogit| = {err:.2e}")
+    # what a launch is said to move: every frame once, the two matrices, queries and outputs
+    assert dec.aed_kernel_work(binding.K_CROSS_ATTN)[0] == 2 * 1024 * (int(wl.enc_lens.sum()) + 2 * 1024) + batch * 1024 * 6
     # frames of another sequence count for nothing, whatever they hold
     at = int(wl.enc_lens[:3].sum())
     wl.enc[at:at + wl.enc_lens[3]] = np.inf
