@@ -18,7 +18,7 @@ constexpr int kPage = 16;  // tokens per self-attention KV page
 // offset) and per-row statistics of x; the gain g of the LayerNorm is multiplied into the matrix once, when the
 // decoder is created (Wg = W . diag(g), rounded to the storage type), and then
 //   W . LN(x) + bias = rstd * (Wg . shadow - (mu - mu_hat) * c1) + c2,  c1 = Wg . 1,  c2 = W . b + bias,
-// so the product streams half the bytes of the float32 rows and needs no pass over them first, and one shadow
+// so the product streams rows of the storage type (bfloat16: half the bytes) and needs no pass over them first, and one shadow
 // serves every product that reads the rows.
 enum GemmPro { PRO_T, PRO_LNS };
 // EPI_RESID_S: residual update that also writes the shadow and the statistics of the updated rows.
@@ -89,7 +89,7 @@ hipError_t launch_fold_ln(Dtype dt, const void* W, const void* g, const void* b,
 hipError_t launch_reorder_weight(Dtype dt, const void* src, const void* gain, void* dst, int N, int K, hipStream_t s,
                                  int dst_k0 = 0, int dst_K = 0);
 
-// Merged products (bfloat16 mode, at most 256 rows).  A residual update x' = x + Wa . o + ba followed by a LayerNorm
+// Merged products (bfloat16, at most 256 rows).  A residual update x' = x + Wa . o + ba followed by a LayerNorm
 // product Wb . LN(x') reads, in folded form, Wbg . (x' - mu_hat) = Wbg . (x - mu_hat) + (Wbg . Wa) . o + Wbg . ba.
 // With the matrix product Wbg . Wa formed once at create, the second product no longer waits for the update:
 //   P1 = Wbg . (x - mu_hat) + cb   needs only the shadow of x: computed by the launch that already reads that shadow
