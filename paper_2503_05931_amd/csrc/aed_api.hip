@@ -139,8 +139,8 @@ void make_layout(const aed_config* c, Layout* L) {
     L->attn_out = take(Bp * d * e);
     L->ffn_h = take(Bp * (size_t)c->d_ffn * e);
     take(Bp * d * e);  // not used: what aed_decode_step_noalloc takes and refuses (act_bytes) stays as it has been
-    // LayerNorm folded around the products (shadow of the residual rows, tile statistics in two
-    // buffers that alternate from one residual update to the next, row shifts, folded gain/shift vectors)
+    // LayerNorm around the products (tile statistics in two buffers that alternate from one residual update to the next, folded
+    // gain/shift vectors; bfloat16: shadow of the residual rows, row shifts -- float32 keeps their room for the same reason)
     L->x_shadow = take(2 * Bp * d * e);  // two buffers, alternating like the statistics
     L->shadow_bytes = Bp * d * e;
     L->stats_elems = (d / 16) * Bp;
@@ -247,7 +247,7 @@ struct aed_decoder {
     struct FragWeights { const void *w_qkv, *w_o, *w_cq, *w_ckv, *w_co, *w_ff1, *w_ff2; };
     std::vector<FragWeights> fw;            // the matrices re-ordered into fragment order (workspace)
     struct LnFold { const float *qkv_c1, *qkv_c2, *cq_c1, *cq_c2, *ff1_c1, *ff1_c2; };
-    std::vector<LnFold> fold;               // W . g and W . b + bias of every LayerNorm product
+    std::vector<LnFold> fold;               // W . g (bfloat16) and W . b + bias of every LayerNorm product
     const float *out_c1 = nullptr, *out_c2 = nullptr;
     struct Merged { const void* w_p2; const float* cb_cq; };  // Wcq.g . Wo (fragment order), Wcq.g . bo
     std::vector<Merged> mw;
@@ -360,7 +360,7 @@ GemmArgs gemm_base(const aed_decoder* d, int layer) {
     return g;
 }
 
-// The LayerNorm products read the shadow of the residual rows and their statistics
+// The LayerNorm products read the residual rows (bfloat16: their shadow) and their statistics
 float2* stats_buf(const aed_decoder* d, int par) {
     return reinterpret_cast<float2*>(d->act + d->lay.ln_stats) + (size_t)par * d->lay.stats_elems;
 }
@@ -375,13 +375,26 @@ char* shadow_buf(const aed_decoder* d, int par) { return d->act + d->lay.x_shado
 // writes buffer 1 for layer 0).  first: this product is the one that reads the rows entering `layer` (QKV, or the
 // vocabulary product with layer = n_layers).
 void ln_consumer(const aed_decoder* d, GemmArgs& g, const float* c1, const float* c2, int layer, bool first) {
-    g.A = shadow_buf(d, d->x_par);
     g.stats_in = stats_buf(d, d->x_par);
+    g.ln_c2 = c2;
+    g.stat_tiles = d->cfg.d_model / 16;
+    if (d->dt == kF32) {
+        g.A = d->act_at<float>(d->lay.x);
+        return;
+    }
+    g.A = shadow_buf(d, d->x_par);
     g.mu_hat_in = shift_buf(d, first ? (layer & 1) ^ 1 : layer & 1);
     g.mu_hat_out = first && layer < d->cfg.n_layers ? shift_buf(d, layer & 1) : nullptr;
     g.ln_c1 = c1;
-    g.ln_c2 = c2;
+}
+// The residual updates leave statistics and (bfloat16) shadow of the new rows
+void ln_producer(aed_decoder* d, GemmArgs& g, int layer) {
+    d->x_par ^= 1;
+    g.stats_out = stats_buf(d, d->x_par);
     g.stat_tiles = d->cfg.d_model / 16;
+    if (d->dt == kF32) return;
+    g.mu_hat_in = shift_buf(d, layer & 1);  // the mean of the rows that entered the layer
+    g.shadow_out = shadow_buf(d, d->x_par);
 }
 
 // Small batches in bfloat16 mode: the cross-attention query product is split over the QKV launch and the launch of the
@@ -445,11 +458,7 @@ hipError_t k_resid(aed_decoder* d, int l, const void* A, const void* W, const vo
     g.A = A; g.W = W; g.bias = bias;
     g.N = d->cfg.d_model; g.K = K;
     g.out = d->act_at<float>(d->lay.x);
-    g.stats_out = stats_buf(d, d->x_par ^ 1);
-    g.mu_hat_in = shift_buf(d, l & 1);  // the mean of the rows that entered the layer
-    g.shadow_out = shadow_buf(d, d->x_par ^ 1);
-    g.stat_tiles = d->cfg.d_model / 16;
-    d->x_par ^= 1;
+    ln_producer(d, g, l);
     return launch_gemm(d->dt, PRO_T, EPI_RESID_S, g, d->stream);
 }
 
@@ -461,17 +470,13 @@ hipError_t k_self_out_crossq(aed_decoder* d, int l) {
     a0.A = d->act + d->lay.attn_out; a0.W = d->fw[l].w_o; a0.bias = w.b_o;
     a0.N = dm; a0.K = dm;
     a0.out = d->act_at<float>(d->lay.x);
-    a0.stats_out = stats_buf(d, d->x_par ^ 1);
-    a0.mu_hat_in = shift_buf(d, l & 1);
-    a0.shadow_out = shadow_buf(d, d->x_par ^ 1);
-    a0.stat_tiles = dm / 16;
+    ln_producer(d, a0, l);
     GemmArgs a1 = gemm_base(d, l);
     a1.A = d->act + d->lay.attn_out;
     a1.W = d->mw[l].w_p2;
     a1.N = dm; a1.K = dm;
     a1.out = d->act_at<float>(d->lay.q);
     a1.addend = d->act_at<float>(d->lay.q_aux);  // P1, left by the layer's QKV launch
-    d->x_par ^= 1;
     return launch_gemm_pair(d->dt, a0, EPI_F32, a1, d->stream);
 }
 
@@ -597,10 +602,12 @@ EmbedArgs embed_args(const aed_decoder* d) {
     ea.x = d->act_at<float>(d->lay.x);
     ea.tok_emb = d->w.tok_emb; ea.pos_emb = d->w.pos_emb;
     ea.d = d->cfg.d_model; ea.max_positions = d->cfg.max_positions; ea.emb_scale = d->cfg.emb_scale;
-    ea.sh.shadow = shadow_buf(d, 0);
     ea.sh.stats = stats_buf(d, 0);
-    ea.sh.mu_hat = shift_buf(d, 1);  // read as the shift of the rows entering layer 0
-    ea.sh.rms = d->cfg.norm_type == 1;
+    if (d->dt == kBF16) {
+        ea.sh.shadow = shadow_buf(d, 0);
+        ea.sh.mu_hat = shift_buf(d, 1);  // read as the shift of the rows entering layer 0
+        ea.sh.rms = d->cfg.norm_type == 1;
+    }
     return ea;
 }
 hipError_t k_embed(aed_decoder* d, const StateArgs& st) { return launch_embed(d->dt, embed_args(d), st, d->stream); }
@@ -901,8 +908,7 @@ aed_status aed_decoder_create(const aed_config* cfg, const aed_weights* weights,
     {
         char* p = d->ws + L.w_frag;
         const int dm = cfg->d_model, F = cfg->d_ffn;
-        // a matrix that follows a LayerNorm is stored with that LayerNorm's gain multiplied into its columns (the folded
-        // LayerNorm, kernels.h)
+        // a matrix that follows a LayerNorm is stored with that LayerNorm's gain multiplied into its columns (PRO_LNS)
         auto put = [&](const void* src, int N, int K, const void* gain = nullptr) -> const void* {
             void* dst = p;
             if (e == hipSuccess) e = launch_reorder_weight(d->dt, src, gain, dst, N, K, d->stream);
@@ -925,14 +931,14 @@ aed_status aed_decoder_create(const aed_config* cfg, const aed_weights* weights,
         d->fw_out = put(d->w.w_out, cfg->vocab, dm, d->w.lnf_g);
         if (e != hipSuccess) return cleanup(e, "weight re-ordering");
     }
-    {   // W . g and W . b + bias of every product that follows a LayerNorm
+    {   // W . g (bfloat16) and W . b + bias of every product that follows a LayerNorm
         float* p = reinterpret_cast<float*>(d->ws + L.ln_fold);
         const int dm = cfg->d_model, F = cfg->d_ffn;
         e = hipSuccess;
         auto fold = [&](const void* Wm, const void* gv, const void* bv, const void* bias, int N, const float** c1,
                         const float** c2) {
             *c1 = p; *c2 = p + N;
-            if (e == hipSuccess) e = launch_fold_ln(d->dt, Wm, gv, bv, bias, p, p + N, N, dm, d->stream);
+            if (e == hipSuccess) e = launch_fold_ln(d->dt, Wm, gv, bv, bias, d->dt == kBF16 ? p : nullptr, p + N, N, dm, d->stream);
             p += 2 * (size_t)N;
         };
         d->fold.resize(cfg->n_layers);
@@ -1497,14 +1503,15 @@ aed_status aed_kernel_work(aed_decoder* d, int32_t cls, double* bytes, double* f
     if (!bytes || !flops) return fail(d, AED_EINVAL, "NULL output");
     HIP_TRY(d, hipStreamSynchronize(d->stream));
     const double e = (double)d->esz, ekv = (double)d->kv_esz, B = d->batch, dm = d->cfg.d_model, F = d->cfg.d_ffn, V = d->cfg.vocab;
-    // ln: the product follows a LayerNorm: the rows' shadow, their tile statistics and shifts, the folded vectors c1, c2.
-    // resid: a residual update (float32 rows read and written, shadow and statistics written).
+    // ln: the product follows a LayerNorm: the rows (bfloat16: their shadow and its shifts), their tile statistics, the folded vectors.
+    // resid: a residual update (float32 rows read and written, statistics and bfloat16's shadow written).
     const double stats = (dm / 16) * B * 8;
+    const bool shadow = d->dt == kBF16;
     auto gemm = [&](double M, double N, double K, double out_bytes, bool ln, bool resid) {
         *bytes = N * K * e + M * N * out_bytes + M * K * e;
-        if (ln) *bytes += stats + M * 4 + 2 * N * 4;
+        if (ln) *bytes += stats + N * 4 + (shadow ? M * 4 + N * 4 : 0);
         else *bytes += N * e;
-        if (resid) *bytes += M * N * e + 2 * stats + M * 4 + N * e;
+        if (resid) *bytes += 2 * stats + N * e + (shadow ? M * N * e + M * 4 : 0);
         *flops = 2 * M * N * K;
     };
     switch (cls) {

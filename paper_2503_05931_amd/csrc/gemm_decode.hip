@@ -20,10 +20,10 @@
 //   * the weight fragment is the first MFMA operand: lane (r, g) then holds
 //     C[m = r][n = 4 g .. 4 g + 3], four consecutive outputs of one row, which
 //     is one 16-byte (fp32) or 8-byte (bf16) store, also into fragment order.
-// A LayerNorm before a product is folded around it (kernels.h) in both storage types.  In float32 it was a prologue that
-// read, normalised and kept the rows before the first multiplication (up to 128 rows), or a launch of its own:
-// us a step of 4 layers of d_model 1024 with it / folded: batch 1 215 / 172, 32 247 / 202, 128 429 / 356, 256 588 / 543,
-// 900 1720 / 1691.
+// A LayerNorm before a product is taken around it (kernels.h) in both storage types.  In float32 it was a prologue that
+// normalised and kept the rows before the first multiplication (up to 128 rows), or a launch of its own; us a step of 4 layers of
+// d_model 1024 with it / with the mean taken off the operands as they arrive: batch 16 233.5 / 190.2, 32 246.6 / 203.7, 128
+// 428.9 / 359.0, 256 588.1 / 563.5, 900 1719 / 1722.
 #include <algorithm>
 
 #include "common.h"
@@ -36,28 +36,31 @@ namespace aed {
 
 // What a workgroup needs before its first request to memory: leading scalar arguments; the rest comes in a tail (kernel_tail.h)
 struct GemmStart { const void *W, *A; const float2* stats_in; int M, K, stat_tiles; };
-template <int PRO, int EPI> struct GemmFields {
+template <typename T, int PRO, int EPI> struct GemmFields {
     static constexpr bool LNS = PRO == PRO_LNS, RS = EPI == EPI_RESID_S, QKV = EPI == EPI_QKV, CKV = EPI == EPI_CROSSKV,
-                          ADD = EPI == EPI_F32 && PRO == PRO_T;
+                          ADD = EPI == EPI_F32 && PRO == PRO_T, SHADOW = sizeof(T) == 2;
     template <typename F> __host__ __device__ __forceinline__ static void fields(GemmArgs& a, F f) {
         f(a.out);
-        if constexpr (LNS) { f(a.ln_c1); f(a.ln_c2); f(a.mu_hat_out); } else f(a.bias);
-        if constexpr (LNS && QKV) { f(a.out2); f(a.raw_bias); }
-        if constexpr (LNS || RS) f(a.mu_hat_in);
-        if constexpr (RS) { f(a.shadow_out); f(a.stats_out); }
+        if constexpr (LNS) f(a.ln_c2); else f(a.bias);
+        if constexpr (LNS && SHADOW) { f(a.ln_c1); f(a.mu_hat_out); }
+        if constexpr (LNS && QKV && SHADOW) { f(a.out2); f(a.raw_bias); }
+        if constexpr ((LNS || RS) && SHADOW) f(a.mu_hat_in);
+        if constexpr (RS) f(a.stats_out);
+        if constexpr (RS && SHADOW) f(a.shadow_out);
         if constexpr (ADD) f(a.addend);
         if constexpr (QKV) { f(a.kv_slot); f(a.k_pool); f(a.v_pool); }
         if constexpr (CKV) { f(a.out_row_map); f(a.kc); f(a.vc); f(a.t_cap); }
         f(a.N);
         if constexpr (LNS) { f(a.rms); f(a.ln_eps); }
-        if constexpr (LNS && QKV) f(a.n_raw);
+        if constexpr (LNS && QKV && SHADOW) f(a.n_raw);
         if constexpr (RS) f(a.stat_tiles);
         if constexpr (QKV) f(a.n_heads);
         if constexpr (QKV || CKV) { f(a.kv_fp8); f(a.head_dim); f(a.d_model); }
     }
     static constexpr int words() {
-        return 2 * (1 + (LNS ? 3 : 1) + (LNS && QKV ? 2 : 0) + (LNS || RS) + 2 * RS + ADD + 3 * QKV + 4 * CKV) +
-               1 + (LNS ? 2 : 0) + (LNS && QKV) + RS + QKV + (QKV || CKV ? 3 : 0);
+        return 2 * (2 + (LNS ? 2 * SHADOW : 0) + (LNS && QKV ? 2 * SHADOW : 0) + ((LNS || RS) && SHADOW) + RS + (RS && SHADOW) + ADD +
+                    3 * QKV + 4 * CKV) +
+               1 + (LNS ? 2 : 0) + (LNS && QKV && SHADOW) + RS + QKV + (QKV || CKV ? 3 : 0);
     }
 };
 
@@ -75,7 +78,7 @@ template <int PRO, int EPI> struct GemmFields {
 //    around conditional loads the compiler waited for the blocks just requested.
 template <typename T, int PRO, int EPI, int MT, int NT, bool WNT, int NB, int NW = 4>
 __device__ __forceinline__ void gemm_decode_body(const GemmStart& st, TailPtr tail, const int bx, const int by) {
-    TailLoad<GemmFields<PRO, EPI>, GemmArgs> rest(tail);
+    TailLoad<GemmFields<T, PRO, EPI>, GemmArgs> rest(tail);
     GemmArgs a;
     constexpr int BM = 16 * MT, BN = 16 * NT;
     constexpr int EP = (MT * NT + NW - 1) / NW;  // output 4-vectors per thread in the epilogue
@@ -88,16 +91,17 @@ __device__ __forceinline__ void gemm_decode_body(const GemmStart& st, TailPtr ta
     const char* __restrict__ W = static_cast<const char*>(st.W);
     const char* __restrict__ A = static_cast<const char*>(st.A);
 
-    constexpr bool LNS = PRO == PRO_LNS;         // LayerNorm folded around the product (see kernels.h)
-    constexpr bool RS = EPI == EPI_RESID_S;      // residual update that also writes shadow and statistics
+    constexpr bool LNS = PRO == PRO_LNS;         // LayerNorm around the product (see kernels.h):
+    constexpr bool SHADOW = LNS && ES == 2;      // of the rows' shadow, corrected behind the product
+    constexpr bool CENTRE = LNS && ES == 4;      // of the rows themselves, their mean taken off in front of it
+    constexpr bool RS = EPI == EPI_RESID_S;      // residual update that also writes statistics (bfloat16: and shadow)
 
     __shared__ f32x4 part[NW][MT * NT][64];
     __shared__ float red[2][BM];  // LNS: the rows' means, the factors their products are scaled with
 
     // float32: either half of every block's products has its own sum.  A float32 decoder's error is made of the roundings along
-    // such sums, and two of half the length have fewer large ones (relative error of the logits against float64, one sum and a
-    // LayerNorm before the product / this: 4 layers of d_model 1024 4.07e-7 / 3.14e-7, 2 of 256 1.59e-7 / 1.44e-7; where every
-    // update moves a row's mean by three times its spread, 4.2e-6 / 5.2e-6: the shadow then carries that offset).
+    // such sums, and two of half the length have fewer large ones (relative error of the logits against float64, LayerNorm and one
+    // sum / this: 4 layers of d_model 1024 4.07e-7 / 3.01e-7, 2 of 256 1.59e-7 / 1.31e-7).
     constexpr int SUMS = ES == 4 ? 2 : 1;
     f32x4 acc[SUMS][MT][NT];
 #pragma unroll
@@ -135,7 +139,14 @@ __device__ __forceinline__ void gemm_decode_body(const GemmStart& st, TailPtr ta
         fetch_w(slot, i);
         fetch_a(slot, i);
     };
+    float mean[MT];  // CENTRE: of this lane's row of every tile (RMSNorm: 0)
     auto compute = [&](int slot) {
+        if constexpr (CENTRE) {
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+                for (int i = 0; i < 16; ++i) af[slot][mt].v[i] -= mean[mt];
+        }
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
@@ -154,8 +165,10 @@ __device__ __forceinline__ void gemm_decode_body(const GemmStart& st, TailPtr ta
     // LNS: tile statistics of the rows being multiplied, 16 lanes per row, four 16-column tiles per lane.  Of 16 rows they
     // are requested in front of the stream and combined while it is on its way (4.13 -> 3.96 us for the QKV product of one
     // row); of more rows they would hold it back (8.2 -> 8.9 us at 256 rows) and are requested behind its first blocks.
+    // CENTRE: the first multiplication waits for them, so they are in front of the stream always (4 layers of d_model 1024, us a step
+    // with them behind its first blocks / in front: 128 rows 359.3 / 349.5, 300 784.2 / 773.4).
     constexpr int SR = 4 * NW, SP = LNS ? (BM + SR - 1) / SR : 1;  // rows a pass, passes
-    constexpr bool ST_FIRST = MT == 1;
+    constexpr bool ST_FIRST = MT == 1 || CENTRE;
     f32x4 sv[SP][2];
     auto fetch_stats = [&]() {
 #pragma unroll
@@ -169,7 +182,8 @@ __device__ __forceinline__ void gemm_decode_body(const GemmStart& st, TailPtr ta
     auto combine_stats = [&]() {
 #pragma unroll
         for (int p = 0; p < SP; ++p) {
-            float2 rs = combine_tile_stats(sv[p][0], sv[p][1], 4 * (tid & 15) < st.stat_tiles, st.stat_tiles);
+            const bool live = 4 * (tid & 15) < st.stat_tiles;
+            float2 rs = combine_tile_stats<CENTRE>(sv[p][0], sv[p][1], 4 * (tid & 15) < st.stat_tiles, st.stat_tiles);
             const float rstd = fold_norm(a.rms, (float)K, a.ln_eps, rs.y, rs.x);
             const int row = SR * p + (tid >> 4);
             if ((tid & 15) == 0 && row < BM) {
@@ -205,9 +219,9 @@ __device__ __forceinline__ void gemm_decode_body(const GemmStart& st, TailPtr ta
     bool raw = false;
     // kept as loaded (null bias / addend: whatever W holds there) until the epilogue uses them: a conversion or a select
     // here would wait for everything requested so far
-    f32x4 e_bias[EP], e_res[EP], e_aux[EP];  // e_aux: c1 (LNS)
+    f32x4 e_bias[EP], e_res[EP], e_aux[EP];  // e_aux: c1 (SHADOW)
     typename Raw4<T>::type e_rbias[EP];      // not LNS
-    float e_mu[EP];                          // LNS: the shift this row's shadow was written with; RS: the row's
+    float e_mu[EP];                          // SHADOW: the shift this row's shadow was written with; RS: the row's
                                              // mean before the update = the shift its new shadow is written with
     int e_slot[EP];                          // EPI_QKV: cache slot of the row; EPI_CROSSKV: its frame
     auto tile_row = [&](int t, int l) { return m0 + (t / NT) * 16 + (l & 15); };
@@ -215,22 +229,24 @@ __device__ __forceinline__ void gemm_decode_body(const GemmStart& st, TailPtr ta
     auto request_epilogue = [&]() {
         rest.get(a);
         bias = static_cast<const T*>(a.bias);
-        if constexpr (LNS && EPI == EPI_QKV) raw = a.n_raw > 0 && n0 >= a.n_raw;
+        if constexpr (SHADOW && EPI == EPI_QKV) raw = a.n_raw > 0 && n0 >= a.n_raw;
 #pragma unroll
         for (int j = 0; j < EP; ++j) {
             const int t = MT * NT < NW ? min(wave, MT * NT - 1) : wave + NW * j;
             const int m = tile_row(t, lane), n = tile_col(t, lane), mc = min(m, M - 1);
             if constexpr (LNS) {
                 const float* c2 = a.ln_c2 + n;
-                if constexpr (EPI == EPI_QKV) c2 = raw ? a.raw_bias + (n - a.n_raw) : c2;
+                if constexpr (SHADOW && EPI == EPI_QKV) c2 = raw ? a.raw_bias + (n - a.n_raw) : c2;
                 e_bias[j] = load_global<f32x4>(c2);
-                int n_c1 = n;
-                if constexpr (EPI == EPI_QKV) n_c1 = raw ? n - a.n_raw : n;
-                e_aux[j] = *reinterpret_cast<const f32x4*>(a.ln_c1 + n_c1);
+                if constexpr (SHADOW) {
+                    int n_c1 = n;
+                    if constexpr (EPI == EPI_QKV) n_c1 = raw ? n - a.n_raw : n;
+                    e_aux[j] = *reinterpret_cast<const f32x4*>(a.ln_c1 + n_c1);
+                }
             } else {
                 e_rbias[j] = load_global<typename Raw4<T>::type>(bias ? static_cast<const void*>(bias + n) : W);
             }
-            if constexpr (LNS || RS) e_mu[j] = a.mu_hat_in[m];
+            if constexpr ((LNS || RS) && ES == 2) e_mu[j] = a.mu_hat_in[m];
             if constexpr (RS) e_res[j] = *reinterpret_cast<const f32x4*>(static_cast<const char*>(a.out) + frag_elem_off<4>(m, n, a.N));
             if constexpr (EPI == EPI_F32 && PRO == PRO_T)  // optional addend, float [M,N] row-major like the output
                 e_res[j] = load_global<f32x4>(a.addend ? static_cast<const void*>(a.addend + (size_t)mc * a.N + n) : W);
@@ -240,6 +256,11 @@ __device__ __forceinline__ void gemm_decode_body(const GemmStart& st, TailPtr ta
         if constexpr (LNS && !ST_FIRST) fetch_stats();
         __builtin_amdgcn_sched_barrier(0);
         if constexpr (LNS && ST_FIRST) combine_stats();
+        if constexpr (CENTRE) {
+            lds_barrier();
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt) mean[mt] = red[0][mt * 16 + (lane & 15)];
+        }
     };
 
     if constexpr (NB > 0) {
@@ -310,22 +331,23 @@ __device__ __forceinline__ void gemm_decode_body(const GemmStart& st, TailPtr ta
         if constexpr (EPI == EPI_CROSSKV) e_slot[j] = a.out_row_map ? e_slot[j] : m;
         if constexpr (LNS) {
             const int rl = m - m0;
-            const float mu = red[0][rl], rstd = red[1][rl], shift = mu - e_mu[j];
-            if constexpr (EPI == EPI_QKV)
+            const float mu = red[0][rl], rstd = red[1][rl];
+            if constexpr (SHADOW && EPI == EPI_QKV)
                 if (raw) {
                     // a product that belongs to a later normalisation of these rows (kernels.h, "merged products"):
                     // the bare sums (plus raw_bias) go to out2, whoever reads them finishes them
                     store4(a.out2 + (size_t)m * (a.N - a.n_raw) + (n - a.n_raw), s + e_bias[j]);
                     continue;
                 }
-            s = (s - shift * e_aux[j]) * rstd + e_bias[j];
+            if constexpr (SHADOW) s -= (mu - e_mu[j]) * e_aux[j];
+            s = s * rstd + e_bias[j];
             gemm_epilogue<T, EPI>(a, m, n, s, e_slot[j]);
-            if (n == 0 && a.mu_hat_out) a.mu_hat_out[m] = mu;  // the layer's residual updates shift their shadows by this
+            if constexpr (SHADOW)
+                if (n == 0 && a.mu_hat_out) a.mu_hat_out[m] = mu;  // the layer's residual updates shift their shadows by this
         } else if constexpr (RS) {
-            const float mu_old = e_mu[j];
             const f32x4 x = e_res[j] + s + e_bias[j];
             *reinterpret_cast<f32x4*>(static_cast<char*>(a.out) + frag_elem_off<4>(m, n, a.N)) = x;
-            store4(reinterpret_cast<T*>(static_cast<char*>(a.shadow_out) + frag_elem_off<ES>(m, n, a.N)), x - mu_old);
+            if constexpr (ES == 2) store4(reinterpret_cast<T*>(static_cast<char*>(a.shadow_out) + frag_elem_off<ES>(m, n, a.N)), x - e_mu[j]);
             // this row's 16 columns of the tile sit in the four lanes l, l ^ 16, l ^ 32, l ^ 48
             const float tmean = rows4_sum((x[0] + x[1]) + (x[2] + x[3])) * (1.f / 16.f);
             const f32x4 dv = x - tmean;
@@ -384,7 +406,7 @@ template <typename T, int PRO, int EPI, int MT, int NT, int NB>
 static hipError_t launch_nb(const GemmArgs& a, hipStream_t s) {
     dim3 grid(a.N / (16 * NT), (a.M + 16 * MT - 1) / (16 * MT));
     const long wgs = (long)grid.x * grid.y;
-    const ArgTail tail = make_tail<GemmFields<PRO, EPI>>(a);
+    const ArgTail tail = make_tail<GemmFields<T, PRO, EPI>>(a);
     unsigned lds = 0;
     // Where one workgroup has a CU to itself, eight wavefronts have its operands under way sooner than four.
     if constexpr (sizeof(T) == 2 && eight_wavefronts(MT * NT, NB)) {
@@ -512,7 +534,7 @@ static bool stat_tiles_ok(int n) { return n >= 4 && n % 4 == 0 && n <= 64; }
 template <typename T> static hipError_t launch_typed(GemmPro pro, GemmEpi epi, const GemmArgs& a, hipStream_t s) {
     constexpr bool tiled = sizeof(T) == 2;  // the kernels with operands in LDS take bfloat16
     if (pro == PRO_LNS) {
-        if (!a.stats_in || !a.mu_hat_in || !a.ln_c1 || !a.ln_c2 || !stat_tiles_ok(a.stat_tiles)) return hipErrorInvalidValue;
+        if (!a.stats_in || !a.ln_c2 || (tiled && (!a.mu_hat_in || !a.ln_c1)) || !stat_tiles_ok(a.stat_tiles)) return hipErrorInvalidValue;
         if (epi == EPI_QKV && !a.kv_slot) return hipErrorInvalidValue;
         if (tiled && use_tiled(a)) return launch_gemm_tiled(epi, a, s);
         if (epi == EPI_QKV) return launch_tiles<T, PRO_LNS, EPI_QKV>(a, s);
@@ -520,7 +542,7 @@ template <typename T> static hipError_t launch_typed(GemmPro pro, GemmEpi epi, c
         if (epi == EPI_RELU_T) return launch_tiles<T, PRO_LNS, EPI_RELU_T>(a, s);
     }
     if (pro == PRO_T && epi == EPI_RESID_S) {
-        if (!a.stats_out || !a.mu_hat_in || !a.shadow_out || !stat_tiles_ok(a.stat_tiles) || a.stat_tiles * 16 != a.N)
+        if (!a.stats_out || (tiled && (!a.mu_hat_in || !a.shadow_out)) || !stat_tiles_ok(a.stat_tiles) || a.stat_tiles * 16 != a.N)
             return hipErrorInvalidValue;
         return launch_tiles<T, PRO_T, EPI_RESID_S>(a, s);
     }
@@ -538,7 +560,7 @@ static hipError_t launch_pair_nb(const GemmArgs& a0, const GemmArgs& a1, hipStre
     const int rows = (a0.M + 16 * MT - 1) / (16 * MT);
     const dim3 grid(a0.N / (16 * NT), rows, 2);
     const long wgs = 2l * grid.x * rows;
-    const ArgTail t0 = make_tail<GemmFields<PRO_T, EPI_RESID_S>>(a0), t1 = make_tail<GemmFields<PRO_T, EPI1>>(a1);
+    const ArgTail t0 = make_tail<GemmFields<T, PRO_T, EPI_RESID_S>>(a0), t1 = make_tail<GemmFields<T, PRO_T, EPI1>>(a1);
     if constexpr (eight_wavefronts(MT * NT, NB)) {
         if (wgs <= kCus) {
             if (hint_w(a0, wgs, rows))
@@ -580,7 +602,7 @@ hipError_t launch_gemm(Dtype dt, GemmPro pro, GemmEpi epi, const GemmArgs& a, hi
 }
 
 // ---------------------------------------------------------------- LayerNorm folding (once, at create)
-// One wavefront per output column: c1[n] = sum_k W[n,k] g[k], c2[n] = sum_k W[n,k] b[k] + bias[n].
+// One wavefront per output column: c1[n] = sum_k W[n,k] g[k] (c1 null: not wanted), c2[n] = sum_k W[n,k] b[k] + bias[n].
 template <typename T>
 __global__ __launch_bounds__(256) void fold_ln_kernel(const T* __restrict__ W, const T* __restrict__ g,
                                                       const T* __restrict__ b, const T* __restrict__ bias,
@@ -599,7 +621,7 @@ __global__ __launch_bounds__(256) void fold_ln_kernel(const T* __restrict__ W, c
         s2 += __shfl_xor(s2, off);
     }
     if (lane == 0) {
-        c1[n] = s1;
+        if (c1) c1[n] = s1;
         c2[n] = s2 + (bias ? (float)bias[n] : 0.f);
     }
 }

@@ -21,7 +21,7 @@ __device__ __forceinline__ int slot_of(const StateArgs& st, int b, int pos) {
 
 __device__ __forceinline__ int clamped(int v, int n) { return v < 0 ? 0 : v >= n ? n - 1 : v; }
 
-// One row's embedding: the residual row and, where the LayerNorm is folded, its shadow, shift and tile statistics.  Every
+// One row's embedding: the residual row and its tile statistics, with bfloat16 its shadow and shift.  Every
 // thread of the workgroup; pv: the thread's elements of the position's row; slot: where the position is cached, -1: nowhere.
 template <typename T>
 __device__ __forceinline__ void embed_row(const EmbedArgs& ea, const StateArgs& st, int b, int tok, f32x4 pv, int slot) {
@@ -40,17 +40,18 @@ __device__ __forceinline__ void embed_row(const EmbedArgs& ea, const StateArgs& 
         o[3] = ea.emb_scale * ev[3] + pv[3];
         store4(reinterpret_cast<float*>(reinterpret_cast<char*>(ea.x) + frag_elem_off<4>(b, i, d)), o);
     }
-    if (!sh.shadow) return;
-    // row mean over the workgroup, then the shadow; tile statistics over the 4 threads of a 16-column tile
-    __shared__ float wsum[4];
-    float s = (o[0] + o[1]) + (o[2] + o[3]);
-    const float t4 = s;
+    float ts = (o[0] + o[1]) + (o[2] + o[3]);
+    float mean = 0.f;  // RMSNorm: no shift
+    if constexpr (sizeof(T) == 2) {  // row mean over the workgroup, for the shadow
+        __shared__ float wsum[4];
+        float s = ts;
 #pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) s += __shfl_xor(s, off);
-    if ((tid & 63) == 0) wsum[tid >> 6] = s;
-    __syncthreads();
-    const float mean = sh.rms ? 0.f : (wsum[0] + wsum[1] + wsum[2] + wsum[3]) / (float)d;  // RMSNorm: no shift
-    float ts = t4;
+        for (int off = 32; off >= 1; off >>= 1) s += __shfl_xor(s, off);
+        if ((tid & 63) == 0) wsum[tid >> 6] = s;
+        __syncthreads();
+        if (!sh.rms) mean = (wsum[0] + wsum[1] + wsum[2] + wsum[3]) / (float)d;
+    }
+    // tile statistics over the 4 threads of a 16-column tile
     ts += __shfl_xor(ts, 1);
     ts += __shfl_xor(ts, 2);
     const float tmean = ts * (1.f / 16.f);
@@ -59,9 +60,11 @@ __device__ __forceinline__ void embed_row(const EmbedArgs& ea, const StateArgs& 
     q += __shfl_xor(q, 1);
     q += __shfl_xor(q, 2);
     if (!live) return;
-    store4(reinterpret_cast<T*>(static_cast<char*>(sh.shadow) + frag_elem_off<sizeof(T)>(b, i, d)), o - mean);
     if ((tid & 3) == 0) sh.stats[(size_t)b * (d >> 4) + (i >> 4)] = float2{tmean, q};
-    if (tid == 0) sh.mu_hat[b] = mean;
+    if constexpr (sizeof(T) == 2) {
+        store4(reinterpret_cast<T*>(static_cast<char*>(sh.shadow) + frag_elem_off<2>(b, i, d)), o - mean);
+        if (tid == 0) sh.mu_hat[b] = mean;
+    }
 }
 
 // this thread's elements of a position's row

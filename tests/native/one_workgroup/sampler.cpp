@@ -116,7 +116,8 @@ template <typename T> void fill(int pos, int n, int limit, int max_new, int best
     args.items = w.items; args.n_items = kItems;
     emb = aed::EmbedArgs{};
     emb.x = w.x; emb.tok_emb = w.tok; emb.pos_emb = w.pos; emb.d = kDim; emb.max_positions = kPos; emb.emb_scale = 3.f;
-    if (shadow) { emb.sh.shadow = w.shadow; emb.sh.stats = w.stats; emb.sh.mu_hat = w.mu_hat; emb.sh.rms = rms; }
+    emb.sh.stats = w.stats;
+    if (shadow) { emb.sh.shadow = w.shadow; emb.sh.mu_hat = w.mu_hat; emb.sh.rms = rms; }
 }
 
 // the row that sequence kSeq feeds next: token tok at position pos, cached in slot
@@ -132,18 +133,18 @@ template <typename T> bool embedded(int tok, int pos, int slot) {
     // float32 sums of 320 values of at most 32: 320 * 2^-24 * 32 relative to the largest
     auto near = [](double a, double b) { return fabs(a - b) <= 7e-4; };
     for (int k = 0; k < kDim; ++k) ok = ok && w.x[aed::frag_elem_off<4>(kSeq, k, kDim) / 4] == (float)o[k];
+    for (int t = 0; t < kDim / 16; ++t) {
+        double m = 0, q = 0;
+        for (int k = 0; k < 16; ++k) m += o[16 * t + k] / 16;
+        for (int k = 0; k < 16; ++k) q += (o[16 * t + k] - m) * (o[16 * t + k] - m);
+        ok = ok && near(w.stats[kSeq * kDim / 16 + t].x, m) && fabs(w.stats[kSeq * kDim / 16 + t].y - q) <= 1e-5 * q + 1e-3;
+    }
     if (!emb.sh.shadow) return ok;
     const double shift = emb.sh.rms ? 0 : mean;
     ok = ok && near(w.mu_hat[kSeq], shift);
     for (int k = 0; k < kDim; ++k) {
         const double v = (float)w.shadow[aed::frag_elem_off<sizeof(T)>(kSeq, k, kDim) / sizeof(T)];
         ok = ok && fabs(v - (o[k] - shift)) <= fabs(o[k] - shift) / 256 + 7e-4;  // rounded to 8 bits
-    }
-    for (int t = 0; t < kDim / 16; ++t) {
-        double m = 0, q = 0;
-        for (int k = 0; k < 16; ++k) m += o[16 * t + k] / 16;
-        for (int k = 0; k < 16; ++k) q += (o[16 * t + k] - m) * (o[16 * t + k] - m);
-        ok = ok && near(w.stats[kSeq * kDim / 16 + t].x, m) && fabs(w.stats[kSeq * kDim / 16 + t].y - q) <= 1e-5 * q + 1e-3;
     }
     return ok;
 }
