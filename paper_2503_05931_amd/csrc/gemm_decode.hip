@@ -345,7 +345,9 @@ __device__ __forceinline__ void gemm_decode_body(const GemmStart& st, TailPtr ta
             if constexpr (SHADOW)
                 if (n == 0 && a.mu_hat_out) a.mu_hat_out[m] = mu;  // the layer's residual updates shift their shadows by this
         } else if constexpr (RS) {
-            const f32x4 x = e_res[j] + s + e_bias[j];
+            f32x4 x;
+            if constexpr (ES == 4) x = e_res[j] + (s + e_bias[j]);  // one rounding at the size of the row, not two
+            else x = e_res[j] + s + e_bias[j];
             *reinterpret_cast<f32x4*>(static_cast<char*>(a.out) + frag_elem_off<4>(m, n, a.N)) = x;
             if constexpr (ES == 2) store4(reinterpret_cast<T*>(static_cast<char*>(a.shadow_out) + frag_elem_off<ES>(m, n, a.N)), x - e_mu[j]);
             // this row's 16 columns of the tile sit in the four lanes l, l ^ 16, l ^ 32, l ^ 48

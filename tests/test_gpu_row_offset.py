@@ -1,5 +1,5 @@
 """float32 decoders whose residual rows have a common offset: the products behind a LayerNorm take the row's mean off in front of the
-multiplication (csrc/gemm_decode.hip).  Teacher-forced logits
+multiplication, and a residual update rounds once at the size of the row (csrc/gemm_decode.hip).  Teacher-forced logits
 against the oracle in float64, relative 2-norm."""
 import numpy as np
 import pytest
@@ -50,3 +50,28 @@ def test_updates_that_move_the_mean(oracle, d_model, per_shift, batch, where, sh
     print(f"d {d_model} batch {batch} {where} {shift}: {err:.2e} = {err / U:.1f} units")
     assert err <= U * (8 + per_shift * shift)
 
+
+# Rows of integers around 2^23, where float32 has integers only; every FFN adds a half of an integer by its product and the other half by
+# its bias.  Added to the row one after the other the halves are lost, which is up to 2e-2 of the logits; added up first
+# the row is exact.  The vocabulary rows have sum 0, so that the rounding of the row's mean does not count.  That of its 16 tiles' means
+# does: 0.35 on average, of means that are 64 / 4 apart, is 2 * 16 * 16 * 0.35 * sqrt(16) of a sum of squares of 256 * 64^2 or
+# 3.4e-4 of its root; three times that.
+@pytest.mark.parametrize("batch", [3, 40, 130])
+def test_a_residual_update_rounds_once(oracle, batch):
+    rng = np.random.default_rng(batch)
+    wl = workload(batch, 256, n_layers=2, emb_scale=1.0)
+    w = wl.weights
+    w["tok_emb"] = rng.integers(-110, 111, size=w["tok_emb"].shape).astype(np.float32)
+    w["pos_emb"] = np.full_like(w["pos_emb"], 2.0 ** 23 + 1000)
+    w["w_out"] = w["w_out"] - w["w_out"].mean(1, keepdims=True)
+    w["lnf_g"] = np.ones_like(w["lnf_g"])
+    for l in w["layers"]:
+        for k in ("w_o", "b_o", "w_co", "b_co", "w_ff1", "w_ff2"):
+            l[k] = np.zeros_like(l[k])
+        l["b_ff1"] = np.ones_like(l["b_ff1"])
+        half = 0.5 * rng.choice([-3, -1, 1, 3], size=wl.cfg.d_model).astype(np.float32)
+        l["w_ff2"][:, 7] = half
+        l["b_ff2"] = half
+    err = relative_error(oracle, wl, 2)
+    print(f"batch {batch}: {err:.2e}")
+    assert err <= 1e-3
