@@ -115,7 +115,8 @@ aed_status check_config(const aed_config* c, std::string& err) {
 
 // A decoder some of whose batches cross-attention may take over the frames (frames_attention)
 bool frames_possible(const aed_config* c) {
-    return c->dtype == 1 && !c->kv_fp8 && c->d_model == 1024 && c->head_dim == 128 && c->max_batch >= kFramesMinBatch;
+    return c->dtype == 1 && !c->kv_fp8 && c->d_model == 1024 && c->head_dim == 128 && c->max_batch >= kFramesMinBatch &&
+           c->max_total_enc_frames >= frames_min_keys(kFramesMinBatch);
 }
 
 void make_layout(const aed_config* c, Layout* L) {

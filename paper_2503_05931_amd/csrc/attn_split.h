@@ -90,8 +90,9 @@ inline void order_items(std::vector<int4>& items) {
 //   12 to 500      414   459    433   485    518   538    617   593    748   734    814   774   1088    982
 //   log-normal     324   460    340   476    396   513    438   546    556   661    599   680    765    819
 constexpr int kFramesMinBatch = 288;
+constexpr long long frames_min_keys(int batch) { return 140ll * batch + 60000; }
 inline bool frames_attention(long long total_keys, int longest_len, int batch) {
-    return batch >= kFramesMinBatch && total_keys >= 140ll * batch + 60000 && 256ll * longest_len <= total_keys;
+    return batch >= kFramesMinBatch && total_keys >= frames_min_keys(batch) && 256ll * longest_len <= total_keys;
 }
 
 // Wavefronts per workgroup, 4 or 8, of a launch of wgs workgroups over caches of kv_bytes an element.  What counts is that

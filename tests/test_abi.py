@@ -53,6 +53,20 @@ def test_workspace_bytes_counts_the_caches(lib):
     assert abs((n - n8) - (cross + self_kv) // 2) < (1 << 20)
 
 
+def test_only_decoders_that_can_read_the_frames_have_room_for_it(lib):
+    # cross-attention over the frames takes batches of 288 and more with 140 frames a sequence and 60 000 beside; its transposed key
+    # matrices and its scratch are no part of a decoder that has no room for such a batch
+    c = good_config()
+    c.max_batch, c.max_total_enc_frames = 512, 140 * 288 + 60000
+    n = binding.aed_workspace_bytes(c)
+    c.max_total_enc_frames -= 1
+    assert n - binding.aed_workspace_bytes(c) > 24 * 2 * 1024 * 1024 + 512 * 2 * 16 * 1024 * 2
+    c.max_batch, c.max_total_enc_frames = 287, 1 << 20
+    n = binding.aed_workspace_bytes(c)
+    c.max_batch = 288
+    assert binding.aed_workspace_bytes(c) - n > 24 * 2 * 1024 * 1024 + 288 * 2 * 16 * 1024 * 2
+
+
 @pytest.mark.parametrize("field,value,status", [
     ("struct_size", 4, binding.AED_EINVAL),
     ("n_layers", 0, binding.AED_EINVAL),
