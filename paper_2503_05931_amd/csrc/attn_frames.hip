@@ -121,8 +121,10 @@ __global__ __launch_bounds__(256) void frames_query_kernel(const float* __restri
 //    after t = 0 .. 3; the quarters of a block are stored 4 rows apart from each other, so that the four pieces lie in different banks;
 //  * the next step's frames are requested as soon as this step's are in LDS: 64 KB a workgroup, 128 KB a CU under way.
 // A prompt pass has several positions of a sequence: NQ of them are taken at once, with one reading of the frames.
+// Q and U begin with row row0.
 template <int NQ>
-__global__ __launch_bounds__(256, NQ == 1 ? 2 : 1) void attn_frames_kernel(const void* E, const void* Q, const int4* items, void* U, int first, int stride) {
+__global__ __launch_bounds__(256, NQ == 1 ? 2 : 1) void attn_frames_kernel(const void* E, const void* Q, const int4* items, void* U, int first, int stride,
+                                                                           int row0) {
     extern __shared__ __align__(16) char lds[];
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63, r = lane & 15, g = lane >> 4;
     const int4 it = items[blockIdx.x * stride + first];
@@ -131,6 +133,8 @@ __global__ __launch_bounds__(256, NQ == 1 ? 2 : 1) void attn_frames_kernel(const
 #pragma unroll
     for (int i = 1; i < NQ; ++i) b[i] = items[blockIdx.x * stride + first + i].x;
     if (b[0] < 0) return;  // the sequence has finished (kItemOff)
+#pragma unroll
+    for (int i = 0; i < NQ; ++i) b[i] -= row0;
     const int n = it.z & 0xFFFF, skip = it.w & 15;
     const int tiles = (skip + n + 15) >> 4, steps = (tiles + 1) >> 1;
     const char* src = static_cast<const char*>(E) + (size_t)(it.w >> 4) * (kD * 32) + wave * 8192;
@@ -273,7 +277,7 @@ __global__ __launch_bounds__(256, NQ == 1 ? 2 : 1) void attn_frames_kernel(const
     }
 }
 
-template <int NQ> static hipError_t launch_positions(const FramesArgs& a, int first, hipStream_t s) {
+template <int NQ> static hipError_t launch_positions(const FramesArgs& a, int first, int row0, hipStream_t s) {
     constexpr int kLds = 4 * kSlab + 2 * NQ * kPart;
     static DeviceOnce once;
     const hipError_t e = once.run([] {
@@ -281,7 +285,7 @@ template <int NQ> static hipError_t launch_positions(const FramesArgs& a, int fi
     });
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(attn_frames_kernel<NQ>, dim3(a.n_items / a.positions), dim3(256), kLds, s, a.frames, a.q_frames, a.items, a.u_frames, first,
-                       a.positions);
+                       a.positions, row0);
     return hipGetLastError();
 }
 
@@ -374,21 +378,24 @@ hipError_t launch_frames_weight(const void* W, void* dst, hipStream_t s) {
 }
 
 hipError_t launch_attn_frames(const FramesArgs& a, hipStream_t s) {
-    if (a.rows < 1 || a.n_items < 1 || !a.items || a.positions < 1 || a.n_items % a.positions != 0) return hipErrorInvalidValue;
-    hipError_t e;
-    const unsigned rows = (a.rows + 31) / 32;
-    hipLaunchKernelGGL(frames_query_kernel, dim3(kH, kD / 256, rows), dim3(256), 0, s, a.q, static_cast<const char*>(a.wk_t), static_cast<bf16_t*>(a.q_frames),
-                       a.rows, a.scale_log2e);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    for (int at = 0; at < a.positions;) {
-        const int nq = std::min(2, a.positions - at);  // of three the sums do not fit the registers
-        e = nq == 2 ? launch_positions<2>(a, at, s) : launch_positions<1>(a, at, s);
+    if (a.rows < 1 || a.n_items < 1 || !a.items || a.positions < 1 || a.n_items % a.positions != 0 || a.rows % a.positions != 0) return hipErrorInvalidValue;
+    const int Bs = a.rows / a.positions;
+    if (a.positions > 1 && Bs % 16 != 0) return hipErrorInvalidValue;  // a part of the output begins with a 16-row tile
+    // A prompt pass in parts of kFramesPositions positions, each with its queries and sums in the same scratch (64 KB a row): a batch
+    // has as much of it as two of its steps need, whatever the pass takes.
+    for (int at = 0; at < a.positions; at += kFramesPositions) {
+        const int nq = std::min(kFramesPositions, a.positions - at), row0 = at * Bs, rows = nq * Bs;
+        const unsigned tiles = (rows + 31) / 32;
+        hipLaunchKernelGGL(frames_query_kernel, dim3(kH, kD / 256, tiles), dim3(256), 0, s, a.q + (size_t)row0 * kD, static_cast<const char*>(a.wk_t),
+                           static_cast<bf16_t*>(a.q_frames), rows, a.scale_log2e);
+        hipError_t e = hipGetLastError();
+        if (e == hipSuccess) e = nq == 2 ? launch_positions<2>(a, at, row0, s) : launch_positions<1>(a, at, row0, s);
         if (e != hipSuccess) return e;
-        at += nq;
+        hipLaunchKernelGGL(frames_out_kernel, dim3(kH, kDh / 64, tiles), dim3(256), 0, s, static_cast<const bf16_t*>(a.u_frames), static_cast<const char*>(a.wv),
+                           static_cast<const bf16_t*>(a.bv), static_cast<char*>(a.out) + frag_block_off<2>(row0 / 16, 0, kD), rows);
+        if ((e = hipGetLastError()) != hipSuccess) return e;
     }
-    hipLaunchKernelGGL(frames_out_kernel, dim3(kH, kDh / 64, rows), dim3(256), 0, s, static_cast<const bf16_t*>(a.u_frames), static_cast<const char*>(a.wv),
-                       static_cast<const bf16_t*>(a.bv), static_cast<char*>(a.out), a.rows);
-    return hipGetLastError();
+    return hipSuccess;
 }
 
 }  // namespace aed

@@ -159,18 +159,20 @@ hipError_t launch_attn_self(Dtype dt, const AttnArgs& a, hipStream_t s);
 hipError_t launch_attn_cross(Dtype dt, const AttnArgs& a, hipStream_t s);
 
 // Cross-attention over the encoder frames themselves (attn_frames.hip): bfloat16, d_model 1024, 8 heads of 128
+constexpr int kFramesPositions = 2;  // positions of a sequence that are taken with one reading of its frames (of three the sums do not fit the registers)
 struct FramesArgs {
     const float* q;       // [rows, 1024]
     const void* wk_t;     // this layer's Wk^T (launch_frames_weight)
     const void* wv;       // rows [1024, 2048) of w_ckv in fragment order
     const void* bv;       // [1024] or null
     const void* frames;   // [.., 1024] in fragment order
-    void* q_frames;       // [rows][16][1024] scratch
-    void* u_frames;       // [rows][16][1024] scratch
+    void* q_frames;       // [rows of kFramesPositions positions][16][1024] scratch
+    void* u_frames;       // the same
     void* out;            // [rows, 1024] in fragment order
     const int4* items;    // AttnArgs::items, whole sequences
     int n_items, rows;
-    int positions;        // items i * positions .. + positions - 1 are positions of one sequence (a prompt pass; else 1)
+    int positions;        // items i * positions .. + positions - 1 are positions of one sequence, row q * (rows / positions) + b is
+                          // position q of sequence b, rows / positions a multiple of 16 (a prompt pass; else 1)
     float scale_log2e;
 };
 hipError_t launch_attn_frames(const FramesArgs& a, hipStream_t s);

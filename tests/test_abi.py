@@ -67,6 +67,18 @@ def test_only_decoders_that_can_read_the_frames_have_room_for_it(lib):
     assert binding.aed_workspace_bytes(c) - n > 24 * 2 * 1024 * 1024 + 288 * 2 * 16 * 1024 * 2
 
 
+def test_rows_of_a_prompt_pass_need_no_scratch_of_the_frames(lib):
+    # a pass takes two positions of every sequence at a time: beyond them a row costs what it costs a decoder that never reads the frames
+    sizes = []
+    for total in (140 * 288 + 60000, 140 * 288 + 60000 - 1):
+        c = good_config()
+        c.max_batch, c.max_total_enc_frames, c.prefill_rows = 500, total, 2 * 512
+        few = binding.aed_workspace_bytes(c)
+        c.prefill_rows = 65535
+        sizes.append(binding.aed_workspace_bytes(c) - few)
+    assert sizes[0] == sizes[1]
+
+
 @pytest.mark.parametrize("field,value,status", [
     ("struct_size", 4, binding.AED_EINVAL),
     ("n_layers", 0, binding.AED_EINVAL),
