@@ -126,6 +126,14 @@ int main() {
         const int got = attn_wavefronts(c.wgs, c.pairs, c.kv, c.keys, c.lng, c.even);
         expect(got == c.want, "wavefronts", c.wgs, got, c.want);
     }
+    // the frames instead of keys and values: 288 sequences and more of more than about 350 to 220 frames, the longest no longer than a
+    // CU's share of all; a decoder that has no room for 140 * 288 + 60 000 frames has no such batch
+    struct { long long total; int longest, batch; bool want; } frames[] = {
+        {140 * 288 + 60000, 390, 288, true}, {140 * 288 + 59999, 390, 288, false}, {1 << 20, 500, 287, false}, {140 * 288 + 60000, 392, 288, false},
+        {512 * 500, 500, 512, true}, {1024 * 500, 500, 1024, true}, {1024 * 500, 2000, 1024, true}, {1024 * 500, 2001, 1024, false},
+        {1024 * 150, 200, 1024, false}, {1024 * 250, 300, 1024, true}, {65535ll * 65535, 65535, 65535, true}};
+    for (const auto& c : frames) expect(frames_attention(c.total, c.longest, c.batch) == c.want, "frames", c.total, c.longest, c.batch);
+    for (int B = kFramesMinBatch; B < 5000; ++B) expect(frames_min_keys(B) >= frames_min_keys(kFramesMinBatch), "least frames", B, 0, 0);
     printf("%d wrong\n", bad);
     return bad != 0;
 }

@@ -62,3 +62,117 @@ def test_frames_attention_in_a_prompt_pass():
     for (k0, v0), (k1, v1) in zip(kv[0], kv[2 * 400]):
         assert np.isfinite(k1[:P]).all() and np.isfinite(v1[:P]).all()
         assert np.abs(k0[:P - 1] - k1[:P - 1]).max() <= 4e-2 and np.abs(v0[:P - 1] - v1[:P - 1]).max() <= 4e-2
+
+
+# positions per pass: 3 (two readings of the frames, two positions and one) and 5 (2 + 2 + 1); then three positions in passes of two
+# and one
+@pytest.mark.parametrize("prompt_len,positions", [(4, 3), (6, 5), (4, 2)])
+def test_prompt_passes_against_the_oracle(oracle, prompt_len, positions):
+    import torch
+    from tests import gpu_util as G
+    batch, N = 389, 3
+    wl = workload(batch, 7 + prompt_len, prompt_len=prompt_len, max_new=N)
+    dec = G.make_decoder(wl, prefill_rows=positions * 400)
+    dec.aed_cross_kv_precompute(dec.to_device(wl.enc), wl.enc_lens)
+    toks = dec.aed_greedy_decode(torch.from_numpy(wl.prompt).to(dec.device), N)[0].cpu().numpy()
+    m = oracle.Model(wl.cfg, wl.weights)
+    worst = 0.0
+    for b in (0, 1, 5, 13, 200, batch - 2, batch - 1):
+        fed = np.concatenate([wl.prompt[b], toks[b, :-1]])
+        kr, vr = m.self_kv(1, wl.subset([b]).enc, fed)  # behind the first layer's cross-attention
+        kg, vg = dec.aed_read_self_kv(1, b)
+        assert kg.shape == kr.shape
+        worst = max(worst, float(np.abs(kg - kr).max()), float(np.abs(vg - vr).max()))
+    print(f"{prompt_len - 1} positions, {positions} a pass: max |dK,dV| = {worst:.2e}")
+    assert worst <= G.TOL["bf16"]
+    dec.close()
+
+
+@pytest.mark.parametrize("prefill_rows", [0, 2 * 400])
+def test_sequences_that_end(oracle, prefill_rows):
+    """Sequences end one after the other: their workgroups exit and the rows of their sums stay as they were.  Twice: the second
+    decode of the batch has them all back."""
+    import torch
+    from tests import gpu_util as G
+    batch, N = 390, 8
+    wl = workload(batch, 17, prompt_len=3, max_new=N)
+    wl.cfg.eos_id, wl.cfg.pad_id = 2, 7
+    target = np.array([1 + (5 * i) % N for i in range(batch)], np.int32)
+    rows = sorted({0, 1, 2, 3, 4, 5, 6, 7, 13, 14, 15, 16, batch // 2, batch - 2, batch - 1})
+    sub = wl.subset(rows)
+    ref_t, ref_l, ref_lg = oracle.Model(wl.cfg, wl.weights).greedy_decode(sub.enc, sub.enc_lens, wl.prompt[rows], N,
+                                                                          max_new_per_seq=target[rows], want_logits=True)
+    near = G.first_near_tie(ref_lg, G.TOL["bf16"])
+    dec = G.make_decoder(wl, prefill_rows=prefill_rows)
+    dec.aed_cross_kv_precompute(dec.to_device(wl.enc), wl.enc_lens)
+    compared = 0
+    for _ in range(2):
+        toks, lens = dec.aed_greedy_decode(torch.from_numpy(wl.prompt).to(dec.device), N, max_new_per_seq=target)
+        toks, lens = toks.cpu().numpy(), lens.cpu().numpy()
+        assert (lens <= target).all()
+        for i, b in enumerate(rows):
+            k = min(int(near[i]), int(ref_l[i]))
+            assert (toks[b, :k] == ref_t[i, :k]).all()
+            compared += k
+            if near[i] >= ref_l[i]:
+                assert lens[b] == ref_l[i] and (toks[b, lens[b]:] == 7).all()
+    assert compared >= 40
+    # the longest's logits of the last step, beside rows that ended before
+    got = dec.aed_read_logits()
+    for i, b in enumerate(rows):
+        if ref_l[i] == N and near[i] >= N - 1:
+            assert np.abs(got[b] - ref_lg[i, N - 1]).max() <= G.TOL["bf16"]
+    dec.close()
+
+
+def test_batches_on_either_side_of_the_rule_in_one_decoder(oracle):
+    """Batches of the same size, one read over the frames, one as keys and values, and the first again: launches recorded for the one
+    are not those of the other."""
+    import torch
+    from tests import gpu_util as G
+    batch, S = 400, 3
+    wl = workload(batch, 3, max_new=S)
+    short = W.custom(W.DecoderConfig(**dict(wl.cfg.__dict__)), [1 + (7 * i) % 60 for i in range(batch)], 3, random_ln=True)
+    short.weights = wl.weights
+    toks = np.random.default_rng(4).integers(0, wl.cfg.vocab, size=(batch, S)).astype(np.int32)
+    rows = [0, 1, 14, 16, batch // 2, batch - 1]
+    m = oracle.Model(wl.cfg, wl.weights)
+    dec = G.make_decoder(wl)
+    bytes_of = []
+    for w in (wl, short, wl):
+        sub = w.subset(rows)
+        ref = m.decode_forced(sub.enc, sub.enc_lens, toks[rows])
+        glog, gids = G.forced_logits_gpu(dec, w, toks, rows)
+        G.check_forced(ref, glog, gids, G.TOL["bf16"])
+        bytes_of.append(dec.aed_kernel_work(binding.K_CROSS_ATTN)[0] / int(w.enc_lens.sum()))
+        out = dec.aed_greedy_decode(torch.from_numpy(w.prompt).to(dec.device), S)[0].cpu().numpy()
+        ref_t, _, ref_lg = m.greedy_decode(sub.enc, sub.enc_lens, w.prompt[rows], S, want_logits=True)
+        near = G.first_near_tie(ref_lg, G.TOL["bf16"])
+        for i, b in enumerate(rows):
+            assert (out[b, :near[i]] == ref_t[i, :near[i]]).all()
+    assert bytes_of[0] < 2200 and bytes_of[1] > 4096 and bytes_of[2] == bytes_of[0]  # each took its way
+    dec.close()
+
+
+def test_padded_frames_without_a_bias(oracle):
+    import torch
+    from tests import gpu_util as G
+    batch, S = 388, 2
+    wl = workload(batch, 23)
+    for l in wl.weights["layers"]:
+        l["b_ckv"] = None
+    at = np.concatenate([[0], np.cumsum(wl.enc_lens)])
+    padded = np.full((batch, int(wl.enc_lens.max()), 1024), np.nan, np.float32)
+    for b in range(batch):
+        padded[b, :wl.enc_lens[b]] = wl.enc[at[b]:at[b + 1]]
+    rows = list(range(len(EDGES))) + [batch // 2, batch - 1]
+    toks = np.random.default_rng(9).integers(0, wl.cfg.vocab, size=(batch, S)).astype(np.int32)
+    sub = wl.subset(rows)
+    ref = oracle.Model(wl.cfg, wl.weights).decode_forced(sub.enc, sub.enc_lens, toks[rows])
+    dec = G.make_decoder(wl)
+    dec.aed_cross_kv_precompute_padded(dec.to_device(padded), wl.enc_lens)
+    steps = [dec.aed_decode_step(torch.from_numpy(toks[:, s].copy()).to(dec.device)) for s in range(S)]
+    torch.cuda.synchronize()
+    G.check_forced(ref, np.stack([lg.cpu().numpy()[rows] for _, lg in steps], 1).astype(np.float64),
+                   np.stack([ids.cpu().numpy()[rows] for ids, _ in steps], 1), G.TOL["bf16"])
+    dec.close()

@@ -119,3 +119,33 @@ def test_create_destroy_many_times_leaves_nothing_behind():
         free_after.append(torch.cuda.mem_get_info()[0])
     # allow the allocator's granularity, not a per-handle loss: 35 more handles may not cost 32 MiB
     assert free_after[4] - free_after[-1] < (32 << 20), f"free memory fell from {free_after[4]} to {free_after[-1]}"
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "fp32"])
+def test_a_steps_results_go_where_they_are_asked_for(dtype):
+    """aed_decode_step with either output missing, and logits to an address that is no multiple of 16: the same values as to
+    tensors of their own, and nothing beside them is written."""
+    import ctypes as C
+    import torch
+    from tests import gpu_util as G
+    wl = _unit(dtype, 256, 4, 64, [9, 33, 1, 64, 17], seed=8)
+    B, V, S = 5, wl.cfg.vocab, 18  # past a page's end
+    toks = torch.from_numpy(np.random.default_rng(3).integers(0, V, size=(S, B)).astype(np.int32)).cuda()
+    dec = G.make_decoder(wl)
+    dec.aed_cross_kv_precompute(dec.to_device(wl.enc), wl.enc_lens)
+    want = [dec.aed_decode_step(toks[s]) for s in range(S)]
+    dec.aed_cross_kv_precompute(dec.to_device(wl.enc), wl.enc_lens)
+    for s in range(S):
+        ids = torch.full((B + 2,), -5, dtype=torch.int32, device="cuda")
+        logits = torch.full((B * V + 8,), -7.0, dtype=torch.float32, device="cuda")
+        off = s % 4 if s % 3 else 0  # 0, 4, 8 and 12 bytes past a multiple of 16
+        torch.cuda.synchronize()
+        st = dec.lib.aed_decode_step(dec.handle, C.c_void_p(toks[s].data_ptr()), C.c_void_p(ids[1:].data_ptr()) if s % 5 else None,
+                                     C.c_void_p(logits[off:].data_ptr()) if s % 7 else None)
+        assert st == 0
+        torch.cuda.synchronize()
+        assert (ids[[0, -1]] == -5).all() and (ids[1:-1] == (want[s][0] if s % 5 else -5)).all()
+        assert (logits[:off] == -7).all() and (logits[off + B * V:] == -7).all()
+        got = logits[off:off + B * V].view(B, V)
+        assert (got == (want[s][1] if s % 7 else -7)).all()
+    dec.close()
