@@ -104,13 +104,12 @@ template <int LPK> __device__ __forceinline__ float keys_max(float v) {
 // (bfloat16 and 8-bit caches: at least four wavefronts per SIMD, i.e. at most 128 registers, so that two workgroups of
 // eight wavefronts share a CU -- with one, half as many bytes are in flight and the launch takes a quarter longer)
 template <bool SELF> struct AttnFields {
-    template <typename F> __host__ __device__ __forceinline__ static void fields(AttnArgs& a, F f) {
+    template <typename F> __host__ __device__ __forceinline__ static constexpr void fields(AttnArgs& a, F&& f) {
         f(a.out); f(a.part); f(a.counters);
         if constexpr (!SELF) { f(a.q_stats); f(a.q_mu_hat); f(a.q_c1); f(a.q_c2); }
         f(a.scale_log2e); f(a.max_chunks);
         if constexpr (!SELF) { f(a.q_eps); f(a.q_stat_tiles); f(a.q_rms); }
     }
-    static constexpr int words() { return SELF ? 8 : 19; }
 };
 
 // list: page table (self) or work items (cross); rows: its pages a sequence (self) or the caches' frames a head (cross);
@@ -119,7 +118,7 @@ template <typename T, typename KV, int LPK, int DH, bool SELF, int NW>
 __global__ __launch_bounds__(64 * NW, sizeof(KV) <= 2 ? 4 : 1) void attn_decode_kernel(const void* K, const void* V, const float* Q, const void* list,
                                                                                          const int* finished, const int* seq_len, int rows,
                                                                                          int chunk_heads, ArgTail) {
-    TailLoad<AttnFields<SELF>, AttnArgs> rest(tail_at(56));
+    TailLoad<AttnFields<SELF>, AttnArgs> rest(tail_of<decltype(attn_decode_kernel<T, KV, LPK, DH, SELF, NW>)>());
     AttnArgs a;
     constexpr int EPL = DH / LPK;   // head_dim elements per lane
     constexpr int KPI = 64 / LPK;   // keys per load instruction

@@ -39,7 +39,7 @@ struct GemmStart { const void *W, *A; const float2* stats_in; int M, K, stat_til
 template <typename T, int PRO, int EPI> struct GemmFields {
     static constexpr bool LNS = PRO == PRO_LNS, RS = EPI == EPI_RESID_S, QKV = EPI == EPI_QKV, CKV = EPI == EPI_CROSSKV,
                           ADD = EPI == EPI_F32 && PRO == PRO_T, SHADOW = sizeof(T) == 2;
-    template <typename F> __host__ __device__ __forceinline__ static void fields(GemmArgs& a, F f) {
+    template <typename F> __host__ __device__ __forceinline__ static constexpr void fields(GemmArgs& a, F&& f) {
         f(a.out);
         if constexpr (LNS) f(a.ln_c2); else f(a.bias);
         if constexpr (LNS && SHADOW) { f(a.ln_c1); f(a.mu_hat_out); }
@@ -56,11 +56,6 @@ template <typename T, int PRO, int EPI> struct GemmFields {
         if constexpr (RS) f(a.stat_tiles);
         if constexpr (QKV) f(a.n_heads);
         if constexpr (QKV || CKV) { f(a.kv_fp8); f(a.head_dim); f(a.d_model); }
-    }
-    static constexpr int words() {
-        return 2 * (2 + (LNS ? 2 * SHADOW : 0) + (LNS && QKV ? 2 * SHADOW : 0) + ((LNS || RS) && SHADOW) + RS + (RS && SHADOW) + ADD +
-                    3 * QKV + 4 * CKV) +
-               1 + (LNS ? 2 : 0) + (LNS && QKV && SHADOW) + RS + QKV + (QKV || CKV ? 3 : 0);
     }
 };
 
@@ -182,7 +177,6 @@ __device__ __forceinline__ void gemm_decode_body(const GemmStart& st, TailPtr ta
     auto combine_stats = [&]() {
 #pragma unroll
         for (int p = 0; p < SP; ++p) {
-            const bool live = 4 * (tid & 15) < st.stat_tiles;
             float2 rs = combine_tile_stats<CENTRE>(sv[p][0], sv[p][1], 4 * (tid & 15) < st.stat_tiles, st.stat_tiles);
             const float rstd = fold_norm(a.rms, (float)K, a.ln_eps, rs.y, rs.x);
             const int row = SR * p + (tid >> 4);
@@ -366,7 +360,8 @@ __device__ __forceinline__ void gemm_decode_body(const GemmStart& st, TailPtr ta
 template <typename T, int PRO, int EPI, int MT, int NT, bool WNT, int NB, int NW = 4>
 __global__ __launch_bounds__(64 * NW) void gemm_decode_kernel(const void* W, const void* A, const float2* stats_in, int M, int K,
                                                               int stat_tiles, ArgTail) {
-    gemm_decode_body<T, PRO, EPI, MT, NT, WNT, NB, NW>(GemmStart{W, A, stats_in, M, K, stat_tiles}, tail_at(40), blockIdx.x, blockIdx.y);
+    gemm_decode_body<T, PRO, EPI, MT, NT, WNT, NB, NW>(
+        GemmStart{W, A, stats_in, M, K, stat_tiles}, tail_of<decltype(gemm_decode_kernel<T, PRO, EPI, MT, NT, WNT, NB, NW>)>(), blockIdx.x, blockIdx.y);
 }
 
 // Two products of the same operand A in one launch: the workgroups of z = 0 are the tiles of a0 (a residual update,
@@ -374,10 +369,11 @@ __global__ __launch_bounds__(64 * NW) void gemm_decode_kernel(const void* W, con
 template <typename T, int MT, int NT, int EPI1, bool WNT, int NB, int NW = 4>
 __global__ __launch_bounds__(64 * NW) void gemm_decode_pair_kernel(const void* W0, const void* W1, const void* A, int M, int K,
                                                                ArgTail, ArgTail) {
+    typedef decltype(gemm_decode_pair_kernel<T, MT, NT, EPI1, WNT, NB, NW>) Self;
     if (blockIdx.z == 0)
-        gemm_decode_body<T, PRO_T, EPI_RESID_S, MT, NT, WNT, NB, NW>(GemmStart{W0, A, nullptr, M, K, 0}, tail_at(32), blockIdx.x, blockIdx.y);
+        gemm_decode_body<T, PRO_T, EPI_RESID_S, MT, NT, WNT, NB, NW>(GemmStart{W0, A, nullptr, M, K, 0}, tail_of<Self, 0>(), blockIdx.x, blockIdx.y);
     else
-        gemm_decode_body<T, PRO_T, EPI1, MT, NT, WNT, NB, NW>(GemmStart{W1, A, nullptr, M, K, 0}, tail_at(32 + sizeof(ArgTail)), blockIdx.x, blockIdx.y);
+        gemm_decode_body<T, PRO_T, EPI1, MT, NT, WNT, NB, NW>(GemmStart{W1, A, nullptr, M, K, 0}, tail_of<Self, 1>(), blockIdx.x, blockIdx.y);
 }
 
 // The non-temporal hint for W (GemmArgs::w_nt) goes with launches of one workgroup per CU in at most four row tiles: the

@@ -11,15 +11,35 @@
 
 #include <string.h>
 
+#include <type_traits>
+
 #include "common.h"
 
 namespace aed {
 
-struct alignas(8) ArgTail { unsigned w[32]; };
+constexpr int kTailWords = 32;
+struct alignas(8) ArgTail { unsigned w[kTailWords]; };
 typedef unsigned u32x16 __attribute__((ext_vector_type(16)));
-typedef const __attribute__((address_space(4))) u32x16* TailPtr;
-// the tail that lies `offset` bytes behind the start of the kernel's arguments
-__device__ __forceinline__ TailPtr tail_at(int offset) {
+typedef u32x16 u32x16_packed __attribute__((aligned(4)));  // a tail begins where the leading arguments end; scalar loads take any dword
+typedef const __attribute__((address_space(4))) u32x16_packed* TailPtr;
+// Where the tails of a kernel lie in its arguments: its function type's arguments one after the other, each at its own alignment
+template <typename Kernel> struct TailOffset;
+template <typename... A> struct TailOffset<void(A...)> {
+    static constexpr int of(int which) {
+        const int size[] = {(int)sizeof(A)...}, align[] = {(int)alignof(A)...};
+        const bool tail[] = {std::is_same<A, ArgTail>::value...};
+        int at = 0;
+        for (int i = 0; i < (int)sizeof...(A); ++i) {
+            at = (at + align[i] - 1) / align[i] * align[i];
+            if (tail[i] && which-- == 0) return at;
+            at += size[i];
+        }
+        return -1;
+    }
+};
+template <typename Kernel, int Which = 0> __device__ __forceinline__ TailPtr tail_of() {
+    constexpr int offset = TailOffset<Kernel>::of(Which);
+    static_assert(offset >= 0, "the kernel has no such tail");
 #if defined(__HIP_DEVICE_COMPILE__)
     return (TailPtr)((const __attribute__((address_space(4))) char*)__builtin_amdgcn_kernarg_segment_ptr() + offset);
 #else
@@ -41,9 +61,22 @@ __device__ __forceinline__ void set_field(long long& v, unsigned long long bits)
 __device__ __forceinline__ void set_field(int& v, unsigned bits) { v = (int)bits; }
 __device__ __forceinline__ void set_field(float& v, unsigned bits) { v = __builtin_bit_cast(float, bits); }
 
-// Fields: a type with words() and fields(Args&, f), which calls f for every argument in the tail, those of 8 bytes first
+// Fields: a type with a constexpr fields(Args&, f), which calls f for every argument in the tail
+struct TailCounter {
+    int words = 0;
+    template <typename V> constexpr void operator()(V&) {
+        static_assert(sizeof(V) == 8 || sizeof(V) == 4, "pointers, long long, int, float");
+        words += sizeof(V) / 4;
+    }
+};
+template <typename Fields, typename Args> constexpr int tail_words() {
+    Args a{};
+    TailCounter c;
+    Fields::fields(a, c);
+    return c.words;
+}
 template <typename Fields, typename Args> static ArgTail make_tail(Args a) {
-    static_assert(Fields::words() <= 32, "a tail is at most two scalar loads");
+    static_assert(tail_words<Fields, Args>() <= kTailWords, "a tail is at most two scalar loads");
     ArgTail t = {};
     size_t at = 0;
     Fields::fields(a, [&](auto& v) {
@@ -54,15 +87,16 @@ template <typename Fields, typename Args> static ArgTail make_tail(Args a) {
 }
 
 template <typename Fields, typename Args> struct TailLoad {
+    static constexpr bool kTwo = tail_words<Fields, Args>() > 16;
     u32x16 lo, hi;
     __device__ __forceinline__ explicit TailLoad(TailPtr p) {
         lo = p[0];
-        if constexpr (Fields::words() > 16) hi = p[1];
+        if constexpr (kTwo) hi = p[1];
     }
     // the arguments; nothing uses them before this
     __device__ __forceinline__ void get(Args& a) {
         settle(lo);
-        if constexpr (Fields::words() > 16) settle(hi);
+        if constexpr (kTwo) settle(hi);
         int at = 0;
         auto word = [&](int i) { return i < 16 ? lo[i & 15] : hi[i & 15]; };
         Fields::fields(a, [&](auto& v) {
