@@ -255,6 +255,7 @@ __global__ __launch_bounds__(256, NQ == 1 ? 2 : 1) void attn_frames_kernel(const
 #pragma unroll
                 for (int i = 0; i < NQ; ++i) acc[i][m][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(e8, pf[i], acc[i][m][t] * alpha[i], 0, 0, 0);
             }
+        other_lanes_wrote();  // the next step's frames go where these were read from (in front of the reads stands the barrier)
     }
 #pragma unroll
     for (int i = 0; i < NQ; ++i) {

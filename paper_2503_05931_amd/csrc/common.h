@@ -75,6 +75,10 @@ template <typename V> __device__ __forceinline__ V load_global(const void* p) {
 // ---- barrier for data exchanged through LDS: loads from memory stay in flight (__syncthreads waits for them too) ----
 __device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
 
+// ---- between LDS writes and reads of one wavefront, which the hardware keeps in order: the compiler, which looks at one lane at a
+// time, must not take what a lane has read before for what it would read now, nor write what other lanes have yet to read ----
+__device__ __forceinline__ void other_lanes_wrote() { asm volatile("" ::: "memory"); }
+
 // ---- 4 consecutive elements as they sit in memory, converted where they are used ----
 template <typename T> struct Raw4;
 template <> struct Raw4<float> { typedef f32x4 type; };

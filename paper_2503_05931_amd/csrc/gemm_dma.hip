@@ -59,9 +59,6 @@ typedef bf16_t bf16x4 __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ void load_to_lds16(const void* g, unsigned lds_base) {
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off\n" ::"s"(lds_base), "v"(g) : "memory");
 }
-// Between LDS writes and reads of one wavefront, which the hardware keeps in order: the compiler, which looks at one lane at a
-// time, must not take what a lane has read before for what it would read now.
-__device__ __forceinline__ void other_lanes_wrote() { asm volatile("" ::: "memory"); }
 // At most N of this wavefront's memory operations still in flight, its LDS reads done, then the barrier.
 template <int N> __device__ __forceinline__ void wait_loads_barrier() {
     asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(N) : "memory");
