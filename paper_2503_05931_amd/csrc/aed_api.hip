@@ -74,7 +74,7 @@ struct Layout {
     size_t shadow_bytes; // bytes per shadow buffer
     size_t act_bytes;    // [0, act_bytes): the step's activations and attention partials (x ... counters)
     size_t seq_len, n_gen, finished, cur_tok, limit, limits_in, n_finished, step_tok, kv_slot;
-    size_t prompt_buf, out_buf, page_table, enc_off, row_map, frame_map, turn_buf, items, part, counters;
+    size_t prompt_buf, out_buf, page_table, row_map, frame_map, turn_buf, items, part, counters;
     size_t v_seq_len, v_finished, v_cur_tok, v_page_table, v_items;  // state of a prompt-prefill pass's rows
     int act_rows;  // rows the activation buffers hold: max(max_batch, prefill_rows)
     size_t k_pool, v_pool, kc, vc, w_frag, enc_frag;
@@ -165,7 +165,6 @@ void make_layout(const aed_config* c, Layout* L) {
     L->prompt_buf = take(B * (size_t)c->max_dec_len * 4);
     L->out_buf = take(B * (size_t)c->max_dec_len * 4);
     L->page_table = take(B * (size_t)L->max_pages * 4);
-    L->enc_off = take((B + 1) * 4);
     L->row_map = take((size_t)c->max_total_enc_frames * 4);
     L->frame_map = take((size_t)c->max_total_enc_frames * 4);  // request queue: where each new frame's K/V goes
     L->turn_buf = take(B * 4 * 4);                            // request queue: slot, old / new request, limit
@@ -272,8 +271,6 @@ struct aed_decoder {
     bool frames = false;                          // this batch's cross-attention reads the frames (attn_frames.hip)
     int last_prompt_len = 0, last_max_new = 0;
     long long total_enc = 0;
-    const void* last_enc = nullptr;
-    bool last_enc_padded = false;
     std::vector<int> enc_lens, enc_off, page_table;
     std::vector<int4> items_host;  // the cross-attention work list of the batch (a prefill pass repeats it per position)
     int* pin_poll = nullptr;  // pinned host memory: poll words of the finished count, the queue's flags, then the next two
@@ -523,7 +520,6 @@ hipError_t k_cross_attn(aed_decoder* d, int l) {
     a.items = d->at<int4>(d->lay.items);
     a.n_items = d->n_items;
     a.wavefronts = cross_wavefronts(d);
-    a.enc_off = d->at<int>(d->lay.enc_off);
     a.t_cap = d->cfg.max_total_enc_frames;
     if (merged_products(d)) {  // q holds the merged product: the kernel finishes the normalisation
         a.q_stats = stats_buf(d, d->x_par);        // of the rows after the self-attention update
@@ -679,8 +675,6 @@ aed_status start_batch(aed_decoder* d, const void* enc, bool padded, int t_max, 
     d->frames = frames;
     d->items_host = items;
     d->total_enc = total;
-    d->last_enc = enc;
-    d->last_enc_padded = padded;
     d->enc_lens.assign(enc_lens, enc_lens + batch);
     d->enc_off = off;
     d->host_pos = 0;
@@ -696,7 +690,6 @@ aed_status start_batch(aed_decoder* d, const void* enc, bool padded, int t_max, 
     memcpy(d->pin_off, off.data(), off.size() * 4);
     memcpy(d->pin_items, items.data(), items.size() * 16);
     sa.src_off = d->pin_off; sa.src_items = d->pin_items;
-    sa.enc_off = d->at<int>(d->lay.enc_off);
     sa.counters = d->at<int>(d->lay.counters);
     sa.n_counters = d->lay.act_rows * d->cfg.n_heads;
     sa.row_map = padded ? d->at<int>(d->lay.row_map) : nullptr;
@@ -1148,7 +1141,7 @@ aed_status aed_greedy_decode(aed_decoder* d, const int32_t* prompt, int32_t prom
             }
         }
     }
-    HIP_TRY(d, launch_reset(st, max_new_per_seq ? d->at<int>(d->lay.limits_in) : nullptr, 1, start_pos, d->stream));
+    HIP_TRY(d, launch_reset(st, max_new_per_seq ? d->at<int>(d->lay.limits_in) : nullptr, start_pos, d->stream));
     HIP_TRY(d, k_embed(d, st));
     d->state = aed_decoder::CONSUMED;
 

@@ -37,16 +37,6 @@ __device__ __forceinline__ Frag16<float> load_frag(const float* blk, int lane) {
     return f;
 }
 __device__ __forceinline__ Frag16<float> load_frag_nt(const float* blk, int lane) { return load_frag(blk, lane); }
-__device__ __forceinline__ void store_frag(bf16_t* blk, int lane, const Frag16<bf16_t>& f) {
-    bf16x8* p = reinterpret_cast<bf16x8*>(blk) + lane;
-    p[0] = f.lo;
-    p[64] = f.hi;
-}
-__device__ __forceinline__ void store_frag(float* blk, int lane, const Frag16<float>& f) {
-    f32x4* p = reinterpret_cast<f32x4*>(blk) + lane;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) p[64 * j] = f32x4{f.v[4 * j], f.v[4 * j + 1], f.v[4 * j + 2], f.v[4 * j + 3]};
-}
 // A 16-row tile of a fragment-order operand, n_rows rows of it present.  Lanes of absent rows point past the descriptor's
 // end: such a load returns zeros and asks memory for nothing.  K up to kMaxK; beyond, 16 rows have more bytes than the
 // descriptor's offsets reach, and a product takes tiles of more rows (choose_tile).
@@ -70,33 +60,13 @@ template <int ES> struct FragRows {
         }
     }
 };
-// row-major source (LayerNorm gain/shift vectors): 16 consecutive elements
-__device__ __forceinline__ Frag16<bf16_t> load_frag_rm(const bf16_t* p) {
-    Frag16<bf16_t> f;
-    f.lo = reinterpret_cast<const bf16x8*>(p)[0];
-    f.hi = reinterpret_cast<const bf16x8*>(p)[1];
-    return f;
-}
-__device__ __forceinline__ Frag16<float> load_frag_rm(const float* p) {
-    Frag16<float> f;
-    load_f32<16>(p, f.v);
-    return f;
-}
 __device__ __forceinline__ void pack_frag(const float* y, Frag16<bf16_t>& f) {
 #pragma unroll
     for (int i = 0; i < 8; ++i) { f.lo[i] = (bf16_t)y[i]; f.hi[i] = (bf16_t)y[8 + i]; }
 }
-__device__ __forceinline__ void pack_frag(const float* y, Frag16<float>& f) {
-#pragma unroll
-    for (int i = 0; i < 16; ++i) f.v[i] = y[i];
-}
 __device__ __forceinline__ void unpack_frag(const Frag16<bf16_t>& f, float* y) {
 #pragma unroll
     for (int i = 0; i < 8; ++i) { y[i] = (float)f.lo[i]; y[8 + i] = (float)f.hi[i]; }
-}
-__device__ __forceinline__ void unpack_frag(const Frag16<float>& f, float* y) {
-#pragma unroll
-    for (int i = 0; i < 16; ++i) y[i] = f.v[i];
 }
 // acc[n-major 16x16] += W-fragment x A-fragment over the 64-wide k block
 __device__ __forceinline__ void mma(f32x4& acc, const Frag16<bf16_t>& w, const Frag16<bf16_t>& a) {

@@ -138,7 +138,6 @@ struct AttnArgs {
     const int4* items;    // {b (| kItemOff: nothing to do), key_start | chunk_idx << 16, n_keys | n_chunks << 16, first frame of b in the
                           // packed layout}, sequences of several chunks first, then longest first
     int n_items;
-    const int* enc_off;   // [B+1] frame offsets in the packed layout
     long long t_cap;
     // split-K merge
     float* part;          // [B*H][max_chunks][Dh+2]
@@ -214,14 +213,14 @@ hipError_t launch_sample(const float* logits, const StateArgs& st, int* step_out
 // a greedy step's end: prompt feeding, argmax, EOS rules, output writes, then launch_embed of the state that this leaves
 hipError_t launch_sample_embed(Dtype dt, const float* logits, const StateArgs& st, const EmbedArgs& ea, hipStream_t s);
 // seq_len = start_pos, cur_tok = prompt[b][start_pos], n_gen = finished = 0, n_finished = 0,
-// limit = limits ? limits[b] : INT_MAX, out_tokens = pad (fill_out)
-hipError_t launch_reset(const StateArgs& st, const int* limits_dev, int fill_out, int start_pos, hipStream_t s);
-// The start of a batch: enc_off[b] = src_off[b], items = src_items (state: n_items of them), counters = 0, state as launch_reset leaves
-// it at position 0 without a prompt; with row_map: row_map[enc_off[b] + t] = b * t_max + t, where the frames of a padded tensor are.
+// limit = limits ? limits[b] : INT_MAX, out_tokens = pad
+hipError_t launch_reset(const StateArgs& st, const int* limits_dev, int start_pos, hipStream_t s);
+// The start of a batch: items = src_items (state: n_items of them), counters = 0, state as launch_reset leaves it at position 0 without
+// a prompt; with row_map: row_map[src_off[b] + t] = b * t_max + t, where the frames of a padded tensor are.
 struct StartArgs {
-    const int* src_off;     // [batch + 1] pinned host memory
+    const int* src_off;     // [batch + 1] frame offsets, pinned host memory
     const int4* src_items;  // pinned host memory
-    int *enc_off, *counters, *row_map;
+    int *counters, *row_map;
     int n_counters, t_max;
 };
 hipError_t launch_start_batch(const StartArgs& a, const StateArgs& st, hipStream_t s);

@@ -218,23 +218,22 @@ hipError_t launch_sample(const float* logits, const StateArgs& st, int* step_out
     return hipGetLastError();
 }
 
-__global__ void reset_kernel(StateArgs st, const int* __restrict__ limits, int fill_out, int start_pos) {
+__global__ void reset_kernel(StateArgs st, const int* __restrict__ limits, int start_pos) {
     const int b = blockIdx.x;
     if (threadIdx.x == 0) {
         st.seq_len[b] = start_pos;
         st.n_gen[b] = 0;
         st.finished[b] = 0;
-        st.cur_tok[b] = st.prompt ? st.prompt[(size_t)b * st.prompt_stride + start_pos] : 0;
+        st.cur_tok[b] = st.prompt[(size_t)b * st.prompt_stride + start_pos];
         st.limit[b] = limits ? limits[b] : INT_MAX;
         if (b == 0) *st.n_finished = 0;
     }
     for (int i = b * blockDim.x + threadIdx.x; i < st.n_items; i += gridDim.x * blockDim.x) st.items[i].x &= ~kItemOff;
-    if (fill_out)
-        for (int t = threadIdx.x; t < st.max_new; t += blockDim.x) st.out_tokens[(size_t)b * st.out_stride + t] = st.pad_id;
+    for (int t = threadIdx.x; t < st.max_new; t += blockDim.x) st.out_tokens[(size_t)b * st.out_stride + t] = st.pad_id;
 }
 
-hipError_t launch_reset(const StateArgs& st, const int* limits_dev, int fill_out, int start_pos, hipStream_t s) {
-    hipLaunchKernelGGL(reset_kernel, dim3(st.batch), dim3(64), 0, s, st, limits_dev, fill_out, start_pos);
+hipError_t launch_reset(const StateArgs& st, const int* limits_dev, int start_pos, hipStream_t s) {
+    hipLaunchKernelGGL(reset_kernel, dim3(st.batch), dim3(64), 0, s, st, limits_dev, start_pos);
     return hipGetLastError();
 }
 
@@ -243,10 +242,7 @@ hipError_t launch_reset(const StateArgs& st, const int* limits_dev, int fill_out
 // uploads, a memset and two kernels the GPU waited 9 to 18 us in front of each.
 __global__ __launch_bounds__(256) void start_batch_kernel(StartArgs a, StateArgs st) {
     const int b = blockIdx.x, tid = threadIdx.x, at = b * blockDim.x + tid, all = gridDim.x * blockDim.x;
-    const int first = a.src_off[b], n = a.src_off[b + 1] - first;
     if (tid == 0) {
-        a.enc_off[b] = first;
-        if (b + 1 == st.batch) a.enc_off[b + 1] = first + n;
         st.seq_len[b] = 0;
         st.n_gen[b] = 0;
         st.finished[b] = 0;
@@ -256,8 +252,10 @@ __global__ __launch_bounds__(256) void start_batch_kernel(StartArgs a, StateArgs
     }
     for (int i = at; i < st.n_items; i += all) st.items[i] = a.src_items[i];
     for (int i = at; i < a.n_counters; i += all) a.counters[i] = 0;
-    if (a.row_map)
+    if (a.row_map) {
+        const int first = a.src_off[b], n = a.src_off[b + 1] - first;
         for (int t = tid; t < n; t += blockDim.x) a.row_map[first + t] = b * a.t_max + t;
+    }
 }
 
 hipError_t launch_start_batch(const StartArgs& a, const StateArgs& st, hipStream_t s) {
