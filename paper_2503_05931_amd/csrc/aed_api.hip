@@ -1,6 +1,6 @@
 // C ABI of the AED decoder library: argument checking, workspace carving, the
 // decode state machine, launch-graph capture/replay and measurement helpers.
-// All device work is in gemm_decode.hip, attn_decode.hip, step_kernels.hip.
+// All device work is in the gemm_*.hip, attn_decode.hip, attn_frames.hip and step_kernels.hip.
 #include <limits.h>
 #include <math.h>
 #include <stdarg.h>
@@ -564,7 +564,7 @@ hipError_t k_cross_kv(aed_decoder* d, int l, long long rows, const int* frame_ma
     g.kc = d->ws + d->lay.kc + (size_t)l * d->lay.cross_layer_elems * d->kv_esz;
     g.vc = d->ws + d->lay.vc + (size_t)l * d->lay.cross_layer_elems * d->kv_esz;
     g.t_cap = d->cfg.max_total_enc_frames;
-    return launch_gemm(d->dt, PRO_T, EPI_CROSSKV, g, d->stream);  // LDS-tiled kernel from 512 rows (bf16)
+    return launch_gemm(d->dt, PRO_T, EPI_CROSSKV, g, d->stream);
 }
 
 // launches of a kernel class per layer in the current mode
@@ -699,7 +699,7 @@ aed_status start_batch(aed_decoder* d, const void* enc, bool padded, int t_max, 
     HIP_TRY(d, launch_reorder_rows(d->dt, enc, padded ? d->at<int>(d->lay.row_map) : nullptr, d->ws + d->lay.enc_frag,
                                    (int)total, d->cfg.d_model, d->stream));
     for (int l = 0; l < d->cfg.n_layers; ++l) HIP_TRY(d, k_cross_kv(d, l, total, nullptr));
-    HIP_TRY(d, hipStreamSynchronize(d->stream));  // host vectors above go out of scope
+    HIP_TRY(d, hipStreamSynchronize(d->stream));  // the caller's frames are the caller's again
     d->state = aed_decoder::STEPPING;
     return AED_OK;
 }

@@ -594,7 +594,7 @@ def test_bf16_logits_through_finished_and_forced_eos(torch_cuda, oracle):
     ("fp32", 256, 4, 64, [1, 15, 16, 17, 63, 64, 65, 130], True),
     ("bf16", 256, 4, 64, [1, 15, 16, 17, 63, 64, 65, 130], True),
     ("bf16", 1024, 8, 128, [257, 1, 64], False),               # no shift vectors (NULL pointers)
-    ("fp32", 256, 4, 64, [1 + (11 * i) % 60 for i in range(131)], False),   # the normalisation as its own launch
+    ("fp32", 256, 4, 64, [1 + (11 * i) % 60 for i in range(131)], False),   # float32 rows of several tiles, statistics alone
     ("bf16", 512, 4, 128, [3 + (5 * i) % 40 for i in range(300)], True),    # large tiles, folded normalisation
     ("bf16", 256, 4, 64, [2 + (3 * i) % 25 for i in range(530)], True),     # LDS-tiled kernels
 ])
