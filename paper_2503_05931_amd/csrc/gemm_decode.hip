@@ -22,8 +22,8 @@
 //     is one 16-byte (fp32) or 8-byte (bf16) store, also into fragment order.
 // A LayerNorm before a product is taken around it (kernels.h) in both storage types.  In float32 it was a prologue that
 // normalised and kept the rows before the first multiplication (up to 128 rows), or a launch of its own; us a step of 4 layers of
-// d_model 1024 with it / with the mean taken off the operands as they arrive: batch 16 233.5 / 190.2, 32 246.6 / 203.7, 128
-// 428.9 / 359.0, 256 588.1 / 563.5, 900 1719 / 1722.
+// d_model 1024 with it / with the mean taken off the operands as they arrive: batch 16 233.5 / 187.8, 32 246.6 / 203.5, 128
+// 428.9 / 356.9, 256 588.1 / 564.5, 900 1719 / 1726.
 #include <algorithm>
 
 #include "common.h"
@@ -136,6 +136,34 @@ __device__ __forceinline__ void gemm_decode_body(const GemmStart& st, TailPtr ta
     };
     float mean[MT];  // CENTRE: of this lane's row of every tile (RMSNorm: 0)
     auto compute = [&](int slot) {
+        if constexpr (CENTRE && NB > 0 && MT * NT <= 2) {
+            // The two sums in turn, and what a multiplication takes subtracted beside the ones before: left to itself the compiler puts
+            // all multiplications of a sum one behind the other, each behind its own subtraction.  4 layers of d_model 1024, us a step
+            // without it and the barrier behind fetch_stats / with both: 16 rows 191.8 / 187.8, 32 208.5 / 203.5, 64 243.2 / 240.4,
+            // 128 353.9 / 356.9; on the larger tiles 1 to 2 % slower.
+#pragma unroll
+            for (int k = 0; k < 16; ++k) {
+                const int i = (k & 1) * 8 + (k >> 1);
+                float v[MT];
+#pragma unroll
+                for (int mt = 0; mt < MT; ++mt) v[mt] = af[slot][mt].v[i] - mean[mt];
+#pragma unroll
+                for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+                    for (int mt = 0; mt < MT; ++mt) {
+                        f32x4& sum = acc[i / 8][mt][nt];
+                        sum = __builtin_amdgcn_mfma_f32_16x16x4f32(wf[slot][nt].v[i], v[mt], sum, 0, 0, 0);
+                    }
+            }
+            __builtin_amdgcn_sched_group_barrier(0x2, 2 * MT, 0);
+#pragma unroll
+            for (int k = 0; k < 14; ++k) {
+                __builtin_amdgcn_sched_group_barrier(0x8, MT * NT, 0);
+                __builtin_amdgcn_sched_group_barrier(0x2, MT, 0);
+            }
+            __builtin_amdgcn_sched_group_barrier(0x8, 2 * MT * NT, 0);
+            return;
+        }
         if constexpr (CENTRE) {
 #pragma unroll
             for (int mt = 0; mt < MT; ++mt)
@@ -187,6 +215,12 @@ __device__ __forceinline__ void gemm_decode_body(const GemmStart& st, TailPtr ta
         }
     };
     if constexpr (LNS && ST_FIRST) fetch_stats();
+    if constexpr (CENTRE && NB > 0 && MT * NT <= 2) {
+        // Every wavefront waits for the statistics that the others fetch: those of all go ahead of anyone's stream.
+        __builtin_amdgcn_sched_barrier(0);
+        asm volatile("s_barrier");
+        __builtin_amdgcn_sched_barrier(0);
+    }
     // Weights that come from memory (WNT): those of all blocks of the ring first, then the rows, which come from the caches.  A
     // CU takes a request of 1 KB every 16 cycles, so the last of 32 leaves 0.8 us after the first; with weights and rows taking
     // turns the weights' longer trip began that much later.  24 layers: batch 64, 131 positions 133.0 -> 129.9 ms; batch 16,
