@@ -49,6 +49,7 @@ template <typename... A> static inline Unreached2 unreached2(A...) { __builtin_t
 #define __builtin_amdgcn_mov_dpp unreached
 #define __builtin_amdgcn_readfirstlane unreached
 #define __builtin_amdgcn_sched_barrier(x) ((void)0)
+#define __builtin_amdgcn_sched_group_barrier(...) ((void)0)
 struct Anything { template <typename T> operator T() const { __builtin_trap(); } };
 template <typename... A> static inline Anything anything(A...) { __builtin_trap(); }
 #define __builtin_amdgcn_mfma_f32_16x16x32_bf16 anything
