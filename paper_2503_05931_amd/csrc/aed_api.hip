@@ -186,7 +186,7 @@ void make_layout(const aed_config* c, Layout* L) {
     L->merge_vec = take(c->dtype == 1 ? (size_t)c->n_layers * d * 4 : 0);
     const bool frames = frames_possible(c);
     L->wk_t = take(frames ? (size_t)c->n_layers * d * d * e : 0);
-    const size_t frames_rows = std::max(B, std::min<size_t>(c->prefill_rows, kFramesPositions * align_up(B, 16)));
+    const size_t frames_rows = std::max(B, std::min<size_t>(c->prefill_rows, kFramesPart * align_up(B, 16)));
     L->q_frames = take(frames ? frames_rows * 16 * d * e : 0);
     L->u_frames = take(frames ? frames_rows * 16 * d * e : 0);
     // the batch's encoder states in fragment order (A operand of the cross K/V GEMMs), whole 256-row tiles

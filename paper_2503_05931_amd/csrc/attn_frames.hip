@@ -382,15 +382,16 @@ hipError_t launch_attn_frames(const FramesArgs& a, hipStream_t s) {
     if (a.rows < 1 || a.n_items < 1 || !a.items || a.positions < 1 || a.n_items % a.positions != 0 || a.rows % a.positions != 0) return hipErrorInvalidValue;
     const int Bs = a.rows / a.positions;
     if (a.positions > 1 && Bs % 16 != 0) return hipErrorInvalidValue;  // a part of the output begins with a 16-row tile
-    // A prompt pass in parts of kFramesPositions positions, each with its queries and sums in the same scratch (64 KB a row): a batch
-    // has as much of it as two of its steps need, whatever the pass takes.
-    for (int at = 0; at < a.positions; at += kFramesPositions) {
-        const int nq = std::min(kFramesPositions, a.positions - at), row0 = at * Bs, rows = nq * Bs;
+    // A prompt pass in parts of kFramesPart positions, each with its queries and sums in the same scratch (64 KB a row): a batch has as
+    // much of it as four of its steps need, whatever the pass takes.  (Of 1024 sequences in three positions a second part costs 27 us a layer.)
+    for (int part = 0; part < a.positions; part += kFramesPart) {
+        const int end = std::min(part + kFramesPart, a.positions), row0 = part * Bs, rows = (end - part) * Bs;
         const unsigned tiles = (rows + 31) / 32;
         hipLaunchKernelGGL(frames_query_kernel, dim3(kH, kD / 256, tiles), dim3(256), 0, s, a.q + (size_t)row0 * kD, static_cast<const char*>(a.wk_t),
                            static_cast<bf16_t*>(a.q_frames), rows, a.scale_log2e);
         hipError_t e = hipGetLastError();
-        if (e == hipSuccess) e = nq == 2 ? launch_positions<2>(a, at, row0, s) : launch_positions<1>(a, at, row0, s);
+        for (int at = part; at < end && e == hipSuccess; at += 2)  // two with one reading of the frames: of three the sums do not fit the registers
+            e = at + 2 <= end ? launch_positions<2>(a, at, row0, s) : launch_positions<1>(a, at, row0, s);
         if (e != hipSuccess) return e;
         hipLaunchKernelGGL(frames_out_kernel, dim3(kH, kDh / 64, tiles), dim3(256), 0, s, static_cast<const bf16_t*>(a.u_frames), static_cast<const char*>(a.wv),
                            static_cast<const bf16_t*>(a.bv), static_cast<char*>(a.out) + frag_block_off<2>(row0 / 16, 0, kD), rows);

@@ -158,14 +158,14 @@ hipError_t launch_attn_self(Dtype dt, const AttnArgs& a, hipStream_t s);
 hipError_t launch_attn_cross(Dtype dt, const AttnArgs& a, hipStream_t s);
 
 // Cross-attention over the encoder frames themselves (attn_frames.hip): bfloat16, d_model 1024, 8 heads of 128
-constexpr int kFramesPositions = 2;  // positions of a sequence that are taken with one reading of its frames (of three the sums do not fit the registers)
+constexpr int kFramesPart = 4;  // positions of a prompt pass that have their queries and sums in the scratch at a time
 struct FramesArgs {
     const float* q;       // [rows, 1024]
     const void* wk_t;     // this layer's Wk^T (launch_frames_weight)
     const void* wv;       // rows [1024, 2048) of w_ckv in fragment order
     const void* bv;       // [1024] or null
     const void* frames;   // [.., 1024] in fragment order
-    void* q_frames;       // [rows of kFramesPositions positions][16][1024] scratch
+    void* q_frames;       // [rows of kFramesPart positions][16][1024] scratch
     void* u_frames;       // the same
     void* out;            // [rows, 1024] in fragment order
     const int4* items;    // AttnArgs::items, whole sequences

@@ -68,11 +68,11 @@ def test_only_decoders_that_can_read_the_frames_have_room_for_it(lib):
 
 
 def test_rows_of_a_prompt_pass_need_no_scratch_of_the_frames(lib):
-    # a pass takes two positions of every sequence at a time: beyond them a row costs what it costs a decoder that never reads the frames
+    # a pass takes four positions of every sequence at a time: beyond them a row costs what it costs a decoder that never reads the frames
     sizes = []
     for total in (140 * 288 + 60000, 140 * 288 + 60000 - 1):
         c = good_config()
-        c.max_batch, c.max_total_enc_frames, c.prefill_rows = 500, total, 2 * 512
+        c.max_batch, c.max_total_enc_frames, c.prefill_rows = 500, total, 4 * 512
         few = binding.aed_workspace_bytes(c)
         c.prefill_rows = 65535
         sizes.append(binding.aed_workspace_bytes(c) - few)

@@ -64,9 +64,9 @@ def test_frames_attention_in_a_prompt_pass():
         assert np.abs(k0[:P - 1] - k1[:P - 1]).max() <= 4e-2 and np.abs(v0[:P - 1] - v1[:P - 1]).max() <= 4e-2
 
 
-# positions per pass: 3 (two readings of the frames, two positions and one) and 5 (2 + 2 + 1); then three positions in passes of two
-# and one
-@pytest.mark.parametrize("prompt_len,positions", [(4, 3), (6, 5), (4, 2)])
+# positions per pass: 3 (two readings of the frames, two positions and one) and 5 (two parts, of 2 + 2 and of 1); 6 in parts of 4 and 2;
+# then three positions in passes of two and one
+@pytest.mark.parametrize("prompt_len,positions", [(4, 3), (6, 5), (7, 6), (4, 2)])
 def test_prompt_passes_against_the_oracle(oracle, prompt_len, positions):
     import torch
     from tests import gpu_util as G
