@@ -383,7 +383,8 @@ hipError_t launch_attn_frames(const FramesArgs& a, hipStream_t s) {
     const int Bs = a.rows / a.positions;
     if (a.positions > 1 && Bs % 16 != 0) return hipErrorInvalidValue;  // a part of the output begins with a 16-row tile
     // A prompt pass in parts of kFramesPart positions, each with its queries and sums in the same scratch (64 KB a row): a batch has as
-    // much of it as four of its steps need, whatever the pass takes.  (Of 1024 sequences in three positions a second part costs 27 us a layer.)
+    // much of it as four of its steps need, whatever the pass takes.  (1024 sequences in three positions, the two products of a layer:
+    // 80 us in one part, 83 in two.)
     for (int part = 0; part < a.positions; part += kFramesPart) {
         const int end = std::min(part + kFramesPart, a.positions), row0 = part * Bs, rows = (end - part) * Bs;
         const unsigned tiles = (rows + 31) / 32;
